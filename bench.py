@@ -248,7 +248,7 @@ def bench_config(name, steps, warmup, hip, with_training, with_cpu, copy_calibra
                         "frac_of_measured_peak": round(achieved_tflops / MEASURED_BF16_TFLOPS, 4), **common}
     else:
         achieved_tflops = up_flops / dom_s / 1e12
-        roofline = {"bound": "alu", "kernel": "grouped_gemm_nt_f32_kernel (fp32 FMA path of the tiny configuration)",
+        roofline = {"bound": "alu", "kernel": "grouped_gemm_f32_kernel (fp32 path of the tiny configuration)",
                     "achieved": round(achieved_tflops, 3), "peak": PEAK_F32_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(achieved_tflops / PEAK_F32_TFLOPS, 5), "traffic": None,
                     "avg_launch_us": round(dom_ms * 1e3, 2), "alg_flops_per_launch": up_flops}

@@ -297,8 +297,7 @@ smile_status smile_layer_forward(smile_ctx *ctx, const smile_layer_io *io, void 
 
 /* Bytes of device scratch memory smile_expert_ffn_backward, smile_gate_weights_backward and
  * smile_layer_backward need: the recomputed h and pre, the gradient at the pre-activation (3 N*C*F
- * elements), partial sums of the router-weight gradient, and for fp32 also transposed copies of the
- * GEMM operands (about 2 N*C*F + 2 N*C*d + N*d*F more).  Host-only.  The memory is the caller's,
+ * elements) and partial sums of the router-weight gradient.  Host-only.  The memory is the caller's,
  * 256-byte aligned, and only used during the call's enqueued work. */
 smile_status smile_backward_workspace_bytes(const smile_layer_desc *desc, size_t *bytes);
 

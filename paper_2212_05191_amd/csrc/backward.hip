@@ -7,10 +7,8 @@
 //   expert_ffn_backward    (pre, h) = xe . W1^T   unless saved by the forward pass (one launch of the forward kernel)
 //                          dpre = (dye . W2) * act'(pre),  dxe = dpre . W1,
 //                          dW2 = dye^T . h,  dW1 = dpre^T . xe   (contraction over the expert's rows)
-//                          bf16: four launches of the MFMA kernel that reads operands whose contraction index is
-//                          the slow one (transposing LDS reads), nothing transposed in memory;
-//                          fp32: the forward kernel on operands transposed by a tiled transpose kernel (zero-padded
-//                          along the row axis, so experts with fewer than C rows contribute exact zeros)
+//                          four launches of the MFMA kernels that read operands whose contraction index is
+//                          the slow one, nothing transposed in memory
 //   dispatch_backward      dx[t] = dxe[row(t)] + dlp[t,:] . W_p + dlq[t,:] . W_q
 //   gate_weights_backward  dW_p = dlp^T . x, dW_q = dlq^T . x: per-block partial sums, then a fixed-order
 //                          reduction over the blocks (bit-reproducible, no atomics)
@@ -196,65 +194,6 @@ __global__ __launch_bounds__(kThreads) void route_backward_tiled_kernel(
     copy_tile(std::false_type{}, tq, sq, nullptr, dlq + (size_t)t0 * m, m);
 }
 
-// ------------------------------------------------------------------------------------ transpose
-
-// out[e][c][r] = r < rows_e ? in[e][r][c] : 0   for c < cols, r < rows_out;
-// in[N][R][cols], out[N][cols][rows_out], rows_e = kept ? min(kept[e], R) : R.  64 x 64 element tiles
-// through LDS, 16-byte global accesses on both sides.  cols and rows_out are multiples of VEC.
-template <typename E, int VEC>
-__global__ __launch_bounds__(kThreads) void transpose_pad_kernel(
-    const E *__restrict__ in, E *__restrict__ out, const int32_t *__restrict__ kept, int R, int cols, int rows_out,
-    int row_tiles, int col_tiles)
-{
-    constexpr int TILE = 64, PPT = TILE / VEC;   // pieces per tile row
-    constexpr int PAD = sizeof(E) == 2 ? 2 : 1;   // row stride of 33 / 65 words: conflict-free column reads
-    __shared__ E tile[TILE][TILE + PAD];
-    typedef E vec_t __attribute__((ext_vector_type(VEC)));
-
-    const int per_e = row_tiles * col_tiles;
-    const int e = blockIdx.x / per_e, rem = blockIdx.x - e * per_e;
-    const int rt = rem / col_tiles, ct = rem - rt * col_tiles;
-    const int rows = kept ? min(kept[e], R) : R;
-    const E *src = in + (size_t)e * R * cols;
-    E *dst = out + (size_t)e * cols * rows_out;
-    const int r0 = rt * TILE, c0 = ct * TILE;
-
-    for (int p = threadIdx.x; p < TILE * PPT; p += kThreads) {
-        const int r = p / PPT, cp = (p - r * PPT) * VEC;
-        vec_t v = {};
-        if (r0 + r < rows && c0 + cp < cols) v = *reinterpret_cast<const vec_t *>(src + (size_t)(r0 + r) * cols + c0 + cp);
-#pragma unroll
-        for (int k = 0; k < VEC; ++k) tile[r][cp + k] = v[k];
-    }
-    __syncthreads();
-    for (int p = threadIdx.x; p < TILE * PPT; p += kThreads) {
-        const int c = p / PPT, rp = (p - c * PPT) * VEC;
-        if (c0 + c >= cols || r0 + rp >= rows_out) continue;
-        vec_t v;
-#pragma unroll
-        for (int k = 0; k < VEC; ++k) v[k] = tile[rp + k][c];
-        *reinterpret_cast<vec_t *>(dst + (size_t)(c0 + c) * rows_out + r0 + rp) = v;
-    }
-}
-
-template <typename E, int VEC>
-hipError_t launch_transpose(const void *in, void *out, const int32_t *kept, int N, int R, int cols, int rows_out,
-                            hipStream_t s)
-{
-    const int row_tiles = (rows_out + 63) / 64, col_tiles = (cols + 63) / 64;
-    SMILE_LAUNCH((transpose_pad_kernel<E, VEC>), dim3((unsigned)((size_t)N * row_tiles * col_tiles)),
-                       dim3(kThreads), 0, s, static_cast<const E *>(in), static_cast<E *>(out), kept, R, cols,
-                       rows_out, row_tiles, col_tiles);
-    return hipGetLastError();
-}
-
-hipError_t transpose_pad(int dtype, const void *in, void *out, const int32_t *kept, int N, int R, int cols,
-                         int rows_out, hipStream_t s)
-{
-    if (is_half(dtype)) return launch_transpose<uint16_t, 8>(in, out, kept, N, R, cols, rows_out, s);
-    return launch_transpose<float, 4>(in, out, kept, N, R, cols, rows_out, s);
-}
-
 // ------------------------------------------------------------------------------------ dispatch backward
 
 // dx[t] = dxe[row(t)] (kept tokens) + sum_i dlp[t,i] W_p[i] + sum_j dlq[t,j] W_q[j], one rounding.
@@ -426,19 +365,11 @@ BackwardLayout backward_workspace_layout(const smile_layer_desc &d)
     const size_t esz = elem_size(d.dtype);
     const size_t N = (size_t)d.n_groups * d.m_local, C = (size_t)d.capacity;
     const size_t dm = (size_t)d.d_model, F = (size_t)d.d_ff;
-    L.k_pad = (int32_t)((d.capacity + 63) / 64 * 64);
     L.gw_blocks = (d.T + kGwTokens - 1) / kGwTokens;
     size_t off = 0;
     L.off_pre = off;     off = align_up(off + N * C * F * esz, 256);
     L.off_h = off;       off = align_up(off + N * C * F * esz, 256);
     L.off_dpre = off;    off = align_up(off + N * C * F * esz, 256);
-    // transposed copies of the operands: the fp32 path only (the bf16 kernel reads them in place)
-    const size_t tr = is_half(d.dtype) ? 0 : 1;
-    L.off_h_t = off;     off = align_up(off + tr * N * F * (size_t)L.k_pad * esz, 256);
-    L.off_dpre_t = off;  off = align_up(off + tr * N * F * (size_t)L.k_pad * esz, 256);
-    L.off_dye_t = off;   off = align_up(off + tr * N * dm * (size_t)L.k_pad * esz, 256);
-    L.off_xe_t = off;    off = align_up(off + tr * N * dm * (size_t)L.k_pad * esz, 256);
-    L.off_w_t = off;     off = align_up(off + tr * N * dm * F * esz, 256);
     L.off_gw_partial = off;
     off = align_up(off + (size_t)L.gw_blocks * (size_t)(d.n_groups + d.m_local) * dm * sizeof(float), 256);
     L.total = off;
@@ -491,9 +422,8 @@ hipError_t launch_expert_ffn_backward(const LayerDesc &d, void *workspace, const
 {
     const BackwardLayout L = backward_workspace_layout(d);
     char *b = static_cast<char *>(workspace);
-    void *dpre = b + L.off_dpre, *h_t = b + L.off_h_t;
-    void *dpre_t = b + L.off_dpre_t, *dye_t = b + L.off_dye_t, *xe_t = b + L.off_xe_t, *w_t = b + L.off_w_t;
-    const int N = d.n_groups * d.m_local, C = d.capacity, dm = d.d_model, F = d.d_ff, Kp = L.k_pad;
+    void *dpre = b + L.off_dpre;
+    const int N = d.n_groups * d.m_local, C = d.capacity, dm = d.d_model, F = d.d_ff;
     const int act = d.act == SMILE_ACT_RELU ? 1 : 2;
     hipError_t err;
 #define SMILE_TRY(call) do { err = (call); if (err != hipSuccess) return err; } while (0)
@@ -506,44 +436,27 @@ hipError_t launch_expert_ffn_backward(const LayerDesc &d, void *workspace, const
         h = h_ws;
         pre = pre_ws;
     }
-    if (is_half(d.dtype)) {
-        // MFMA kernel that reads operands with the contraction index as the slow index: no transposed copies
-        const long long cd = (long long)C * dm, cf = (long long)C * F, df = (long long)dm * F;
-        // dpre[r,f] = (sum_c dye[r,c] W2[c,f]) * act'(pre[r,f])
-        SMILE_TRY(launch_grouped_gemm_t(
-            d.dtype, TransposedGemm{dye, w2, dpre, pre, kept_count, nullptr, N, C, F, dm, dm, F, cd, df, cf, false, true, act, d.tune}, s));
-        // dW2[c,f] = sum_r dye[r,c] h[r,f]
-        SMILE_TRY(launch_grouped_gemm_t(
-            d.dtype, TransposedGemm{dye, h, dw2, nullptr, nullptr, kept_count, N, dm, F, C, dm, F, cd, cf, df, true, true, 0, d.tune}, s));
-        // dxe[r,k] = sum_f dpre[r,f] W1[f,k]
-        SMILE_TRY(launch_grouped_gemm_t(
-            d.dtype, TransposedGemm{dpre, w1, dxe, nullptr, kept_count, nullptr, N, C, dm, F, F, dm, cf, df, cd, false, true, 0, d.tune}, s));
-        // dW1[f,k] = sum_r dpre[r,f] xe[r,k]
-        SMILE_TRY(launch_grouped_gemm_t(
-            d.dtype, TransposedGemm{dpre, xe, dw1, nullptr, nullptr, kept_count, N, F, dm, C, F, dm, cf, cd, df, true, true, 0, d.tune}, s));
-        return hipSuccess;
-    }
-    // fp32: the same four products on the x . w^T kernel, with explicitly transposed operands
-    // dpre = (dye . W2) * act'(pre)   (W2 is [d][F]: transposed so that the contraction index is contiguous)
-    SMILE_TRY(transpose_pad(d.dtype, w2, w_t, nullptr, N, dm, F, dm, s));                      // W2^T [N][F][d]
-    {
-        GroupedGemm g{dye, w_t, dpre, nullptr, kept_count, N, C, F, dm, 0};
-        g.aux = pre;
-        g.post = act;
-        g.tune = d.tune;
-        SMILE_TRY(launch_grouped_gemm_nt(d.dtype, g, s));
-    }
-    // dW2[c][f] = sum_r dye[r][c] h[r][f]
-    SMILE_TRY(transpose_pad(d.dtype, dye, dye_t, kept_count, N, C, dm, Kp, s));                 // [N][d][Kp]
-    SMILE_TRY(transpose_pad(d.dtype, h, h_t, kept_count, N, C, F, Kp, s));                      // [N][F][Kp]
-    SMILE_TRY(launch_grouped_gemm_nt(d.dtype, GroupedGemm{dye_t, h_t, dw2, nullptr, nullptr, N, dm, F, Kp, 0, nullptr, nullptr, nullptr, 0, d.tune}, s));
-    // dxe = dpre . W1   (W1 is [F][d])
-    SMILE_TRY(transpose_pad(d.dtype, w1, w_t, nullptr, N, F, dm, F, s));                        // W1^T [N][d][F]
-    SMILE_TRY(launch_grouped_gemm_nt(d.dtype, GroupedGemm{dpre, w_t, dxe, nullptr, kept_count, N, C, dm, F, 0, nullptr, nullptr, nullptr, 0, d.tune}, s));
-    // dW1[f][k] = sum_r dpre[r][f] xe[r][k]
-    SMILE_TRY(transpose_pad(d.dtype, dpre, dpre_t, kept_count, N, C, F, Kp, s));                // [N][F][Kp]
-    SMILE_TRY(transpose_pad(d.dtype, xe, xe_t, kept_count, N, C, dm, Kp, s));                   // [N][d][Kp]
-    SMILE_TRY(launch_grouped_gemm_nt(d.dtype, GroupedGemm{dpre_t, xe_t, dw1, nullptr, nullptr, N, F, dm, Kp, 0, nullptr, nullptr, nullptr, 0, d.tune}, s));
+    // kernels that read operands with the contraction index as the slow index: no transposed copies
+    const long long cd = (long long)C * dm, cf = (long long)C * F, df = (long long)dm * F;
+    auto product = [&](const void *x, const void *w, void *y, const void *aux, const int32_t *rows, const int32_t *k, int M,
+                       int Nout, int K, int ldx, int ldw, long long sx, long long sw, long long sy, bool xt, int post) {
+        if (is_half(d.dtype))
+            return launch_grouped_gemm_t(d.dtype, TransposedGemm{x, w, y, aux, rows, k, N, M, Nout, K, ldx, ldw, sx, sw, sy, xt, true,
+                                                                 post, d.tune}, s);
+        F32Gemm g{};
+        g.x = x, g.w = w, g.y = y, g.aux = aux, g.rows_valid = rows, g.k_valid = k;
+        g.N = N, g.Mrows = M, g.Nout = Nout, g.K = K, g.ldx = ldx, g.ldw = ldw, g.sx = sx, g.sw = sw, g.sy = sy;
+        g.x_transposed = xt, g.w_transposed = true, g.post = post, g.tune = d.tune;
+        return launch_grouped_gemm_f32(g, s);
+    };
+    // dpre[r,f] = (sum_c dye[r,c] W2[c,f]) * act'(pre[r,f])
+    SMILE_TRY(product(dye, w2, dpre, pre, kept_count, nullptr, C, F, dm, dm, F, cd, df, cf, false, act));
+    // dW2[c,f] = sum_r dye[r,c] h[r,f]
+    SMILE_TRY(product(dye, h, dw2, nullptr, nullptr, kept_count, dm, F, C, dm, F, cd, cf, df, true, 0));
+    // dxe[r,k] = sum_f dpre[r,f] W1[f,k]
+    SMILE_TRY(product(dpre, w1, dxe, nullptr, kept_count, nullptr, C, dm, F, F, dm, cf, df, cd, false, 0));
+    // dW1[f,k] = sum_r dpre[r,f] xe[r,k]
+    SMILE_TRY(product(dpre, xe, dw1, nullptr, nullptr, kept_count, F, dm, C, F, dm, cf, cd, df, true, 0));
 #undef SMILE_TRY
     return hipSuccess;
 }

@@ -37,7 +37,7 @@
 // capacity this is up to 25 % faster: a workgroup of an empty tile still has to wait for a free slot (its
 // LDS) before it can exit, in turn with the live ones.
 //
-// fp32 kernel (small / reference-precision configurations): classic LDS-tiled FMA GEMM.
+// fp32 storage: gemm_f32.hip.
 #include <type_traits>
 
 #include <hip/hip_ext.h>
@@ -442,103 +442,6 @@ int pick_tile(const Tuning &tune, int N, int C, int Nout, int K)
     return tiles <= 256 ? 1 : 2;
 }
 
-// ------------------------------------------------------------------------------------ fp32 / FMA
-
-template <int ACT>
-__global__ __launch_bounds__(256) void grouped_gemm_nt_f32_kernel(
-    const float *__restrict__ x, const float *__restrict__ w, const float *__restrict__ bias,
-    float *__restrict__ y, const int32_t *__restrict__ kept, int C, int Nout, int K, int row_tiles, int col_tiles,
-    const int32_t *__restrict__ x_rows, const int32_t *__restrict__ y_rows, float *__restrict__ y_tok,
-    const float *__restrict__ gate, float *__restrict__ y2, const float *__restrict__ aux, int post)
-{
-    constexpr int BT = 64, BK = 16;
-    __shared__ float xs[BK][BT + 4];
-    __shared__ float wsh[BK][BT + 4];
-
-    const int per_expert = row_tiles * col_tiles;
-    const int e = blockIdx.x / per_expert;
-    const int rem = blockIdx.x - e * per_expert;
-    const int ct = rem / row_tiles, rt = rem - ct * row_tiles;
-    const int rows = kept ? min(kept[e], C) : C;
-    if (rt * BT >= rows) return;
-
-    const float *X = x + (x_rows ? (size_t)0 : (size_t)e * C * K);
-    const float *W = w + (size_t)e * Nout * K;
-    const int tid = threadIdx.x;
-    const int lr = tid >> 2, lk = (tid & 3) * 4;            // loader: row lr, 4 floats at k offset lk
-    const int xr = min(rt * BT + lr, rows - 1);
-    const int xrow = x_rows ? x_rows[(size_t)e * C + xr] : xr, wrow = min(ct * BT + lr, Nout - 1);
-    const int ty = tid >> 4, tx = tid & 15;                  // compute: rows ty*4.., cols tx*4..
-
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += BK) {
-        f32x4 xv = {0.f, 0.f, 0.f, 0.f}, wv = {0.f, 0.f, 0.f, 0.f};
-        if (k0 + lk < K) {
-            xv = *reinterpret_cast<const f32x4 *>(X + (size_t)xrow * K + k0 + lk);
-            wv = *reinterpret_cast<const f32x4 *>(W + (size_t)wrow * K + k0 + lk);
-        }
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { xs[lk + i][lr] = xv[i]; wsh[lk + i][lr] = wv[i]; }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < BK; ++k) {
-            float xa[4], wb[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { xa[i] = xs[k][ty * 4 + i]; wb[i] = wsh[k][tx * 4 + i]; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(xa[i], wb[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-    float *Y = y ? y + (size_t)e * C * Nout : nullptr;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int row = rt * BT + ty * 4 + i;
-        if (row >= rows) continue;
-        const int tok = y_rows ? y_rows[(size_t)e * C + row] : 0;
-        const float g = y_rows ? gate[tok] : 0.f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int col = ct * BT + tx * 4 + j;
-            if (col >= Nout) continue;
-            float f = acc[i][j];
-            if (bias) f += bias[(size_t)e * Nout + col];
-            if (y2) y2[((size_t)e * C + row) * Nout + col] = f;   // the bare product as well
-            if (post) {   // times act'(aux), with the exact erf form in fp32
-                const float p = aux[((size_t)e * C + row) * Nout + col];
-                f *= post == 1 ? (p > 0.f ? 1.f : 0.f)
-                               : 0.5f * (1.0f + erff(p * 0.70710678118654752f)) +
-                                     p * 0.3989422804014327f * expf(-0.5f * p * p);
-            }
-            f = activate<ACT>(f);
-            if (Y) Y[(size_t)row * Nout + col] = f;
-            if (y_rows) y_tok[(size_t)tok * Nout + col] = f * g;
-        }
-    }
-}
-
-hipError_t launch_f32(const float *x, const float *w, const float *bias, float *y, const int32_t *kept, int N,
-                      int C, int Nout, int K, int act, hipStream_t s, const int32_t *x_rows = nullptr,
-                      const int32_t *y_rows = nullptr, float *y_tok = nullptr, const float *gate = nullptr,
-                      float *y2 = nullptr, const float *aux = nullptr, int post = 0)
-{
-    const int row_tiles = (C + 63) / 64, col_tiles = (Nout + 63) / 64;
-    const dim3 grid(N * row_tiles * col_tiles), block(256);
-    if (act == 0)
-        SMILE_LAUNCH(grouped_gemm_nt_f32_kernel<0>, grid, block, 0, s, x, w, bias, y, kept, C, Nout, K, row_tiles, col_tiles,
-                           x_rows, y_rows, y_tok, gate, y2, aux, post);
-    else if (act == 1)
-        SMILE_LAUNCH(grouped_gemm_nt_f32_kernel<1>, grid, block, 0, s, x, w, bias, y, kept, C, Nout, K, row_tiles, col_tiles,
-                           x_rows, y_rows, y_tok, gate, y2, aux, post);
-    else
-        SMILE_LAUNCH(grouped_gemm_nt_f32_kernel<2>, grid, block, 0, s, x, w, bias, y, kept, C, Nout, K, row_tiles, col_tiles,
-                           x_rows, y_rows, y_tok, gate, y2, aux, post);
-    return hipGetLastError();
-}
-
-
 // dtype dispatch of the two MFMA launchers
 hipError_t launch_half(int dtype, const GemmArgs &a, int N, int act, int tile, const Tuning &tune, hipStream_t s,
                        hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr)
@@ -562,21 +465,26 @@ bool use_persistent_grid(const Tuning &tune, int N, long long tiles, int slots)
     return tiles >= 4LL * slots;
 }
 
+// the fp32 product of the same description (gemm_f32.hip)
+static F32Gemm f32_gemm(const GroupedGemm &g)
+{
+    F32Gemm f{};
+    f.x = g.x, f.w = g.w, f.y = g.y, f.y2 = g.y2, f.bias = g.bias, f.aux = g.aux, f.x_rows = g.x_rows;
+    f.rows_valid = g.kept, f.N = g.N, f.Mrows = g.C, f.Nout = g.Nout, f.K = g.K, f.ldx = g.K, f.ldw = g.K;
+    f.sx = (long long)g.C * g.K, f.sw = (long long)g.Nout * g.K, f.sy = (long long)g.C * g.Nout;
+    f.act = g.act, f.post = g.post, f.tune = g.tune;
+    return f;
+}
+
 hipError_t launch_grouped_gemm_nt(int dtype, const GroupedGemm &g, hipStream_t s)
 {
     const int act = g.act == 0 ? 0 : (g.act == 1 ? 1 : 2);
     if ((g.y2 && act == 0) || (g.post && (act != 0 || g.y2 || !g.aux))) return hipErrorInvalidValue;
-    if (is_half(dtype)) {
-        if (g.K % 64 || g.Nout % 8) return hipErrorInvalidValue;
-        GemmArgs a{g.x, g.w, g.bias, g.y, g.kept, g.C, g.Nout, g.K, 0, 0, 0, g.x_rows, nullptr, nullptr, nullptr, g.y2, g.aux};
-        if (g.y2 || g.post) return launch_half_special(dtype, a, g.N, act, g.post, g.tune, s);
-        return launch_half(dtype, a, g.N, act, pick_tile(g.tune, g.N, g.C, g.Nout, g.K), g.tune, s);
-    }
-    if (g.K % 4) return hipErrorInvalidValue;
-    return launch_f32(static_cast<const float *>(g.x), static_cast<const float *>(g.w),
-                      static_cast<const float *>(g.bias), static_cast<float *>(g.y), g.kept, g.N, g.C, g.Nout, g.K, act,
-                      s, g.x_rows, nullptr, nullptr, nullptr, static_cast<float *>(g.y2),
-                      static_cast<const float *>(g.aux), g.post);
+    if (!is_half(dtype)) return launch_grouped_gemm_f32(f32_gemm(g), s);
+    if (g.K % 64 || g.Nout % 8) return hipErrorInvalidValue;
+    GemmArgs a{g.x, g.w, g.bias, g.y, g.kept, g.C, g.Nout, g.K, 0, 0, 0, g.x_rows, nullptr, nullptr, nullptr, g.y2, g.aux};
+    if (g.y2 || g.post) return launch_half_special(dtype, a, g.N, act, g.post, g.tune, s);
+    return launch_half(dtype, a, g.N, act, pick_tile(g.tune, g.N, g.C, g.Nout, g.K), g.tune, s);
 }
 
 hipError_t launch_expert_ffn_up(const LayerDesc &d, const Workspace &ws, const void *xe,
@@ -601,9 +509,9 @@ hipError_t launch_expert_ffn_up(const LayerDesc &d, const Workspace &ws, const v
         return launch_half(d.dtype, g, N, act, pick_tile(d.tune, N, d.capacity, d.d_ff, d.d_model), d.tune, s, t0, t1);
     }
     if (t0 && t1) (void)hipEventRecord(t0, s);
-    const hipError_t err = launch_f32(static_cast<const float *>(src), static_cast<const float *>(w1),
-                                      static_cast<const float *>(b1), static_cast<float *>(ws.hidden), kept_count, N,
-                                      d.capacity, d.d_ff, d.d_model, act, s, x_rows);
+    const hipError_t err = launch_grouped_gemm_f32(
+        f32_gemm(GroupedGemm{src, w1, ws.hidden, nullptr, kept_count, N, d.capacity, d.d_ff, d.d_model, act, b1, x_rows, nullptr, 0,
+                             d.tune}), s);
     if (t0 && t1) (void)hipEventRecord(t1, s);
     return err;
 }
@@ -620,9 +528,10 @@ hipError_t launch_expert_ffn_down(const LayerDesc &d, const Workspace &ws, const
         GemmArgs g{hidden, w2, b2, ye, kept_count, d.capacity, d.d_model, d.d_ff, 0, 0, 0, nullptr, y_rows, y_tokens, gate};
         return launch_half(d.dtype, g, N, 0, pick_tile(d.tune, N, d.capacity, d.d_model, d.d_ff), d.tune, s);
     }
-    return launch_f32(static_cast<const float *>(hidden), static_cast<const float *>(w2),
-                      static_cast<const float *>(b2), static_cast<float *>(ye), kept_count, N, d.capacity,
-                      d.d_model, d.d_ff, 0, s, nullptr, y_rows, static_cast<float *>(y_tokens), gate);
+    F32Gemm f = f32_gemm(GroupedGemm{hidden, w2, ye, nullptr, kept_count, N, d.capacity, d.d_model, d.d_ff, 0, b2, nullptr, nullptr, 0,
+                                     d.tune});
+    f.y_rows = y_rows, f.y_tok = y_tokens, f.gate = gate;
+    return launch_grouped_gemm_f32(f, s);
 }
 
 }  // namespace smile

@@ -388,6 +388,27 @@ struct TransposedGemm {
 };
 hipError_t launch_grouped_gemm_t(int dtype, const TransposedGemm &g, hipStream_t s);
 
+// One grouped fp32 product y[e][i][j] = sum_k X(i,k) W(j,k), operands and per-group extents as in TransposedGemm
+// (a normal w is [Nout][K]), with the epilogue of GroupedGemm: bias, act (0 none, 1 ReLU, 2 GELU), y2 = the product without
+// the activation, post (1, 2) = times act'(aux), y_tok[y_rows[.]] = gate * row; y may be null when y_rows is given.
+// Supported: neither operand transposed, w only, or both.
+struct F32Gemm {
+    const void *x, *w;
+    void *y;
+    const int32_t *rows_valid = nullptr, *k_valid = nullptr;
+    int N, Mrows, Nout, K, ldx, ldw;
+    long long sx, sw, sy;
+    bool x_transposed = false, w_transposed = false;
+    int act = 0, post = 0;
+    const void *bias = nullptr, *aux = nullptr;
+    void *y2 = nullptr;
+    const int32_t *x_rows = nullptr, *y_rows = nullptr;
+    void *y_tok = nullptr;
+    const float *gate = nullptr;
+    Tuning tune = {};
+};
+hipError_t launch_grouped_gemm_f32(const F32Gemm &g, hipStream_t s);
+
 // Last routing step for the fully fused forward pass: pos_in_group / slot as launch_route's finalize
 // kernel, plus the slot -> token map in ws.slot_token, zero output rows for dropped tokens in y, and
 // (loss.out3 != nullptr) the Eq. 4 loss.
@@ -397,8 +418,7 @@ hipError_t launch_finalize_map(const smile_layer_desc &d, const Workspace &ws, c
 
 // ---- backward pass.  Its workspace is separate from the ctx's and supplied by the caller per call.
 struct BackwardLayout {
-    size_t off_pre, off_h, off_dpre, off_h_t, off_dpre_t, off_dye_t, off_xe_t, off_w_t, off_gw_partial, total;
-    int32_t k_pad;       // capacity rounded up to the GEMM slab depth: contraction length of the weight-gradient GEMMs
+    size_t off_pre, off_h, off_dpre, off_gw_partial, total;
     int32_t gw_blocks;   // token blocks of the router-weight gradient
 };
 BackwardLayout backward_workspace_layout(const smile_layer_desc &d);
