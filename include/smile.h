@@ -164,10 +164,10 @@ smile_status smile_route_bilevel(smile_ctx *ctx, const float *logits_inter, cons
 /* smile_route_bilevel for callers that cannot allocate device memory or create a ctx: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels, same arguments
  * and bit-identical results; instead of a ctx it takes the layer description, and its scratch memory
- * (per-block histograms, partial probability sums, block-local ranks: about 4*(T/256)*(N+2n+2m) +
- * 8*T bytes) is a fixed array of SMILE_STATIC_SCRATCH_BYTES inside the library's device image, which
+ * (per-block histograms, partial probability sums, block-local ranks: 8*T bytes and, up to 65536 tokens,
+ * at most 2 MB, beyond about 4*(T/256)*(N+2n+2m) bytes) is a fixed array of SMILE_STATIC_SCRATCH_BYTES inside the library's device image, which
  * every GPU the library runs on holds until the process ends.  Returns SMILE_WORKSPACE when the shape
- * needs more than that (T = 65536 with 256 experts needs 0.9 MB) and enqueues nothing then.  It calls
+ * needs more than that (T = 65536 with 256 experts needs 1.9 MB) and enqueues nothing then.  It calls
  * no hipMalloc / hipFree and nothing that allocates; the first call on a device looks up the array's
  * address (make that call outside a graph capture).  All calls on one GPU share the array: calls that
  * overlap there (other streams, other threads) race, calls in stream order do not, and no call
@@ -270,16 +270,17 @@ typedef struct smile_layer_io {
 
 /* The whole forward pass in one call: enqueues the six steps above in order on
  * `stream` (gate logits, route, dispatch, expert FFN, combine, loss).  Same checks
- * and bit-identical results as calling them one by one, with fewer launches:
+ * and bit-identical results as calling them one by one, with fewer launches: the router logits
+ * are computed by the kernel that routes them, and the last routing kernel evaluates the loss.
  *   - io->xe and io->ye given: the expert buffers are materialised as by
- *     smile_dispatch / smile_expert_ffn; the last routing step and the loss run
- *     inside the dispatch kernel and the down-projection also writes y (6 launches
- *     instead of 9);
+ *     smile_dispatch / smile_expert_ffn; the last routing kernel moves the rows and the down-projection also
+ *     writes y;
  *   - io->xe == io->ye == NULL: the permutations are fused into the expert GEMMs --
  *     the up-projection gathers its rows from x through a slot -> token map and the
  *     down-projection returns gate-weighted rows straight to y; rows of dropped
- *     tokens are zeroed by the routing (6 launches, 5 for batches of at most
- *     16384 tokens; no [N,C,d] traffic). */
+ *     tokens are zeroed by the routing (no [N,C,d] traffic).
+ * Four launches up to 16384 tokens with up to about 100 experts (three for a batch of at most 64 tokens and 64 KB of
+ * x), five beyond; a group capacity adds one or two. */
 smile_status smile_layer_forward(smile_ctx *ctx, const smile_layer_io *io, void *stream);
 
 /* ---------------------------------------------------------------------------

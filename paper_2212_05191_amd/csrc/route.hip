@@ -1,34 +1,40 @@
 // Bi-level top-1 routing with per-expert capacity (Section 3.2.1, Section 3.2.2 statistics,
-// Section 4.2 capacity), as three small kernels:
+// Section 4.2 capacity).  Tokens are cut into routing blocks; a workgroup decides one block, and the blocks are put in
+// order afterwards:
 //
-//   route_decide   one thread per token: biased logits (both rows fetched at once and kept in registers
-//                  for routers of up to 32 columns) -> top-1 group and local expert, the two softmax
-//                  probabilities (Eq. 1 read as a softmax), the gate p*q (Eq. 3); per-block column sums
-//                  of p and q in a fixed order (wave butterflies for routers of up to 8 columns, an
-//                  LDS tile summed in segments otherwise); the token's rank among
-//                  EARLIER tokens of the same block with the same group / the same expert (wave64
-//                  ballots + per-wave LDS counters combined after one barrier); per-block histograms.
-//   route_scan     one wave per histogram column: exclusive scan along the block axis (turning the
-//                  histograms into block offsets; 64 blocks per shuffle scan), totals, kept counts,
-//                  and the fixed-order sums of p and q.
-//   route_finalize one thread per token: global rank = block offset + in-block rank; capacity cut.
-//                  (The chained forward pass skips this kernel and does the same inside dispatch.)
+//   gate_logits_route  one workgroup per block of 16, 32, 64 or 256 tokens: (chained forward pass) the router logits of the
+//                      block on the matrix cores, then from an LDS tile of the logits: top-1 group and local expert, the
+//                      two softmax probabilities (Eq. 1 read as a softmax), the gate p*q (Eq. 3), column sums of p and
+//                      q, the token's rank among EARLIER tokens of the block with the same group / the same expert
+//                      (wave64 ballots + per-wave LDS counters combined after one barrier), block histograms.
+//   route_finish       one workgroup per block: the offsets of the block (sum of the histograms of the blocks before
+//                      it, one 16-byte load per lane and column), final slots with the capacity cut, and, as the caller
+//                      needs, the slot -> token map, zero output rows of dropped tokens, the row move into the expert
+//                      buffers; the first and last workgroup write the totals, the sums and the loss.
 //
-// With a group capacity (a first-hop buffer of Cg rows per group, Section 3.2.3) two more kernels run
-// between the scan and the last step: route_first_hop recomputes the in-block expert ranks over the
-// tokens whose stage-1 position is below Cg only (the others get a rank no capacity admits), and
-// route_scan_experts scans the new per-block expert histograms.
+// Two launches; a batch small enough for a single workgroup (route_plan) needs only the first one.  More
+// than 256 blocks, or histograms too large for every workgroup to read, take the column scan (route_scan) as a
+// launch of its own, and routers too wide for an LDS tile the kernel that re-reads its rows (route_decide).
 //
-// Everything that decides an integer is integer arithmetic or an fp32 compare of the caller's logits,
+// With a group capacity (a first-hop buffer of Cg rows per group, Section 3.2.3) route_first_hop
+// recomputes the in-block expert ranks over the tokens whose stage-1 position is below Cg only (the others get a rank
+// no capacity admits) between the two.
+//
+// Histograms and partial sums are stored per column, [column][block], so that one load of a wave covers 64-256 blocks.
+//
+// Everything that decides an integer is integer arithmetic or an fp32 compare of the logits,
 // so the result depends only on the logits and the token order, never on the launch geometry.  No
 // atomics order, no inter-workgroup waiting, no memory that must be cleared beforehand.
 #include <algorithm>
 
-#include "smile_internal.hpp"
+#include "gate_device.hpp"
+#include "permute_device.hpp"
 
 namespace smile {
 
 namespace {
+
+typedef mfma_f32x4 f32x4;
 
 __device__ __forceinline__ unsigned long long lanemask_lt()
 {
@@ -97,73 +103,16 @@ __device__ __forceinline__ void top1_softmax(const float *__restrict__ row, cons
     inv_z = 1.0f / z;
 }
 
-// A whole logit row kept in registers (routers of up to CAP columns): every load is issued before the first
-// use, and the argmax, the exp-sum and the per-column probabilities all come from the same registers, so a
-// token waits for memory once per router instead of once per pass.  Columns >= len hold -inf.
-template <int CAP>
-__device__ __forceinline__ void load_row(const float *__restrict__ row, const float *__restrict__ bias, int len,
-                                         float (&a)[CAP])
-{
-    float v[CAP], bv[CAP];
-#pragma unroll
-    for (int k = 0; k < CAP; ++k) {
-        const int i = min(k, len - 1);
-        v[k] = row[i];
-        bv[k] = bias ? bias[i] : 0.f;
-    }
-#pragma unroll
-    for (int k = 0; k < CAP; ++k) a[k] = k < len ? (bias ? __fadd_rn(v[k], bv[k]) : v[k]) : -INFINITY;
-}
-
-template <int CAP>
-__device__ __forceinline__ void top1_softmax_row(const float (&a)[CAP], int &arg, float &mx, float &inv_z)
-{
-    arg = 0;
-    mx = -INFINITY;
-#pragma unroll
-    for (int k = 0; k < CAP; ++k)
-        if (a[k] > mx) { mx = a[k]; arg = k; }   // strict: the lowest index of the maximum wins
-    float z = 0.f;
-#pragma unroll
-    for (int k = 0; k < CAP; ++k) z += exp_neg(a[k] - mx);   // exp2(-inf) = 0 for the padding
-    inv_z = 1.0f / z;
-}
-
-// block_column_sums (below) on a row held in registers
-template <int CAP>
-__device__ __forceinline__ void block_column_sums_row(const float (&a)[CAP], int len, float mx, float inv_z, bool valid,
-                                                      float *__restrict__ part, float *__restrict__ out)
-{
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-    for (int k = 0; k < CAP; ++k) {
-        if (k < len) {   // uniform
-            float v = valid ? exp_neg(a[k] - mx) * inv_z : 0.f;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-            if (lane == 0) part[wave * len + k] = v;
-        }
-    }
-    __syncthreads();
-    for (int c = tid; c < len; c += kRouteBlock) {
-        float sum = part[c];
-#pragma unroll
-        for (int w = 1; w < kRouteBlock / 64; ++w) sum += part[w * len + c];
-        out[c] = sum;
-    }
-    __syncthreads();
-}
-
 constexpr int kColChunk = 32;   // probability columns summed per LDS pass
 
-// Column sums over the block's tokens of prob[t, c] = exp(a[t,c] - mx_t) * inv_z_t, written to out[c], for
-// routers of more than 8 columns: the probabilities go through an LDS tile, 32 columns at a time, and are summed
+// Column sums over the block's tokens of prob[t, c] = exp(a[t,c] - mx_t) * inv_z_t, written to out[c * out_stride]:
+// the probabilities go through an LDS tile, 32 columns at a time, and are summed
 // in a fixed order (8 segments of 32 tokens serially, then the 8 partials serially).  GET(c) yields the biased
-// logit of column c (from registers or from memory).
+// logit of column c.
 template <typename Get>
 __device__ __forceinline__ void block_column_sums_tile(Get get, int len, float mx, float inv_z, bool valid,
                                                        float (*tile)[kColChunk + 1], float (*part)[kColChunk],
-                                                       float *__restrict__ out)
+                                                       float *__restrict__ out, int out_stride)
 {
     const int tid = threadIdx.x;
     for (int c0 = 0; c0 < len; c0 += kColChunk) {
@@ -185,35 +134,335 @@ __device__ __forceinline__ void block_column_sums_tile(Get get, int len, float m
         if (tid < w) {
             float s = 0.f;
             for (int sg = 0; sg < 8; ++sg) s += part[sg][tid];
-            out[c0 + tid] = s;
+            out[(size_t)(c0 + tid) * out_stride] = s;
         }
         __syncthreads();
     }
 }
 
+// Zero the output rows of the block's dropped tokens (to[tk] < 0; Eq. 3 gives them no expert output): a wave looks at 64 tokens
+// at a time and takes every waves-th of the dropped ones.
+__device__ __forceinline__ void zero_dropped_rows(const int32_t *to, int live, int t0, u32x4 *y, int ppr, int wave, int waves)
+{
+    const int lane = __lane_id();
+    int k = 0;
+    for (int tk0 = 0; tk0 < live; tk0 += 64) {
+        unsigned long long mask = __ballot(tk0 + lane < live && to[min(tk0 + lane, live - 1)] < 0);
+        for (; mask; mask &= mask - 1, k = k + 1 == waves ? 0 : k + 1)
+            if (k == wave) zero_row(y + (size_t)(t0 + tk0 + __ffsll((long long)mask) - 1) * ppr, ppr, lane, 64);
+    }
+}
+
+// ------------------------------------------------------------------------------------ decision from an LDS tile
+
+struct RouteArgs {
+    const void *x, *w_inter, *w_intra;   // GATE kernels: the logits are computed here
+    int d;
+    RouteIo io;
+    int T, n, m, bits_n, bits_N, Bp;     // Bp: blocks per column of the histograms
+    Workspace ws;
+    // a batch of one block is finished here
+    bool one;
+    int C, Cg, ppr;
+    RouteTail tail;
+    float alpha, beta;
+};
+
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) { return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true); }
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) { return __int_as_float(dpp<CTRL>(__float_as_int(v))); }
+
+// F combines the lane's value with those of the other lanes of its aligned group of P (4, 8 or 16), one step per factor of two:
+// quad permutations, then mirrored halves (every lane of a finished half holds the same value).
+template <int P, typename F>
+__device__ __forceinline__ void group_reduce(F step)
+{
+    step(std::integral_constant<int, 0xB1>{});                       // lane ^ 1
+    step(std::integral_constant<int, 0x4E>{});                       // lane ^ 2
+    if constexpr (P >= 8) step(std::integral_constant<int, 0x141>{});    // mirror of 8
+    if constexpr (P >= 16) step(std::integral_constant<int, 0x140>{});   // mirror of 16
+}
+
+// Softmax and top-1 of one logit row in LDS by the P neighbouring lanes that own the token (columns part, part + P, ...):
+// lowest index of the maximum of row + bias, its probability, and the row overwritten with all probabilities (zeros
+// for a token that does not exist).  K > 0: at most K P columns, held in registers between the passes.
+template <int P, int K>
+__device__ __forceinline__ void softmax_top1(float *row, const float *__restrict__ bias, int len, int part, bool valid, int &arg,
+                                             float &p_top)
+{
+    float mx = -INFINITY, z = 0.f, v[K > 0 ? K : 1];
+    arg = len;
+    auto look = [&](int c, float a) {
+        if (a > mx) { mx = a; arg = c; }   // strict: the lowest index of the maximum wins
+    };
+    if constexpr (K > 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int c = part + k * P;
+            v[k] = c < len ? row[c] : -INFINITY;
+            if (bias && c < len) v[k] = __fadd_rn(v[k], bias[c]);
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) look(part + k * P, v[k]);
+    } else {
+        for (int c = part; c < len; c += P) {
+            float a = row[c];
+            if (bias) { a = __fadd_rn(a, bias[c]); row[c] = a; }
+            look(c, a);
+        }
+    }
+    group_reduce<P>([&](auto ctrl) {
+        const float ov = dpp<decltype(ctrl)::value>(mx);
+        const int oa = dpp<decltype(ctrl)::value>(arg);
+        if (ov > mx || (ov == mx && oa < arg)) { mx = ov; arg = oa; }
+    });
+    arg = min(arg, len - 1);
+    if constexpr (K > 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            v[k] = exp_neg(v[k] - mx);   // exp2(-inf) = 0 for the padding
+            z += v[k];
+        }
+    } else {
+        for (int c = part; c < len; c += P) {
+            const float p = exp_neg(row[c] - mx);
+            row[c] = p;
+            z += p;
+        }
+    }
+    group_reduce<P>([&](auto ctrl) { z += dpp<decltype(ctrl)::value>(z); });
+    p_top = 1.0f / z;
+    if constexpr (K > 0) {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (part + k * P < len) row[part + k * P] = valid ? v[k] * p_top : 0.f;
+    } else {
+        for (int c = part; c < len; c += P) row[c] = valid ? row[c] * p_top : 0.f;
+    }
+}
+
+// NT threads, P per token: blocks of NT / P tokens.  GATE: logits from x and the router weights (16 * CT columns per pass
+// over the block's rows, which come from L2 after the first), else from memory.
+// Dynamic LDS (route_lds_bytes): logit / probability tile, 8 segment sums per column, packed decisions, per-wave counters,
+// counts and sums for the loss.
+// Bound: the read of x (GATE), else latency.  One CU draws about 28 GB/s from HBM however much it requests, so the blocks
+// are as small as leaves 256 of them; several threads per token because a token's serial loops over its columns are what
+// a wave spends its time on.  Measured against a gate kernel and a decision kernel with one thread per token (us, routing
+// and block order included): 512 tokens fp32 13 -> 10, 128 tokens of 768 16 -> 12, 8192 of 768 20 -> 17, 16384 of
+// 1024 29 -> 23, 32768 of 768 with 16 + 8 columns 39 -> 36 and with 129 columns 127 -> 72; 65536 of 1024 with 40 columns
+// 71 -> 74 (the launch saved there is no more than the wait of 1024 resident blocks for the read of x).
+template <int DT, int CT, int NT, int P, bool GATE>
+__global__ __launch_bounds__(NT, (NT == 1024 || (CT > 1 && CT <= 3) ? 4 : 2)) void gate_logits_route_kernel(RouteArgs a)
+{
+    constexpr int RB = NT / P, kRankWaves = (RB + 63) / 64, kWaves = NT / 64;
+    extern __shared__ float lds_f[];
+    const int n = a.n, m = a.m, N = n * m, cols = n + m, stride = cols | 1, NC = N + n;
+    float *tile = lds_f;                                                    // [RB][stride]
+    float *seg_sum = tile + RB * stride;                                    // [8][cols]
+    int32_t *decision = reinterpret_cast<int32_t *>(seg_sum + 8 * cols);    // [RB] e | g << 12, -1 beyond T
+    int32_t *hist = decision + RB;                                          // [kRankWaves][N experts, then n groups]
+    int32_t *cnt = hist + kRankWaves * NC;                                  // [cols]  (one block only)
+    float *sum = reinterpret_cast<float *>(cnt + cols);                     // [cols]
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int b = blockIdx.x, t0 = b * RB, live = min(RB, a.T - t0);
+
+    for (int i = tid; i < kRankWaves * NC; i += NT) hist[i] = 0;
+
+    // logit rows between memory and the tile: a power-of-two number of neighbouring threads per row (no divisions)
+    auto copy_rows = [&](auto to_lds, float *at, const float *src, float *dst, int len) {
+        const int sh = min(32 - __clz(max(len, 2) - 1), 6), rows = NT >> sh;
+        for (int r = tid >> sh; r < live; r += rows)
+            for (int c = tid & ((1 << sh) - 1); c < len; c += 1 << sh) {
+                if constexpr (decltype(to_lds)::value) at[r * stride + c] = src[(size_t)r * len + c];
+                else dst[(size_t)r * len + c] = at[r * stride + c];
+            }
+    };
+    if constexpr (GATE) {
+        constexpr int RT = RB < 64 ? RB / 16 : 4;               // row tiles per unit of four waves: at most 64 tokens
+        constexpr int kAhead = CT * RT <= 4 ? 3 : NT < 1024 && CT * RT <= 6 ? 2 : 1;   // chunks in flight, as registers allow
+        const int unit = wave / kGateWaves, uw = wave % kGateWaves, r16 = lane & 15, kg = lane >> 4;
+        const bool any = unit * 64 < live;
+#pragma unroll 1
+        for (int col0 = 0; col0 < cols; col0 += 16 * CT) {
+            f32x4 acc[RT][CT];
+            if (any) gate_partial<DT, CT, RT, kAhead>(a.x, a.w_inter, a.w_intra, t0 + unit * 64, a.T, a.d, n, m, col0, uw, acc);
+            // the four partial sums are added in wave order (all reads of a turn before its writes)
+            float *at = tile + (unit * 64 + kg * 4) * stride + col0 + r16;
+#pragma unroll 1
+            for (int w = 0; w < kGateWaves; ++w) {
+                if (any && uw == w) {
+                    if (w > 0) {
+#pragma unroll
+                        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                            for (int ct = 0; ct < CT; ++ct)
+                                if (col0 + ct * 16 + r16 < cols)
+#pragma unroll
+                                    for (int i = 0; i < 4; ++i) acc[rt][ct][i] = at[(rt * 16 + i) * stride + ct * 16] + acc[rt][ct][i];
+                    }
+#pragma unroll
+                    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                        for (int ct = 0; ct < CT; ++ct)
+                            if (col0 + ct * 16 + r16 < cols)
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) at[(rt * 16 + i) * stride + ct * 16] = acc[rt][ct][i];
+                }
+                __syncthreads();
+            }
+        }
+        copy_rows(std::false_type{}, tile, nullptr, a.io.logits_inter + (size_t)t0 * n, n);
+        copy_rows(std::false_type{}, tile + n, nullptr, a.io.logits_intra + (size_t)t0 * m, m);
+    } else {
+        copy_rows(std::true_type{}, tile, a.io.logits_inter + (size_t)t0 * n, nullptr, n);
+        copy_rows(std::true_type{}, tile + n, a.io.logits_intra + (size_t)t0 * m, nullptr, m);
+    }
+    __syncthreads();
+
+    {   // ---- top-1 at both levels
+        const int tk = tid / P, part = tid % P, t = t0 + tk;
+        const bool valid = tk < live;
+        int g, l;
+        float p_top, q_top;
+        float *row = tile + tk * stride;
+        auto level = [&](float *r, const float *bias, int len, int &arg, float &top) {
+            if (len <= 2 * P) softmax_top1<P, 2>(r, bias, len, part, valid, arg, top);
+            else if (len <= 8 * P) softmax_top1<P, 8>(r, bias, len, part, valid, arg, top);
+            else softmax_top1<P, 0>(r, bias, len, part, valid, arg, top);
+        };
+        level(row, a.io.bias_inter, n, g, p_top);
+        level(row + n, a.io.bias_intra && valid ? a.io.bias_intra + (size_t)g * m : nullptr, m, l, q_top);
+        if (part == 0) decision[tk] = valid ? (g * m + l) | (g << 12) : -1;
+        if (valid && part == 0) {
+            a.io.group_idx[t] = g;
+            a.io.local_idx[t] = l;
+            a.io.p_top[t] = p_top;
+            a.io.q_top[t] = q_top;
+            a.io.gate[t] = p_top * q_top;
+        }
+    }
+    __syncthreads();
+
+    // ---- rank among earlier tokens of this block with the same expert / the same group: one thread per token
+    const bool ranks = tid < RB;
+    const int dec = ranks ? decision[tid] : -1, e = dec & 4095, g = dec >> 12;
+    const bool ok = dec >= 0;
+    int rank = 0, pos = 0;
+    // counts the tokens of `in` by expert (and group) into the per-wave counters
+    auto count = [&](bool in, unsigned long long &me, unsigned long long *mg) {
+        me = match_any(e, a.bits_N, in);
+        if (mg) *mg = match_any(g, a.bits_n, in);
+        if (in) {   // the last lane of each matching set publishes the wave's count
+            if (63 - __clzll(me) == lane) hist[wave * NC + e] = __popcll(me);
+            if (mg && 63 - __clzll(*mg) == lane) hist[wave * NC + N + g] = __popcll(*mg);
+        }
+    };
+    auto total = [&](int i) {
+        int c = 0;
+#pragma unroll
+        for (int w = 0; w < kRankWaves; ++w) c += hist[w * NC + i];
+        return c;
+    };
+    unsigned long long me = 0, mg = 0;
+    if (ranks) count(ok, me, &mg);
+    // column sums of p and q in a fixed order: eight segments of the block, then the eight
+    for (int seg = kWaves - 1 - wave; seg < 8; seg += kWaves)   // the waves without a rank start first
+        for (int c = lane; c < cols; c += 64) {
+            float s = 0.f;
+#pragma unroll 8
+            for (int j = 0; j < RB / 8; ++j) s += tile[(seg * (RB / 8) + j) * stride + c];
+            seg_sum[seg * cols + c] = s;
+        }
+    __syncthreads();
+    if (ok) {
+        for (int w = 0; w < wave; ++w) {
+            rank += hist[w * NC + e];
+            pos += hist[w * NC + N + g];
+        }
+        rank += __popcll(me & lanemask_lt());
+        pos += __popcll(mg & lanemask_lt());
+    }
+    for (int c = tid; c < cols; c += NT) {
+        float s = seg_sum[c];
+#pragma unroll
+        for (int seg = 1; seg < 8; ++seg) s += seg_sum[seg * cols + c];
+        if (a.one) {
+            sum[c] = s;
+            (c < n ? a.io.p_sum : a.io.q_sum - n)[c] = s;
+        } else if (c < n) {
+            a.ws.block_p_sum[(size_t)c * a.Bp + b] = s;
+        } else {
+            a.ws.block_q_sum[(size_t)(c - n) * a.Bp + b] = s;
+        }
+    }
+    for (int j = tid; j < cols; j += NT) {   // counts by group and, summed over the groups, by local index
+        int c = 0;
+        if (j < n) c = total(N + j);
+        else for (int i = 0; i < n; ++i) c += total(i * m + j - n);
+        if (a.one) {
+            cnt[j] = c;
+            (j < n ? a.io.group_count : a.io.local_count - n)[j] = c;
+        } else {
+            a.ws.block_group_hist[(size_t)j * a.Bp + b] = c;
+        }
+    }
+    if (!a.one) {
+        for (int i = tid; i < N; i += NT) a.ws.block_expert_hist[(size_t)i * a.Bp + b] = total(i);
+        if (ok) {
+            a.ws.rank_in_block[t0 + tid] = rank;
+            a.ws.pos_in_block[t0 + tid] = pos;
+        }
+        return;
+    }
+
+    // ---- the only block: ranks and counts are final
+    for (int i = tid; i < N; i += NT) {
+        const int c = total(i);
+        a.io.expert_count[i] = c;
+        if (a.Cg == 0) a.io.kept_count[i] = min(c, a.C);
+    }
+    if (a.Cg > 0) {   // ranks again over the tokens that pass the first hop
+        const bool through = ok && pos < a.Cg;
+        __syncthreads();
+        for (int i = tid; i < kRankWaves * NC; i += NT) hist[i] = 0;
+        __syncthreads();
+        if (ranks) count(through, me, nullptr);
+        __syncthreads();
+        rank = kHop1Dropped;
+        if (through) {
+            rank = __popcll(me & lanemask_lt());
+            for (int w = 0; w < wave; ++w) rank += hist[w * NC + e];
+        }
+        for (int i = tid; i < N; i += NT) a.io.kept_count[i] = min(total(i), a.C);
+    }
+    if (ok) {
+        const int sl = rank < a.C ? rank : -1;
+        a.io.slot[t0 + tid] = sl;
+        a.io.pos_in_group[t0 + tid] = pos;
+        if (sl >= 0 && a.tail.slot_token) a.tail.slot_token[(size_t)e * a.C + sl] = t0 + tid;
+        decision[tid] = sl;
+    }
+    __syncthreads();
+    if (a.tail.loss3 && wave == 0) aux_loss_wave(cnt, cnt + n, sum, sum + n, a.T, n, m, a.alpha, a.beta, a.tail.loss3);
+    if (a.tail.y) zero_dropped_rows(decision, live, t0, static_cast<u32x4 *>(a.tail.y), a.ppr, wave, kWaves);
+}
+
+// ------------------------------------------------------------------------------------ decision, very wide routers
+
+// One thread per token, rows re-read from memory by every pass, probabilities through a 32-column LDS tile.
 // PERWAVE: every wave counts into its own copy of the LDS histograms and the copies are combined after one
 // barrier (needs 4 x (N + n) counters); otherwise the four waves take turns on one copy.
-// CP / CQ: register capacity for the inter / intra logit row (0: rows longer than 32 columns are re-read from
-// memory by every pass).
-template <bool PERWAVE, int CP, int CQ>
-__global__ __launch_bounds__(kRouteBlock) void route_decide_kernel(
-    const float *__restrict__ logits_inter, const float *__restrict__ logits_intra,
-    const float *__restrict__ bias_inter, const float *__restrict__ bias_intra,
-    int T, int n, int m, int bits_n, int bits_N,
-    int32_t *__restrict__ group_idx, int32_t *__restrict__ local_idx,
-    int32_t *__restrict__ pos_in_block, int32_t *__restrict__ rank_in_block,
-    float *__restrict__ gate, float *__restrict__ p_top, float *__restrict__ q_top,
-    int32_t *__restrict__ block_expert_hist, int32_t *__restrict__ block_group_hist,
-    float *__restrict__ block_p_sum, float *__restrict__ block_q_sum)
+template <bool PERWAVE>
+__global__ __launch_bounds__(kRouteBlock) void route_decide_kernel(RouteArgs a)
 {
-    // [N] expert counters then [n] group counters (PERWAVE: one such set per wave); reused afterwards as the
-    // [4][max(n, m)] partial probability sums (both fit: n, m <= N + n)
+    // [N] expert counters then [n] group counters (PERWAVE: one such set per wave)
     extern __shared__ int32_t hist[];
     __shared__ float tile[kRouteBlock][kColChunk + 1];
     __shared__ float part8[8][kColChunk];
     constexpr int kWaves = kRouteBlock / 64;
 
-    const int N = n * m, NC = N + n;
+    const int T = a.T, n = a.n, m = a.m, N = n * m, NC = N + n;
     const int tid = threadIdx.x;
     const int b = blockIdx.x;
     const int t = b * kRouteBlock + tid;
@@ -223,37 +472,25 @@ __global__ __launch_bounds__(kRouteBlock) void route_decide_kernel(
 
     int g = 0, l = 0;
     float mx_p = 0.f, iz_p = 0.f, mx_q = 0.f, iz_q = 0.f;
-    const float *rp = logits_inter + (size_t)(valid ? t : 0) * n;
-    const float *rq = logits_intra + (size_t)(valid ? t : 0) * m;
+    const float *rp = a.io.logits_inter + (size_t)(valid ? t : 0) * n;
+    const float *rq = a.io.logits_intra + (size_t)(valid ? t : 0) * m;
     const float *bq = nullptr;
-    float ap[CP > 0 ? CP : 1], aq[CQ > 0 ? CQ : 1];
     if (valid) {
-        // the intra row does not depend on the chosen group (only its bias row does): fetch both rows at once
-        if constexpr (CP > 0) load_row<CP>(rp, bias_inter, n, ap);
-        if constexpr (CQ > 0) {
-            if (!bias_intra) load_row<CQ>(rq, nullptr, m, aq);
-        }
-        if constexpr (CP > 0) top1_softmax_row<CP>(ap, g, mx_p, iz_p);
-        else top1_softmax(rp, bias_inter, n, g, mx_p, iz_p);
-        bq = bias_intra ? bias_intra + (size_t)g * m : nullptr;
-        if constexpr (CQ > 0) {
-            if (bias_intra) load_row<CQ>(rq, bq, m, aq);
-            top1_softmax_row<CQ>(aq, l, mx_q, iz_q);
-        } else {
-            top1_softmax(rq, bq, m, l, mx_q, iz_q);
-        }
-        group_idx[t] = g;
-        local_idx[t] = l;
-        p_top[t] = iz_p;
-        q_top[t] = iz_q;
-        gate[t] = iz_p * iz_q;
+        top1_softmax(rp, a.io.bias_inter, n, g, mx_p, iz_p);
+        bq = a.io.bias_intra ? a.io.bias_intra + (size_t)g * m : nullptr;
+        top1_softmax(rq, bq, m, l, mx_q, iz_q);
+        a.io.group_idx[t] = g;
+        a.io.local_idx[t] = l;
+        a.io.p_top[t] = iz_p;
+        a.io.q_top[t] = iz_q;
+        a.io.gate[t] = iz_p * iz_q;
     }
     __syncthreads();   // counters are zero
 
     // rank among earlier tokens of this block with the same expert / the same group
     const int e = g * m + l;
-    const unsigned long long me = match_any(e, bits_N, valid);
-    const unsigned long long mg = match_any(g, bits_n, valid);
+    const unsigned long long me = match_any(e, a.bits_N, valid);
+    const unsigned long long mg = match_any(g, a.bits_n, valid);
     const unsigned long long lt = lanemask_lt();
     const int lane = __lane_id();
     const int wave = tid >> 6;
@@ -270,28 +507,8 @@ __global__ __launch_bounds__(kRouteBlock) void route_decide_kernel(
                 base_e += hist[w * NC + e];
                 base_g += hist[w * NC + N + g];
             }
-            rank_in_block[t] = base_e + __popcll(me & lt);
-            pos_in_block[t] = base_g + __popcll(mg & lt);
-        }
-        for (int i = tid; i < N; i += kRouteBlock) {
-            int c = 0;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) c += hist[w * NC + i];
-            block_expert_hist[(size_t)b * N + i] = c;
-        }
-        for (int i = tid; i < n; i += kRouteBlock) {
-            int c = 0;
-#pragma unroll
-            for (int w = 0; w < kWaves; ++w) c += hist[w * NC + N + i];
-            block_group_hist[(size_t)b * n + i] = c;
-        }
-        // per-block counts by local index (summed over groups), stored behind the [B][n] group histograms
-        for (int j = tid; j < m; j += kRouteBlock) {
-            int c = 0;
-            for (int i = 0; i < n; ++i)
-#pragma unroll
-                for (int w = 0; w < kWaves; ++w) c += hist[w * NC + i * m + j];
-            block_group_hist[(size_t)gridDim.x * n + (size_t)b * m + j] = c;
+            a.ws.rank_in_block[t] = base_e + __popcll(me & lt);
+            a.ws.pos_in_block[t] = base_g + __popcll(mg & lt);
         }
     } else {
         int32_t *ghist = hist + N;
@@ -299,85 +516,213 @@ __global__ __launch_bounds__(kRouteBlock) void route_decide_kernel(
             if (wave == w && valid) {
                 const int base_e = hist[e];
                 const int base_g = ghist[g];
-                rank_in_block[t] = base_e + __popcll(me & lt);
-                pos_in_block[t] = base_g + __popcll(mg & lt);
+                a.ws.rank_in_block[t] = base_e + __popcll(me & lt);
+                a.ws.pos_in_block[t] = base_g + __popcll(mg & lt);
                 if (63 - __clzll(me) == lane) hist[e] = base_e + __popcll(me);
                 if (63 - __clzll(mg) == lane) ghist[g] = base_g + __popcll(mg);
             }
             __syncthreads();
         }
-        for (int i = tid; i < N; i += kRouteBlock) block_expert_hist[(size_t)b * N + i] = hist[i];
-        for (int i = tid; i < n; i += kRouteBlock) block_group_hist[(size_t)b * n + i] = ghist[i];
-        for (int j = tid; j < m; j += kRouteBlock) {
-            int c = 0;
-            for (int i = 0; i < n; ++i) c += hist[i * m + j];
-            block_group_hist[(size_t)gridDim.x * n + (size_t)b * m + j] = c;
-        }
     }
-    __syncthreads();   // the counters have been read: the memory becomes the partial-sum buffer
+    auto total = [&](int i) {
+        int c = 0;
+#pragma unroll
+        for (int w = 0; w < (PERWAVE ? kWaves : 1); ++w) c += hist[w * NC + i];
+        return c;
+    };
+    for (int i = tid; i < N; i += kRouteBlock) a.ws.block_expert_hist[(size_t)i * a.Bp + b] = total(i);
+    // counts by group, then by local index (summed over groups)
+    for (int j = tid; j < n + m; j += kRouteBlock) {
+        int c = 0;
+        if (j < n) c = total(N + j);
+        else for (int i = 0; i < n; ++i) c += total(i * m + j - n);
+        a.ws.block_group_hist[(size_t)j * a.Bp + b] = c;
+    }
+    __syncthreads();
 
-    // per-block column sums of p and q: wave butterflies for routers of at most 8 columns (registers), else
-    // through the LDS tile
-    float *part = reinterpret_cast<float *>(hist);
-    if constexpr (CP == 8) {
-        block_column_sums_row<CP>(ap, n, mx_p, iz_p, valid, part, block_p_sum + (size_t)b * n);
-    } else if constexpr (CP > 0) {
-        block_column_sums_tile([&](int c0, int w, float *dst) {
-#pragma unroll
-            for (int k = 0; k < CP; ++k)
-                if (k >= c0 && k < c0 + w) dst[k - c0] = ap[k];
-        }, n, mx_p, iz_p, valid, tile, part8, block_p_sum + (size_t)b * n);
-    } else {
-        block_column_sums_tile([&](int c0, int w, float *dst) {
+    auto from = [&](const float *row, const float *bias, int len) {
+        return [=](int c0, int w, float *dst) {
             if (!valid) return;
             for (int i0 = 0; i0 < w; i0 += kLoadChunk) {
-                float a[kLoadChunk];
-                load_biased(rp, bias_inter, c0 + i0, n, -INFINITY, a);
+                float v[kLoadChunk];
+                load_biased(row, bias, c0 + i0, len, -INFINITY, v);
 #pragma unroll
                 for (int k = 0; k < kLoadChunk; ++k)
-                    if (i0 + k < w) dst[i0 + k] = a[k];
+                    if (i0 + k < w) dst[i0 + k] = v[k];
             }
-        }, n, mx_p, iz_p, valid, tile, part8, block_p_sum + (size_t)b * n);
-    }
-    if constexpr (CQ == 8) {
-        block_column_sums_row<CQ>(aq, m, mx_q, iz_q, valid, part, block_q_sum + (size_t)b * m);
-    } else if constexpr (CQ > 0) {
-        block_column_sums_tile([&](int c0, int w, float *dst) {
+        };
+    };
+    block_column_sums_tile(from(rp, a.io.bias_inter, n), n, mx_p, iz_p, valid, tile, part8, a.ws.block_p_sum + b, a.Bp);
+    block_column_sums_tile(from(rq, bq, m), m, mx_q, iz_q, valid, tile, part8, a.ws.block_q_sum + b, a.Bp);
+}
+
+// ------------------------------------------------------------------------------------ order of the blocks
+
+__device__ __forceinline__ int wave_sum(int v)
+{
 #pragma unroll
-            for (int k = 0; k < CQ; ++k)
-                if (k >= c0 && k < c0 + w) dst[k - c0] = aq[k];
-        }, m, mx_q, iz_q, valid, tile, part8, block_q_sum + (size_t)b * m);
-    } else {
-        block_column_sums_tile([&](int c0, int w, float *dst) {
-            if (!valid) return;
-            for (int i0 = 0; i0 < w; i0 += kLoadChunk) {
-                float a[kLoadChunk];
-                load_biased(rq, bq, c0 + i0, m, -INFINITY, a);
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+// Sums over the blocks before block b (b <= 256) of `count` histogram columns ([column][Bp], Bp a multiple of 4): out(c, sum) is
+// called by one lane per column.  A column of Bp counts is Bp / 4 16-byte loads, so 2^sh >= Bp / 4 lanes take a column, a wave 64 >> sh
+// of them at once, eight such groups in flight.
+template <typename Out>
+__device__ __forceinline__ void column_prefixes(const int32_t *__restrict__ hist, int Bp, int count, int b, int wave, int waves, Out out)
+{
+    const int lane = __lane_id();
+    const int sh = 32 - __clz(max((Bp >> 2) - 1, 0)), per = 64 >> sh;   // Bp <= 256: sh <= 6
+    const int k = 4 * (lane & ((1 << sh) - 1)), sub = lane >> sh;
+    constexpr int kFlight = 8;
+    for (int c0 = wave * per; c0 < count; c0 += waves * per * kFlight) {
+        int4 v[kFlight];
 #pragma unroll
-                for (int k = 0; k < kLoadChunk; ++k)
-                    if (i0 + k < w) dst[i0 + k] = a[k];
-            }
-        }, m, mx_q, iz_q, valid, tile, part8, block_q_sum + (size_t)b * m);
+        for (int u = 0; u < kFlight; ++u) {
+            const int c = c0 + u * waves * per + sub;
+            v[u] = int4{0, 0, 0, 0};
+            if (c < count && k < b) v[u] = *reinterpret_cast<const int4 *>(hist + (size_t)c * Bp + k);   // k + 3 < Bp
+        }
+#pragma unroll
+        for (int u = 0; u < kFlight; ++u) {
+            if (c0 + u * waves * per >= count) break;   // uniform
+            int s = v[u].x + (k + 1 < b ? v[u].y : 0) + (k + 2 < b ? v[u].z : 0) + (k + 3 < b ? v[u].w : 0);
+            // window sums over 2^sh lanes ending at each lane; the last lane of a column has its total
+            if (sh > 0) s += dpp<0x111>(s);   // row_shr 1, 2, 4, 8: rows of 16 lanes
+            if (sh > 1) s += dpp<0x112>(s);
+            if (sh > 2) s += dpp<0x114>(s);
+            if (sh > 3) s += dpp<0x118>(s);
+            if (sh > 4) s += dpp<0x142>(s);   // row_bcast 15, 31: the last lane of the row(s) before
+            if (sh > 5) s += dpp<0x143>(s);
+            const int c = c0 + u * waves * per + sub;
+            if (k == 4 * ((1 << sh) - 1) && c < count) out(c, s);
+        }
     }
 }
 
-// Exclusive scan along the block axis of one histogram column (64 blocks per step, one per lane,
-// Hillis-Steele over the wave); returns the column total.  hist[b*stride + col] is rewritten in place.
-__device__ __forceinline__ int wave_scan_column(int32_t *__restrict__ hist, int B, int stride, int col)
+struct FinishArgs {
+    RouteIo io;
+    Workspace ws;
+    const int32_t *expert_off_hist;   // histograms the slots follow: block_expert_hist, or those of the first hop
+    int T, RB, B, Bp, n, m, C, ppr;
+    RouteTail tail;
+    float alpha, beta;
+};
+
+// Two workgroups for the totals (dispatched first, they take longest): workgroup 0 writes the counts by
+// group and local index, the probability sums and the loss, workgroup 1 the expert counts.  Then one per routing block, tokens of a
+// block <= its threads.  LPR > 0: the rows of the block's tokens are
+// moved to the expert buffers by LPR lanes each.  Dynamic LDS: [N + n] offsets, [RB] destinations, or [n + m] counts, [n + m] sums.
+// Latency-bound except for the row moves: one round of loads for the offsets, one for the tokens, the stores.
+template <int LPR>
+__global__ __launch_bounds__(1024) void route_finish_kernel(FinishArgs a)
 {
-    const int lane = __lane_id();
-    int carry = 0;
-    for (int b0 = 0; b0 < B; b0 += 64) {
-        const int b = b0 + lane;
-        const int v = b < B ? hist[(size_t)b * stride + col] : 0;
-        int incl = v;
+    extern __shared__ int32_t lds_i[];
+    const int n = a.n, m = a.m, N = n * m, cols = n + m, b = (int)blockIdx.x - 2, Bp = a.Bp;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, waves = blockDim.x >> 6;
+    if (b == -2) {
+        int32_t *cnt = lds_i;
+        float *sum = reinterpret_cast<float *>(cnt + cols);
+        column_prefixes(a.ws.block_group_hist, Bp, cols, a.B, wave, waves, [&](int c, int s) {
+            cnt[c] = s;
+            (c < n ? a.io.group_count : a.io.local_count - n)[c] = s;
+        });
+        for (int c0 = wave; c0 < cols; c0 += waves * 4) {   // four columns in flight
+            float s[4];
 #pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int up = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += up;
+            for (int u = 0; u < 4; ++u) {
+                const int c = c0 + u * waves;
+                s[u] = 0.f;
+                if (c < cols)
+                    for (int k = lane; k < a.B; k += 64) s[u] += c < n ? a.ws.block_p_sum[(size_t)c * Bp + k] : a.ws.block_q_sum[(size_t)(c - n) * Bp + k];
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int c = c0 + u * waves;
+#pragma unroll
+                for (int off = 32; off > 0; off >>= 1) s[u] += __shfl_xor(s[u], off, 64);
+                if (lane == 0 && c < cols) {
+                    sum[c] = s[u];
+                    (c < n ? a.io.p_sum : a.io.q_sum - n)[c] = s[u];
+                }
+            }
         }
-        if (b < B) hist[(size_t)b * stride + col] = carry + incl - v;
-        carry += __shfl(incl, 63, 64);
+        __syncthreads();
+        if (a.tail.loss3 && wave == 0) aux_loss_wave(cnt, cnt + n, sum, sum + n, a.T, n, m, a.alpha, a.beta, a.tail.loss3);
+        return;
+    }
+    if (b == -1) {
+        const int32_t *own = a.ws.block_expert_hist;
+        const bool hop = a.expert_off_hist != own;   // with a first-hop limit the counts before drops come from other histograms
+        column_prefixes(a.expert_off_hist, Bp, N, a.B, wave, waves, [&](int e, int s) {
+            a.io.kept_count[e] = min(s, a.C);
+            if (!hop) a.io.expert_count[e] = s;
+        });
+        if (hop) column_prefixes(own, Bp, N, a.B, wave, waves, [&](int e, int s) { a.io.expert_count[e] = s; });
+        return;
+    }
+
+    int32_t *dest = lds_i + N + n;
+    const int t0 = b * a.RB, live = min(a.RB, a.T - t0);
+    int g = 0, e = 0, rank = 0, pos = 0;
+    if (tid < live) {   // requested before the offsets
+        const int t = t0 + tid;
+        g = a.io.group_idx[t], e = g * m + a.io.local_idx[t];
+        rank = a.ws.rank_in_block[t], pos = a.ws.pos_in_block[t];
+    }
+    column_prefixes(a.expert_off_hist, Bp, N, b, wave, waves, [&](int c, int s) { lds_i[c] = s; });
+    column_prefixes(a.ws.block_group_hist, Bp, n, b, wave, waves, [&](int c, int s) { lds_i[N + c] = s; });
+    __syncthreads();
+    if (tid < live) {
+        const int t = t0 + tid;
+        rank += lds_i[e];
+        const int sl = rank < a.C ? rank : -1;
+        a.io.slot[t] = sl;
+        a.io.pos_in_group[t] = lds_i[N + g] + pos;
+        if (sl >= 0 && a.tail.slot_token) a.tail.slot_token[(size_t)e * a.C + sl] = t;
+        dest[tid] = sl < 0 ? -1 : e * a.C + sl;   // N*C < 2^31
+    }
+    __syncthreads();
+    if constexpr (LPR > 0) {
+        const int rows = blockDim.x / LPR, sub = tid % LPR;
+        for (int tk = tid / LPR; tk < live; tk += rows) {
+            const int to = dest[tk];
+            const size_t t = t0 + tk;
+            if (to < 0) zero_row(static_cast<u32x4 *>(a.tail.y) + t * a.ppr, a.ppr, sub, LPR);
+            else
+                move_row<LPR>(static_cast<const u32x4 *>(a.tail.x) + t * a.ppr, static_cast<u32x4 *>(a.tail.xe) + (size_t)to * a.ppr, a.ppr, sub,
+                              [](u32x4 v) { return v; });
+        }
+    } else if (a.tail.y) {
+        zero_dropped_rows(dest, live, t0, static_cast<u32x4 *>(a.tail.y), a.ppr, wave, waves);
+    }
+}
+
+// Exclusive scan along the block axis of one histogram column by one wave, 1024 blocks per step with all their loads in
+// flight; returns the column total.  hist[col*Bp + b] is rewritten in place.
+__device__ __forceinline__ int wave_scan_column(int32_t *__restrict__ hist, int B, int Bp, int col)
+{
+    constexpr int kFlight = 16;
+    const int lane = __lane_id();
+    int32_t *h = hist + (size_t)col * Bp;
+    int carry = 0;
+    for (int b0 = 0; b0 < B; b0 += 64 * kFlight) {
+        int v[kFlight];
+#pragma unroll
+        for (int k = 0; k < kFlight; ++k) v[k] = b0 + k * 64 + lane < B ? h[b0 + k * 64 + lane] : 0;
+#pragma unroll
+        for (int k = 0; k < kFlight; ++k) {
+            if (b0 + k * 64 >= B) break;   // uniform
+            int incl = v[k];               // inclusive prefix over the wave: rows of 16 lanes, then across rows
+            incl += dpp<0x111>(incl);
+            incl += dpp<0x112>(incl);
+            incl += dpp<0x114>(incl);
+            incl += dpp<0x118>(incl);
+            incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xA, 0xF, false);   // lane 15 of rows 0, 2 to rows 1, 3
+            incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xC, 0xF, false);   // lane 31 to rows 2, 3
+            if (b0 + k * 64 + lane < B) h[b0 + k * 64 + lane] = carry + incl - v[k];
+            carry += __builtin_amdgcn_readlane(incl, 63);
+        }
     }
     return carry;
 }
@@ -387,111 +732,115 @@ __device__ __forceinline__ int wave_scan_column(int32_t *__restrict__ hist, int 
 // 4 waves per workgroup; the columns are independent, so the grid spreads them over the chip.
 constexpr int kScanWaves = 4;
 
-__global__ __launch_bounds__(64 * kScanWaves) void route_scan_kernel(
-    int B, int n, int m, int C,
-    int32_t *__restrict__ block_expert_hist, int32_t *__restrict__ block_group_hist,
-    const float *__restrict__ block_p_sum, const float *__restrict__ block_q_sum,
-    int32_t *__restrict__ group_count, int32_t *__restrict__ local_count,
-    int32_t *__restrict__ expert_count, int32_t *__restrict__ kept_count,
-    float *__restrict__ p_sum, float *__restrict__ q_sum)
+__global__ __launch_bounds__(64 * kScanWaves) void route_scan_kernel(RouteIo io, Workspace ws, int B, int Bp, int n, int m, int C)
 {
     const int N = n * m;
     const int lane = threadIdx.x & 63;
     const int w = blockIdx.x * kScanWaves + (threadIdx.x >> 6);
     if (w < N) {
-        const int total = wave_scan_column(block_expert_hist, B, N, w);
+        const int total = wave_scan_column(ws.block_expert_hist, B, Bp, w);
         if (lane == 0) {
-            expert_count[w] = total;
-            kept_count[w] = min(total, C);
+            io.expert_count[w] = total;
+            io.kept_count[w] = min(total, C);
         }
     } else if (w < N + n) {
-        const int total = wave_scan_column(block_group_hist, B, n, w - N);
-        if (lane == 0) group_count[w - N] = total;
+        const int total = wave_scan_column(ws.block_group_hist, B, Bp, w - N);
+        if (lane == 0) io.group_count[w - N] = total;
     } else if (w < N + 2 * n) {
-        const float s = wave_sum_column(block_p_sum, B, n, w - N - n);
-        if (lane == 0) p_sum[w - N - n] = s;
+        const float s = wave_sum_column(ws.block_p_sum, B, Bp, w - N - n);
+        if (lane == 0) io.p_sum[w - N - n] = s;
     } else if (w < N + 2 * n + m) {
-        const float s = wave_sum_column(block_q_sum, B, m, w - N - 2 * n);
-        if (lane == 0) q_sum[w - N - 2 * n] = s;
+        const float s = wave_sum_column(ws.block_q_sum, B, Bp, w - N - 2 * n);
+        if (lane == 0) io.q_sum[w - N - 2 * n] = s;
     } else if (w < N + 2 * n + 2 * m) {
-        // local_count[j] = tokens whose local index is j, over all groups.  The expert columns are
-        // being rewritten by other waves, so it is summed from the per-block counts by local index
-        // that route_decide stored behind the group histograms.
-        const int j = w - N - 2 * n - m;
+        const int j = w - N - 2 * n - m;   // local_count[j] = tokens whose local index is j, over all groups
         int s = 0;
-        for (int b = lane; b < B; b += 64) s += block_group_hist[(size_t)B * n + (size_t)b * m + j];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-        if (lane == 0) local_count[j] = s;
+        for (int b = lane; b < B; b += 64) s += ws.block_group_hist[(size_t)(n + j) * Bp + b];
+        s = wave_sum(s);
+        if (lane == 0) io.local_count[j] = s;
     }
 }
 
-// Group capacity, step 1: tokens whose stage-1 position (block offset of the group + in-block
-// position) reaches Cg are dropped at the first hop.  The in-block expert ranks and the per-block
-// expert histograms are rebuilt over the remaining tokens, overwriting those of route_decide (whose
-// totals the first scan has already turned into expert_count).
-__global__ __launch_bounds__(kRouteBlock) void route_first_hop_kernel(
-    int T, int n, int m, int Cg, int bits_N,
-    const int32_t *__restrict__ group_idx, const int32_t *__restrict__ local_idx,
-    const int32_t *__restrict__ block_group_off, const int32_t *__restrict__ pos_in_block,
-    int32_t *__restrict__ rank_in_block, int32_t *__restrict__ block_expert_hist)
+// Group capacity: tokens whose stage-1 position (block offset of the group + in-block
+// position) reaches Cg are dropped at the first hop.  The in-block expert ranks are rebuilt over the remaining tokens,
+// overwriting those of the decision, and so are the block histograms of the experts (into hist_out).
+// SCANNED: the group histograms hold block offsets already; otherwise they are summed here (at most 256 blocks).
+template <bool SCANNED>
+__global__ __launch_bounds__(kRouteBlock) void route_first_hop_kernel(RouteIo io, Workspace ws, int T, int RB, int Bp, int n, int m, int Cg,
+                                                                      int bits_N, int32_t *__restrict__ hist_out)
 {
-    extern __shared__ int32_t hist[];   // [N]
+    extern __shared__ int32_t hist[];   // [N], then [n] group offsets
     const int N = n * m;
     const int tid = threadIdx.x;
     const int b = blockIdx.x;
-    const int t = b * kRouteBlock + tid;
-    for (int i = tid; i < N; i += kRouteBlock) hist[i] = 0;
-    int e = 0;
-    bool through = false;
-    if (t < T) {
-        const int g = group_idx[t];
-        e = g * m + local_idx[t];
-        through = block_group_off[(size_t)b * n + g] + pos_in_block[t] < Cg;
-    }
-    __syncthreads();
-    const unsigned long long me = match_any(e, bits_N, through);
-    const unsigned long long lt = lanemask_lt();
+    const int t = b * RB + tid;
+    const bool valid = tid < RB && t < T;
     const int lane = __lane_id();
     const int wave = tid >> 6;
+    for (int i = tid; i < N; i += kRouteBlock) hist[i] = 0;
+    if constexpr (SCANNED) {
+        for (int i = tid; i < n; i += kRouteBlock) hist[N + i] = ws.block_group_hist[(size_t)i * Bp + b];
+    } else {
+        column_prefixes(ws.block_group_hist, Bp, n, b, wave, kRouteBlock / 64, [&](int c, int s) { hist[N + c] = s; });
+    }
+    __syncthreads();
+    int e = 0;
+    bool through = false;
+    if (valid) {
+        const int g = io.group_idx[t];
+        e = g * m + io.local_idx[t];
+        through = hist[N + g] + ws.pos_in_block[t] < Cg;
+    }
+    const unsigned long long me = match_any(e, bits_N, through);
+    const unsigned long long lt = lanemask_lt();
     for (int w = 0; w < kRouteBlock / 64; ++w) {
         if (wave == w && through) {
             const int base = hist[e];
-            rank_in_block[t] = base + __popcll(me & lt);
+            ws.rank_in_block[t] = base + __popcll(me & lt);
             if (63 - __clzll(me) == lane) hist[e] = base + __popcll(me);
         }
         __syncthreads();
     }
-    if (t < T && !through) rank_in_block[t] = kHop1Dropped;
-    for (int i = tid; i < N; i += kRouteBlock) block_expert_hist[(size_t)b * N + i] = hist[i];
+    if (valid && !through) ws.rank_in_block[t] = kHop1Dropped;
+    for (int i = tid; i < N; i += kRouteBlock) hist_out[(size_t)i * Bp + b] = hist[i];
 }
 
-// Group capacity, step 2: block offsets of the rebuilt expert histograms; kept_count = tokens that
+// Group capacity, many blocks: block offsets of the rebuilt expert histograms; kept_count = tokens that
 // reached the expert, cut at C.
 __global__ __launch_bounds__(64 * kScanWaves) void route_scan_experts_kernel(
-    int B, int N, int C, int32_t *__restrict__ block_expert_hist, int32_t *__restrict__ kept_count)
+    int B, int Bp, int N, int C, int32_t *__restrict__ block_expert_hist, int32_t *__restrict__ kept_count)
 {
     const int w = blockIdx.x * kScanWaves + (threadIdx.x >> 6);
     if (w >= N) return;
-    const int total = wave_scan_column(block_expert_hist, B, N, w);
+    const int total = wave_scan_column(block_expert_hist, B, Bp, w);
     if ((threadIdx.x & 63) == 0) kept_count[w] = min(total, C);
 }
 
-__global__ __launch_bounds__(kRouteBlock) void route_finalize_kernel(
-    int T, int n, int m, int C,
-    const int32_t *__restrict__ group_idx, const int32_t *__restrict__ local_idx,
-    const int32_t *__restrict__ block_expert_off, const int32_t *__restrict__ block_group_off,
-    const int32_t *__restrict__ rank_in_block, const int32_t *__restrict__ pos_in_block,
-    int32_t *__restrict__ pos_in_group, int32_t *__restrict__ slot)
+// Final slots from scanned histograms (many blocks), one thread per token; see RouteTail for what else is written.
+// (The row move of the chained forward pass is a kernel of its own: dispatch_finalize.)
+__global__ __launch_bounds__(256) void route_slots_kernel(FinishArgs a)
 {
-    const int b = blockIdx.x;
-    const int t = b * kRouteBlock + threadIdx.x;
-    if (t >= T) return;
-    const int g = group_idx[t], l = local_idx[t];
-    const int N = n * m;
-    const int rank = block_expert_off[(size_t)b * N + g * m + l] + rank_in_block[t];
-    slot[t] = rank < C ? rank : -1;
-    pos_in_group[t] = block_group_off[(size_t)b * n + g] + pos_in_block[t];
+    const int n = a.n, m = a.m;
+    if (a.tail.loss3 && blockIdx.x == gridDim.x - 1 && threadIdx.x < 64)
+        aux_loss_wave(a.io.group_count, a.io.local_count, a.io.p_sum, a.io.q_sum, a.T, n, m, a.alpha, a.beta, a.tail.loss3);
+    const int t = blockIdx.x * 256 + threadIdx.x, lane = threadIdx.x & 63, t0 = t - lane;
+    bool dropped = false;
+    if (t < a.T) {
+        const int b = t / a.RB, g = a.io.group_idx[t], e = g * m + a.io.local_idx[t];
+        const int rank = a.ws.block_expert_hist[(size_t)e * a.Bp + b] + a.ws.rank_in_block[t];
+        const int sl = rank < a.C ? rank : -1;
+        a.io.slot[t] = sl;
+        a.io.pos_in_group[t] = a.ws.block_group_hist[(size_t)g * a.Bp + b] + a.ws.pos_in_block[t];
+        if (sl >= 0 && a.tail.slot_token) a.tail.slot_token[(size_t)e * a.C + sl] = t;
+        dropped = sl < 0;
+    }
+    if (!a.tail.y) return;
+    unsigned long long mask = __ballot(dropped);
+    while (mask) {   // output rows of dropped tokens, a wave at a time (Eq. 3 gives them no expert output)
+        const int src = __ffsll((long long)mask) - 1;
+        zero_row(static_cast<u32x4 *>(a.tail.y) + (size_t)(t0 + src) * a.ppr, a.ppr, lane, 64);
+        mask &= mask - 1;
+    }
 }
 
 int ceil_log2(int v)
@@ -501,60 +850,149 @@ int ceil_log2(int v)
     return b;
 }
 
+size_t route_lds_bytes(int rb, int n, int m)
+{
+    const size_t cols = n + m, NC = (size_t)n * m + n;
+    return 4 * (rb * (cols | 1) + 8 * cols + rb + (rb + 63) / 64 * NC + 2 * cols);
+}
+
+template <int NT, int P, bool GATE, int DT, int CT>
+hipError_t launch_block(const RouteArgs &a, int blocks, size_t lds, hipStream_t s)
+{
+    SMILE_LAUNCH((gate_logits_route_kernel<DT, CT, NT, P, GATE>), dim3(blocks), dim3(NT), lds, s, a);
+    return hipGetLastError();
+}
+
+// column tiles per pass: all of them while the accumulators (4 x CT tiles of 4 registers) fit beside the operands
+template <int NT, int P, int DT>
+hipError_t launch_gate_ct(const RouteArgs &a, int blocks, size_t lds, hipStream_t s)
+{
+    const int ct = (a.n + a.m + 15) / 16;
+    if (ct <= 1) return launch_block<NT, P, true, DT, 1>(a, blocks, lds, s);
+    if (ct <= 2) return launch_block<NT, P, true, DT, 2>(a, blocks, lds, s);
+    if (NT >= 1024 || ct <= 3) return launch_block<NT, P, true, DT, 3>(a, blocks, lds, s);
+    if constexpr (NT < 1024) return launch_block<NT, P, true, DT, 5>(a, blocks, lds, s);
+    return hipErrorInvalidValue;
+}
+
+template <int NT, int P>
+hipError_t launch_decide(int dtype, bool gate, const RouteArgs &a, int blocks, size_t lds, hipStream_t s)
+{
+    if (!gate) return launch_block<NT, P, false, SMILE_DTYPE_F32, 1>(a, blocks, lds, s);
+    if (dtype == SMILE_DTYPE_BF16) return launch_gate_ct<NT, P, SMILE_DTYPE_BF16>(a, blocks, lds, s);
+    if (dtype == SMILE_DTYPE_F16) return launch_gate_ct<NT, P, SMILE_DTYPE_F16>(a, blocks, lds, s);
+    return launch_gate_ct<NT, P, SMILE_DTYPE_F32>(a, blocks, lds, s);
+}
+
 }  // namespace
 
-hipError_t launch_route(const smile_layer_desc &d, const Workspace &ws, const float *logits_inter,
-                        const float *logits_intra, const float *bias_inter, const float *bias_intra,
-                        int32_t *group_idx, int32_t *local_idx, int32_t *pos_in_group, int32_t *slot, float *gate,
-                        float *p_top, float *q_top, int32_t *group_count, int32_t *local_count,
-                        int32_t *expert_count, int32_t *kept_count, float *p_sum, float *q_sum, hipStream_t s,
-                        bool finalize, bool scan)
+// How a layer's tokens are routed; a function of the layer description only, so that every entry point sums
+// in the same order.
+RoutePlan route_plan(const smile_layer_desc &d)
 {
     const int n = d.n_groups, m = d.m_local, N = n * m;
-    const int B = (d.T + kRouteBlock - 1) / kRouteBlock;
-    // one histogram copy per wave while four of them fit beside the kernel's static LDS (the probability tile and
-    // its partial sums) in the 64 KB a workgroup may have without opting in: N + n <= 1920
-    constexpr size_t kStaticLds = sizeof(float) * (kRouteBlock * (kColChunk + 1) + 8 * kColChunk);
-    const bool per_wave = (size_t)(N + n) * (kRouteBlock / 64) * sizeof(int32_t) + kStaticLds <= 64 * 1024;
-    // the counters' memory is reused for the [4][max(n, m)] partial probability sums
-    const size_t counters = (size_t)(N + n) * (per_wave ? kRouteBlock / 64 : 1);
-    const size_t lds1 = sizeof(int32_t) * std::max(counters, (size_t)(kRouteBlock / 64) * std::max(n, m));
-    const int cp = n <= 8 ? 8 : (n <= 32 ? 32 : 0), cq = m <= 8 ? 8 : (m <= 32 ? 32 : 0);
-#define SMILE_DECIDE(PW, CP, CQ)                                                                                     \
-    SMILE_LAUNCH((route_decide_kernel<PW, CP, CQ>), dim3(B), dim3(kRouteBlock), lds1, s, logits_inter,          \
-                       logits_intra, bias_inter, bias_intra, d.T, n, m, ceil_log2(n), ceil_log2(N), group_idx,        \
-                       local_idx, ws.pos_in_block, ws.rank_in_block, gate, p_top, q_top, ws.block_expert_hist,         \
-                       ws.block_group_hist, ws.block_p_sum, ws.block_q_sum)
-    if (!per_wave) SMILE_DECIDE(false, 0, 0);
-    else if (cp == 8 && cq == 8) SMILE_DECIDE(true, 8, 8);
-    else if (cp == 32 && cq == 8) SMILE_DECIDE(true, 32, 8);
-    else if (cp == 8 && cq == 32) SMILE_DECIDE(true, 8, 32);
-    else if (cp == 32 && cq == 32) SMILE_DECIDE(true, 32, 32);
-    else SMILE_DECIDE(true, 0, 0);
-#undef SMILE_DECIDE
-    hipError_t err = hipGetLastError();
-    if (err != hipSuccess || !scan) return err;   // !scan: the caller's last step scans the histograms itself
+    constexpr size_t kLdsMost = 64 * 1024;
+    RoutePlan p{};
+    // One workgroup does it all while reading the batch through one CU (28 GB/s) is faster than a second launch (4 us)
+    if (d.T <= 64 && (size_t)d.T * d.d_model * elem_size(d.dtype) <= 64 * 1024) {
+        const int rb = d.T <= 16 ? 16 : d.T <= 32 ? 32 : 64;
+        if (route_lds_bytes(rb, n, m) <= kLdsMost) {
+            p.rb = rb, p.tile = p.one = true;
+            p.blocks = p.stride = 1;
+            return p;
+        }
+    }
+    // Blocks as small as leaves at most 256 of them (more CUs read x, and 256 blocks are one load in route_finish), from 64
+    // tokens on as many blocks as there are: several share a CU then, and one block's latency hides under another's reads.
+    // 256 tokens where the histograms would grow past 2 MB otherwise.
+    int rb = d.T <= 16 * 256 ? 16 : d.T <= 32 * 256 ? 32 : 64;
+    if (d.T > 65536 || (size_t)((d.T + rb - 1) / rb) * (N + 2 * n + 2 * m) > 512 * 1024) rb = 256;
+    p.tile = route_lds_bytes(rb, n, m) <= kLdsMost;
+    if (!p.tile) rb = kRouteBlock;
+    p.rb = rb;
+    p.blocks = (d.T + rb - 1) / rb;
+    // every workgroup of route_finish reads the histograms of the blocks before it: worth a launch up to 128 KB
+    const int padded = (p.blocks + 3) / 4 * 4;
+    p.scan_inline = p.blocks <= 256 && (size_t)(N + n) * padded * 4 <= 128 * 1024;
+    p.stride = p.scan_inline ? padded : p.blocks;
+    return p;
+}
+
+hipError_t launch_routing(const smile_layer_desc &d, const Workspace &ws, const GateInputs *gate, const RouteIo &io, const RouteTail &tail,
+                          hipStream_t s)
+{
+    const int n = d.n_groups, m = d.m_local, N = n * m;
+    const RoutePlan p = route_plan(d);
+    const int ppr = d.d_model * elem_size(d.dtype) / 16;
+    hipError_t err;
+    RouteArgs a{};
+    if (gate) a.x = gate->x, a.w_inter = gate->w_inter, a.w_intra = gate->w_intra;
+    a.d = d.d_model, a.io = io, a.T = d.T, a.n = n, a.m = m, a.bits_n = ceil_log2(n), a.bits_N = ceil_log2(N), a.Bp = p.stride, a.ws = ws;
+    a.one = p.one, a.C = d.capacity, a.Cg = d.group_capacity, a.ppr = ppr, a.tail = tail, a.alpha = d.alpha, a.beta = d.beta;
+    if (p.tile) {
+        const size_t lds = route_lds_bytes(p.rb, n, m);
+        if (p.rb == 16) err = launch_decide<256, 16>(d.dtype, gate != nullptr, a, p.blocks, lds, s);
+        else if (p.rb == 32) err = launch_decide<256, 8>(d.dtype, gate != nullptr, a, p.blocks, lds, s);
+        else if (p.rb == 64) err = launch_decide<256, 4>(d.dtype, gate != nullptr, a, p.blocks, lds, s);
+        else err = launch_decide<1024, 4>(d.dtype, gate != nullptr, a, p.blocks, lds, s);
+    } else {
+        if (gate) {
+            err = launch_gate_logits(d, gate->x, gate->w_inter, gate->w_intra, io.logits_inter, io.logits_intra, s);
+            if (err != hipSuccess) return err;
+        }
+        // one histogram copy per wave while four of them fit beside the kernel's static LDS in 64 KB: N + n <= 1920
+        constexpr size_t kStaticLds = sizeof(float) * (kRouteBlock * (kColChunk + 1) + 8 * kColChunk);
+        const bool per_wave = (size_t)(N + n) * (kRouteBlock / 64) * sizeof(int32_t) + kStaticLds <= 64 * 1024;
+        const size_t lds = sizeof(int32_t) * (size_t)(N + n) * (per_wave ? kRouteBlock / 64 : 1);
+        if (per_wave) SMILE_LAUNCH(route_decide_kernel<true>, dim3(p.blocks), dim3(kRouteBlock), lds, s, a);
+        else SMILE_LAUNCH(route_decide_kernel<false>, dim3(p.blocks), dim3(kRouteBlock), lds, s, a);
+        err = hipGetLastError();
+    }
+    if (err != hipSuccess) return err;
+    if (p.one) {   // everything but the row move is done
+        if (tail.xe) err = launch_dispatch(d, tail.x, io.group_idx, io.local_idx, io.slot, tail.xe, s);
+        return err;
+    }
+    FinishArgs f{io, ws, ws.block_expert_hist, d.T, p.rb, p.blocks, p.stride, n, m, d.capacity, ppr, tail, d.alpha, d.beta};
+    const size_t hop_lds = sizeof(int32_t) * (size_t)(N + n);
+    if (p.scan_inline) {
+        if (d.group_capacity > 0) {
+            SMILE_LAUNCH(route_first_hop_kernel<false>, dim3(p.blocks), dim3(kRouteBlock), hop_lds, s, io, ws, d.T, p.rb, p.stride, n, m,
+                         d.group_capacity, a.bits_N, ws.block_expert_hist2);
+            err = hipGetLastError();
+            if (err != hipSuccess) return err;
+            f.expert_off_hist = ws.block_expert_hist2;
+        }
+        const size_t lds = sizeof(int32_t) * (size_t)std::max(N + n + p.rb, 2 * (n + m));
+        const dim3 grid(p.blocks + 2);
+        if (tail.xe) {
+            const int lpr = lanes_per_row(ppr), threads = std::min(std::max(p.rb * 16, 256), 1024);   // half the block's rows at once
+            if (lpr == 8) SMILE_LAUNCH(route_finish_kernel<8>, grid, dim3(threads), lds, s, f);
+            else if (lpr == 16) SMILE_LAUNCH(route_finish_kernel<16>, grid, dim3(threads), lds, s, f);
+            else SMILE_LAUNCH(route_finish_kernel<32>, grid, dim3(threads), lds, s, f);
+        } else {
+            // enough waves to have the loads of all columns in flight at once
+            SMILE_LAUNCH(route_finish_kernel<0>, grid, dim3(N > 32 || p.rb > 64 ? 1024 : 256), lds, s, f);
+        }
+        return hipGetLastError();
+    }
     const int columns = N + 2 * n + 2 * m;
-    SMILE_LAUNCH(route_scan_kernel, dim3((columns + kScanWaves - 1) / kScanWaves), dim3(64 * kScanWaves), 0, s, B, n,
-                       m, d.capacity, ws.block_expert_hist, ws.block_group_hist, ws.block_p_sum, ws.block_q_sum,
-                       group_count, local_count, expert_count, kept_count, p_sum, q_sum);
+    SMILE_LAUNCH(route_scan_kernel, dim3((columns + kScanWaves - 1) / kScanWaves), dim3(64 * kScanWaves), 0, s, io, ws, p.blocks, p.stride, n,
+                 m, d.capacity);
     err = hipGetLastError();
     if (err != hipSuccess) return err;
     if (d.group_capacity > 0) {
-        SMILE_LAUNCH(route_first_hop_kernel, dim3(B), dim3(kRouteBlock), sizeof(int32_t) * (size_t)N, s, d.T, n, m,
-                           d.group_capacity, ceil_log2(N), group_idx, local_idx, ws.block_group_hist, ws.pos_in_block,
-                           ws.rank_in_block, ws.block_expert_hist);
+        SMILE_LAUNCH(route_first_hop_kernel<true>, dim3(p.blocks), dim3(kRouteBlock), hop_lds, s, io, ws, d.T, p.rb, p.stride, n, m,
+                     d.group_capacity, a.bits_N, ws.block_expert_hist);
         err = hipGetLastError();
         if (err != hipSuccess) return err;
-        SMILE_LAUNCH(route_scan_experts_kernel, dim3((N + kScanWaves - 1) / kScanWaves), dim3(64 * kScanWaves), 0,
-                           s, B, N, d.capacity, ws.block_expert_hist, kept_count);
+        SMILE_LAUNCH(route_scan_experts_kernel, dim3((N + kScanWaves - 1) / kScanWaves), dim3(64 * kScanWaves), 0, s, p.blocks, p.stride, N,
+                     d.capacity, ws.block_expert_hist, io.kept_count);
         err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
-    if (!finalize) return err;
-    SMILE_LAUNCH(route_finalize_kernel, dim3(B), dim3(kRouteBlock), 0, s, d.T, n, m, d.capacity, group_idx,
-                       local_idx, ws.block_expert_hist, ws.block_group_hist, ws.rank_in_block, ws.pos_in_block,
-                       pos_in_group, slot);
+    if (tail.xe) return launch_dispatch_finalize(d, ws, p, io, tail, s);
+    SMILE_LAUNCH(route_slots_kernel, dim3((d.T + 255) / 256), dim3(256), 0, s, f);
     return hipGetLastError();
 }
 

@@ -34,21 +34,32 @@ static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 Layout workspace_layout(const smile_layer_desc &d)
 {
     Layout L{};
-    const size_t B = ((size_t)d.T + kRouteBlock - 1) / kRouteBlock;
+    const size_t B = route_plan(d).stride;
     const size_t N = (size_t)d.n_groups * d.m_local;
     const size_t esz = elem_size(d.dtype);
     size_t off = 0;
-    L.route_blocks = (int32_t)B;
-    L.off_block_expert_hist = off; off = align_up(off + B * N * sizeof(int32_t), 256);
-    L.off_block_group_hist = off;  off = align_up(off + B * (d.n_groups + d.m_local) * sizeof(int32_t), 256);
-    L.off_block_p_sum = off;       off = align_up(off + B * d.n_groups * sizeof(float), 256);
-    L.off_block_q_sum = off;       off = align_up(off + B * d.m_local * sizeof(float), 256);
+    L.off_block_expert_hist = off;  off = align_up(off + B * N * sizeof(int32_t), 256);
+    L.off_block_expert_hist2 = off; off = align_up(off + (d.group_capacity > 0 && route_plan(d).scan_inline ? B * N : 0) * sizeof(int32_t), 256);
+    L.off_block_group_hist = off;   off = align_up(off + B * (d.n_groups + d.m_local) * sizeof(int32_t), 256);
+    L.off_block_p_sum = off;        off = align_up(off + B * d.n_groups * sizeof(float), 256);
+    L.off_block_q_sum = off;        off = align_up(off + B * d.m_local * sizeof(float), 256);
     L.off_rank_in_block = off;     off = align_up(off + (size_t)d.T * sizeof(int32_t), 256);
     L.off_pos_in_block = off;      off = align_up(off + (size_t)d.T * sizeof(int32_t), 256);
     L.off_slot_token = off;        off = align_up(off + N * (size_t)d.capacity * sizeof(int32_t), 256);
     L.off_hidden = off;            off = align_up(off + N * (size_t)d.capacity * d.d_ff * esz, 256);
     L.total = off;
     return L;
+}
+
+void place_routing(Workspace &ws, const Layout &L, char *base)
+{
+    ws.block_expert_hist = reinterpret_cast<int32_t *>(base + L.off_block_expert_hist);
+    ws.block_expert_hist2 = reinterpret_cast<int32_t *>(base + L.off_block_expert_hist2);
+    ws.block_group_hist = reinterpret_cast<int32_t *>(base + L.off_block_group_hist);
+    ws.block_p_sum = reinterpret_cast<float *>(base + L.off_block_p_sum);
+    ws.block_q_sum = reinterpret_cast<float *>(base + L.off_block_q_sum);
+    ws.rank_in_block = reinterpret_cast<int32_t *>(base + L.off_rank_in_block);
+    ws.pos_in_block = reinterpret_cast<int32_t *>(base + L.off_pos_in_block);
 }
 
 static bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -165,12 +176,7 @@ static smile_status make_ctx(const smile_layer_desc *desc, void *workspace, size
     c->base = workspace;
     c->bytes = bytes;
     c->owns = owns;
-    c->ws.block_expert_hist = reinterpret_cast<int32_t *>(b + L.off_block_expert_hist);
-    c->ws.block_group_hist = reinterpret_cast<int32_t *>(b + L.off_block_group_hist);
-    c->ws.block_p_sum = reinterpret_cast<float *>(b + L.off_block_p_sum);
-    c->ws.block_q_sum = reinterpret_cast<float *>(b + L.off_block_q_sum);
-    c->ws.rank_in_block = reinterpret_cast<int32_t *>(b + L.off_rank_in_block);
-    c->ws.pos_in_block = reinterpret_cast<int32_t *>(b + L.off_pos_in_block);
+    place_routing(c->ws, L, b);
     c->ws.slot_token = reinterpret_cast<int32_t *>(b + L.off_slot_token);
     c->ws.hidden = b + L.off_hidden;
     *out = c;
@@ -254,10 +260,9 @@ smile_status smile_route_bilevel(smile_ctx *ctx, const float *logits_inter, cons
         bad(q_top) || bad(group_count) || bad(local_count) || bad(expert_count) || bad(kept_count) ||
         bad(p_sum) || bad(q_sum))
         return SMILE_INVALID_ARG;
-    return from_hip(launch_route(ctx->desc, ctx->ws, logits_inter, logits_intra, bias_inter, bias_intra,
-                                 group_idx, local_idx, pos_in_group, slot, gate, p_top, q_top, group_count,
-                                 local_count, expert_count, kept_count, p_sum, q_sum,
-                                 static_cast<hipStream_t>(stream)));
+    const RouteIo io{const_cast<float *>(logits_inter), const_cast<float *>(logits_intra), bias_inter, bias_intra, group_idx, local_idx,
+                     pos_in_group, slot, gate, p_top, q_top, group_count, local_count, expert_count, kept_count, p_sum, q_sum};
+    return from_hip(launch_routing(ctx->desc, ctx->ws, nullptr, io, RouteTail{}, static_cast<hipStream_t>(stream)));
 }
 
 smile_status smile_dispatch(smile_ctx *ctx, const void *x, const int32_t *group_idx, const int32_t *local_idx,
@@ -365,53 +370,29 @@ smile_status smile_layer_forward(smile_ctx *ctx, const smile_layer_io *io, void 
     if ((io->prof_up_start == nullptr) != (io->prof_up_stop == nullptr)) return SMILE_INVALID_ARG;
     if (bad_opt(io->h_save) || bad_opt(io->pre_save) || (io->h_save == nullptr) != (io->pre_save == nullptr))
         return SMILE_INVALID_ARG;
-    // Same kernels as the step-by-step calls with fewer launches.  With expert buffers (xe, ye given):
-    // the last routing step and the loss run inside the dispatch kernel, and the down-projection also
-    // returns the gate-weighted rows to y (no combine launch).  Without them (both NULL):
-    // nothing is materialised -- a per-token kernel finishes the routing, builds the slot -> token map
-    // and zeroes the rows of dropped tokens; the up GEMM gathers its rows from x through that map and
+    // Same arithmetic as the step-by-step calls with fewer launches: the router logits are computed by the kernel that
+    // routes them, and the last routing kernel also evaluates the loss, zeroes the output rows of dropped tokens and
+    // builds the slot -> token map.  With expert buffers (xe, ye given) it moves the rows too, and the down-projection
+    // returns the gate-weighted rows to y beside ye.  Without them (both NULL)
+    // nothing is materialised: the up GEMM gathers its rows from x through the map and
     // the down GEMM returns gate-weighted rows straight to y.
     const LayerDesc &d = ctx->desc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     const bool fused = io->xe == nullptr;
-    const LossArgs loss{io->group_count, io->local_count, io->p_sum, io->q_sum, io->loss3};
-    // small batches: the fused path's last routing kernel scans the few per-block histograms itself
-    const int route_blocks = (d.T + kRouteBlock - 1) / kRouteBlock;
-    const bool scan_in_finalize = fused && d.group_capacity == 0 && route_blocks <= kScanInFinalizeBlocks;
-    hipError_t err = launch_gate_logits(d, io->x, io->w_inter, io->w_intra, io->logits_inter, io->logits_intra, s);
+    const RouteIo route{io->logits_inter, io->logits_intra, io->bias_inter, io->bias_intra, io->group_idx, io->local_idx, io->pos_in_group,
+                        io->slot, io->gate, io->p_top, io->q_top, io->group_count, io->local_count, io->expert_count, io->kept_count,
+                        io->p_sum, io->q_sum};
+    const GateInputs gate{io->x, io->w_inter, io->w_intra};
+    RouteTail tail;
+    tail.slot_token = ctx->ws.slot_token, tail.y = io->y, tail.loss3 = io->loss3;
+    if (!fused) tail.x = io->x, tail.xe = io->xe;
+    hipError_t err = launch_routing(d, ctx->ws, &gate, route, tail, s);
     if (err == hipSuccess)
-        err = launch_route(d, ctx->ws, io->logits_inter, io->logits_intra, io->bias_inter, io->bias_intra,
-                           io->group_idx, io->local_idx, io->pos_in_group, io->slot, io->gate, io->p_top, io->q_top,
-                           io->group_count, io->local_count, io->expert_count, io->kept_count, io->p_sum, io->q_sum,
-                           s, /*finalize=*/false, /*scan=*/!scan_in_finalize);
-    if (fused) {
-        if (err == hipSuccess && scan_in_finalize)
-            err = launch_finalize_map_scan(d, ctx->ws, io->group_idx, io->local_idx, io->pos_in_group, io->slot, io->y,
-                                           io->group_count, io->local_count, io->expert_count, io->kept_count,
-                                           io->p_sum, io->q_sum, io->loss3, s);
-        else if (err == hipSuccess)
-            err = launch_finalize_map(d, ctx->ws, io->group_idx, io->local_idx, io->pos_in_group, io->slot, io->y,
-                                      loss, s);
-        if (err == hipSuccess)
-            err = launch_expert_ffn_up(d, ctx->ws, nullptr, io->kept_count, io->w1, io->b1, s,
-                                       static_cast<hipEvent_t>(io->prof_up_start),
-                                       static_cast<hipEvent_t>(io->prof_up_stop), io->x, io->h_save, io->pre_save);
-        if (err == hipSuccess)
-            err = launch_expert_ffn_down(d, ctx->ws, io->kept_count, io->w2, io->b2, nullptr, s, io->y, io->gate,
-                                         io->h_save);
-        return from_hip(err);
-    }
+        err = launch_expert_ffn_up(d, ctx->ws, io->xe, io->kept_count, io->w1, io->b1, s, static_cast<hipEvent_t>(io->prof_up_start),
+                                   static_cast<hipEvent_t>(io->prof_up_stop), fused ? io->x : nullptr, io->h_save, io->pre_save);
+    // the down-projection writes ye (if there is one) and, through the slot -> token map, the gate-weighted rows of y
     if (err == hipSuccess)
-        err = launch_dispatch_finalize(d, ctx->ws, io->x, io->group_idx, io->local_idx, io->pos_in_group, io->slot,
-                                       io->xe, io->y, loss, s);
-    if (err == hipSuccess)
-        err = launch_expert_ffn_up(d, ctx->ws, io->xe, io->kept_count, io->w1, io->b1, s,
-                                   static_cast<hipEvent_t>(io->prof_up_start), static_cast<hipEvent_t>(io->prof_up_stop),
-                                   nullptr, io->h_save, io->pre_save);
-    // the down-projection writes ye and, through the slot -> token map, the gate-weighted rows of y
-    if (err == hipSuccess)
-        err = launch_expert_ffn_down(d, ctx->ws, io->kept_count, io->w2, io->b2, io->ye, s, io->y, io->gate,
-                                     io->h_save);
+        err = launch_expert_ffn_down(d, ctx->ws, io->kept_count, io->w2, io->b2, io->ye, s, io->y, io->gate, io->h_save);
     return from_hip(err);
 }
 

@@ -68,7 +68,7 @@ struct Half<_Float16> {
     }
 };
 
-// tokens handled by one workgroup of the routing kernels
+// tokens per routing block of the kernels for very wide routers, and the most of any but a single block
 constexpr int kRouteBlock = 256;
 
 // in-block rank given to a token dropped at the first hop (group capacity): any block offset added to
@@ -76,11 +76,12 @@ constexpr int kRouteBlock = 256;
 constexpr int32_t kHop1Dropped = 1 << 30;
 
 struct Workspace {
-    // routing: per-block histograms turned into exclusive block offsets by the scan kernel
-    int32_t *block_expert_hist;   // [B][N]
-    int32_t *block_group_hist;    // [B][n] per group, then [B][m] per local index
-    float *block_p_sum;           // [B][n]
-    float *block_q_sum;           // [B][m]
+    // routing, B columns of blocks (RoutePlan::stride): histograms and partial sums of the routing blocks
+    int32_t *block_expert_hist;   // [N][B]
+    int32_t *block_expert_hist2;  // [N][B] counts of the tokens that pass the first hop (group capacity only)
+    int32_t *block_group_hist;    // [n][B] per group, then [m][B] per local index
+    float *block_p_sum;           // [n][B]
+    float *block_q_sum;           // [m][B]
     int32_t *rank_in_block;       // [T] rank among earlier tokens of the same block with the same expert
     int32_t *pos_in_block;        // [T] ... with the same group
     int32_t *slot_token;          // [N][C] token sitting in each expert-buffer row (rows < kept only)
@@ -89,12 +90,45 @@ struct Workspace {
 };
 
 struct Layout {
-    size_t off_block_expert_hist, off_block_group_hist, off_block_p_sum, off_block_q_sum, off_rank_in_block,
-        off_pos_in_block, off_slot_token, off_hidden, total;
-    int32_t route_blocks;
+    size_t off_block_expert_hist, off_block_expert_hist2, off_block_group_hist, off_block_p_sum, off_block_q_sum,
+        off_rank_in_block, off_pos_in_block, off_slot_token, off_hidden, total;
 };
 
 Layout workspace_layout(const smile_layer_desc &d);
+// the routing part of a workspace at `base`
+void place_routing(Workspace &ws, const Layout &L, char *base);
+
+// How a layer's tokens are cut into routing blocks and which kernels put the blocks in order (route.hip)
+struct RoutePlan {
+    int rb, blocks;      // tokens per block, blocks
+    int stride;          // blocks per column of the histograms (padded to a multiple of 4 for scan_inline)
+    bool tile;           // the block's logits fit an LDS tile (else: the kernels for very wide routers)
+    bool one;            // a single workgroup routes the whole batch
+    bool scan_inline;    // every workgroup of the finishing kernel sums the histograms before its block itself
+};
+RoutePlan route_plan(const smile_layer_desc &d);
+
+// Inputs and outputs of the routing steps (smile_route_bilevel), and the router operands when the logits are computed in
+// the same launch
+struct RouteIo {
+    float *logits_inter, *logits_intra;   // read; written when GateInputs are given
+    const float *bias_inter, *bias_intra;
+    int32_t *group_idx, *local_idx, *pos_in_group, *slot;
+    float *gate, *p_top, *q_top;
+    int32_t *group_count, *local_count, *expert_count, *kept_count;
+    float *p_sum, *q_sum;
+};
+struct GateInputs {
+    const void *x, *w_inter, *w_intra;
+};
+// What a chained forward pass adds to the last routing kernel; null members are left out
+struct RouteTail {
+    int32_t *slot_token = nullptr;   // [N][C] token sitting in each expert-buffer row
+    void *y = nullptr;               // rows of dropped tokens are zeroed
+    float *loss3 = nullptr;          // Eq. 4
+    const void *x = nullptr;         // with xe: the rows of kept tokens are moved to the expert buffers (needs slot_token and y)
+    void *xe = nullptr;
+};
 
 // Eq. 4 on one wave (64 lanes): lane-strided serial sums, fixed butterfly.  Shared by the stand-alone
 // loss kernel and the routing scan kernel so that both give identical bits.
@@ -121,12 +155,12 @@ __device__ __forceinline__ void aux_loss_wave(const int32_t *group_count, const 
     }
 }
 
-// Sum over blocks of one column of per-block partial sums, in a fixed order: lane l adds blocks
+// Sum over blocks of one column of per-block partial sums ([column][stride]), in a fixed order: lane l adds blocks
 // l, l+64, ... serially, then a fixed butterfly over the wave.
 __device__ __forceinline__ float wave_sum_column(const float *__restrict__ part, int B, int stride, int col)
 {
     float s = 0.f;
-    for (int b = __lane_id(); b < B; b += 64) s += part[(size_t)b * stride + col];
+    for (int b = __lane_id(); b < B; b += 64) s += part[(size_t)col * stride + b];
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
     return s;
@@ -296,26 +330,14 @@ struct smile_ctx {
 
 namespace smile {
 
-struct LossArgs {
-    const int32_t *group_count, *local_count;
-    const float *p_sum, *q_sum;
-    float *out3;   // null: no loss
-};
-
 // Launchers: enqueue on `s`, return the launch status.  Shapes were validated by the caller.
 hipError_t launch_gate_logits(const smile_layer_desc &d, const void *x, const void *w_inter, const void *w_intra,
                               float *logits_inter, float *logits_intra, hipStream_t s);
 
-// finalize = false leaves pos_in_group / slot unwritten (the block-local ranks stay in the workspace
-// for launch_dispatch_finalize).  scan = false (needs finalize = false, no group capacity) also leaves the
-// per-block histograms and partial sums unscanned and the counts / sums unwritten: launch_finalize_map_scan
-// does both.
-hipError_t launch_route(const smile_layer_desc &d, const Workspace &ws, const float *logits_inter,
-                        const float *logits_intra, const float *bias_inter, const float *bias_intra,
-                        int32_t *group_idx, int32_t *local_idx, int32_t *pos_in_group, int32_t *slot, float *gate,
-                        float *p_top, float *q_top, int32_t *group_count, int32_t *local_count,
-                        int32_t *expert_count, int32_t *kept_count, float *p_sum, float *q_sum, hipStream_t s,
-                        bool finalize = true, bool scan = true);
+// The routing steps: decision, block order, counts and sums, slots; with `gate` the router logits in front of them in the
+// same launch; `tail`: see RouteTail.
+hipError_t launch_routing(const smile_layer_desc &d, const Workspace &ws, const GateInputs *gate, const RouteIo &io, const RouteTail &tail,
+                          hipStream_t s);
 
 hipError_t launch_dispatch(const smile_layer_desc &d, const void *x, const int32_t *group_idx,
                            const int32_t *local_idx, const int32_t *slot, void *xe, hipStream_t s);
@@ -327,13 +349,10 @@ hipError_t launch_dispatch_hop2(const smile_layer_desc &d, const void *xg, const
                                 const int32_t *local_idx, const int32_t *pos_in_group, const int32_t *slot,
                                 int group_rows, void *xe, hipStream_t s);
 
-// dispatch fused with the last routing step: computes pos_in_group / slot from the workspace ranks
-// and block offsets, writes them, moves the rows, records the slot -> token map in ws.slot_token and
-// zeroes the rows of dropped tokens in y; loss != nullptr: one wave also evaluates Eq. 4 from the
-// routing statistics (saves the separate loss launch)
-hipError_t launch_dispatch_finalize(const smile_layer_desc &d, const Workspace &ws, const void *x,
-                                    const int32_t *group_idx, const int32_t *local_idx, int32_t *pos_in_group,
-                                    int32_t *slot, void *xe, void *y, const LossArgs &loss, hipStream_t s);
+// dispatch fused with the last routing step when the histograms were scanned by a kernel of their own: pos_in_group / slot
+// from the workspace ranks and block offsets, and everything of the tail
+hipError_t launch_dispatch_finalize(const smile_layer_desc &d, const Workspace &ws, const RoutePlan &p, const RouteIo &io,
+                                    const RouteTail &tail, hipStream_t s);
 
 hipError_t launch_combine(const smile_layer_desc &d, const void *ye, const int32_t *group_idx,
                           const int32_t *local_idx, const int32_t *slot, const float *gate, void *y, hipStream_t s);
@@ -409,13 +428,6 @@ struct F32Gemm {
 };
 hipError_t launch_grouped_gemm_f32(const F32Gemm &g, hipStream_t s);
 
-// Last routing step for the fully fused forward pass: pos_in_group / slot as launch_route's finalize
-// kernel, plus the slot -> token map in ws.slot_token, zero output rows for dropped tokens in y, and
-// (loss.out3 != nullptr) the Eq. 4 loss.
-hipError_t launch_finalize_map(const smile_layer_desc &d, const Workspace &ws, const int32_t *group_idx,
-                               const int32_t *local_idx, int32_t *pos_in_group, int32_t *slot, void *y,
-                               const LossArgs &loss, hipStream_t s);
-
 // ---- backward pass.  Its workspace is separate from the ctx's and supplied by the caller per call.
 struct BackwardLayout {
     size_t off_pre, off_h, off_dpre, off_gw_partial, total;
@@ -450,15 +462,6 @@ hipError_t launch_gate_weights_mfma(const smile_layer_desc &d, const void *x, co
                                     float *partial, int blocks, int tokens_per_block, hipStream_t s);
 hipError_t launch_gate_weights_backward(const LayerDesc &d, void *workspace, const void *x, const float *dlp,
                                         const float *dlq, float *dw_inter, float *dw_intra, hipStream_t s);
-
-// The same for small batches, without the separate scan kernel: every block sums the histogram rows of the
-// blocks before it (at most kScanInFinalizeBlocks - 1 rows), and the last block produces the counts, the
-// probability sums (same summation order as the scan kernel: identical bits) and the loss.
-constexpr int kScanInFinalizeBlocks = 64;
-hipError_t launch_finalize_map_scan(const smile_layer_desc &d, const Workspace &ws, const int32_t *group_idx,
-                                    const int32_t *local_idx, int32_t *pos_in_group, int32_t *slot, void *y,
-                                    int32_t *group_count, int32_t *local_count, int32_t *expert_count,
-                                    int32_t *kept_count, float *p_sum, float *q_sum, float *loss3, hipStream_t s);
 
 hipError_t launch_aux_loss(const smile_layer_desc &d, const int32_t *group_count, const int32_t *local_count,
                            const float *p_sum, const float *q_sum, float *out3, hipStream_t s);

@@ -75,15 +75,10 @@ extern "C" smile_status smile_route_bilevel_static(const smile_layer_desc *desc,
     char *base = static_cast<char *>(scratch_address());
     if (!base) return SMILE_HIP_ERROR;
     Workspace ws{};
-    ws.block_expert_hist = reinterpret_cast<int32_t *>(base + L.off_block_expert_hist);
-    ws.block_group_hist = reinterpret_cast<int32_t *>(base + L.off_block_group_hist);
-    ws.block_p_sum = reinterpret_cast<float *>(base + L.off_block_p_sum);
-    ws.block_q_sum = reinterpret_cast<float *>(base + L.off_block_q_sum);
-    ws.rank_in_block = reinterpret_cast<int32_t *>(base + L.off_rank_in_block);
-    ws.pos_in_block = reinterpret_cast<int32_t *>(base + L.off_pos_in_block);
-    const hipError_t err = launch_route(*desc, ws, logits_inter, logits_intra, bias_inter, bias_intra, group_idx,
-                                        local_idx, pos_in_group, slot, gate, p_top, q_top, group_count, local_count,
-                                        expert_count, kept_count, p_sum, q_sum, static_cast<hipStream_t>(stream));
+    place_routing(ws, L, base);
+    const RouteIo io{const_cast<float *>(logits_inter), const_cast<float *>(logits_intra), bias_inter, bias_intra, group_idx, local_idx,
+                     pos_in_group, slot, gate, p_top, q_top, group_count, local_count, expert_count, kept_count, p_sum, q_sum};
+    const hipError_t err = launch_routing(*desc, ws, nullptr, io, RouteTail{}, static_cast<hipStream_t>(stream));
     if (err == hipSuccess) return SMILE_OK;
     (void)hipGetLastError();
     return SMILE_HIP_ERROR;

@@ -47,3 +47,41 @@ F32_TILES = [
 @pytest.mark.parametrize("cfg", F32_TILES, ids=lambda c: c.name)
 def test_f32_gemm_tiles(torch_cuda, cfg):
     _forward_and_backward(cfg)
+
+
+# Routing: the block sizes (16, 32, 64, 256 tokens) at the batch sizes where they change, one token more and the single-block
+# case; router widths on both sides of what a token's threads keep in registers; histograms summed by every block and scanned by a
+# kernel of their own; the first-hop limit in each.
+ROUTE_EDGES = [
+    wl.small_config("route_one_block_16", 16, 64, 64, 2, 3, 2, "bf16", "relu", seed=311),
+    wl.small_config("route_one_block_64_cap", 63, 72, 64, 3, 2, 9, "f32", "gelu", skew=True, seed=312, group_capacity=20),
+    wl.small_config("route_two_blocks", 65, 64, 64, 1, 9, 5, "f16", "relu", seed=313),
+    wl.small_config("route_256_blocks_16", 4096, 64, 64, 33, 3, 40, "bf16", "relu", seed=314, group_capacity=110),
+    wl.small_config("route_16_to_32", 4097, 64, 64, 17, 4, 60, "bf16", "gelu", skew=True, seed=315),
+    wl.small_config("route_32_to_64", 8193, 104, 64, 2, 8, 500, "f32", "relu", seed=316),
+    wl.small_config("route_inline_to_scan", 16385, 64, 64, 4, 5, 800, "bf16", "relu", skew=True, seed=317, group_capacity=3000),
+    wl.small_config("route_64_to_256", 65537, 64, 64, 3, 2, 9000, "bf16", "relu", seed=318),
+    wl.small_config("route_wide_tile", 500, 64, 64, 1, 200, 4, "bf16", "relu", seed=319),
+    wl.small_config("route_beyond_tile", 300, 64, 64, 300, 2, 2, "bf16", "relu", seed=320, group_capacity=1),
+]
+
+
+@pytest.mark.parametrize("cfg", ROUTE_EDGES, ids=lambda c: c.name)
+def test_routing_blocks(torch_cuda, cfg):
+    """The chained forward passes (logits and routing in one launch) and the separate calls give the same bits; the
+    outputs match the oracle."""
+    import numpy as np
+    from test_gpu_parity import _run
+    outs = {}
+    for how in ("steps", "fused", "chained"):
+        layer = _run(cfg, how)
+        try:
+            outs[how] = parity.fetch(layer)
+            if how == "chained":
+                parity.check_full(cfg, layer)
+        finally:
+            layer.close()
+    for how in ("fused", "chained"):
+        for k, v in outs["steps"].items():
+            if k not in ("xe", "ye"):
+                np.testing.assert_array_equal(outs[how][k], v, err_msg=f"{how} {k}")
