@@ -41,21 +41,23 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
 typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) char lds_char;
 
 constexpr int kXcds = 8;
 constexpr int BK = 64;
 
 __device__ __attribute__((aligned(16))) const uint32_t kZeroPiece[4] = {0u, 0u, 0u, 0u};
 
-// The two transposing reads of one fragment, HALF bytes apart.  Not the compiler's builtin: before that one it waits for every
-// outstanding global -> LDS load, which undoes the ring.  Whoever uses the fragment waits for lgkmcnt(0) first.  Measured at 48
-// experts x 512 rows, 1600 x 6400, bf16: dxe 376 -> 261 us, dpre 303 -> 250, dW2 235 -> 227, dW1 254 -> 247.
-template <int OFFSET, int HALF, typename V>
-__device__ __forceinline__ void read_transposed(V &f, unsigned at)
+// The two transposing reads of one fragment, HALF bytes apart.  Unless the compiler knows that they do not touch what the
+// global -> LDS loads in flight write, it waits for all of those before each read, which undoes the ring: slab_step_in's
+// restrict pointers (the stage read, the stage filled) tell it.  Measured at 48 experts x 512 rows, 1600 x 6400, bf16:
+// dxe 376 -> 261 us, dpre 303 -> 250, dW2 235 -> 227, dW1 254 -> 247.
+template <int HALF, typename V>
+__device__ __forceinline__ void read_transposed(V &f, const lds_char *at)
 {
     struct { s16x4 lo, hi; } t;
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(t.lo) : "v"(at), "n"(OFFSET));
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(t.hi) : "v"(at), "n"(OFFSET + HALF));
+    t.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)at);
+    t.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(at + HALF));
     f = __builtin_bit_cast(V, t);
 }
 
@@ -202,10 +204,10 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
     const size_t adv_x = XT ? (size_t)BK * a.ldx : (size_t)BK, adv_w = WT ? (size_t)BK * a.ldw : (size_t)BK;
     const E *zero = reinterpret_cast<const E *>(kZeroPiece);
     // load instruction i of slab `slab` into `stage`
-    auto load_one = [&](int wave, int i, int slab, int stage) {
+    auto load_one = [&](int wave, int i, int slab, lds_char *to) {
         const E *p = src[i] + (size_t)slab * (i < XG ? adv_x : adv_w);
         if (KRAGGED && slab * BK + krow[i] >= kv) p = zero;   // beyond the contraction length
-        __builtin_amdgcn_global_load_lds(SMILE_GPTR(p), SMILE_LPTR(&lds[stage * STAGE + (wave + i * NW) * 64]), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(SMILE_GPTR(p), SMILE_LPTR(to + (wave + i * NW) * 1024), 16, 0, 0);
     };
     // Per-lane indices are derived afresh wherever they are needed (PERSIST: through an opaque copy of the
     // thread id), so that nothing computed from them stays in registers from one tile to the next.
@@ -236,7 +238,7 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
         for (int s = 0; s < STAGES - 1; ++s)
             if (s < slabs) {
 #pragma unroll
-                for (int i = 0; i < GPW; ++i) load_one(wave, i, s, s);
+                for (int i = 0; i < GPW; ++i) load_one(wave, i, s, (lds_char *)(lds + s * STAGE));
             }
     };
 
@@ -289,10 +291,11 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
 
     const bool wave_live = rt * BM + wm * WM < rows;   // wave-uniform
     int stage = 0;
-    // One K slab.  ISSUE: this iteration also issues the loads of slab kt+STAGES-1.  As in the forward kernel
+    // One K slab, read from cur_stage.  ISSUE: this iteration also issues the loads of slab kt+STAGES-1, into
+    // next_stage, which is another one (STAGES >= 2).  As in the forward kernel
     // the fragments of k-step kk+1 are fetched while the MFMAs of k-step kk run, the next slab's load
     // instructions are spread over the k-steps, and the instruction order is pinned.
-    auto slab_step = [&](auto issue_tag, int kt) {
+    auto slab_step_in = [&](auto issue_tag, int kt, const lds_char *__restrict cur_stage, lds_char *__restrict next_stage) {
         constexpr bool ISSUE = decltype(issue_tag)::value;
         if (ISSUE) {
             // a prefetched tile's first slabs were requested before the previous tile's stores: wait for all
@@ -306,26 +309,23 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
             else wait_vmcnt<0>();
         }
         __builtin_amdgcn_s_barrier();
-        const int nstage = stage == 0 ? STAGES - 1 : stage - 1;
         const int nxt = kt + STAGES - 1;
-        const char *cur_stage = reinterpret_cast<const char *>(lds + stage * STAGE);
-        const unsigned cur_at = (unsigned)(size_t)(__attribute__((address_space(3))) const char *)cur_stage;
         bf16x8 xf[2][TM], wf[2][TN];
         auto fetch_one = [&](auto slot, auto kstep) {   // fragment `slot` (x tiles first) of k-step `kstep`
             constexpr int F = decltype(slot)::value, KK = decltype(kstep)::value;
             if constexpr (F < TM) {
-                if constexpr (XT) read_transposed<KK * 16 * XTile::kPiecesPerK * 16, 4 * XTile::kPiecesPerK * 16>(xf[KK & 1][F], cur_at + xoff[F]);
-                else xf[KK & 1][F] = *reinterpret_cast<const bf16x8 *>(cur_stage + xoff[F] + (((2 * KK + fhi) ^ fsw) * 16));
+                if constexpr (XT) read_transposed<4 * XTile::kPiecesPerK * 16>(xf[KK & 1][F], cur_stage + xoff[F] + KK * 16 * XTile::kPiecesPerK * 16);
+                else xf[KK & 1][F] = *(const __attribute__((address_space(3))) bf16x8 *)(cur_stage + xoff[F] + (((2 * KK + fhi) ^ fsw) * 16));
             } else {
                 constexpr int I = F - TM;
-                if constexpr (WT) read_transposed<KK * 16 * WTile::kPiecesPerK * 16, 4 * WTile::kPiecesPerK * 16>(wf[KK & 1][I], cur_at + woff[I]);
-                else wf[KK & 1][I] = *reinterpret_cast<const bf16x8 *>(cur_stage + woff[I] + (((2 * KK + fhi) ^ fsw) * 16));
+                if constexpr (WT) read_transposed<4 * WTile::kPiecesPerK * 16>(wf[KK & 1][I], cur_stage + woff[I] + KK * 16 * WTile::kPiecesPerK * 16);
+                else wf[KK & 1][I] = *(const __attribute__((address_space(3))) bf16x8 *)(cur_stage + woff[I] + (((2 * KK + fhi) ^ fsw) * 16));
             }
         };
         auto issue_part = [&](int l0, int l1) {
 #pragma unroll
             for (int i = 0; i < GPW; ++i)
-                if (i >= l0 && i < l1) load_one(wave, i, nxt, nstage);
+                if (i >= l0 && i < l1) load_one(wave, i, nxt, next_stage);
         };
         constexpr int KS = BK / 16;
         if (!wave_live) {
@@ -352,6 +352,10 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
             });
         });
         stage = stage + 1 == STAGES ? 0 : stage + 1;
+    };
+    auto slab_step = [&](auto issue_tag, int kt) {
+        const int at = stage;
+        slab_step_in(issue_tag, kt, (const lds_char *)(lds + at * STAGE), (lds_char *)(lds + (at == 0 ? STAGES - 1 : at - 1) * STAGE));
     };
     // the next tile is chosen before the main loop, so that the loads of its row counts are long back when
     // the epilogue needs them
