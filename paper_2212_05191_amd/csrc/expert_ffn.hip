@@ -14,13 +14,16 @@
 //     (global_load_lds_dwordx4: no staging registers, no ds_write) into a ring of STAGES buffers
 //     with STAGES-1 slabs in flight.  Per slab: wait until this wave's part has landed (s_waitcnt
 //     vmcnt), one s_barrier (every wave's part landed, and every wave is done reading the buffer
-//     about to be refilled), issue the loads of the slab STAGES-1 ahead, then the MFMAs.
+//     about to be refilled), issue the loads of the slab STAGES-1 ahead beside the MFMAs.  The wait for the next slab comes
+//     before the LAST k-step of a slab, so that no LDS read at a slab's start is waited for with the matrix cores idle
+//     (with the reads moved to the front of a k-step, us: 16 experts x 512 rows, 768 x 3072 forward 125.4 -> 123.2,
+//     128 experts 501 -> 486, 256 experts skewed 1024 -> 961).
 //   * A direct load writes 64 lanes x 16 bytes to consecutive LDS addresses, i.e. whole rows of a
 //     slab.  The bank swizzle is therefore applied on the global side: the lane that fills position
 //     p of a row fetches piece p ^ f(row), so piece c of a row sits at position c ^ f(row) and the
 //     32 rows a wave reads for one MFMA operand fall on distinct banks.
 //   * The weight tile is the MFMA "A" operand and the token tile the "B" operand, so a lane ends up
-//     with 4 consecutive output columns of one token row.  The epilogue (bias, activation, round
+//     with 4 consecutive output columns of one token row.  The epilogue (activation, round
 //     to the storage type) writes them to LDS and the workgroup then stores whole rows, 16 bytes per lane, so
 //     every global store instruction covers full cache lines.
 //   * Traffic L2 -> LDS per flop falls as 1/BM + 1/BN; that path (about 64 B/clk per CU at best)
@@ -164,83 +167,83 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_nt_kernel(Gem
     const int frow = lane & 31, fhi = lane >> 5, fsw = swz<BK, SWZ>(lane);   // tile bases are multiples of 32
     const int xbase = (wm * WM + frow) * PPR, wbase = (BM + wn * WN + frow) * PPR;
 
+    // The accumulators start at the bias: element v of a lane is column 8*(v/4) + 4*(lane/32) + v%4 of its 32x32 tile, four
+    // columns to an 8-byte load (Nout % 8 == 0, so a block of four is inside the row or outside as a whole).  Added in the
+    // epilogue element by element it was 96 waits in a row (15 experts x 334 rows, 960 x 3840, f16 with biases: 186 -> 159 us).
     f32x16 acc[TN][TM];
+    if (a.bias) {
+        const E *bias = static_cast<const E *>(a.bias) + (size_t)e * Nout;
+        bf16x4 b[TN][4];
 #pragma unroll
-    for (int i = 0; i < TN; ++i)
+        for (int i = 0; i < TN; ++i)
 #pragma unroll
-        for (int j = 0; j < TM; ++j)
+            for (int q = 0; q < 4; ++q)
+                b[i][q] = *reinterpret_cast<const bf16x4 *>(bias + min(ct * BN + wn * WN + i * 32 + 8 * q + 4 * fhi, Nout - 4));
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = (float)b[i][v / 4][v % 4];
+    } else {
+#pragma unroll
+        for (int i = 0; i < TN; ++i)
+#pragma unroll
+            for (int j = 0; j < TM; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    }
 
-    int stage = 0;
     const bool wave_live = rt * BM + wm * WM < rows;   // wave-uniform
-    // One K slab.  ISSUE: this iteration also issues the loads of slab kt+STAGES-1 (always true in
-    // the steady state, false in the last STAGES-1 iterations).  The loads are spread over the
-    // k-steps and the instruction order is pinned (sched_group_barrier: one MFMA, one LDS read, ...,
-    // then the k-step's share of the global loads) so that the three pipes stay busy together
-    // instead of in bursts.
-    auto slab_step = [&](auto issue_tag, int kt) {
-        constexpr bool ISSUE = decltype(issue_tag)::value;
-        if (ISSUE) {
-            // a prefetched tile's first slabs were requested before the previous tile's stores: wait for all
-            if (PREFETCH && STAGES > 2 && kt == 0) wait_vmcnt<0>();
-            else wait_vmcnt<(STAGES - 2) * GPW>();
-        } else {
-            const int ahead = slabs - 1 - kt;   // 0 .. STAGES-2 slabs were issued after this one
-            if (PREFETCH && kt == 0) wait_vmcnt<0>();
-            else if (STAGES >= 4 && ahead == 2) wait_vmcnt<2 * GPW>();
-            else if (STAGES >= 3 && ahead == 1) wait_vmcnt<GPW>();
-            else wait_vmcnt<0>();
-        }
+    constexpr int KS = BK / 16, NM = TM * TN, NF = TM + TN;
+    bf16x8 xf[2][TM], wf[2][TN];   // fragments of the k-step being multiplied and of the next one
+    auto fetch_one = [&](auto slot, auto kstep, const u32x4 *from) {   // fragment `slot` (token tiles first) of k-step `kstep`
+        constexpr int F = decltype(slot)::value, KK = decltype(kstep)::value;
+        const int p = (2 * KK + fhi) ^ fsw;
+        if constexpr (F < TM) xf[KK & 1][F] = __builtin_bit_cast(bf16x8, from[xbase + F * 32 * PPR + p]);
+        else wf[KK & 1][F - TM] = __builtin_bit_cast(bf16x8, from[wbase + (F - TM) * 32 * PPR + p]);
+    };
+    auto issue_one = [&](int i, int slab, int to) {
+        __builtin_amdgcn_global_load_lds(SMILE_GPTR(src[i] + slab * BK), SMILE_LPTR(&lds[to * STAGE + (wave + i * NW) * 64]), 16, 0, 0);
+    };
+    // Waits for slab `s` (this wave's part landed, then everybody's).  Every wave is then also done reading slab s-1, so
+    // slab s-1+STAGES may overwrite it.  `issued_after`: slabs requested after s by now.
+    auto enter_slab = [&](int issued_after, bool first) {
+        // a prefetched tile's first slabs were requested before the previous tile's stores: wait for all
+        if (PREFETCH && first) wait_vmcnt<0>();
+        else if (STAGES >= 4 && issued_after == 2) wait_vmcnt<2 * GPW>();
+        else if (STAGES >= 3 && issued_after == 1) wait_vmcnt<GPW>();
+        else wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();
-        const int nstage = stage == 0 ? STAGES - 1 : stage - 1;
-        const int nxt = kt + STAGES - 1;
-        const u32x4 *cur_stage = lds + stage * STAGE;
-        bf16x8 xf[2][TM], wf[2][TN];
-        auto fetch = [&](int buf, int kk) {
-            const int p = (2 * kk + fhi) ^ fsw;
-#pragma unroll
-            for (int j = 0; j < TM; ++j) xf[buf][j] = __builtin_bit_cast(bf16x8, cur_stage[xbase + j * 32 * PPR + p]);
-#pragma unroll
-            for (int i = 0; i < TN; ++i) wf[buf][i] = __builtin_bit_cast(bf16x8, cur_stage[wbase + i * 32 * PPR + p]);
-        };
-        constexpr int KS = BK / 16;
-        if (!wave_live) {
-            // none of this wave's token rows exists (ragged tile): it only helps loading
-            if (ISSUE) issue(wave, nxt, nstage);
-            stage = stage + 1 == STAGES ? 0 : stage + 1;
-            return;
-        }
-        fetch(0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int kk = 0; kk < KS; ++kk) {
-            // this k-step's share of the next slab's load instructions
-            const int l0 = GPW * kk / KS, l1 = GPW * (kk + 1) / KS;
-            if (kk + 1 < KS) fetch((kk + 1) & 1, kk + 1);
-            if (ISSUE) {
-#pragma unroll
-                for (int i = 0; i < GPW; ++i)
-                    if (i >= l0 && i < l1)
-                        __builtin_amdgcn_global_load_lds(SMILE_GPTR(src[i] + nxt * BK),
-                                                         SMILE_LPTR(&lds[nstage * STAGE + (wave + i * NW) * 64]), 16, 0, 0);
-            }
-#pragma unroll
-            for (int i = 0; i < TN; ++i)
-#pragma unroll
-                for (int j = 0; j < TM; ++j)
-                    acc[i][j] = Half<E>::mfma_32x32x16(wf[kk & 1][i], xf[kk & 1][j], acc[i][j]);
-            // order inside the k-step: MFMA, LDS read, MFMA, LDS read, ... then MFMA + global loads
-            constexpr int NM = TM * TN, ND = TM + TN;
-#pragma unroll
-            for (int r = 0; r < NM; ++r) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                       // 1 MFMA
-                if (kk + 1 < KS && r < ND) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);   // 1 LDS read
-                if (ISSUE && r >= NM - (l1 - l0) ) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);   // 1 global load
-            }
+    };
+    // One K slab, its first fragments already in registers.  MORE: slabs kt+1 .. kt+STAGES-1 exist (steady state).  The wait
+    // and the barrier for slab kt+1 stand in front of this slab's LAST k-step, whose MFMAs cover the LDS reads of the next
+    // slab's first fragments; the load instructions of slab kt+STAGES-1 are spread over the other k-steps.  Inside a k-step
+    // the reads come right behind the first MFMAs, so that the last MFMAs cover their latency (the order is pinned).
+    auto slab_step = [&](auto more_tag, int kt, int stage) {
+        constexpr bool MORE = decltype(more_tag)::value;
+        const int nstage = stage == 0 ? STAGES - 1 : stage - 1, next = stage + 1 == STAGES ? 0 : stage + 1;
+        for_constants<KS>([&](auto kstep) {
+            constexpr int KK = decltype(kstep)::value;
+            constexpr bool LAST = KK + 1 == KS;
+            constexpr int L0 = LAST ? 0 : GPW * KK / (KS - 1), L1 = LAST ? 0 : GPW * (KK + 1) / (KS - 1);
+            __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this k-step's fragments
+            if (LAST && (MORE || kt + 1 < slabs)) enter_slab(MORE ? STAGES - 2 : min(STAGES - 2, slabs - 2 - kt), false);
             __builtin_amdgcn_sched_barrier(0);
-        }
-        stage = stage + 1 == STAGES ? 0 : stage + 1;
+            const u32x4 *from = lds + (LAST ? next : stage) * STAGE;   // after the last slab: stale, and never multiplied
+            for_constants<NM>([&](auto m) {
+                constexpr int R = decltype(m)::value;
+                acc[R / TM][R % TM] = Half<E>::mfma_32x32x16(wf[KK & 1][R / TM], xf[KK & 1][R % TM], acc[R / TM][R % TM]);
+                constexpr int F0 = min_int(NF, 2 * R), F1 = min_int(NF, 2 * R + 2);
+                for_constants<F1 - F0>([&](auto f) {
+                    fetch_one(std::integral_constant<int, F0 + decltype(f)::value>{}, std::integral_constant<int, (KK + 1) % KS>{}, from);
+                });
+                constexpr int G0 = L0 + (L1 - L0) * R / NM, G1 = L0 + (L1 - L0) * (R + 1) / NM;
+                if constexpr (MORE)
+                    for_constants<G1 - G0>([&](auto g) { issue_one(G0 + decltype(g)::value, kt + STAGES - 1, nstage); });
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        });
     };
     // the next tile is chosen before the main loop, so that the loads of its row counts are long back when
     // the epilogue needs them (after it where registers are short: DUAL)
@@ -250,20 +253,37 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_nt_kernel(Gem
         walk.advance();
         more = select(nxt_tile);
     }
-    int kt = 0;
-    for (; kt + STAGES - 1 < slabs; ++kt) slab_step(std::true_type{}, kt);
-    for (; kt < slabs; ++kt) slab_step(std::false_type{}, kt);
+    enter_slab(min(STAGES - 2, slabs - 1), true);
+    if (wave_live) {
+        for_constants<NF>([&](auto f) { fetch_one(f, std::integral_constant<int, 0>{}, lds); });
+        int kt = 0, stage = 0;
+        for (; kt + STAGES - 1 < slabs; ++kt) {
+            slab_step(std::true_type{}, kt, stage);
+            stage = stage + 1 == STAGES ? 0 : stage + 1;
+        }
+        for (; kt < slabs; ++kt) {
+            slab_step(std::false_type{}, kt, stage);
+            stage = stage + 1 == STAGES ? 0 : stage + 1;
+        }
+    } else {
+        // none of this wave's token rows exists (ragged tile): it only helps loading
+        int stage = 0;
+        for (int kt = 0; kt < slabs; ++kt) {
+            if (kt > 0) enter_slab(min(STAGES - 2, slabs - 1 - kt), false);
+            if (kt + STAGES - 1 < slabs) issue(wave, kt + STAGES - 1, stage == 0 ? STAGES - 1 : stage - 1);
+            stage = stage + 1 == STAGES ? 0 : stage + 1;
+        }
+    }
     if constexpr (PERSIST && DUAL) {
         walk.advance();
         more = select(nxt_tile);
     }
 
     // ---- epilogue.  Accumulator element v of a lane is (column 8*(v/4) + 4*(lane/32) + v%4,
-    // row lane%32) of its 32x32 tile.  One pass per 32-row slice of the wave tiles: bias +
+    // row lane%32) of its 32x32 tile.  One pass per 32-row slice of the wave tiles:
     // activation + rounding, 8-byte writes into a [OROWS][BN] staging tile, then row-contiguous
     // 16-byte global stores by the whole workgroup.
     const int32_t *y_rows = a.y_rows ? a.y_rows + (size_t)e * a.C : nullptr;
-    const E *bias = a.bias ? static_cast<const E *>(a.bias) + (size_t)e * Nout : nullptr;
     u32x2 *stg = reinterpret_cast<u32x2 *>(lds + STG);
     constexpr int OPR = BN / 8;   // 16-byte pieces per output row
 #pragma unroll
@@ -283,8 +303,7 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_nt_kernel(Gem
                     bf16x4 out;
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
-                        float f = acc[i][j][4 * q + v];
-                        if (bias) f += (float)bias[min(ct * BN + lcol + v, Nout - 1)];
+                        const float f = acc[i][j][4 * q + v];
                         out[v] = (E)(pass == 0 ? activate<ACT>(f) : f);
                     }
                     stg[((wm * 32 + frow) * OSTRIDE) * 2 + (lcol >> 2)] = __builtin_bit_cast(u32x2, out);

@@ -29,7 +29,6 @@
 //   * epilogue as in the forward kernel: fp32 -> bf16, staged through LDS, row-contiguous 16-byte
 //     stores; POST multiplies by act'(aux) there (the gradient at the pre-activation).
 #include <type_traits>
-#include <utility>
 
 #include "smile_internal.hpp"
 
@@ -49,7 +48,7 @@ constexpr int BK = 64;
 __device__ __attribute__((aligned(16))) const uint32_t kZeroPiece[4] = {0u, 0u, 0u, 0u};
 
 // The two transposing reads of one fragment, HALF bytes apart.  Unless the compiler knows that they do not touch what the
-// global -> LDS loads in flight write, it waits for all of those before each read, which undoes the ring: slab_step_in's
+// global -> LDS loads in flight write, it waits for all of those before each read, which undoes the ring: front_steps'
 // restrict pointers (the stage read, the stage filled) tell it.  Measured at 48 experts x 512 rows, 1600 x 6400, bf16:
 // dxe 376 -> 261 us, dpre 303 -> 250, dW2 235 -> 227, dW1 254 -> 247.
 template <int HALF, typename V>
@@ -59,17 +58,6 @@ __device__ __forceinline__ void read_transposed(V &f, const lds_char *at)
     t.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)at);
     t.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(at + HALF));
     f = __builtin_bit_cast(V, t);
-}
-
-template <int N, typename F, int... I>
-__device__ __forceinline__ void for_constants(F &&f, std::integer_sequence<int, I...>)
-{
-    (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void for_constants(F &&f)
-{
-    for_constants<N>(f, std::make_integer_sequence<int, N>{});
 }
 
 #define SMILE_GPTR(p) ((const __attribute__((address_space(1))) void *)(p))
@@ -290,72 +278,68 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
 
     const bool wave_live = rt * BM + wm * WM < rows;   // wave-uniform
-    int stage = 0;
-    // One K slab, read from cur_stage.  ISSUE: this iteration also issues the loads of slab kt+STAGES-1, into
-    // next_stage, which is another one (STAGES >= 2).  As in the forward kernel
-    // the fragments of k-step kk+1 are fetched while the MFMAs of k-step kk run, the next slab's load
-    // instructions are spread over the k-steps, and the instruction order is pinned.
-    auto slab_step_in = [&](auto issue_tag, int kt, const lds_char *__restrict cur_stage, lds_char *__restrict next_stage) {
-        constexpr bool ISSUE = decltype(issue_tag)::value;
-        if (ISSUE) {
-            // a prefetched tile's first slabs were requested before the previous tile's stores: wait for all
-            if (PREFETCH && STAGES > 2 && kt == 0) wait_vmcnt<0>();
-            else wait_vmcnt<(STAGES - 2) * GPW>();
+    constexpr int KS = BK / 16, NM = TM * TN, NF = TM + TN;
+    bf16x8 xf[2][TM], wf[2][TN];   // fragments of the k-step being multiplied and of the next one
+    auto fetch_one = [&](auto slot, auto kstep, const lds_char *from) {   // fragment `slot` (x tiles first) of k-step `kstep`
+        constexpr int F = decltype(slot)::value, KK = decltype(kstep)::value;
+        if constexpr (F < TM) {
+            if constexpr (XT) read_transposed<4 * XTile::kPiecesPerK * 16>(xf[KK & 1][F], from + xoff[F] + KK * 16 * XTile::kPiecesPerK * 16);
+            else xf[KK & 1][F] = *(const __attribute__((address_space(3))) bf16x8 *)(from + xoff[F] + (((2 * KK + fhi) ^ fsw) * 16));
         } else {
-            const int ahead = slabs - 1 - kt;   // 0 .. STAGES-2 slabs were issued after this one
-            if (PREFETCH && kt == 0) wait_vmcnt<0>();
-            else if (STAGES >= 4 && ahead == 2) wait_vmcnt<2 * GPW>();
-            else if (STAGES >= 3 && ahead == 1) wait_vmcnt<GPW>();
-            else wait_vmcnt<0>();
+            constexpr int I = F - TM;
+            if constexpr (WT) read_transposed<4 * WTile::kPiecesPerK * 16>(wf[KK & 1][I], from + woff[I] + KK * 16 * WTile::kPiecesPerK * 16);
+            else wf[KK & 1][I] = *(const __attribute__((address_space(3))) bf16x8 *)(from + woff[I] + (((2 * KK + fhi) ^ fsw) * 16));
         }
-        __builtin_amdgcn_s_barrier();
-        const int nxt = kt + STAGES - 1;
-        bf16x8 xf[2][TM], wf[2][TN];
-        auto fetch_one = [&](auto slot, auto kstep) {   // fragment `slot` (x tiles first) of k-step `kstep`
-            constexpr int F = decltype(slot)::value, KK = decltype(kstep)::value;
-            if constexpr (F < TM) {
-                if constexpr (XT) read_transposed<4 * XTile::kPiecesPerK * 16>(xf[KK & 1][F], cur_stage + xoff[F] + KK * 16 * XTile::kPiecesPerK * 16);
-                else xf[KK & 1][F] = *(const __attribute__((address_space(3))) bf16x8 *)(cur_stage + xoff[F] + (((2 * KK + fhi) ^ fsw) * 16));
-            } else {
-                constexpr int I = F - TM;
-                if constexpr (WT) read_transposed<4 * WTile::kPiecesPerK * 16>(wf[KK & 1][I], cur_stage + woff[I] + KK * 16 * WTile::kPiecesPerK * 16);
-                else wf[KK & 1][I] = *(const __attribute__((address_space(3))) bf16x8 *)(cur_stage + woff[I] + (((2 * KK + fhi) ^ fsw) * 16));
-            }
-        };
-        auto issue_part = [&](int l0, int l1) {
-#pragma unroll
-            for (int i = 0; i < GPW; ++i)
-                if (i >= l0 && i < l1) load_one(wave, i, nxt, next_stage);
-        };
-        constexpr int KS = BK / 16;
-        if (!wave_live) {
-            if (ISSUE) issue_part(0, GPW);   // none of this wave's rows exists: it only helps loading
-            stage = stage + 1 == STAGES ? 0 : stage + 1;
-            return;
-        }
-        constexpr int NM = TM * TN, NF = TM + TN;
-        for_constants<NF>([&](auto f) { fetch_one(f, std::integral_constant<int, 0>{}); });
-        for_constants<KS>([&](auto kstep) {
-            constexpr int KK = decltype(kstep)::value, L0 = GPW * KK / KS, L1 = GPW * (KK + 1) / KS;
-            __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this k-step's fragments
-            __builtin_amdgcn_sched_barrier(0);
-            for_constants<NM>([&](auto m) {   // MFMA, its share of the next k-step's LDS reads; global loads beside the last MFMAs
-                constexpr int R = decltype(m)::value;
-                acc[R / TM][R % TM] = Half<E>::mfma_32x32x16(wf[KK & 1][R / TM], xf[KK & 1][R % TM], acc[R / TM][R % TM]);
-                constexpr int F0 = NF * R / NM, F1 = NF * (R + 1) / NM;
-                if constexpr (KK + 1 < KS)
-                    for_constants<F1 - F0>([&](auto f) {
-                        fetch_one(std::integral_constant<int, F0 + decltype(f)::value>{}, std::integral_constant<int, KK + 1>{});
-                    });
-                if constexpr (ISSUE && R >= NM - (L1 - L0)) issue_part(L0 + R - NM + L1 - L0, L0 + R - NM + L1 - L0 + 1);
-                __builtin_amdgcn_sched_barrier(0);
-            });
-        });
-        stage = stage + 1 == STAGES ? 0 : stage + 1;
     };
-    auto slab_step = [&](auto issue_tag, int kt) {
-        const int at = stage;
-        slab_step_in(issue_tag, kt, (const lds_char *)(lds + at * STAGE), (lds_char *)(lds + (at == 0 ? STAGES - 1 : at - 1) * STAGE));
+    // Waits for a slab (this wave's part landed, then everybody's); every wave is then also done reading the slab before it,
+    // whose buffer may be filled again.  `issued_after`: slabs requested after it by now.
+    auto enter_slab = [&](int issued_after, bool first) {
+        // a prefetched tile's first slabs were requested before the previous tile's stores: wait for all
+        if (PREFETCH && first) wait_vmcnt<0>();
+        else if (STAGES >= 4 && issued_after == 2) wait_vmcnt<2 * GPW>();
+        else if (STAGES >= 3 && issued_after == 1) wait_vmcnt<GPW>();
+        else wait_vmcnt<0>();
+        __builtin_amdgcn_s_barrier();
+    };
+    // The MFMAs of k-step KK, and behind the first of them the reads of the k-step after it, so that the last ones cover
+    // the reads' latency; load instructions L0 .. L1-1 of slab `slab` are spread over all (the order is pinned).
+    auto multiply = [&](auto kstep, auto l0, auto l1, const lds_char *from, int slab, lds_char *fill) {
+        constexpr int KK = decltype(kstep)::value, L0 = decltype(l0)::value, L1 = decltype(l1)::value;
+        __builtin_amdgcn_sched_barrier(0);
+        for_constants<NM>([&](auto m) {
+            constexpr int R = decltype(m)::value;
+            acc[R / TM][R % TM] = Half<E>::mfma_32x32x16(wf[KK & 1][R / TM], xf[KK & 1][R % TM], acc[R / TM][R % TM]);
+            constexpr int F0 = min_int(NF, 2 * R), F1 = min_int(NF, 2 * R + 2);
+            for_constants<F1 - F0>([&](auto f) {
+                fetch_one(std::integral_constant<int, F0 + decltype(f)::value>{}, std::integral_constant<int, (KK + 1) % KS>{}, from);
+            });
+            constexpr int G0 = L0 + (L1 - L0) * R / NM, G1 = L0 + (L1 - L0) * (R + 1) / NM;
+            for_constants<G1 - G0>([&](auto g) { load_one(wave, G0 + decltype(g)::value, slab, fill); });
+            __builtin_amdgcn_sched_barrier(0);
+        });
+    };
+    // All k-steps of a slab but the last, its first fragments already in registers, reading `from`.  MORE: with the load
+    // instructions of slab `slab`, into `fill`, which is another stage (STAGES >= 2).
+    auto front_steps = [&](auto more_tag, int slab, const lds_char *__restrict from, lds_char *__restrict fill) {
+        constexpr int G = decltype(more_tag)::value ? GPW : 0;
+        for_constants<KS - 1>([&](auto kstep) {
+            constexpr int KK = decltype(kstep)::value;
+            __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): this k-step's fragments
+            multiply(kstep, std::integral_constant<int, G * KK / (KS - 1)>{}, std::integral_constant<int, G * (KK + 1) / (KS - 1)>{}, from, slab, fill);
+        });
+    };
+    // One K slab.  MORE: slabs kt+1 .. kt+STAGES-1 exist (steady state).  The wait and the barrier for slab kt+1 stand in front
+    // of this slab's LAST k-step, whose MFMAs cover the LDS reads of the next slab's first fragments (training step with
+    // 256 skewed experts, forward GEMMs arranged alike: 3601 -> 3426 us).
+    auto slab_step = [&](auto more_tag, int kt, int stage) {
+        constexpr bool MORE = decltype(more_tag)::value;
+        const int fill = stage == 0 ? STAGES - 1 : stage - 1, next = stage + 1 == STAGES ? 0 : stage + 1;
+        front_steps(more_tag, kt + STAGES - 1, (const lds_char *)(lds + stage * STAGE), (lds_char *)(lds + fill * STAGE));
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the last k-step's fragments, this wave's last reads of the slab
+        if (MORE || kt + 1 < slabs) enter_slab(MORE ? STAGES - 2 : min(STAGES - 2, slabs - 2 - kt), false);
+        // after the last slab: stale fragments, never multiplied
+        multiply(std::integral_constant<int, KS - 1>{}, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{},
+                 (const lds_char *)(lds + next * STAGE), 0, nullptr);
     };
     // the next tile is chosen before the main loop, so that the loads of its row counts are long back when
     // the epilogue needs them
@@ -365,9 +349,30 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
         walk.advance();
         more = select(nxt_tile);
     }
-    int kt = 0;
-    for (; kt + STAGES - 1 < slabs; ++kt) slab_step(std::true_type{}, kt);
-    for (; kt < slabs; ++kt) slab_step(std::false_type{}, kt);
+    if (slabs > 0) enter_slab(min(STAGES - 2, slabs - 1), true);
+    int kt = 0, stage = 0;
+    if (wave_live) {
+        if (slabs > 0) for_constants<NF>([&](auto f) { fetch_one(f, std::integral_constant<int, 0>{}, (const lds_char *)lds); });
+        for (; kt + STAGES - 1 < slabs; ++kt) {
+            slab_step(std::true_type{}, kt, stage);
+            stage = stage + 1 == STAGES ? 0 : stage + 1;
+        }
+        for (; kt < slabs; ++kt) {
+            slab_step(std::false_type{}, kt, stage);
+            stage = stage + 1 == STAGES ? 0 : stage + 1;
+        }
+    } else {
+        // none of this wave's rows exists: it only helps loading
+        for (; kt < slabs; ++kt) {
+            if (kt > 0) enter_slab(min(STAGES - 2, slabs - 1 - kt), false);
+            if (kt + STAGES - 1 < slabs) {
+                lds_char *fill = (lds_char *)(lds + (stage == 0 ? STAGES - 1 : stage - 1) * STAGE);
+#pragma unroll
+                for (int i = 0; i < GPW; ++i) load_one(wave, i, kt + STAGES - 1, fill);
+            }
+            stage = stage + 1 == STAGES ? 0 : stage + 1;
+        }
+    }
 
     // ---- epilogue.  Accumulator element v of a lane is (column 8*(v/4) + 4*(lane/32) + v%4, row lane%32)
     // of its 32x32 tile: rounded to bf16, staged as a [OROWS][BN] tile, stored row-contiguously.

@@ -5,6 +5,7 @@
 #include <hip/hip_ext.h>
 #include <stdint.h>
 #include <stddef.h>
+#include <utility>
 
 #include "smile.h"
 
@@ -18,6 +19,20 @@ inline bool is_half(int dtype) { return dtype == SMILE_DTYPE_BF16 || dtype == SM
 // 32-bit word holding two elements to and from fp32 (round to nearest even).
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float mfma_f32x4;
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float mfma_f32x16;
+
+// f(0), f(1), ... f(N - 1), each index a compile-time constant
+template <int N, typename F, int... I>
+__device__ __forceinline__ void for_constants(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void for_constants(F &&f)
+{
+    for_constants<N>(f, std::make_integer_sequence<int, N>{});
+}
+
+__host__ __device__ constexpr int min_int(int a, int b) { return a < b ? a : b; }
 
 template <typename E>
 struct Half;
