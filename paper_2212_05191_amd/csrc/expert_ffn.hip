@@ -396,29 +396,42 @@ hipError_t launch_half_tile(GemmArgs a, int N, int act, const Tuning &tune, hipS
     return hipGetLastError();
 }
 
-// The two epilogue variants of the backward pass, on the up-projection tile shape only:
-//   a.y2 given: act(product) and the bare product in one launch;   post != 0: output times act'(a.aux).
-template <typename E>
-hipError_t launch_half_special_typed(GemmArgs a, int N, int act, int post, const Tuning &tune, hipStream_t s)
+// The dual-output launch (a.y2 given: act(product) and the bare product) of one tile shape, four waves.
+template <typename E, int BM, int BN, int STAGES, int OCC>
+hipError_t launch_half_dual(GemmArgs a, int N, int act, const Tuning &tune, hipStream_t s)
 {
+    a.row_tiles = (a.C + BM - 1) / BM;
+    a.col_tiles = (a.Nout + BN - 1) / BN;
+    a.tiles = N * a.row_tiles * a.col_tiles;
+    a.N = N;
+    const int slots = workgroup_slots(tune, workgroups_per_cu(4, OCC, STAGES * (BM + BN) * 64 * 2));
+    const bool persist = use_persistent_grid(tune, N, a.tiles, slots);
+    const dim3 grid(persist ? slots : (a.tiles + kXcds - 1) / kXcds * kXcds), block(256);
+    if (act == 1 && persist) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 1, true, 0, true>), grid, block, 0, s, a);
+    else if (act == 1) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 1, true>), grid, block, 0, s, a);
+    else if (persist) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 3, true, 0, true>), grid, block, 0, s, a);
+    else SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 3, true>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
+// The two epilogue variants of the backward pass: a.y2 given (launch_half_dual; `tile` as pick_tile says, with the
+// shapes that exist for it), post != 0: output times act'(a.aux), on the up-projection tile shape.
+template <typename E>
+hipError_t launch_half_special_typed(GemmArgs a, int N, int act, int post, int tile, const Tuning &tune, hipStream_t s)
+{
+    if (a.y2) {
+        if (tile == 9 || tile == 7) return launch_half_dual<E, 64, 64, 3, 3>(a, N, act, tune, s);
+        if (tile == 8 || tile == 5) return launch_half_dual<E, 64, 128, 3, 2>(a, N, act, tune, s);
+        return launch_half_dual<E, 128, 192, 2, 2>(a, N, act, tune, s);
+    }
     constexpr int BM = 128, BN = 192;
     a.row_tiles = (a.C + BM - 1) / BM;
     a.col_tiles = (a.Nout + BN - 1) / BN;
     a.tiles = N * a.row_tiles * a.col_tiles;
     a.N = N;
-    const int slots = workgroup_slots(tune, workgroups_per_cu(4, 2, 2 * (BM + BN) * 64 * 2));
-    const bool persist = use_persistent_grid(tune, N, a.tiles, slots);
-    const dim3 plain((a.tiles + kXcds - 1) / kXcds * kXcds), grid(persist ? dim3(slots) : plain), block(256);
-    if (a.y2) {
-        if (act == 1 && persist) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, 2, 2, 1, 1, true, 0, true>), grid, block, 0, s, a);
-        else if (act == 1) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, 2, 2, 1, 1, true>), grid, block, 0, s, a);
-        else if (persist) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, 2, 2, 1, 3, true, 0, true>), grid, block, 0, s, a);
-        else SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, 2, 2, 1, 3, true>), grid, block, 0, s, a);
-    } else if (post == 1) {
-        SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, 2, 2, 1, 0, false, 1>), plain, block, 0, s, a);
-    } else {
-        SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, 2, 2, 1, 0, false, 2>), plain, block, 0, s, a);
-    }
+    const dim3 plain((a.tiles + kXcds - 1) / kXcds * kXcds), block(256);
+    if (post == 1) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, 2, 2, 1, 0, false, 1>), plain, block, 0, s, a);
+    else SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, 2, 2, 1, 0, false, 2>), plain, block, 0, s, a);
     return hipGetLastError();
 }
 
@@ -434,6 +447,7 @@ hipError_t launch_half_special_typed(GemmArgs a, int N, int act, int post, const
 //     every tile was a workgroup of its own; with the persistent walk over live tiles 128x256 is equal or
 //     better on every shape measured (256 experts at 21 % / 50 % / 95 % fill: 386 / 440 / 653 us against
 //     418 / 496 / 651), so they are only reachable through the override now.
+//   * 64-row tiles (5, 7-9) for few or small buffers: see pick_tile.
 // Larger tiles (256x128 .. 256x256) move fewer bytes L2 -> LDS per flop but were never faster here.
 template <typename E>
 hipError_t launch_half_typed(const GemmArgs &a, int N, int act, int tile, const Tuning &tune, hipStream_t s,
@@ -447,16 +461,36 @@ hipError_t launch_half_typed(const GemmArgs &a, int N, int act, int tile, const 
     case 4: return launch_half_tile<E, 128, 128, 2, 2, 32, 4, 2>(a, N, act, tune, s, t0, t1);
     case 5: return launch_half_tile<E, 64, 256, 1, 4, 64, 2, 2>(a, N, act, tune, s, t0, t1);
     case 6: return launch_half_tile<E, 256, 256, 2, 4, 32, 4, 2>(a, N, act, tune, s, t0, t1);
+    case 7: return launch_half_tile<E, 64, 64, 2, 2, 64, 4, 2>(a, N, act, tune, s, t0, t1);
+    case 8: return launch_half_tile<E, 64, 128, 2, 2, 64, 3, 2>(a, N, act, tune, s, t0, t1);
+    case 9: return launch_half_tile<E, 64, 64, 2, 2, 64, 3, 3>(a, N, act, tune, s, t0, t1);
     default: return hipErrorInvalidValue;
     }
 }
-constexpr int kNumTiles = 7;
+constexpr int kNumTiles = 10;
 
-// Tile choice; Tuning::ffn_tile (0..6) overrides it for tuning runs.
+// Tile choice; Tuning::ffn_tile (0..9) overrides it for tuning runs.  Small buffers and narrow layers leave most of the chip
+// without a 128-row tile (16 experts x 768 columns: 64 tiles of 192 columns on 256 CUs, each a serial chain of K / 64 slabs),
+// so they take 64-row tiles as long as those are few; the counts are those of 64 x 64 tiles over the whole buffers.  bf16, us:
+//   * up, one round of three workgroups per CU (<= 768): 64 x 64, three stages.  16 experts x 16 rows, 768 -> 3072: 22.3 -> 15.9;
+//     32 x 188 rows, 256 -> 512: 10.8 -> 6.6; 4 x 100 rows, 960 -> 3840: 19.9 -> 9.1.  Beyond the line, 16 x 80 rows (1536 tiles): 24.4 -> 28.2.
+//   * up, buffers of at most 64 rows: 64 x 128 up to 8192 (64 x 6 rows, 1024 -> 4096: 107.6 -> 93.1; 128 x 16, 768 -> 3072: 123.8 -> 114.8),
+//     beyond that the chip is full anyway and 64 x 256 reads the token rows least often (256 x 63 rows, 1024 -> 4096: 444.6 -> 404.4; 64 x 128: 415.1).
+//   * down, two rounds of two per CU (<= 1024): 64 x 64 with four stages, K is long.  16 x 16 rows, 3072 -> 768: 31.0 -> 17.2;
+//     8 x 469 rows, 1024 -> 256: 17.2 -> 7.2; 64 x 6, 4096 -> 1024: 123.1 -> 97.0; at 768 of 256 rows 44.8 -> 42.7-44.1, at 1536 of 512 rows 46.9 -> 75.2.
+//   * down, buffers of at most 64 rows: 64 x 128 up to 2048 (128 x 16 rows, 3072 -> 768: 117.0 -> 104.9), then 64 x 256
+//     (256 x 63 rows, 4096 -> 1024: 374.9 -> 369.2; 64 x 128: 379.8).
+// Every tile adds a row's products in the same order: the results are the same bits.
 int pick_tile(const Tuning &tune, int N, int C, int Nout, int K)
 {
     if (tune.ffn_tile >= 0 && tune.ffn_tile < kNumTiles) return tune.ffn_tile;
-    if (Nout >= K) return 0;
+    const long long small = (long long)N * ((C + 63) / 64) * ((Nout + 63) / 64);   // 64 x 64 tiles
+    if (Nout >= K) {
+        if (small <= 768) return 9;
+        return C > 64 ? 0 : small <= 8192 ? 8 : 5;
+    }
+    if (small <= 1024) return 7;
+    if (C <= 64) return small <= 2048 ? 8 : 5;
     const long long tiles = (long long)N * ((C + 127) / 128) * ((Nout + 191) / 192);
     return tiles <= 256 ? 1 : 2;
 }
@@ -471,8 +505,9 @@ hipError_t launch_half(int dtype, const GemmArgs &a, int N, int act, int tile, c
 
 hipError_t launch_half_special(int dtype, const GemmArgs &a, int N, int act, int post, const Tuning &tune, hipStream_t s)
 {
-    if (dtype == SMILE_DTYPE_BF16) return launch_half_special_typed<__bf16>(a, N, act, post, tune, s);
-    return launch_half_special_typed<_Float16>(a, N, act, post, tune, s);
+    const int tile = pick_tile(tune, N, a.C, a.Nout, a.K);
+    if (dtype == SMILE_DTYPE_BF16) return launch_half_special_typed<__bf16>(a, N, act, post, tile, tune, s);
+    return launch_half_special_typed<_Float16>(a, N, act, post, tile, tune, s);
 }
 
 }  // namespace

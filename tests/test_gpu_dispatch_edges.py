@@ -85,3 +85,41 @@ def test_routing_blocks(torch_cuda, cfg):
         for k, v in outs["steps"].items():
             if k not in ("xe", "ye"):
                 np.testing.assert_array_equal(outs[how][k], v, err_msg=f"{how} {k}")
+
+
+# 16-bit forward tiles of 64 rows: both sides of every line of the choice (64 x 64 tiles over the buffers: 768, 8192 for the
+# up-projection, 1024, 2048 for the down-projection; 64 rows), row counts one off a tile edge, columns that end inside a
+# 128- or 256-wide tile, one K slab and more slabs than a ring has stages.
+FFN_TILES = [
+    wl.small_config("ffn_one_row", 5, 64, 64, 2, 2, 1, "bf16", "gelu", seed=331),
+    wl.small_config("ffn_up_64x64_last", 700, 64, 2048, 4, 6, 63, "bf16", "gelu", seed=332),
+    wl.small_config("ffn_up_64x128_first", 700, 64, 2112, 5, 5, 64, "f16", "relu", skew=True, seed=333),
+    wl.small_config("ffn_65_rows", 900, 192, 832, 3, 3, 65, "f16", "gelu", seed=334),
+    wl.small_config("ffn_up_64x128_persistent", 300, 64, 4032, 13, 10, 3, "bf16", "relu", seed=335),
+    wl.small_config("ffn_up_64x256", 300, 64, 4160, 16, 8, 3, "bf16", "gelu", seed=336),
+    wl.small_config("ffn_down_64x64_last", 2000, 512, 576, 8, 8, 127, "bf16", "gelu", seed=337),
+    wl.small_config("ffn_down_64x128", 400, 576, 640, 16, 8, 4, "bf16", "relu", seed=338),
+    wl.small_config("ffn_down_64x256", 600, 576, 640, 29, 8, 4, "bf16", "gelu", skew=True, seed=339),
+]
+
+
+@pytest.mark.parametrize("cfg", FFN_TILES, ids=lambda c: c.name)
+def test_small_ffn_tiles(torch_cuda, cfg, monkeypatch):
+    """Forward (with and without expert buffers, and with both saved outputs) and backward against the oracle; the same bits
+    as the 128 x 192 tile."""
+    import numpy as np
+    from test_gpu_parity import _run
+    outs = {}
+    for how, tile in (("steps", "0"), ("steps", None), ("fused", None)):
+        if tile is None:
+            monkeypatch.delenv("SMILE_FFN_TILE", raising=False)
+        else:
+            monkeypatch.setenv("SMILE_FFN_TILE", tile)
+        layer = _run(cfg, how)
+        try:
+            outs[how, tile] = parity.fetch(layer)["y"]
+        finally:
+            layer.close()
+    for key, y in outs.items():
+        np.testing.assert_array_equal(y, outs["steps", "0"], err_msg=str(key))
+    _forward_and_backward(cfg)
