@@ -184,9 +184,19 @@ __device__ __forceinline__ void group_reduce(F step)
     if constexpr (P >= 16) step(std::integral_constant<int, 0x140>{});   // mirror of 16
 }
 
+// LDS written before by lanes of this wave may be read after by others of it (a wave's LDS operations complete in order, so
+// this only holds the compiler back).
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
 // Softmax and top-1 of one logit row in LDS by the P neighbouring lanes that own the token (columns part, part + P, ...):
 // lowest index of the maximum of row + bias, its probability, and the row overwritten with all probabilities (zeros
 // for a token that does not exist).  K > 0: at most K P columns, held in registers between the passes.
+// Every lane adds the whole denominator up in column order, from the exponentials in LDS: p_top, and with it the gate,
+// then has the same bits for every block size and in the kernel for very wide routers.
 template <int P, int K>
 __device__ __forceinline__ void softmax_top1(float *row, const float *__restrict__ bias, int len, int part, bool valid, int &arg,
                                              float &p_top)
@@ -221,17 +231,16 @@ __device__ __forceinline__ void softmax_top1(float *row, const float *__restrict
     if constexpr (K > 0) {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
-            v[k] = exp_neg(v[k] - mx);   // exp2(-inf) = 0 for the padding
-            z += v[k];
+            v[k] = exp_neg(v[k] - mx);
+            if (part + k * P < len) row[part + k * P] = v[k];
         }
     } else {
-        for (int c = part; c < len; c += P) {
-            const float p = exp_neg(row[c] - mx);
-            row[c] = p;
-            z += p;
-        }
+        for (int c = part; c < len; c += P) row[c] = exp_neg(row[c] - mx);
     }
-    group_reduce<P>([&](auto ctrl) { z += dpp<decltype(ctrl)::value>(z); });
+    wave_lds_fence();
+#pragma unroll 8
+    for (int c = 0; c < len; ++c) z += row[c];
+    wave_lds_fence();
     p_top = 1.0f / z;
     if constexpr (K > 0) {
 #pragma unroll

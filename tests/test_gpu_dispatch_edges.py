@@ -123,3 +123,39 @@ def test_small_ffn_tiles(torch_cuda, cfg, monkeypatch):
     for key, y in outs.items():
         np.testing.assert_array_equal(y, outs["steps", "0"], err_msg=str(key))
     _forward_and_backward(cfg)
+
+
+# ---- routing decisions must not depend on how the batch is cut into blocks.  One batch size for each block size (a single block,
+# 16, 32, 64 and 256 tokens)
+ROUTE_BATCHES = (40, 300, 5000, 10000, 70000)
+
+
+def _route(torch, T, li, lq, bi=None, bq=None):
+    """smile_route_bilevel on the first T rows of the logits; the per-token outputs as host tensors."""
+    n, m = li.shape[1], lq.shape[1]
+    desc = B.make_desc(T, 64, 64, n, m, 8, "f32", "relu")
+    ctx, b = B.Ctx(desc), B.alloc_buffers(desc)
+    li, lq = li[:T].contiguous(), lq[:T].contiguous()
+    B.smile_route_bilevel(ctx, li, lq, bi, bq, b.group_idx, b.local_idx, b.pos_in_group, b.slot, b.gate, b.p_top, b.q_top,
+                          b.group_count, b.local_count, b.expert_count, b.kept_count, b.p_sum, b.q_sum)
+    torch.cuda.synchronize()
+    ctx.close()
+    return {k: getattr(b, k).cpu() for k in ("group_idx", "local_idx", "gate", "p_top", "q_top")}
+
+
+@pytest.mark.parametrize("n,m", [(2, 8), (5, 3), (17, 9), (1, 129), (34, 40)])
+def test_gates_do_not_depend_on_the_batch(torch_cuda, n, m):
+    """A token's gate has the same bits in every block size and in the kernel for very wide routers, which adds the softmax
+    denominator in column order (reached here through extra columns that a bias of -inf takes out of the sum)."""
+    torch = torch_cuda
+    g = torch.Generator(device="cuda:0").manual_seed(341)
+    T, wide = max(ROUTE_BATCHES), max(m, 100)
+    li = torch.empty(T, n, device="cuda:0").normal_(0, 1.5, generator=g)
+    lq = torch.empty(T, wide, device="cuda:0").normal_(0, 1.5, generator=g)
+    bq = torch.zeros(n, wide, device="cuda:0")
+    bq[:, m:] = float("-inf")
+    want = _route(torch, T, li, lq, None, bq)
+    lq = lq[:, :m].contiguous()
+    for t in ROUTE_BATCHES:
+        for k, v in _route(torch, t, li, lq).items():
+            assert torch.equal(v, want[k][:t]), f"T={t} {k}: {(v != want[k][:t]).sum()} of {t} differ"
