@@ -227,7 +227,7 @@ __device__ __forceinline__ void softmax_top1(float *row, const float *__restrict
         const int oa = dpp<decltype(ctrl)::value>(arg);
         if (ov > mx || (ov == mx && oa < arg)) { mx = ov; arg = oa; }
     });
-    arg = min(arg, len - 1);
+    if (arg == len) arg = 0;   // nothing above -inf: a row of -inf or NaN
     if constexpr (K > 0) {
 #pragma unroll
         for (int k = 0; k < K; ++k) {

@@ -159,3 +159,27 @@ def test_gates_do_not_depend_on_the_batch(torch_cuda, n, m):
     for t in ROUTE_BATCHES:
         for k, v in _route(torch, t, li, lq).items():
             assert torch.equal(v, want[k][:t]), f"T={t} {k}: {(v != want[k][:t]).sum()} of {t} differ"
+
+
+@pytest.mark.parametrize("n", [4, 9, 40])
+def test_rows_without_a_maximum(torch_cuda, n):
+    """Logits that are not finite have unspecified results, but the same index in every block size and in the kernel for very wide
+    routers: the first column above all before it, 0 where no column is above -inf."""
+    torch = torch_cuda
+    inf, nan = float("inf"), float("nan")
+    rows = torch.zeros(6, n, device="cuda:0")
+    rows[0] = -inf
+    rows[1] = nan
+    rows[2, 0], rows[2, 1:] = nan, -inf
+    rows[3, :-1], rows[3, -1] = nan, -5.0
+    rows[4] = inf
+    rows[5, 1] = inf
+    want = torch.tensor([0, 0, 0, n - 1, 0, 1], dtype=torch.int32)
+    T = max(ROUTE_BATCHES)
+    li = rows.repeat(T // 6 + 1, 1)[:T].contiguous()
+    want = want.repeat(T // 6 + 1)[:T]
+    for t in ROUTE_BATCHES:
+        out = _route(torch, t, li, li)
+        assert torch.equal(out["group_idx"], want[:t]) and torch.equal(out["local_idx"], want[:t]), t
+    out = _route(torch, T, li, torch.full((T, 4000 // n), -inf, device="cuda:0"))
+    assert torch.equal(out["group_idx"], want) and not out["local_idx"].any()
