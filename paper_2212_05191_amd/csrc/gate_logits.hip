@@ -4,10 +4,17 @@
 // one-level router the paper compares against), so the kernel is
 // bound by the single read of x from HBM; the weights (<= 80 KB) stay in L2.
 //
-// One workgroup of 4 waves owns RT x 16 token rows (gate_device.hpp); the 4 partial accumulators are summed
+// One workgroup of 4 waves owns RT x 16 token rows and takes the contraction in turns; the 4 partial accumulators are summed
 // through LDS in a fixed order.  Every workgroup re-reads the router weights from L2, so RT grows with T (weight
 // traffic / RT) while keeping >= 512 workgroups: RT = 1 for the smallest paper-shaped batch (T = 8192), 4 from
-// T = 32768.  (The chained forward pass computes the same logits inside the routing kernel.)
+// T = 32768.
+//
+// One chunk and one column tile's weights at a time: what keeps HBM busy here is the number of waves, so registers count.
+// Against the loop of the routing kernel (gate_device.hpp: two chunks in flight, all weights of a chunk requested at once), bf16, us:
+// 131072 x 768, 10 / 24 / 40 / 72 columns: 41 / 47 / 51 / 83 against 48 / 53 / 59 / 96; 65536 x 1024: 23 / 26 / 32 / 55
+// against 24 / 30 / 36 / 61; 32768 x 768: 10.5 / 13.0 / 15.4 / 23.4 against 12.2 / 14.0 / 16.7 / 24.0; equal below 16384 rows.  Only with eight
+// column tiles over several row tiles (16-bit) are the weights of a chunk worth requesting at once: 65536 x 1024 with 129 columns 107
+// against 119.  Products and order are the same in both: the same bits.
 #include <algorithm>
 
 #include "gate_device.hpp"
@@ -28,8 +35,51 @@ __global__ __launch_bounds__(64 * kGateWaves) void gate_logits_kernel(
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int r = lane & 15, kg = lane >> 4;
     const int row0 = blockIdx.x * 16 * RT;
+
+    typedef typename GateType<DT>::elem E;
+    typedef typename GateType<DT>::vec vec;
+    constexpr int kChunk = GateType<DT>::kChunk, kLane = kChunk / 4, kVec = kChunk / 8;   // elements per lane, per 16 bytes
+    constexpr bool kAtOnce = CT == 8 && RT > 1 && DT != SMILE_DTYPE_F32;
+    const E *xrow[RT], *wrow[CT];   // wrow: the weight row of this lane in column tile ct, null beyond n + m
     f32x4 acc[RT][CT];
-    gate_partial<DT, CT, RT, (RT + CT <= 5 ? 2 : 1)>(x, w_inter, w_intra, row0, T, d, n, m, col0, wave, acc);
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) xrow[rt] = static_cast<const E *>(x) + (size_t)min(row0 + rt * 16 + r, T - 1) * d;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+        const int c = col0 + ct * 16 + r;
+        wrow[ct] = c < n ? static_cast<const E *>(w_inter) + (size_t)c * d
+                         : (c < n + m ? static_cast<const E *>(w_intra) + (size_t)(c - n) * d : nullptr);
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt) acc[rt][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const int chunks = (d + kChunk - 1) / kChunk;
+    for (int chunk = wave; chunk < chunks; chunk += kGateWaves) {
+        const int k = chunk * kChunk + kg * kLane;
+        const bool in = DT != SMILE_DTYPE_F32 || k < d;   // 16-bit rows are whole chunks; a float row may end inside one
+        vec a[RT][2];
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) a[rt][h] = in ? *reinterpret_cast<const vec *>(xrow[rt] + k + h * kVec) : vec{};
+        vec b[kAtOnce ? CT : 1][2];
+        auto weights = [&](int ct) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                b[kAtOnce ? ct : 0][h] = in && wrow[ct] ? *reinterpret_cast<const vec *>(wrow[ct] + k + h * kVec) : vec{};
+        };
+        if constexpr (kAtOnce) {
+#pragma unroll
+            for (int ct = 0; ct < CT; ++ct) weights(ct);
+        }
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) {
+            if constexpr (!kAtOnce) weights(ct);
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) acc[rt][ct] = GateType<DT>::mfma(a[rt][h], b[kAtOnce ? ct : 0][h], acc[rt][ct]);
+        }
+    }
     if (wave > 0) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt)

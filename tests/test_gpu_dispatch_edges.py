@@ -183,3 +183,24 @@ def test_rows_without_a_maximum(torch_cuda, n):
         assert torch.equal(out["group_idx"], want[:t]) and torch.equal(out["local_idx"], want[:t]), t
     out = _route(torch, T, li, torch.full((T, 4000 // n), -inf, device="cuda:0"))
     assert torch.equal(out["group_idx"], want) and not out["local_idx"].any()
+
+
+def test_router_logits_of_very_long_rows(torch_cuda):
+    """16 rows of 286,331,200 elements: the offset of the last row does not fit 32 bits.  Every row has one element that the
+    weights see, at its end."""
+    torch = torch_cuda
+    T, d = 16, 286331200
+    assert (T - 1) * d >= 1 << 32 and d % 64 == 0
+    if torch.cuda.mem_get_info()[0] < 16 << 30:
+        pytest.skip("needs 16 GB of device memory")
+    x = torch.zeros(T, d, dtype=torch.bfloat16, device="cuda:0")
+    x[:, -1] = torch.arange(1, T + 1, device="cuda:0")
+    w = torch.zeros(1, d, dtype=torch.bfloat16, device="cuda:0")
+    w[0, -1] = 2.0
+    li, lq = torch.empty(T, 1, device="cuda:0"), torch.empty(T, 1, device="cuda:0")
+    ctx = B.Ctx(B.make_desc(T, d, 64, 1, 1, 1, "bf16", "relu"))
+    B.smile_gate_logits(ctx, x, w, w, li, lq)
+    torch.cuda.synchronize()
+    ctx.close()
+    want = 2.0 * torch.arange(1, T + 1, device="cuda:0").float()
+    assert torch.equal(li[:, 0], want) and torch.equal(lq[:, 0], want)
