@@ -1,5 +1,5 @@
-// Router logits on the matrix cores, shared by the stand-alone gate kernel and the kernel that routes in the same
-// launch: one unit of four waves multiplies RT x 16 token rows by CT x 16 router columns, the waves taking the
+// Router logits on the matrix cores: operand types shared by the stand-alone gate kernel and the kernel that routes in the same
+// launch, and the latter's product: one unit of four waves multiplies RT x 16 token rows by CT x 16 router columns, the waves taking the
 // contraction in turns (wave w: chunks w, w + 4, ...).  Operands go straight from global memory into the MFMA layout: a
 // lane reads 32 contiguous bytes of its row, four lanes a full 128-byte line.  A chunk is 64 elements of a 16-bit type
 // (two v_mfma_f32_16x16x32) or 32 floats (eight v_mfma_f32_16x16x4_f32).  The four partial sums are added in wave order by
@@ -53,7 +53,7 @@ __device__ __forceinline__ void gate_partial(const void *x_, const void *w_inter
     constexpr int kChunk = GateType<DT>::kChunk, kLane = kChunk / 4, kVec = kChunk / 8;   // elements per lane, per 16 bytes
     const E *x = static_cast<const E *>(x_), *w_inter = static_cast<const E *>(w_inter_), *w_intra = static_cast<const E *>(w_intra_);
     const int lane = threadIdx.x & 63, r = lane & 15, kg = lane >> 4;
-    // rows of x as 32-bit offsets from the unit's first row (at most 16 RT rows), which is uniform
+    // rows of x as 32-bit offsets from the unit's first row, which is uniform (route_plan: 16 RT d <= 2^32)
     unsigned xoff[RT];
     const E *wrow[CT];
     x += (size_t)row0 * d;

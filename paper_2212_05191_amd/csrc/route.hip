@@ -2,8 +2,8 @@
 // Section 4.2 capacity).  Tokens are cut into routing blocks; a workgroup decides one block, and the blocks are put in
 // order afterwards:
 //
-//   gate_logits_route  one workgroup per block of 16, 32, 64 or 256 tokens: (chained forward pass) the router logits of the
-//                      block on the matrix cores, then from an LDS tile of the logits: top-1 group and local expert, the
+//   gate_logits_route  one workgroup per block of 16, 32, 64 or 256 tokens: (chained forward pass, up to 64 tokens) the router
+//                      logits of the block on the matrix cores, then from an LDS tile of the logits: top-1 group and local expert, the
 //                      two softmax probabilities (Eq. 1 read as a softmax), the gate p*q (Eq. 3), column sums of p and
 //                      q, the token's rank among EARLIER tokens of the block with the same group / the same expert
 //                      (wave64 ballots + per-wave LDS counters combined after one barrier), block histograms.
@@ -251,6 +251,20 @@ __device__ __forceinline__ void softmax_top1(float *row, const float *__restrict
     }
 }
 
+// Waves per SIMD the registers must leave room for: four blocks of 64 tokens per CU hide each other's reads of x, where the
+// operands of a chunk are more than 128 registers' worth (four and five column tiles) two have to do.
+constexpr int gate_waves_per_simd(int NT, int CT) { return NT == 1024 || (CT > 1 && CT <= 3) ? 4 : 2; }
+
+// Chunks in flight of the logits (gate_partial's U): as many, up to three, as fit the registers without spilling -- 8 (RT + CT) of
+// operands a chunk, 4 RT CT of accumulators, the addresses and about 24 others, in the 128 of four waves per SIMD, else in the 168 of
+// three.  One chunk more spilled 44-96 bytes per lane: with 40 columns 8192 x 768 took 17.2 us instead of 13.9, 4096 x 768 14.8 instead of 12.7.
+constexpr int gate_chunks_in_flight(int CT, int RT, int waves)
+{
+    for (int u = 3; u > 1; --u)
+        if (8 * u * (RT + CT) + 4 * RT * CT + RT + 2 * CT + 24 <= (waves == 4 ? 128 : 168)) return u;
+    return 1;
+}
+
 // NT threads, P per token: blocks of NT / P tokens.  GATE: logits from x and the router weights (16 * CT columns per pass
 // over the block's rows, which come from L2 after the first), else from memory.
 // Dynamic LDS (route_lds_bytes): logit / probability tile, 8 segment sums per column, packed decisions, per-wave counters,
@@ -258,11 +272,11 @@ __device__ __forceinline__ void softmax_top1(float *row, const float *__restrict
 // Bound: the read of x (GATE), else latency.  One CU draws about 28 GB/s from HBM however much it requests, so the blocks
 // are as small as leaves 256 of them; several threads per token because a token's serial loops over its columns are what
 // a wave spends its time on.  Measured against a gate kernel and a decision kernel with one thread per token (us, routing
-// and block order included): 512 tokens fp32 13 -> 10, 128 tokens of 768 16 -> 12, 8192 of 768 20 -> 17, 16384 of
-// 1024 29 -> 23, 32768 of 768 with 16 + 8 columns 39 -> 36 and with 129 columns 127 -> 72; 65536 of 1024 with 40 columns
-// 71 -> 74 (the launch saved there is no more than the wait of 1024 resident blocks for the read of x).
+// and block order included): 512 tokens fp32 13 -> 10, 128 tokens of 768 17 -> 11, 8192 of 768 20 -> 16, 16384 of
+// 1024 22 -> 22, 32768 of 768 with 16 + 8 columns 36 -> 33 and with 129 columns 117 -> 70; whole layers of 64-wide experts gain
+// the launch too (16384 of 1024: 64 -> 50, 65536 of 1024: 170 -> 141).
 template <int DT, int CT, int NT, int P, bool GATE>
-__global__ __launch_bounds__(NT, (NT == 1024 || (CT > 1 && CT <= 3) ? 4 : 2)) void gate_logits_route_kernel(RouteArgs a)
+__global__ __launch_bounds__(NT, gate_waves_per_simd(NT, CT)) void gate_logits_route_kernel(RouteArgs a)
 {
     constexpr int RB = NT / P, kRankWaves = (RB + 63) / 64, kWaves = NT / 64;
     extern __shared__ float lds_f[];
@@ -289,7 +303,7 @@ __global__ __launch_bounds__(NT, (NT == 1024 || (CT > 1 && CT <= 3) ? 4 : 2)) vo
     };
     if constexpr (GATE) {
         constexpr int RT = RB < 64 ? RB / 16 : 4;               // row tiles per unit of four waves: at most 64 tokens
-        constexpr int kAhead = CT * RT <= 4 ? 3 : NT < 1024 && CT * RT <= 6 ? 2 : 1;   // chunks in flight, as registers allow
+        constexpr int kAhead = gate_chunks_in_flight(CT, RT, gate_waves_per_simd(NT, CT));
         const int unit = wave / kGateWaves, uw = wave % kGateWaves, r16 = lane & 15, kg = lane >> 4;
         const bool any = unit * 64 < live;
 #pragma unroll 1
@@ -872,25 +886,27 @@ hipError_t launch_block(const RouteArgs &a, int blocks, size_t lds, hipStream_t 
     return hipGetLastError();
 }
 
-// column tiles per pass: all of them while the accumulators (4 x CT tiles of 4 registers) fit beside the operands
+// Column tiles per pass: all of them while the accumulators (RT x CT tiles of 4 registers) fit beside the operands.  Three over the
+// four row tiles of 64 tokens do not (24 bytes spilled); route_plan leaves those logits to the gate kernel.
 template <int NT, int P, int DT>
 hipError_t launch_gate_ct(const RouteArgs &a, int blocks, size_t lds, hipStream_t s)
 {
     const int ct = (a.n + a.m + 15) / 16;
     if (ct <= 1) return launch_block<NT, P, true, DT, 1>(a, blocks, lds, s);
     if (ct <= 2) return launch_block<NT, P, true, DT, 2>(a, blocks, lds, s);
-    if (NT >= 1024 || ct <= 3) return launch_block<NT, P, true, DT, 3>(a, blocks, lds, s);
-    if constexpr (NT < 1024) return launch_block<NT, P, true, DT, 5>(a, blocks, lds, s);
-    return hipErrorInvalidValue;
+    if constexpr (NT / P < 64)
+        if (ct <= 3) return launch_block<NT, P, true, DT, 3>(a, blocks, lds, s);
+    return launch_block<NT, P, true, DT, 5>(a, blocks, lds, s);
 }
 
 template <int NT, int P>
 hipError_t launch_decide(int dtype, bool gate, const RouteArgs &a, int blocks, size_t lds, hipStream_t s)
 {
     if (!gate) return launch_block<NT, P, false, SMILE_DTYPE_F32, 1>(a, blocks, lds, s);
-    if (dtype == SMILE_DTYPE_BF16) return launch_gate_ct<NT, P, SMILE_DTYPE_BF16>(a, blocks, lds, s);
-    if (dtype == SMILE_DTYPE_F16) return launch_gate_ct<NT, P, SMILE_DTYPE_F16>(a, blocks, lds, s);
-    return launch_gate_ct<NT, P, SMILE_DTYPE_F32>(a, blocks, lds, s);
+    if constexpr (NT / P > 64) return hipErrorInvalidValue;   // route_plan: larger blocks read logits
+    else if (dtype == SMILE_DTYPE_BF16) return launch_gate_ct<NT, P, SMILE_DTYPE_BF16>(a, blocks, lds, s);
+    else if (dtype == SMILE_DTYPE_F16) return launch_gate_ct<NT, P, SMILE_DTYPE_F16>(a, blocks, lds, s);
+    else return launch_gate_ct<NT, P, SMILE_DTYPE_F32>(a, blocks, lds, s);
 }
 
 }  // namespace
@@ -906,7 +922,7 @@ RoutePlan route_plan(const smile_layer_desc &d)
     if (d.T <= 64 && (size_t)d.T * d.d_model * elem_size(d.dtype) <= 64 * 1024) {
         const int rb = d.T <= 16 ? 16 : d.T <= 32 ? 32 : 64;
         if (route_lds_bytes(rb, n, m) <= kLdsMost) {
-            p.rb = rb, p.tile = p.one = true;
+            p.rb = rb, p.tile = p.one = p.gate = true;
             p.blocks = p.stride = 1;
             return p;
         }
@@ -922,6 +938,12 @@ RoutePlan route_plan(const smile_layer_desc &d)
     p.blocks = (d.T + rb - 1) / rb;
     // every workgroup of route_finish reads the histograms of the blocks before it: worth a launch up to 128 KB
     const int padded = (p.blocks + 3) / 4 * 4;
+    // Logits in the routing launch: with blocks of up to 64 tokens.  256 tokens are one workgroup per CU, whose waves all wait for the same
+    // barriers (bf16, routing us, in one launch against two: 70000 x 768 with 10 / 24 / 40 columns 63 / 78 / 95 against 46 / 56 / 67, 131072 x 768
+    // 84 / 95 / 107 against 77 / 87 / 92).  33 to 48 columns over 64 tokens spill (launch_gate_ct): 40 columns, 65536 x 1024 67 against 64,
+    // 12000 x 768 31.4 against 30.1.  The kernel's row offsets inside a block are 32-bit.
+    const int cols = n + m;
+    p.gate = p.tile && rb <= 64 && (rb < 64 || cols <= 32 || cols > 48) && (int64_t)rb * d.d_model <= (int64_t)1 << 32;
     p.scan_inline = p.blocks <= 256 && (size_t)(N + n) * padded * 4 <= 128 * 1024;
     p.stride = p.scan_inline ? padded : p.blocks;
     return p;
@@ -938,6 +960,11 @@ hipError_t launch_routing(const smile_layer_desc &d, const Workspace &ws, const 
     if (gate) a.x = gate->x, a.w_inter = gate->w_inter, a.w_intra = gate->w_intra;
     a.d = d.d_model, a.io = io, a.T = d.T, a.n = n, a.m = m, a.bits_n = ceil_log2(n), a.bits_N = ceil_log2(N), a.Bp = p.stride, a.ws = ws;
     a.one = p.one, a.C = d.capacity, a.Cg = d.group_capacity, a.ppr = ppr, a.tail = tail, a.alpha = d.alpha, a.beta = d.beta;
+    if (gate && !p.gate) {
+        err = launch_gate_logits(d, gate->x, gate->w_inter, gate->w_intra, io.logits_inter, io.logits_intra, s);
+        if (err != hipSuccess) return err;
+        gate = nullptr;
+    }
     if (p.tile) {
         const size_t lds = route_lds_bytes(p.rb, n, m);
         if (p.rb == 16) err = launch_decide<256, 16>(d.dtype, gate != nullptr, a, p.blocks, lds, s);
@@ -945,10 +972,6 @@ hipError_t launch_routing(const smile_layer_desc &d, const Workspace &ws, const 
         else if (p.rb == 64) err = launch_decide<256, 4>(d.dtype, gate != nullptr, a, p.blocks, lds, s);
         else err = launch_decide<1024, 4>(d.dtype, gate != nullptr, a, p.blocks, lds, s);
     } else {
-        if (gate) {
-            err = launch_gate_logits(d, gate->x, gate->w_inter, gate->w_intra, io.logits_inter, io.logits_intra, s);
-            if (err != hipSuccess) return err;
-        }
         // one histogram copy per wave while four of them fit beside the kernel's static LDS in 64 KB: N + n <= 1920
         constexpr size_t kStaticLds = sizeof(float) * (kRouteBlock * (kColChunk + 1) + 8 * kColChunk);
         const bool per_wave = (size_t)(N + n) * (kRouteBlock / 64) * sizeof(int32_t) + kStaticLds <= 64 * 1024;

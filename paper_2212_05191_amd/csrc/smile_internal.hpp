@@ -118,6 +118,7 @@ struct RoutePlan {
     int rb, blocks;      // tokens per block, blocks
     int stride;          // blocks per column of the histograms (padded to a multiple of 4 for scan_inline)
     bool tile;           // the block's logits fit an LDS tile (else: the kernels for very wide routers)
+    bool gate;           // the routing kernel also computes the router logits of a chained forward pass
     bool one;            // a single workgroup routes the whole batch
     bool scan_inline;    // every workgroup of the finishing kernel sums the histograms before its block itself
 };

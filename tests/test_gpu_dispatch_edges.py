@@ -61,6 +61,12 @@ ROUTE_EDGES = [
     wl.small_config("route_32_to_64", 8193, 104, 64, 2, 8, 500, "f32", "relu", seed=316),
     wl.small_config("route_inline_to_scan", 16385, 64, 64, 4, 5, 800, "bf16", "relu", skew=True, seed=317, group_capacity=3000),
     wl.small_config("route_64_to_256", 65537, 64, 64, 3, 2, 9000, "bf16", "relu", seed=318),
+    # logits left to the gate kernel: 33 to 48 columns over 64 tokens (on both sides: 32, 49), blocks of 256 tokens
+    wl.small_config("route_32_columns_64", 8300, 128, 64, 24, 8, 60, "f16", "relu", seed=321),
+    wl.small_config("route_33_columns_64", 8193, 136, 64, 25, 8, 60, "f32", "relu", seed=322, group_capacity=300),
+    wl.small_config("route_48_columns_64", 9000, 128, 64, 40, 8, 30, "bf16", "relu", skew=True, seed=323),
+    wl.small_config("route_49_columns_64", 9000, 128, 64, 41, 8, 30, "bf16", "relu", seed=324),
+    wl.small_config("route_256_below_65536", 52000, 64, 64, 64, 8, 110, "bf16", "relu", seed=325),
     wl.small_config("route_wide_tile", 500, 64, 64, 1, 200, 4, "bf16", "relu", seed=319),
     wl.small_config("route_beyond_tile", 300, 64, 64, 300, 2, 2, "bf16", "relu", seed=320, group_capacity=1),
 ]
