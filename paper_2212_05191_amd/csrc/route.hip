@@ -932,7 +932,9 @@ RoutePlan route_plan(const smile_layer_desc &d)
     // 256 tokens where the histograms would grow past 2 MB otherwise.
     int rb = d.T <= 16 * 256 ? 16 : d.T <= 32 * 256 ? 32 : 64;
     if (d.T > 65536 || (size_t)((d.T + rb - 1) / rb) * (N + 2 * n + 2 * m) > 512 * 1024) rb = 256;
-    p.tile = route_lds_bytes(rb, n, m) <= kLdsMost;
+    // The 1024 threads of a 256-token block are alone on their CU anyway and may have nearly all of its LDS: routers of about 60 to 140
+    // columns (bf16, 131072 x 768, decision of 64 / 68 / 129 columns 32 / 33 / 66 us; the kernel that re-reads its rows 62 / 71 / 117).
+    p.tile = route_lds_bytes(rb, n, m) <= (rb == kRouteBlock ? 152 * 1024 : kLdsMost);
     if (!p.tile) rb = kRouteBlock;
     p.rb = rb;
     p.blocks = (d.T + rb - 1) / rb;

@@ -67,6 +67,7 @@ ROUTE_EDGES = [
     wl.small_config("route_48_columns_64", 9000, 128, 64, 40, 8, 30, "bf16", "relu", skew=True, seed=323),
     wl.small_config("route_49_columns_64", 9000, 128, 64, 41, 8, 30, "bf16", "relu", seed=324),
     wl.small_config("route_256_below_65536", 52000, 64, 64, 64, 8, 110, "bf16", "relu", seed=325),
+    wl.small_config("route_256_wide_tile", 66000, 64, 64, 32, 32, 70, "bf16", "relu", skew=True, seed=326, group_capacity=2000),
     wl.small_config("route_wide_tile", 500, 64, 64, 1, 200, 4, "bf16", "relu", seed=319),
     wl.small_config("route_beyond_tile", 300, 64, 64, 300, 2, 2, "bf16", "relu", seed=320, group_capacity=1),
 ]
@@ -155,7 +156,7 @@ def test_gates_do_not_depend_on_the_batch(torch_cuda, n, m):
     denominator in column order (reached here through extra columns that a bias of -inf takes out of the sum)."""
     torch = torch_cuda
     g = torch.Generator(device="cuda:0").manual_seed(341)
-    T, wide = max(ROUTE_BATCHES), max(m, 100)
+    T, wide = max(ROUTE_BATCHES), max(m, min(160, 4096 // n))
     li = torch.empty(T, n, device="cuda:0").normal_(0, 1.5, generator=g)
     lq = torch.empty(T, wide, device="cuda:0").normal_(0, 1.5, generator=g)
     bq = torch.zeros(n, wide, device="cuda:0")
