@@ -930,14 +930,15 @@ RoutePlan route_plan(const smile_layer_desc &d)
     // Blocks as small as leaves at most 256 of them (more CUs read x, and 256 blocks are one load in route_finish), from 64
     // tokens on as many blocks as there are: several share a CU then, and one block's latency hides under another's reads.
     // 256 tokens where the histograms would grow past 2 MB otherwise.
+    auto blocks_of = [&](int tokens) { return ((size_t)d.T + tokens - 1) / tokens; };   // T may be 2^31 - 1
     int rb = d.T <= 16 * 256 ? 16 : d.T <= 32 * 256 ? 32 : 64;
-    if (d.T > 65536 || (size_t)((d.T + rb - 1) / rb) * (N + 2 * n + 2 * m) > 512 * 1024) rb = 256;
+    if (d.T > 65536 || blocks_of(rb) * (N + 2 * n + 2 * m) > 512 * 1024) rb = 256;
     // The 1024 threads of a 256-token block are alone on their CU anyway and may have nearly all of its LDS: routers of about 60 to 140
     // columns (bf16, 131072 x 768, decision of 64 / 68 / 129 columns 32 / 33 / 66 us; the kernel that re-reads its rows 62 / 71 / 117).
     p.tile = route_lds_bytes(rb, n, m) <= (rb == kRouteBlock ? 152 * 1024 : kLdsMost);
     if (!p.tile) rb = kRouteBlock;
     p.rb = rb;
-    p.blocks = (d.T + rb - 1) / rb;
+    p.blocks = (int)blocks_of(rb);
     // every workgroup of route_finish reads the histograms of the blocks before it: worth a launch up to 128 KB
     const int padded = (p.blocks + 3) / 4 * 4;
     // Logits in the routing launch: with blocks of up to 64 tokens.  256 tokens are one workgroup per CU, whose waves all wait for the same
@@ -1026,7 +1027,7 @@ hipError_t launch_routing(const smile_layer_desc &d, const Workspace &ws, const 
         if (err != hipSuccess) return err;
     }
     if (tail.xe) return launch_dispatch_finalize(d, ws, p, io, tail, s);
-    SMILE_LAUNCH(route_slots_kernel, dim3((d.T + 255) / 256), dim3(256), 0, s, f);
+    SMILE_LAUNCH(route_slots_kernel, dim3(((size_t)d.T + 255) / 256), dim3(256), 0, s, f);
     return hipGetLastError();
 }
 

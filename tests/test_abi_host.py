@@ -113,6 +113,22 @@ def test_workspace_size_and_alignment_checks():
     assert lib.smile_destroy(h) == B.OK
 
 
+def test_workspace_size_of_the_largest_batches():
+    """T up to 2^31 - 1: the sizes are computed without overflow, block counts included (histograms and sums of 256-token
+    blocks, two ranks per token, the slot map, the hidden rows; each part padded to 256 bytes)."""
+    def pad(v):
+        return (v + 255) // 256 * 256
+    n, m, F, C_ = 1, 2, 8, 4
+    last = 0
+    for T in (2147483647 - 300, 2147483647 - 255, 2147483647 - 15, 2147483647):
+        blocks = -(-T // 256)
+        want = pad(4 * blocks * n * m) + pad(4 * blocks * (n + m)) + pad(4 * blocks * n) + pad(4 * blocks * m) + 2 * pad(4 * T)
+        want += pad(4 * n * m * C_) + pad(4 * n * m * C_ * F)
+        got = B.smile_workspace_bytes(_desc(T=T, d_model=8, d_ff=F, n_groups=n, m_local=m, capacity=C_, dtype="f32"))
+        assert got == want >= last, (T, got, want)
+        last = got
+
+
 def test_entry_points_reject_bad_pointers_before_any_launch():
     lib = B.load()
     d = _desc(n_groups=100, m_local=40)
