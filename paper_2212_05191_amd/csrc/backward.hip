@@ -432,7 +432,7 @@ hipError_t launch_expert_ffn_backward(const LayerDesc &d, void *workspace, const
     const void *h = h_saved, *pre = pre_saved;
     if (!h) {
         void *h_ws = b + L.off_h, *pre_ws = b + L.off_pre;
-        SMILE_TRY(launch_grouped_gemm_nt(d.dtype, GroupedGemm{xe, w1, h_ws, pre_ws, kept_count, N, C, F, dm, act, nullptr, nullptr, nullptr, 0, d.tune}, s));
+        SMILE_TRY(launch_grouped_gemm_nt(d.dtype, GroupedGemm{xe, w1, h_ws, pre_ws, kept_count, N, C, F, dm, act, nullptr, nullptr, d.tune}, s));
         h = h_ws;
         pre = pre_ws;
     }

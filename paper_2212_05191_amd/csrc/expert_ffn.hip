@@ -55,11 +55,9 @@ namespace {
 // workgroup has 4 waves).
 // DUAL: the epilogue runs twice, storing act(product) to y and the bare product to y2 (the hidden
 // activation and its pre-activation from one GEMM, for the backward pass).
-// POST (1 ReLU, 2 GELU): the rounded output is multiplied by act'(aux) on its way out (the gradient at the
-// pre-activation, dh * act'(pre)); aux is read with the same row-contiguous 16-byte accesses as the store.
 // E: the 16-bit storage type (__bf16 or _Float16).
 template <typename E, int BM, int BN, int WGM, int WGN, int BK, int STAGES, int OCC, int SWZ, int ACT,
-          bool DUAL = false, int POST = 0, bool PERSIST = false>
+          bool DUAL = false, bool PERSIST = false>
 __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_nt_kernel(GemmArgs a)
 {
     typedef typename Half<E>::vec8 bf16x8;                                  // one MFMA operand: 8 elements
@@ -317,14 +315,6 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_nt_kernel(Gem
                 const int row = rt * BM + (orow >> 5) * WM + j * 32 + (orow & 31);
                 const int col = ct * BN + piece * 8;
                 if (id < OROWS * OPR && row < rows && col < Nout) {
-                    if constexpr (POST != 0) {
-                        const u32x4 p = *reinterpret_cast<const u32x4 *>(
-                            static_cast<const E *>(a.aux) + ((size_t)e * a.C + row) * Nout + col);
-#pragma unroll
-                        for (int k = 0; k < 4; ++k)
-                            v[k] = Half<E>::pack(Half<E>::lo(v[k]) * activate_grad<POST>(Half<E>::lo(p[k])),
-                                                 Half<E>::hi(v[k]) * activate_grad<POST>(Half<E>::hi(p[k])));
-                    }
                     if (Y) *reinterpret_cast<u32x4 *>(Y + (size_t)row * Nout + col) = v;
                     if (pass == 0 && y_rows) {   // gate-weighted return to token order (Eq. 3), fused
                         const int tok = y_rows[row];
@@ -384,9 +374,9 @@ hipError_t launch_half_tile(GemmArgs a, int N, int act, const Tuning &tune, hipS
     const dim3 block(WGM * WGN * 64);
     if (use_persistent_grid(tune, N, a.tiles, slots)) {
         const dim3 grid(slots);
-        if (act == 0) launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, BK, STAGES, OCC, SWZ, 0, false, 0, true>, grid, block, s, t0, t1, a);
-        else if (act == 1) launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, BK, STAGES, OCC, SWZ, 1, false, 0, true>, grid, block, s, t0, t1, a);
-        else launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, BK, STAGES, OCC, SWZ, 3, false, 0, true>, grid, block, s, t0, t1, a);
+        if (act == 0) launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, BK, STAGES, OCC, SWZ, 0, false, true>, grid, block, s, t0, t1, a);
+        else if (act == 1) launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, BK, STAGES, OCC, SWZ, 1, false, true>, grid, block, s, t0, t1, a);
+        else launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, BK, STAGES, OCC, SWZ, 3, false, true>, grid, block, s, t0, t1, a);
         return hipGetLastError();
     }
     const dim3 grid((a.tiles + kXcds - 1) / kXcds * kXcds);
@@ -407,32 +397,20 @@ hipError_t launch_half_dual(GemmArgs a, int N, int act, const Tuning &tune, hipS
     const int slots = workgroup_slots(tune, workgroups_per_cu(4, OCC, STAGES * (BM + BN) * 64 * 2));
     const bool persist = use_persistent_grid(tune, N, a.tiles, slots);
     const dim3 grid(persist ? slots : (a.tiles + kXcds - 1) / kXcds * kXcds), block(256);
-    if (act == 1 && persist) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 1, true, 0, true>), grid, block, 0, s, a);
+    if (act == 1 && persist) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 1, true, true>), grid, block, 0, s, a);
     else if (act == 1) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 1, true>), grid, block, 0, s, a);
-    else if (persist) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 3, true, 0, true>), grid, block, 0, s, a);
+    else if (persist) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 3, true, true>), grid, block, 0, s, a);
     else SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 3, true>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
-// The two epilogue variants of the backward pass: a.y2 given (launch_half_dual; `tile` as pick_tile says, with the
-// shapes that exist for it), post != 0: output times act'(a.aux), on the up-projection tile shape.
+// `tile` as pick_tile says, with the shapes that exist for two outputs
 template <typename E>
-hipError_t launch_half_special_typed(GemmArgs a, int N, int act, int post, int tile, const Tuning &tune, hipStream_t s)
+hipError_t launch_half_dual_typed(const GemmArgs &a, int N, int act, int tile, const Tuning &tune, hipStream_t s)
 {
-    if (a.y2) {
-        if (tile == 9 || tile == 7) return launch_half_dual<E, 64, 64, 3, 3>(a, N, act, tune, s);
-        if (tile == 8 || tile == 5) return launch_half_dual<E, 64, 128, 3, 2>(a, N, act, tune, s);
-        return launch_half_dual<E, 128, 192, 2, 2>(a, N, act, tune, s);
-    }
-    constexpr int BM = 128, BN = 192;
-    a.row_tiles = (a.C + BM - 1) / BM;
-    a.col_tiles = (a.Nout + BN - 1) / BN;
-    a.tiles = N * a.row_tiles * a.col_tiles;
-    a.N = N;
-    const dim3 plain((a.tiles + kXcds - 1) / kXcds * kXcds), block(256);
-    if (post == 1) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, 2, 2, 1, 0, false, 1>), plain, block, 0, s, a);
-    else SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, 2, 2, 1, 0, false, 2>), plain, block, 0, s, a);
-    return hipGetLastError();
+    if (tile == 9 || tile == 7) return launch_half_dual<E, 64, 64, 3, 3>(a, N, act, tune, s);
+    if (tile == 8 || tile == 5) return launch_half_dual<E, 64, 128, 3, 2>(a, N, act, tune, s);
+    return launch_half_dual<E, 128, 192, 2, 2>(a, N, act, tune, s);
 }
 
 // Tile shapes: id -> (BM, BN, waves along M, waves along N, BK, stages, waves/SIMD budget).
@@ -503,11 +481,11 @@ hipError_t launch_half(int dtype, const GemmArgs &a, int N, int act, int tile, c
     return launch_half_typed<_Float16>(a, N, act, tile, tune, s, t0, t1);
 }
 
-hipError_t launch_half_special(int dtype, const GemmArgs &a, int N, int act, int post, const Tuning &tune, hipStream_t s)
+hipError_t launch_half_dual(int dtype, const GemmArgs &a, int N, int act, const Tuning &tune, hipStream_t s)
 {
     const int tile = pick_tile(tune, N, a.C, a.Nout, a.K);
-    if (dtype == SMILE_DTYPE_BF16) return launch_half_special_typed<__bf16>(a, N, act, post, tile, tune, s);
-    return launch_half_special_typed<_Float16>(a, N, act, post, tile, tune, s);
+    if (dtype == SMILE_DTYPE_BF16) return launch_half_dual_typed<__bf16>(a, N, act, tile, tune, s);
+    return launch_half_dual_typed<_Float16>(a, N, act, tile, tune, s);
 }
 
 }  // namespace
@@ -523,21 +501,21 @@ bool use_persistent_grid(const Tuning &tune, int N, long long tiles, int slots)
 static F32Gemm f32_gemm(const GroupedGemm &g)
 {
     F32Gemm f{};
-    f.x = g.x, f.w = g.w, f.y = g.y, f.y2 = g.y2, f.bias = g.bias, f.aux = g.aux, f.x_rows = g.x_rows;
+    f.x = g.x, f.w = g.w, f.y = g.y, f.y2 = g.y2, f.bias = g.bias, f.x_rows = g.x_rows;
     f.rows_valid = g.kept, f.N = g.N, f.Mrows = g.C, f.Nout = g.Nout, f.K = g.K, f.ldx = g.K, f.ldw = g.K;
     f.sx = (long long)g.C * g.K, f.sw = (long long)g.Nout * g.K, f.sy = (long long)g.C * g.Nout;
-    f.act = g.act, f.post = g.post, f.tune = g.tune;
+    f.act = g.act, f.tune = g.tune;
     return f;
 }
 
 hipError_t launch_grouped_gemm_nt(int dtype, const GroupedGemm &g, hipStream_t s)
 {
     const int act = g.act == 0 ? 0 : (g.act == 1 ? 1 : 2);
-    if ((g.y2 && act == 0) || (g.post && (act != 0 || g.y2 || !g.aux))) return hipErrorInvalidValue;
+    if (g.y2 && act == 0) return hipErrorInvalidValue;
     if (!is_half(dtype)) return launch_grouped_gemm_f32(f32_gemm(g), s);
     if (g.K % 64 || g.Nout % 8) return hipErrorInvalidValue;
-    GemmArgs a{g.x, g.w, g.bias, g.y, g.kept, g.C, g.Nout, g.K, 0, 0, 0, g.x_rows, nullptr, nullptr, nullptr, g.y2, g.aux};
-    if (g.y2 || g.post) return launch_half_special(dtype, a, g.N, act, g.post, g.tune, s);
+    GemmArgs a{g.x, g.w, g.bias, g.y, g.kept, g.C, g.Nout, g.K, 0, 0, 0, g.x_rows, nullptr, nullptr, nullptr, g.y2};
+    if (g.y2) return launch_half_dual(dtype, a, g.N, act, g.tune, s);
     return launch_half(dtype, a, g.N, act, pick_tile(g.tune, g.N, g.C, g.Nout, g.K), g.tune, s);
 }
 
@@ -554,7 +532,7 @@ hipError_t launch_expert_ffn_up(const LayerDesc &d, const Workspace &ws, const v
         if (t0 && t1) (void)hipEventRecord(t0, s);
         const hipError_t err = launch_grouped_gemm_nt(
             d.dtype, GroupedGemm{src, w1, h_save, pre_save, kept_count, N, d.capacity, d.d_ff, d.d_model, act, b1, x_rows,
-                                 nullptr, 0, d.tune}, s);
+                                 d.tune}, s);
         if (t0 && t1) (void)hipEventRecord(t1, s);
         return err;
     }
@@ -564,8 +542,7 @@ hipError_t launch_expert_ffn_up(const LayerDesc &d, const Workspace &ws, const v
     }
     if (t0 && t1) (void)hipEventRecord(t0, s);
     const hipError_t err = launch_grouped_gemm_f32(
-        f32_gemm(GroupedGemm{src, w1, ws.hidden, nullptr, kept_count, N, d.capacity, d.d_ff, d.d_model, act, b1, x_rows, nullptr, 0,
-                             d.tune}), s);
+        f32_gemm(GroupedGemm{src, w1, ws.hidden, nullptr, kept_count, N, d.capacity, d.d_ff, d.d_model, act, b1, x_rows, d.tune}), s);
     if (t0 && t1) (void)hipEventRecord(t1, s);
     return err;
 }
@@ -582,8 +559,7 @@ hipError_t launch_expert_ffn_down(const LayerDesc &d, const Workspace &ws, const
         GemmArgs g{hidden, w2, b2, ye, kept_count, d.capacity, d.d_model, d.d_ff, 0, 0, 0, nullptr, y_rows, y_tokens, gate};
         return launch_half(d.dtype, g, N, 0, pick_tile(d.tune, N, d.capacity, d.d_model, d.d_ff), d.tune, s);
     }
-    F32Gemm f = f32_gemm(GroupedGemm{hidden, w2, ye, nullptr, kept_count, N, d.capacity, d.d_model, d.d_ff, 0, b2, nullptr, nullptr, 0,
-                                     d.tune});
+    F32Gemm f = f32_gemm(GroupedGemm{hidden, w2, ye, nullptr, kept_count, N, d.capacity, d.d_model, d.d_ff, 0, b2, nullptr, d.tune});
     f.y_rows = y_rows, f.y_tok = y_tokens, f.gate = gate;
     return launch_grouped_gemm_f32(f, s);
 }

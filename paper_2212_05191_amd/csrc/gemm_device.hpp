@@ -21,7 +21,6 @@ struct GemmArgs {
     void *y_tok;            // [T][Nout]
     const float *gate;      // [T]
     void *y2 = nullptr;     // [N][C][Nout]: the same product without the activation (DUAL kernels only)
-    const void *aux = nullptr;   // [N][C][Nout]: POST kernels multiply the output by act'(aux)
     int N = 0;                   // experts (PERSIST kernels walk the live row tiles of all of them)
 };
 
@@ -53,26 +52,6 @@ __device__ __forceinline__ float activate(float v)
         const float ex = __builtin_amdgcn_exp2f(v * v * (-0.5f * 1.4426950408889634f));
         return fmaxf(v, 0.f) - av * (poly * t * ex);
     } else return v;
-}
-
-// Derivative of the activation at v.  POST 1: ReLU, 2: GELU, d/dv [v Phi(v)] = Phi(v) + v phi(v), with
-// Phi from the same rational erfc approximation as above (|error| < 1.5e-7) and phi sharing its exp.
-template <int POST>
-__device__ __forceinline__ float activate_grad(float v)
-{
-    if constexpr (POST == 1) return v > 0.f ? 1.f : 0.f;
-    else {
-        const float av = fabsf(v);
-        const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, av, 1.0f));
-        float poly = fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
-        poly = fmaf(poly, t, 0.5f * 1.421413741f);
-        poly = fmaf(poly, t, 0.5f * -0.284496736f);
-        poly = fmaf(poly, t, 0.5f * 0.254829592f);
-        const float ex = __builtin_amdgcn_exp2f(v * v * (-0.5f * 1.4426950408889634f));
-        const float q = poly * t * ex;                      // 1 - Phi(|v|)
-        const float cdf = v >= 0.f ? 1.0f - q : q;
-        return fmaf(v * 0.3989422804014327f, ex, cdf);
-    }
 }
 
 // ------------------------------------------------------------------------------------ bf16 / fp16: MFMA

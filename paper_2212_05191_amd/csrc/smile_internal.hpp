@@ -391,7 +391,6 @@ hipError_t launch_expert_ffn_down(const LayerDesc &d, const Workspace &ws, const
 // below kept[e] only (kept == nullptr: all C rows).  act: 0 none, 1 ReLU, 2 GELU.  y2 != nullptr: the product
 // without the activation goes there as well.  bf16 needs K % 64 == 0 and Nout % 8 == 0, fp32 K % 4 == 0.
 // bias: [N][Nout] or null.  x_rows != nullptr: input row r of group e is row x_rows[e*C + r] of the matrix x[.][K].
-// post (1 ReLU, 2 GELU; needs act == 0 and aux[N][C][Nout]): the output is multiplied by act'(aux).
 struct GroupedGemm {
     const void *x, *w;
     void *y, *y2;
@@ -399,8 +398,6 @@ struct GroupedGemm {
     int N, C, Nout, K, act;
     const void *bias = nullptr;
     const int32_t *x_rows = nullptr;
-    const void *aux = nullptr;
-    int post = 0;
     Tuning tune = {};
 };
 hipError_t launch_grouped_gemm_nt(int dtype, const GroupedGemm &g, hipStream_t s);
