@@ -242,11 +242,15 @@ PERSISTENT_CASES = [
 ]
 
 
+@pytest.mark.parametrize("tile", [None, "0"], ids=["own_tile", "tile_128x192"])
 @pytest.mark.parametrize("cfg", PERSISTENT_CASES, ids=lambda c: c.name)
-def test_persistent_grid_forward_and_backward(torch_cuda, cfg, monkeypatch):
+def test_persistent_grid_forward_and_backward(torch_cuda, cfg, tile, monkeypatch):
     """The expert GEMMs launched as persistent workgroups that walk the live tiles (normally chosen only for grids
-    of many tiles), forced here on small ragged shapes: forward (both paths) and backward against the oracle."""
+    of many tiles), forced here on small ragged shapes, in the tile that the library takes for them (64 rows for most) and in
+    128 x 192: forward (both paths) and backward against the oracle."""
     monkeypatch.setenv("SMILE_FFN_PERSIST", "1")
+    if tile is not None:
+        monkeypatch.setenv("SMILE_FFN_TILE", tile)
     layer = _forward_backward(cfg, dloss=0.7)
     try:
         _say(f"   forward {parity.check_full(cfg, layer)}")

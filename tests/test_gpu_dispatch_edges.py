@@ -69,14 +69,54 @@ ROUTE_EDGES = [
     wl.small_config("route_256_below_65536", 52000, 64, 64, 64, 8, 110, "bf16", "relu", seed=325),
     wl.small_config("route_256_wide_tile", 66000, 64, 64, 32, 32, 70, "bf16", "relu", skew=True, seed=326, group_capacity=2000),
     wl.small_config("route_wide_tile", 500, 64, 64, 1, 200, 4, "bf16", "relu", seed=319),
-    wl.small_config("route_beyond_tile", 300, 64, 64, 300, 2, 2, "bf16", "relu", seed=320, group_capacity=1),
+    wl.small_config("route_300_groups_cap", 300, 64, 64, 300, 2, 2, "bf16", "relu", seed=320, group_capacity=1),
 ]
+# kernels that a case is there for (by default: logits and decision in one launch, from an LDS tile)
+ROUTE_KERNELS = {
+    "route_33_columns_64": ["gate_logits_kernel", "gate_logits_route_kernel", "route_first_hop_kernel<false>", "route_finish_kernel"],
+    "route_48_columns_64": ["gate_logits_kernel", "gate_logits_route_kernel", "route_scan_kernel"],
+    "route_64_to_256": ["gate_logits_kernel", "gate_logits_route_kernel", "route_scan_kernel"],
+    "route_256_below_65536": ["gate_logits_kernel", "gate_logits_route_kernel", "route_scan_kernel"],
+    "route_256_wide_tile": ["gate_logits_kernel", "gate_logits_route_kernel", "route_first_hop_kernel<true>"],
+    "route_256_blocks_16": ["gate_logits_route_kernel", "route_first_hop_kernel<true>", "route_scan_kernel"],
+}
+# Routers too wide for a tile: per-wave histograms or one copy, block order summed inside route_finish or scanned, each with
+# and without a first-hop limit.
+WIDE_ROUTERS = {
+    wl.small_config("wide_inline", 300, 64, 64, 1, 1024, 2, "bf16", "relu", seed=351):
+        ["gate_logits_kernel", "route_decide_kernel<true>", "route_finish_kernel"],
+    wl.small_config("wide_inline_hop", 500, 64, 64, 600, 2, 3, "f32", "relu", seed=352, group_capacity=1):
+        ["gate_logits_kernel", "route_decide_kernel<true>", "route_first_hop_kernel<false>", "route_finish_kernel"],
+    wl.small_config("wide_inline_one_copy", 700, 64, 64, 1000, 2, 2, "bf16", "relu", skew=True, seed=353, group_capacity=2):
+        ["gate_logits_kernel", "route_decide_kernel<false>", "route_first_hop_kernel<false>", "route_finish_kernel"],
+    wl.small_config("wide_scan", 20000, 64, 64, 2, 900, 20, "f16", "relu", seed=354):
+        ["gate_logits_kernel", "route_decide_kernel<true>", "route_scan_kernel"],
+    wl.small_config("wide_scan_hop", 12000, 64, 64, 48, 60, 9, "bf16", "relu", skew=True, seed=355, group_capacity=200):
+        ["gate_logits_kernel", "route_decide_kernel<false>", "route_first_hop_kernel<true>"],
+}
 
 
-@pytest.mark.parametrize("cfg", ROUTE_EDGES, ids=lambda c: c.name)
+def _launched(layer, call):
+    """Names of the kernels that a library call on the layer's ctx launches."""
+    import ctypes
+    import torch
+    lib, evs = B.load(), [torch.cuda.Event(enable_timing=True) for _ in range(32)]
+    for e in evs:
+        e.record()
+    torch.cuda.synchronize()
+    arr = (ctypes.c_void_p * 32)(*[e.cuda_event for e in evs])
+    assert lib.smile_kernel_timing(layer.ctx.handle, arr, 16) == 0
+    call()
+    torch.cuda.synchronize()
+    names = [lib.smile_kernel_timing_name(layer.ctx.handle, i).decode() for i in range(lib.smile_kernel_timing_count(layer.ctx.handle))]
+    assert lib.smile_kernel_timing(layer.ctx.handle, None, 0) == 0
+    return names
+
+
+@pytest.mark.parametrize("cfg", ROUTE_EDGES + list(WIDE_ROUTERS), ids=lambda c: c.name)
 def test_routing_blocks(torch_cuda, cfg):
     """The chained forward passes (logits and routing in one launch) and the separate calls give the same bits; the
-    outputs match the oracle."""
+    outputs match the oracle; the kernels that the case is there for ran."""
     import numpy as np
     from test_gpu_parity import _run
     outs = {}
@@ -86,6 +126,10 @@ def test_routing_blocks(torch_cuda, cfg):
             outs[how] = parity.fetch(layer)
             if how == "chained":
                 parity.check_full(cfg, layer)
+                names = _launched(layer, layer.forward)
+                want = WIDE_ROUTERS.get(cfg) or ROUTE_KERNELS.get(cfg.name, ["gate_logits_route_kernel"])
+                assert all(any(w in k for k in names) for w in want), (want, names)
+                assert ("gate_logits_kernel" in want) == any("gate_logits_kernel" in k for k in names), (want, names)
         finally:
             layer.close()
     for how in ("fused", "chained"):
@@ -211,3 +255,62 @@ def test_router_logits_of_very_long_rows(torch_cuda):
     ctx.close()
     want = 2.0 * torch.arange(1, T + 1, device="cuda:0").float()
     assert torch.equal(li[:, 0], want) and torch.equal(lq[:, 0], want)
+
+
+# ---- expert biases.  Every 16-bit tile shape, plain and persistent, on columns that end inside a 128-, 192- and 256-wide tile (448, 320)
+# and rows that end inside a tile; fp32 too.
+def _layer_with_biases(cfg):
+    import numpy as np
+    from paper_2212_05191_amd.runner import GpuLayer, to_device
+    layer = GpuLayer(cfg)
+    rng = np.random.default_rng(9)
+    b1 = wl.quantize(rng.standard_normal((cfg.N, cfg.d_ff)).astype(np.float32), cfg.dtype)
+    b2 = wl.quantize(rng.standard_normal((cfg.N, cfg.d_model)).astype(np.float32), cfg.dtype)
+    layer.b1, layer.b2 = to_device(b1, cfg.dtype), to_device(b2, cfg.dtype)
+    for io in (layer.io, layer.io_fused):
+        io.b1, io.b2 = layer.b1.data_ptr(), layer.b2.data_ptr()
+    return layer, b1, b2
+
+
+@pytest.mark.parametrize("persist", ["0", "1"])
+@pytest.mark.parametrize("tile,dtype", [(t, "bf16") for t in range(10)] + [(t, "f16") for t in (0, 1, 2, 5, 8, 9)] + [(None, "f32"), (None, "bf16")])
+def test_expert_biases_in_every_tile(torch_cuda, tile, dtype, persist, monkeypatch):
+    """The separate calls against the oracle with biases; the chained, the buffer-free and the activation-saving forward passes
+    (two outputs: the pre-activation has the bias too) give the same bits."""
+    import numpy as np
+    import oracle
+    from paper_2212_05191_amd.runner import to_host
+    monkeypatch.setenv("SMILE_FFN_PERSIST", persist)
+    if tile is not None:
+        monkeypatch.setenv("SMILE_FFN_TILE", str(tile))
+    cfg = wl.small_config(f"biases_{dtype}_{tile}", 900, 320, 448, 2, 3, 170, dtype, "gelu", seed=361)
+    layer, b1, b2 = _layer_with_biases(cfg)
+    try:
+        layer.buf.ye.zero_()
+        layer.forward_steps()
+        out = parity.fetch(layer)
+        x, wi, wq, bi, bq = parity.host_inputs(cfg)
+        r, _ = parity.check_logits_and_routing(cfg, out, x, wi, wq, bi, bq)
+        xe = parity.check_dispatch_exact(cfg, out, x, r)
+        w1 = np.stack([wl.gen_expert_weights(cfg, e)[0] for e in range(cfg.N)])
+        w2 = np.stack([wl.gen_expert_weights(cfg, e)[1] for e in range(cfg.N)])
+        ye = oracle.expert_ffn(xe, r.kept_count, w1, w2, cfg.act, dtype, b1, b2)
+        mask = np.arange(cfg.capacity)[None, :] < r.kept_count[:, None]
+        assert parity.normwise(out["ye"][mask], ye[mask]) <= parity.TOL[dtype]
+        y = oracle.combine(ye, r.group_idx, r.local_idx, r.slot, r.gate, cfg.m_local, dtype)
+        assert parity.normwise(out["y"], y) <= parity.TOL[dtype]
+        for run in (layer.forward, layer.forward_fused):
+            layer.buf.y.fill_(-7)
+            run()
+            np.testing.assert_array_equal(parity.fetch(layer)["y"], out["y"])
+        layer.enable_saved_activations()
+        layer.pre_save.zero_()
+        layer.buf.y.fill_(-7)
+        layer.forward_fused()
+        np.testing.assert_array_equal(parity.fetch(layer)["y"], out["y"])
+        # the pre-activation: one rounding to the storage type of a sum that is exact to fp32 rounding
+        pre = np.matmul(xe.astype(np.float64), w1.astype(np.float64).transpose(0, 2, 1)) + b1[:, None, :]
+        step = {"f32": 1e-5, "bf16": 2.0 ** -8, "f16": 2.0 ** -11}[dtype]
+        assert parity.normwise(to_host(layer.pre_save)[mask], pre[mask]) <= step
+    finally:
+        layer.close()

@@ -332,7 +332,7 @@ def test_expert_biases(torch_cuda):
         layer.close()
 
 
-@pytest.mark.parametrize("tile,dtype", [(t, "bf16") for t in range(7)] + [(0, "f16"), (2, "f16"), (6, "f16")])
+@pytest.mark.parametrize("tile,dtype", [(t, "bf16") for t in range(10)] + [(0, "f16"), (2, "f16"), (6, "f16"), (9, "f16")])
 def test_every_ffn_tile_shape(torch_cuda, tile, dtype, monkeypatch):
     """Each MFMA tile shape of the grouped GEMM, on a shape with ragged row and column tiles."""
     monkeypatch.setenv("SMILE_FFN_TILE", str(tile))
