@@ -14,7 +14,7 @@ the same JSON line.  For every configuration:
     the launch of the dominant kernel, the up-projection grouped GEMM, so that `roofline` comes from that kernel's
     own duration inside the timed region;
   * a second, instrumented pass attaches an event pair to EVERY kernel of the step (smile_kernel_timing) and to the
-    stand-alone dispatch / combine kernels: `kernels_us`, `hbm` and the launch-gap sum come from those
+    stand-alone gate / dispatch / combine kernels: `kernels_us`, `hbm` and the launch-gap sum come from those
     kernel-own durations, not from intervals that include launch latency.
 `roofline.bound` is the binding one of the two lower bounds of the up-projection: 2*K*d*F flop at the bf16 MFMA
 peak against its compulsory bytes (all expert weights once + kept rows in + hidden rows out) at the HBM peak;
@@ -182,16 +182,17 @@ def bench_config(name, steps, warmup, hip, with_training, with_cpu, copy_calibra
     up_bytes = N * d * F * s + kept * d * s + kept * F * s
 
     # ---- instrumented pass (not part of `value`): an event pair on every kernel of the fused step, then on the
-    # stand-alone dispatch / combine kernels of the materialised path
+    # stand-alone gate / dispatch / combine kernels of the materialised path
     reps = max(5, min(steps, 20))
     fused = timed_kernels(hip, lib, h, step, reps)
     kernels_us = {}
-    gemms = [i for i, (lbl, _) in enumerate(fused) if lbl.startswith("grouped_gemm_nt")]
+    gemms = [i for i, (lbl, _) in enumerate(fused) if lbl.startswith("grouped_gemm")]
+    assert len(gemms) == 2, fused
     for i, (lbl, us) in enumerate(fused):
         key = lbl
-        if gemms and i == gemms[0]:
+        if i == gemms[0]:
             key = "expert_ffn_up"
-        elif gemms and i == gemms[-1]:
+        elif i == gemms[1]:
             key = "expert_ffn_down"
         kernels_us[key] = round(kernels_us.get(key, 0.0) + us, 2)
     kernel_sum_us = sum(us for _, us in fused)
@@ -206,11 +207,19 @@ def bench_config(name, steps, warmup, hip, with_training, with_cpu, copy_calibra
         assert st == 0
     # combine reads the expert buffer it is given: xe (just dispatched, same shape and dtype as ye) serves as input
     comb = timed_kernels(hip, lib, h, separate2, reps)
-    gate_us = sum(us for lbl, us in fused if lbl.startswith("gate_logits")) or None   # wide routers: several passes
-    route_us = sum(us for lbl, us in fused if lbl.startswith("route_") or lbl.startswith("finalize_map"))
-    up_us, down_us = kernels_us.get("expert_ffn_up"), kernels_us.get("expert_ffn_down")
+
+    def separate3():
+        st = lib.smile_gate_logits(h, p(layer.x), p(layer.w_inter), p(layer.w_intra), p(b.logits_inter), p(b.logits_intra), stream)
+        assert st == 0
+    gate_us = sum(us for _, us in timed_kernels(hip, lib, h, separate3, reps))   # wide routers: several passes
+    # logits, decision, block order, slots: everything of the fused step in front of the expert GEMMs (logits and decision
+    # are one kernel for most shapes)
+    route_us = sum(us for _, us in fused[:gemms[0]])
+    up_us, down_us = kernels_us["expert_ffn_up"], kernels_us["expert_ffn_down"]
+    gate_bytes = T * d * s + (n + m) * d * s + 4 * T * (n + m)
     alg_bytes = {
-        "gate_logits": (T * d * s + (n + m) * d * s + 4 * T * (n + m), gate_us),
+        "gate_logits_alone": (gate_bytes, gate_us),
+        "gate_and_route": (gate_bytes + 28 * T, route_us),   # seven routing results of 4 bytes per token
         "dispatch": (2 * kept * d * s + 12 * T, disp[0][1]),
         "combine": (kept * d * s + T * d * s + 16 * T, comb[0][1]),
         "expert_ffn_up": (up_bytes, up_us),
@@ -266,7 +275,7 @@ def bench_config(name, steps, warmup, hip, with_training, with_cpu, copy_calibra
         "expert_gemm_mfma_frac": (round(2 * up_flops / ((up_us + down_us) * 1e-6) / 1e12 / PEAK_BF16_TFLOPS, 4)
                                   if half and up_us and down_us else None),
         "kernels_us": kernels_us,
-        "route_kernels_us": round(route_us, 2),
+        "gate_and_route_kernels_us": round(route_us, 2),
         "launches_per_step": len(fused),
         # event-timed step minus the sum of the kernel-own durations of the instrumented pass (launch gaps; the
         # instrumented kernels run a little slower than in the timed region, so this can come out negative)
@@ -415,7 +424,7 @@ def main():
         "roofline": head["roofline"],
         "expert_gemm_mfma_frac": head["expert_gemm_mfma_frac"],
         "kernels_us": head["kernels_us"],
-        "route_kernels_us": head["route_kernels_us"],
+        "gate_and_route_kernels_us": head["gate_and_route_kernels_us"],
         "launches_per_step": head["launches_per_step"],
         "step_minus_kernel_sum_us": head["step_minus_kernel_sum_us"],
         "pre_warm_ms": PRE_WARM_S * 1e3, "pre_warm_steps": head["pre_warm_steps"],
