@@ -43,10 +43,10 @@ MEASURED_BF16_TFLOPS = 2485.0
 # scaled by what the same counter reads for a plain device copy of known size); the summary that backs each
 # figure is named beside it.  Workloads without a tracked summary report null.
 MEASURED_TRAFFIC = {
-    "cfg2": (137.38e6, "profiles/bench_cfg2_hbm_traffic_pmc.txt"),
-    "cfg3": (738.33e6, "profiles/bench_cfg3_hbm_traffic_pmc.txt"),
-    "cfg4": (840.35e6, "profiles/bench_cfg4_hbm_traffic_pmc.txt"),
-    "cfg5": (2262.06e6, "profiles/bench_cfg5_hbm_traffic_pmc.txt"),
+    "cfg2": (137.32e6, "profiles/bench_cfg2_hbm_traffic_pmc.txt"),
+    "cfg3": (739.80e6, "profiles/bench_cfg3_hbm_traffic_pmc.txt"),
+    "cfg4": (840.30e6, "profiles/bench_cfg4_hbm_traffic_pmc.txt"),
+    "cfg5": (2266.25e6, "profiles/bench_cfg5_hbm_traffic_pmc.txt"),
 }
 
 PRE_WARM_S = 0.25   # untimed ramp before the warm-up steps of every configuration
