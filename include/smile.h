@@ -35,7 +35,7 @@
  *     router of Section 2 (Eq. 1-2, k = 1).
  *   - Floating-point inputs must be finite; NaN/Inf give unspecified results.
  *   - Tuning switches (never needed in normal use; tests and sweeps set them): smile_create and
- *     smile_create_with_workspace read the environment variables SMILE_FFN_TILE (0-6: tile shape of
+ *     smile_create_with_workspace read the environment variables SMILE_FFN_TILE (0-9: tile shape of
  *     the forward expert GEMMs), SMILE_TGEMM_TILE (0-3: tile shape of the gradient GEMMs),
  *     SMILE_FFN_PERSIST (0/1: plain or persistent GEMM grid) and SMILE_ROUTER_GRAD_MFMA (0: vector-ALU
  *     router-gradient kernels) ONCE and keep the values in the ctx; no other call looks at the
@@ -164,10 +164,11 @@ smile_status smile_route_bilevel(smile_ctx *ctx, const float *logits_inter, cons
 /* smile_route_bilevel for callers that cannot allocate device memory or create a ctx: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels, same arguments
  * and bit-identical results; instead of a ctx it takes the layer description, and its scratch memory
- * (per-block histograms, partial probability sums, block-local ranks: 8*T bytes and, up to 65536 tokens,
- * at most 2 MB, beyond about 4*(T/256)*(N+2n+2m) bytes) is a fixed array of SMILE_STATIC_SCRATCH_BYTES inside the library's device image, which
+ * (per-block histograms, partial probability sums, block-local ranks: 8*T bytes and 4*(N+2n+2m) bytes for
+ * each block of 16, 32 or 64 tokens while these make at most 2 MB and T <= 65536, otherwise for each block of
+ * 256 tokens) is a fixed array of SMILE_STATIC_SCRATCH_BYTES inside the library's device image, which
  * every GPU the library runs on holds until the process ends.  Returns SMILE_WORKSPACE when the shape
- * needs more than that (T = 65536 with 256 experts needs 1.9 MB) and enqueues nothing then.  It calls
+ * needs more than that (T = 65536 with 32 x 8 experts needs 1.9 MB, with 64 x 64 experts 5 MB) and enqueues nothing then.  It calls
  * no hipMalloc / hipFree and nothing that allocates; the first call on a device looks up the array's
  * address (make that call outside a graph capture).  All calls on one GPU share the array: calls that
  * overlap there (other streams, other threads) race, calls in stream order do not, and no call
@@ -271,7 +272,7 @@ typedef struct smile_layer_io {
 /* The whole forward pass in one call: enqueues the six steps above in order on
  * `stream` (gate logits, route, dispatch, expert FFN, combine, loss).  Same checks
  * and bit-identical results as calling them one by one, with fewer launches: the router logits
- * are computed by the kernel that routes them, and the last routing kernel evaluates the loss.
+ * are computed by the kernel that routes them (most shapes), and the last routing kernel evaluates the loss.
  *   - io->xe and io->ye given: the expert buffers are materialised as by
  *     smile_dispatch / smile_expert_ffn; the last routing kernel moves the rows and the down-projection also
  *     writes y;
@@ -279,8 +280,11 @@ typedef struct smile_layer_io {
  *     the up-projection gathers its rows from x through a slot -> token map and the
  *     down-projection returns gate-weighted rows straight to y; rows of dropped
  *     tokens are zeroed by the routing (no [N,C,d] traffic).
- * Four launches up to 16384 tokens with up to about 100 experts (three for a batch of at most 64 tokens and 64 KB of
- * x), five beyond; a group capacity adds one or two. */
+ * Launches: three for a batch of at most 64 tokens and 64 KB of x (router of at most some hundred columns; four with expert
+ * buffers); otherwise four, one more where a kernel of its own orders the routing blocks (more than 256 of them, or
+ * (N + n) * blocks beyond 32768 counts: from about 16384 tokens or 100 experts on), one more (per 128 router columns) where the
+ * logits have a kernel of their own (33 to 48 router columns from 8193 tokens on, more than 65536 tokens, routers of
+ * several hundred columns); a group capacity adds one or two. */
 smile_status smile_layer_forward(smile_ctx *ctx, const smile_layer_io *io, void *stream);
 
 /* ---------------------------------------------------------------------------

@@ -16,8 +16,8 @@
 //     vmcnt), one s_barrier (every wave's part landed, and every wave is done reading the buffer
 //     about to be refilled), issue the loads of the slab STAGES-1 ahead beside the MFMAs.  The wait for the next slab comes
 //     before the LAST k-step of a slab, so that no LDS read at a slab's start is waited for with the matrix cores idle
-//     (with the reads moved to the front of a k-step, us: 16 experts x 512 rows, 768 x 3072 forward 125.4 -> 123.2,
-//     128 experts 501 -> 486, 256 experts skewed 1024 -> 961).
+//     (with the reads moved to the front of a k-step, whole forward pass, both sides in turn on one card, us: 16 experts x 512 rows,
+//     768 x 3072 125.1 -> 121.2, 128 experts 498.6 -> 487.1, 256 experts skewed 1006 -> 998).
 //   * A direct load writes 64 lanes x 16 bytes to consecutive LDS addresses, i.e. whole rows of a
 //     slab.  The bank swizzle is therefore applied on the global side: the lane that fills position
 //     p of a row fetches piece p ^ f(row), so piece c of a row sits at position c ^ f(row) and the
