@@ -251,13 +251,14 @@ __device__ __forceinline__ void softmax_top1(float *row, const float *__restrict
     }
 }
 
-// Waves per SIMD the registers must leave room for: four blocks of 64 tokens per CU hide each other's reads of x, where the
-// operands of a chunk are more than 128 registers' worth (four and five column tiles) two have to do.
+// Waves per SIMD the registers must leave room for: four 4-wave blocks per CU hide each other's reads of x; with five column tiles a
+// chunk's operands and accumulators alone are more than 128 registers, and one column tile spends its registers on chunks in flight instead
+// (170 with three chunks over 64 tokens: two blocks per CU).
 constexpr int gate_waves_per_simd(int NT, int CT) { return NT == 1024 || (CT > 1 && CT <= 3) ? 4 : 2; }
 
 // Chunks in flight of the logits (gate_partial's U): as many, up to three, as fit the registers without spilling -- 8 (RT + CT) of
-// operands a chunk, 4 RT CT of accumulators, the addresses and about 24 others, in the 128 of four waves per SIMD, else in the 168 of
-// three.  One chunk more spilled 44-96 bytes per lane: with 40 columns 8192 x 768 took 17.2 us instead of 13.9, 4096 x 768 14.8 instead of 12.7.
+// operands a chunk, 4 RT CT of accumulators, the addresses and about 24 others, in the 128 of four waves per SIMD, else in about 170.
+// One chunk more spilled 44-96 bytes per lane: with 40 columns 8192 x 768 took 17.2 us instead of 13.9, 4096 x 768 14.8 instead of 12.7.
 constexpr int gate_chunks_in_flight(int CT, int RT, int waves)
 {
     for (int u = 3; u > 1; --u)
