@@ -432,7 +432,7 @@ hipError_t launch_expert_ffn_backward(const LayerDesc &d, void *workspace, const
     const void *h = h_saved, *pre = pre_saved;
     if (!h) {
         void *h_ws = b + L.off_h, *pre_ws = b + L.off_pre;
-        SMILE_TRY(launch_grouped_gemm_nt(d.dtype, GroupedGemm{xe, w1, h_ws, pre_ws, kept_count, N, C, F, dm, act, nullptr, nullptr, d.tune}, s));
+        SMILE_TRY(launch_grouped_gemm_nt(d.dtype, GroupedGemm{xe, w1, h_ws, pre_ws, kept_count, N, C, F, dm, act, nullptr, nullptr, d.tune, d.T}, s));
         h = h_ws;
         pre = pre_ws;
     }
@@ -442,7 +442,7 @@ hipError_t launch_expert_ffn_backward(const LayerDesc &d, void *workspace, const
                        int Nout, int K, int ldx, int ldw, long long sx, long long sw, long long sy, bool xt, int post) {
         if (is_half(d.dtype))
             return launch_grouped_gemm_t(d.dtype, TransposedGemm{x, w, y, aux, rows, k, N, M, Nout, K, ldx, ldw, sx, sw, sy, xt, true,
-                                                                 post, d.tune}, s);
+                                                                 post, d.tune, d.T}, s);
         F32Gemm g{};
         g.x = x, g.w = w, g.y = y, g.aux = aux, g.rows_valid = rows, g.k_valid = k;
         g.N = N, g.Mrows = M, g.Nout = Nout, g.K = K, g.ldx = ldx, g.ldw = ldw, g.sx = sx, g.sw = sw, g.sy = sy;

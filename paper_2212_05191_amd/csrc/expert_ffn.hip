@@ -99,7 +99,7 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_nt_kernel(Gem
     // the tile of the current ticket (PERSIST) / of this workgroup (plain); false when there is none
     auto select = [&](Tile &t) {
         if constexpr (PERSIST) {
-            if (!walk.tile(t.e, t.rt, t.ct)) return false;
+            return walk.tile(t.e, t.rt, t.ct, t.rows);
         } else {
             const int per_xcd = (a.tiles + kXcds - 1) / kXcds;
             const int lid = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
@@ -413,41 +413,35 @@ hipError_t launch_half_dual_typed(const GemmArgs &a, int N, int act, int tile, c
     return launch_half_dual<E, 128, 192, 2, 2>(a, N, act, tune, s);
 }
 
-// Tile shapes: id -> (BM, BN, waves along M, waves along N, BK, stages, waves/SIMD budget).
-// Measured on the four bf16 workloads (T = 8192..65536 tokens, 16..256 experts):
-//   * up-projection (short K = d_model, wide output, GELU epilogue): 128x192 with two stages and two
-//     co-resident workgroups per CU wins everywhere -- the second workgroup's MFMAs cover the first
-//     one's prologue latency and activation epilogue;
-//   * down-projection (long K = d_ff, narrow output): a single workgroup per CU with a deeper ring
-//     wins -- four stages of 128x192 when the grid has at most one tile per CU, else three stages
-//     of 128x256 (fewer weight bytes through L2 per flop).  256x128 tiles with eight waves (one tile per
-//     expert and column tile when buffers hold at most 256 rows) were the choice for many small buffers while
-//     every tile was a workgroup of its own; with the persistent walk over live tiles 128x256 is equal or
-//     better on every shape measured (256 experts at 21 % / 50 % / 95 % fill: 386 / 440 / 653 us against
-//     418 / 496 / 651), so they are only reachable through the override now.
-//   * 64-row tiles (5, 7-9) for few or small buffers: see pick_tile.
-// Larger tiles (256x128 .. 256x256) move fewer bytes L2 -> LDS per flop but were never faster here.
+// Tile shapes of grouped_gemm_nt_kernel: id -> (BM, BN, waves along M, waves along N, BK, stages, waves/SIMD budget).  0 is the
+// shape for contractions of one or two slabs, which the ring kernels do not take; the 64-row tiles are for few or small buffers: see
+// pick_tile.
 template <typename E>
 hipError_t launch_half_typed(const GemmArgs &a, int N, int act, int tile, const Tuning &tune, hipStream_t s,
                              hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr)
 {
     switch (tile) {
     case 0: return launch_half_tile<E, 128, 192, 2, 2, 64, 2, 2>(a, N, act, tune, s, t0, t1);
-    case 1: return launch_half_tile<E, 128, 192, 2, 2, 64, 4, 1>(a, N, act, tune, s, t0, t1);
-    case 2: return launch_half_tile<E, 128, 256, 2, 2, 64, 3, 1>(a, N, act, tune, s, t0, t1);
-    case 3: return launch_half_tile<E, 256, 128, 4, 2, 64, 3, 2>(a, N, act, tune, s, t0, t1);
-    case 4: return launch_half_tile<E, 128, 128, 2, 2, 32, 4, 2>(a, N, act, tune, s, t0, t1);
     case 5: return launch_half_tile<E, 64, 256, 1, 4, 64, 2, 2>(a, N, act, tune, s, t0, t1);
-    case 6: return launch_half_tile<E, 256, 256, 2, 4, 32, 4, 2>(a, N, act, tune, s, t0, t1);
     case 7: return launch_half_tile<E, 64, 64, 2, 2, 64, 4, 2>(a, N, act, tune, s, t0, t1);
     case 8: return launch_half_tile<E, 64, 128, 2, 2, 64, 3, 2>(a, N, act, tune, s, t0, t1);
     case 9: return launch_half_tile<E, 64, 64, 2, 2, 64, 3, 3>(a, N, act, tune, s, t0, t1);
     default: return hipErrorInvalidValue;
     }
 }
-constexpr int kNumTiles = 10;
+constexpr int kRingTile0 = 1;   // ids 1 .. 4: the shapes of the ring kernels (RingTile)
+constexpr bool is_ring_tile(int tile) { return tile >= kRingTile0 && tile < kRingTile0 + kRingTiles; }
 
-// Tile choice; Tuning::ffn_tile (0..9) overrides it for tuning runs.  Small buffers and narrow layers leave most of the chip
+RingArgs ring_args(const GemmArgs &g, int N)
+{
+    RingArgs a{};
+    a.x = g.x, a.w = g.w, a.y = g.y, a.y2 = g.y2, a.bias = g.bias, a.rows_valid = g.kept, a.x_rows = g.x_rows, a.y_rows = g.y_rows;
+    a.y_tok = g.y_tok, a.gate = g.gate, a.N = N, a.Mrows = g.C, a.Nout = g.Nout, a.K = g.K, a.ldx = g.K, a.ldw = g.K;
+    a.sx = (long long)g.C * g.K, a.sw = (long long)g.Nout * g.K, a.sy = (long long)g.C * g.Nout, a.backwards = g.backwards;
+    return a;
+}
+
+// Tile choice; Tuning::ffn_tile (0..9 without 6) overrides it for tuning runs.  Large buffers take the ring kernels (pick_ring_tile).  Small buffers and narrow layers leave most of the chip
 // without a 128-row tile (16 experts x 768 columns: 64 tiles of 192 columns on 256 CUs, each a serial chain of K / 64 slabs),
 // so they take 64-row tiles as long as those are few; the counts are those of 64 x 64 tiles over the whole buffers.  bf16, us:
 //   * up, one round of three workgroups per CU (<= 768): 64 x 64, three stages.  16 experts x 16 rows, 768 -> 3072: 22.3 -> 15.9;
@@ -459,31 +453,38 @@ constexpr int kNumTiles = 10;
 //   * down, buffers of at most 64 rows: 64 x 128 up to 2048 (128 x 16 rows, 3072 -> 768: 117.0 -> 104.9), then 64 x 256
 //     (256 x 63 rows, 4096 -> 1024: 374.9 -> 369.2; 64 x 128: 379.8).
 // Every tile adds a row's products in the same order: the results are the same bits.
-int pick_tile(const Tuning &tune, int N, int C, int Nout, int K)
+int pick_tile(const Tuning &tune, const GemmArgs &g, int N)
 {
-    if (tune.ffn_tile >= 0 && tune.ffn_tile < kNumTiles) return tune.ffn_tile;
+    const int C = g.C, Nout = g.Nout, K = g.K;
+    const RingArgs ring = ring_args(g, N);
+    const bool ring_ok = ring_applies(ring, g.x_rows ? g.tokens : C, false, false);
+    if (tune.ffn_tile >= 0 && tune.ffn_tile != 6) return is_ring_tile(tune.ffn_tile) && !ring_ok ? 0 : tune.ffn_tile;
     const long long small = (long long)N * ((C + 63) / 64) * ((Nout + 63) / 64);   // 64 x 64 tiles
     if (Nout >= K) {
         if (small <= 768) return 9;
-        return C > 64 ? 0 : small <= 8192 ? 8 : 5;
+        if (C <= 64) return small <= 8192 ? 8 : 5;
+    } else {
+        if (small <= 1024) return 7;
+        if (C <= 64) return small <= 2048 ? 8 : 5;
     }
-    if (small <= 1024) return 7;
-    if (C <= 64) return small <= 2048 ? 8 : 5;
-    const long long tiles = (long long)N * ((C + 127) / 128) * ((Nout + 191) / 192);
-    return tiles <= 256 ? 1 : 2;
+    if (!ring_ok) return 0;
+    const int rows = g.tokens > 0 ? (g.tokens + N - 1) / N : C;
+    return kRingTile0 + pick_ring_tile(tune, ring, rows < C ? rows : C, false);
 }
 
 // dtype dispatch of the two MFMA launchers
 hipError_t launch_half(int dtype, const GemmArgs &a, int N, int act, int tile, const Tuning &tune, hipStream_t s,
                        hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr)
 {
+    if (is_ring_tile(tile)) return launch_ring_forward(dtype, ring_args(a, N), act, RingTile(tile - kRingTile0), tune, s, t0, t1);
     if (dtype == SMILE_DTYPE_BF16) return launch_half_typed<__bf16>(a, N, act, tile, tune, s, t0, t1);
     return launch_half_typed<_Float16>(a, N, act, tile, tune, s, t0, t1);
 }
 
 hipError_t launch_half_dual(int dtype, const GemmArgs &a, int N, int act, const Tuning &tune, hipStream_t s)
 {
-    const int tile = pick_tile(tune, N, a.C, a.Nout, a.K);
+    const int tile = pick_tile(tune, a, N);
+    if (is_ring_tile(tile)) return launch_ring_forward(dtype, ring_args(a, N), act, RingTile(tile - kRingTile0), tune, s);
     if (dtype == SMILE_DTYPE_BF16) return launch_half_dual_typed<__bf16>(a, N, act, tile, tune, s);
     return launch_half_dual_typed<_Float16>(a, N, act, tile, tune, s);
 }
@@ -515,8 +516,9 @@ hipError_t launch_grouped_gemm_nt(int dtype, const GroupedGemm &g, hipStream_t s
     if (!is_half(dtype)) return launch_grouped_gemm_f32(f32_gemm(g), s);
     if (g.K % 64 || g.Nout % 8) return hipErrorInvalidValue;
     GemmArgs a{g.x, g.w, g.bias, g.y, g.kept, g.C, g.Nout, g.K, 0, 0, 0, g.x_rows, nullptr, nullptr, nullptr, g.y2};
+    a.tokens = g.tokens;
     if (g.y2) return launch_half_dual(dtype, a, g.N, act, g.tune, s);
-    return launch_half(dtype, a, g.N, act, pick_tile(g.tune, g.N, g.C, g.Nout, g.K), g.tune, s);
+    return launch_half(dtype, a, g.N, act, pick_tile(g.tune, a, g.N), g.tune, s);
 }
 
 hipError_t launch_expert_ffn_up(const LayerDesc &d, const Workspace &ws, const void *xe,
@@ -532,13 +534,14 @@ hipError_t launch_expert_ffn_up(const LayerDesc &d, const Workspace &ws, const v
         if (t0 && t1) (void)hipEventRecord(t0, s);
         const hipError_t err = launch_grouped_gemm_nt(
             d.dtype, GroupedGemm{src, w1, h_save, pre_save, kept_count, N, d.capacity, d.d_ff, d.d_model, act, b1, x_rows,
-                                 d.tune}, s);
+                                 d.tune, d.T}, s);
         if (t0 && t1) (void)hipEventRecord(t1, s);
         return err;
     }
     if (is_half(d.dtype)) {
         GemmArgs g{src, w1, b1, ws.hidden, kept_count, d.capacity, d.d_ff, d.d_model, 0, 0, 0, x_rows, nullptr, nullptr, nullptr};
-        return launch_half(d.dtype, g, N, act, pick_tile(d.tune, N, d.capacity, d.d_ff, d.d_model), d.tune, s, t0, t1);
+        g.tokens = d.T;
+        return launch_half(d.dtype, g, N, act, pick_tile(d.tune, g, N), d.tune, s, t0, t1);
     }
     if (t0 && t1) (void)hipEventRecord(t0, s);
     const hipError_t err = launch_grouped_gemm_f32(
@@ -557,7 +560,8 @@ hipError_t launch_expert_ffn_down(const LayerDesc &d, const Workspace &ws, const
     const int32_t *y_rows = y_tokens ? ws.slot_token : nullptr;
     if (is_half(d.dtype)) {
         GemmArgs g{hidden, w2, b2, ye, kept_count, d.capacity, d.d_model, d.d_ff, 0, 0, 0, nullptr, y_rows, y_tokens, gate};
-        return launch_half(d.dtype, g, N, 0, pick_tile(d.tune, N, d.capacity, d.d_model, d.d_ff), d.tune, s);
+        g.tokens = d.T;
+        return launch_half(d.dtype, g, N, 0, pick_tile(d.tune, g, N), d.tune, s);
     }
     F32Gemm f = f32_gemm(GroupedGemm{hidden, w2, ye, nullptr, kept_count, N, d.capacity, d.d_model, d.d_ff, 0, b2, nullptr, d.tune});
     f.y_rows = y_rows, f.y_tok = y_tokens, f.gate = gate;

@@ -1,5 +1,6 @@
 // Device-side pieces shared by the grouped expert GEMM kernels (HIP, gfx950): vector types, the activation
-// functions of the epilogues, the kernel argument block, direct-to-LDS load helpers and the LDS bank swizzle.
+// functions of the epilogues and their derivatives, the kernel argument block, direct-to-LDS load helpers, the transposing LDS read and
+// the LDS bank swizzle.
 #pragma once
 
 #include "smile_internal.hpp"
@@ -22,6 +23,8 @@ struct GemmArgs {
     const float *gate;      // [T]
     void *y2 = nullptr;     // [N][C][Nout]: the same product without the activation (DUAL kernels only)
     int N = 0;                   // experts (PERSIST kernels walk the live row tiles of all of them)
+    bool backwards = false;      // walk the tiles from the last expert to the first
+    int tokens = 0;              // T: rows of the gathered matrix, and what the experts' rows add up to at most (0: full buffers)
 };
 
 namespace {
@@ -81,6 +84,44 @@ __device__ __forceinline__ void wait_vmcnt()
     static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);   // expcnt, lgkmcnt: no wait
 }
+
+// d/dv GELU(v) = Phi(v) + v phi(v) (POST 2), or the step function (POST 1); Phi from the rational erfc approximation 7.1.26 of
+// Abramowitz & Stegun (|error| < 1.5e-7), phi sharing its exponential
+template <int POST>
+__device__ __forceinline__ float activate_grad(float v)
+{
+    if constexpr (POST == 1) return v > 0.f ? 1.f : 0.f;
+    else {
+        const float av = fabsf(v);
+        const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, av, 1.0f));
+        float poly = fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
+        poly = fmaf(poly, t, 0.5f * 1.421413741f);
+        poly = fmaf(poly, t, 0.5f * -0.284496736f);
+        poly = fmaf(poly, t, 0.5f * 0.254829592f);
+        const float ex = __builtin_amdgcn_exp2f(v * v * (-0.5f * 1.4426950408889634f));
+        const float q = poly * t * ex;   // 1 - Phi(|v|)
+        return fmaf(v * 0.3989422804014327f, ex, v >= 0.f ? 1.0f - q : q);
+    }
+}
+
+typedef __attribute__((address_space(3))) char lds_char;
+
+// The two transposing reads of one fragment, HALF bytes apart.  Unless the compiler knows that they do not touch what the
+// global -> LDS loads in flight write, it waits for all of those before each read, which undoes the ring: restrict pointers for the
+// stage read and the stage filled tell it.  Measured at 48 experts x 512 rows, 1600 x 6400, bf16, on the two-stage kernel:
+// dxe 376 -> 261 us, dpre 303 -> 250, dW2 235 -> 227, dW1 254 -> 247.
+template <int HALF, typename V>
+__device__ __forceinline__ void read_transposed(V &f, const lds_char *at)
+{
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    struct { s16x4 lo, hi; } t;
+    t.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)at);
+    t.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(at + HALF));
+    f = __builtin_bit_cast(V, t);
+}
+
+// source of k-rows beyond a ragged contraction length
+__device__ __attribute__((aligned(16))) const uint32_t kZeroPiece[4] = {0u, 0u, 0u, 0u};
 
 // Swizzle term of a row: rows are BK*2 bytes; consecutive rows must land on different banks.
 template <int BK, int SWZ>

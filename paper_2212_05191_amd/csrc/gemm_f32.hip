@@ -30,8 +30,6 @@ namespace smile {
 
 namespace {
 
-__device__ __attribute__((aligned(16))) const uint32_t kZeroPiece[4] = {0u, 0u, 0u, 0u};
-
 struct F32Args {
     const float *x, *w, *bias;
     float *y, *y2;

@@ -30,64 +30,13 @@
 //     stores; POST multiplies by act'(aux) there (the gradient at the pre-activation).
 #include <type_traits>
 
-#include "smile_internal.hpp"
+#include "gemm_device.hpp"
 
 namespace smile {
 
 namespace {
 
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
-typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
-typedef __attribute__((__vector_size__(2 * sizeof(uint32_t)))) uint32_t u32x2;
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) char lds_char;
-
-constexpr int kXcds = 8;
 constexpr int BK = 64;
-
-__device__ __attribute__((aligned(16))) const uint32_t kZeroPiece[4] = {0u, 0u, 0u, 0u};
-
-// The two transposing reads of one fragment, HALF bytes apart.  Unless the compiler knows that they do not touch what the
-// global -> LDS loads in flight write, it waits for all of those before each read, which undoes the ring: front_steps'
-// restrict pointers (the stage read, the stage filled) tell it.  Measured at 48 experts x 512 rows, 1600 x 6400, bf16:
-// dxe 376 -> 261 us, dpre 303 -> 250, dW2 235 -> 227, dW1 254 -> 247.
-template <int HALF, typename V>
-__device__ __forceinline__ void read_transposed(V &f, const lds_char *at)
-{
-    struct { s16x4 lo, hi; } t;
-    t.lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)at);
-    t.hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4 *)(at + HALF));
-    f = __builtin_bit_cast(V, t);
-}
-
-#define SMILE_GPTR(p) ((const __attribute__((address_space(1))) void *)(p))
-#define SMILE_LPTR(p) ((__attribute__((address_space(3))) void *)(p))
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt()
-{
-    static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);   // expcnt, lgkmcnt: no wait
-}
-
-template <int POST>
-__device__ __forceinline__ float activate_grad(float v)
-{
-    if constexpr (POST == 1) return v > 0.f ? 1.f : 0.f;
-    else {
-        // d/dv [v Phi(v)] = Phi(v) + v phi(v); Phi from the rational erfc approximation 7.1.26 of
-        // Abramowitz & Stegun (|error| < 1.5e-7), phi sharing its exponential
-        const float av = fabsf(v);
-        const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, av, 1.0f));
-        float poly = fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
-        poly = fmaf(poly, t, 0.5f * 1.421413741f);
-        poly = fmaf(poly, t, 0.5f * -0.284496736f);
-        poly = fmaf(poly, t, 0.5f * 0.254829592f);
-        const float ex = __builtin_amdgcn_exp2f(v * v * (-0.5f * 1.4426950408889634f));
-        const float q = poly * t * ex;   // 1 - Phi(|v|)
-        return fmaf(v * 0.3989422804014327f, ex, v >= 0.f ? 1.0f - q : q);
-    }
-}
 
 // E: the 16-bit storage type (__bf16 or _Float16)
 template <typename E>
@@ -163,7 +112,7 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
     };
     auto select = [&](Tile &t) {
         if constexpr (PERSIST) {
-            if (!walk.tile(t.e, t.rt, t.ct)) return false;
+            if (!walk.tile(t.e, t.rt, t.ct, t.rows)) return false;
         } else {
             const int per_xcd = (a.tiles + kXcds - 1) / kXcds;
             const int lid = (blockIdx.x % kXcds) * per_xcd + blockIdx.x / kXcds;
@@ -173,7 +122,7 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
             const int rem = lid - t.e * per_group;
             t.ct = rem / a.row_tiles, t.rt = rem - t.ct * a.row_tiles;
         }
-        t.rows = a.rows_valid ? min(a.rows_valid[t.e], a.Mrows) : a.Mrows;
+        if constexpr (!PERSIST) t.rows = a.rows_valid ? min(a.rows_valid[t.e], a.Mrows) : a.Mrows;
         t.kv = a.k_valid ? min(a.k_valid[t.e], a.K) : a.K;
         return t.rt * BM < t.rows;
     };
@@ -457,35 +406,16 @@ hipError_t launch_tile(TGemmArgs<E> a, int N, const Tuning &tune, hipStream_t s)
     return hipGetLastError();
 }
 
-// Tile shapes: id -> (BM, BN, stages, workgroups per CU).  Measured on the backward pass of the bf16
-// workloads: two co-resident workgroups with a two-stage ring beat one workgroup with a larger tile or a
-// deeper ring for all four products; 128 x 192 (fewer LDS bytes per MFMA) wins when it still gives every CU
-// its two workgroups and does not pad the columns much, else 128 x 128.  Tuning::tgemm_tile (0..3) overrides the choice for tuning runs.
-template <typename E, bool XT, bool WT, int POST>
-hipError_t launch_shape(const TGemmArgs<E> &a, int N, const Tuning &tune, hipStream_t s)
-{
-    const long long wide = (long long)N * ((a.Mrows + 127) / 128) * ((a.Nout + 191) / 192);
-    int tile = wide >= 512 ? 3 : 2;
-    // 192-wide column tiles that would be padded by more than a tenth over 128-wide ones (e.g. 1024 columns: 6 x 192
-    // against 8 x 128): the narrower tile wins (6 % on 64 experts of 320 x 1024 x 4096)
-    if ((a.Nout + 191) / 192 * 192 * 10 > (a.Nout + 127) / 128 * 128 * 11) tile = 2;
-    if (tune.tgemm_tile >= 0 && tune.tgemm_tile <= 3) tile = tune.tgemm_tile;
-    if (tile == 0) return launch_tile<E, 128, 256, 3, 1, XT, WT, POST>(a, N, tune, s);
-    if (tile == 1) return launch_tile<E, 128, 128, 4, 1, XT, WT, POST>(a, N, tune, s);
-    if (tile == 2) return launch_tile<E, 128, 128, 2, 2, XT, WT, POST>(a, N, tune, s);
-    return launch_tile<E, 128, 192, 2, 2, XT, WT, POST>(a, N, tune, s);
-}
-
 template <typename E>
 hipError_t launch_typed(const TransposedGemm &g, hipStream_t s)
 {
     TGemmArgs<E> a{static_cast<const E *>(g.x), static_cast<const E *>(g.w), static_cast<E *>(g.y),
                    static_cast<const E *>(g.aux), g.rows_valid, g.k_valid, g.Mrows, g.Nout, g.K, g.ldx, g.ldw,
                    g.sx, g.sw, g.sy, 0, 0, 0, g.N};
-    if (g.x_transposed) return launch_shape<E, true, true, 0>(a, g.N, g.tune, s);
-    if (g.post == 1) return launch_shape<E, false, true, 1>(a, g.N, g.tune, s);
-    if (g.post == 2) return launch_shape<E, false, true, 2>(a, g.N, g.tune, s);
-    return launch_shape<E, false, true, 0>(a, g.N, g.tune, s);
+    if (g.x_transposed) return launch_tile<E, 128, 128, 2, 2, true, true, 0>(a, g.N, g.tune, s);
+    if (g.post == 1) return launch_tile<E, 128, 128, 2, 2, false, true, 1>(a, g.N, g.tune, s);
+    if (g.post == 2) return launch_tile<E, 128, 128, 2, 2, false, true, 2>(a, g.N, g.tune, s);
+    return launch_tile<E, 128, 128, 2, 2, false, true, 0>(a, g.N, g.tune, s);
 }
 
 }  // namespace
@@ -497,6 +427,14 @@ hipError_t launch_grouped_gemm_t(int dtype, const TransposedGemm &g, hipStream_t
     if (!g.x_transposed && g.K % BK) return hipErrorInvalidValue;   // a normal operand is read in whole 64-k slabs
     if (!g.w_transposed) return hipErrorInvalidValue;               // not needed by any caller
     if (g.x_transposed && (g.Mrows % 8 || g.post)) return hipErrorInvalidValue;
+    RingArgs a{};
+    a.x = g.x, a.w = g.w, a.y = g.y, a.aux = g.aux, a.rows_valid = g.rows_valid, a.k_valid = g.k_valid, a.N = g.N, a.Mrows = g.Mrows;
+    a.Nout = g.Nout, a.K = g.K, a.ldx = g.ldx, a.ldw = g.ldw, a.sx = g.sx, a.sw = g.sw, a.sy = g.sy;
+    if (g.tune.tgemm_tile != 0 && g.Nout % 64 == 0 && ring_applies(a, g.Mrows, g.x_transposed, true)) {
+        const int rows = g.tokens > 0 && g.rows_valid ? (g.tokens + g.N - 1) / g.N : g.Mrows;
+        const RingTile tile = g.tune.tgemm_tile > 0 ? RingTile(g.tune.tgemm_tile - 1) : pick_ring_tile(g.tune, a, rows < g.Mrows ? rows : g.Mrows, true);
+        return launch_ring_gradient(dtype, a, g.x_transposed, g.post, tile, g.tune, s);
+    }
     if (dtype == SMILE_DTYPE_BF16) return launch_typed<__bf16>(g, s);
     return launch_typed<_Float16>(g, s);
 }

@@ -153,7 +153,7 @@ static Tuning read_tuning()
 {
     Tuning t;
     t.ffn_tile = env_switch("SMILE_FFN_TILE", 0, 9);
-    t.tgemm_tile = env_switch("SMILE_TGEMM_TILE", 0, 3);
+    t.tgemm_tile = env_switch("SMILE_TGEMM_TILE", 0, 4);
     t.persist = env_switch("SMILE_FFN_PERSIST", 0, 1);
     t.router_grad_mfma = env_switch("SMILE_ROUTER_GRAD_MFMA", 0, 1);
     int dev = 0, cus = 0;

@@ -200,44 +200,54 @@ template <int BM>
 struct LiveTileWalk {
     const int32_t *rows;   // [N] or null: `cap` rows in every group
     int N, cap, col_tiles;
+    bool backwards;
     int lane;
     int chunk_tiles, chunk_incl;           // lane c: live row tiles of groups 64c..64c+63, and their inclusive prefix
-    int cur_chunk, cur_cnt, cur_incl;      // the chunk the last ticket fell in: lane l = group 64*cur_chunk + l
+    int cur_chunk, cur_rows, cur_incl;     // the chunk the last ticket fell in: lane l = group 64*cur_chunk + l
     int local, local_step, xcd, tickets, chunk;   // position in the XCD's own sequence of tickets; chunk size
 
-    __device__ __forceinline__ int live_row_tiles(int g) const
+    __device__ __forceinline__ int live_rows(int g) const
     {
         if (g >= N) return 0;
-        const int r = rows ? min(max(rows[g], 0), cap) : cap;
-        return (r + BM - 1) / BM;
+        return rows ? min(max(rows[g], 0), cap) : cap;   // never trust a count beyond the buffer
     }
-    __device__ __forceinline__ int scan(int v) const   // inclusive prefix sum over the 64 lanes
+    __device__ __forceinline__ static int row_tiles(int r) { return (r + BM - 1) / BM; }
+    // Inclusive prefix sum over the 64 lanes, in the vector ALU (row shifts by 1, 2, 4, 8, then the last lane of a row of 16
+    // into the next row, and of the first 32 lanes into the others): a shuffle through LDS costs its latency in each of six steps,
+    // and the walk's set-up stands in front of the kernel's first load.
+    __device__ __forceinline__ static int scan(int v)
     {
-#pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-            const int o = __shfl_up(v, off, 64);
-            if (lane >= off) v += o;
-        }
+        v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);
+        v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
         return v;
     }
-    __device__ __forceinline__ void init(const int32_t *rows_, int N_, int cap_, int col_tiles_, bool interleave)
+    __device__ __forceinline__ void enter_chunk(int c, int r)   // r: lane's row count in chunk c
     {
-        rows = rows_, N = N_, cap = cap_, col_tiles = col_tiles_;
+        cur_chunk = c, cur_rows = r, cur_incl = scan(row_tiles(r));
+    }
+    __device__ __forceinline__ void init(const int32_t *rows_, int N_, int cap_, int col_tiles_, bool interleave, bool backwards_ = false)
+    {
+        rows = rows_, N = N_, cap = cap_, col_tiles = col_tiles_, backwards = backwards_;
         lane = threadIdx.x & 63;
-        chunk_tiles = 0, cur_chunk = -1, cur_cnt = 0, cur_incl = 0;
+        enter_chunk(0, live_rows(lane));
+        const int first = __builtin_amdgcn_readlane(cur_incl, 63);
+        chunk_tiles = lane == 0 ? first : 0;
         const int nchunks = (N + 63) / 64;
-        for (int c0 = 0; c0 < nchunks; c0 += 4) {   // four chunks at a time: their loads overlap
+        for (int c0 = 1; c0 < nchunks; c0 += 4) {   // four chunks at a time: their loads overlap
             int v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = live_row_tiles((c0 + u) * 64 + lane);   // 0 beyond N
+            for (int u = 0; u < 4; ++u) v[u] = live_rows((c0 + u) * 64 + lane);   // 0 beyond N
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-#pragma unroll
-                for (int off = 32; off > 0; off >>= 1) v[u] += __shfl_xor(v[u], off, 64);
-                if (lane == c0 + u) chunk_tiles = v[u];
+                const int sum = __builtin_amdgcn_readlane(scan(row_tiles(v[u])), 63);
+                if (lane == c0 + u) chunk_tiles = sum;
             }
         }
-        chunk_incl = scan(chunk_tiles);
+        chunk_incl = nchunks > 1 ? scan(chunk_tiles) : first;
         tickets = __builtin_amdgcn_readlane(chunk_incl, 63) * col_tiles;
         // 8 k chunks of equal size: k = 1 (contiguous eighths), or enough for chunks of at most 128 tickets
         const int k = interleave ? max(1, (tickets + 1023) / 1024) : 1;
@@ -246,23 +256,21 @@ struct LiveTileWalk {
         local = blockIdx.x / 8;
         local_step = gridDim.x / 8;
     }
-    // the tile of the current ticket; false when this workgroup has no ticket left
-    __device__ __forceinline__ bool tile(int &e, int &rt, int &ct)
+    // the tile of the current ticket and its group's row count; false when this workgroup has no ticket left
+    __device__ __forceinline__ bool tile(int &e, int &rt, int &ct, int &group_rows)
     {
         // the XCD's local-th ticket: chunk (local / chunk) * 8 + xcd, offset local % chunk; increasing in local
-        const int ticket = ((local / chunk) * 8 + xcd) * chunk + local % chunk;
+        int ticket = ((local / chunk) * 8 + xcd) * chunk + local % chunk;
         if (ticket >= tickets) return false;
+        if (backwards) ticket = tickets - 1 - ticket;
         const int I = ticket / col_tiles;   // index of the live row tile
         const int c = __builtin_ctzll(__ballot(chunk_incl > I));
-        const int cbase = __builtin_amdgcn_readlane(chunk_incl - chunk_tiles, c);
-        if (c != cur_chunk) {
-            cur_cnt = live_row_tiles(c * 64 + lane);
-            cur_incl = scan(cur_cnt);
-            cur_chunk = c;
-        }
+        const int cbase = c ? __builtin_amdgcn_readlane(chunk_incl - chunk_tiles, c) : 0;
+        if (c != cur_chunk) enter_chunk(c, live_rows(c * 64 + lane));
         const int l = __builtin_ctzll(__ballot(cbase + cur_incl > I));
-        const int first = cbase + __builtin_amdgcn_readlane(cur_incl - cur_cnt, l);
-        const int cnt = __builtin_amdgcn_readlane(cur_cnt, l);
+        group_rows = __builtin_amdgcn_readlane(cur_rows, l);
+        const int cnt = row_tiles(group_rows);
+        const int first = cbase + __builtin_amdgcn_readlane(cur_incl, l) - cnt;
         const int u = ticket - first * col_tiles;   // 0 .. cnt*col_tiles-1, row tile fastest
         e = c * 64 + l;
         ct = u / cnt;
@@ -301,7 +309,7 @@ inline void launch_kernel(const char *name, Kernel kernel, dim3 grid, dim3 block
 // variables once and asks the runtime for the compute-unit count); -1 = the library's own choice.
 struct Tuning {
     int ffn_tile = -1;           // SMILE_FFN_TILE: tile shape of the forward expert GEMMs
-    int tgemm_tile = -1;         // SMILE_TGEMM_TILE: tile shape of the gradient GEMMs
+    int tgemm_tile = -1;         // SMILE_TGEMM_TILE: tile shape of the gradient GEMMs (0 two-stage, 1-4 ring)
     int persist = -1;            // SMILE_FFN_PERSIST: 0 plain grid, 1 persistent grid
     int router_grad_mfma = -1;   // SMILE_ROUTER_GRAD_MFMA: 0 keeps the vector-ALU router-gradient kernels
     int cus = 256;               // compute units of the device the ctx was created on
@@ -399,6 +407,7 @@ struct GroupedGemm {
     const void *bias = nullptr;
     const int32_t *x_rows = nullptr;
     Tuning tune = {};
+    int tokens = 0;   // T: rows of the gathered matrix, and what the groups' rows add up to at most (0: all C rows of every group)
 };
 hipError_t launch_grouped_gemm_nt(int dtype, const GroupedGemm &g, hipStream_t s);
 
@@ -417,8 +426,41 @@ struct TransposedGemm {
     bool x_transposed, w_transposed;
     int post;
     Tuning tune = {};
+    int tokens = 0;   // T, as in GroupedGemm
 };
 hipError_t launch_grouped_gemm_t(int dtype, const TransposedGemm &g, hipStream_t s);
+
+// Arguments of the ring kernels.  Strides and leading dimensions in elements.
+struct RingArgs {
+    const void *x, *w;
+    void *y;                     // [N][Mrows][Nout], or null when only the scattered output is wanted
+    void *y2;                    // DUAL: the product without the activation
+    const void *aux;             // POST: shaped as y
+    const void *bias;            // [N][Nout] or null
+    const int32_t *rows_valid;   // [N] valid output rows per group, or null: Mrows for all
+    const int32_t *k_valid;      // [N] valid contraction length per group (both operands transposed), or null: K
+    const int32_t *x_rows;       // gather: row r of group e is row x_rows[e*Mrows + r] of x
+    const int32_t *y_rows;       // scatter: the row also goes to y_tok[y_rows[e*Mrows + r]], times gate
+    void *y_tok;
+    const float *gate;
+    int N, Mrows, Nout, K, ldx, ldw;
+    long long sx, sw, sy;
+    int col_tiles;
+    bool backwards;
+};
+// Tile shapes of the ring kernels: rows x columns, two workgroups on a CU or one
+enum RingTile { kRing128x192x2, kRing128x256, kRing256x192, kRing128x128x2, kRingTiles };
+// The shape for one product (gemm_ring_forward.hip); `rows`: expected rows per group
+RingTile pick_ring_tile(const Tuning &tune, const RingArgs &a, int rows, bool gradient);
+// Whether the ring kernels take a product: three slabs or more where an operand is read in whole slabs, and byte offsets that fit
+// the 32 bits a lane keeps (x_rows: rows of the gathered matrix, or of a group's operand)
+bool ring_applies(const RingArgs &a, long long x_rows, bool x_transposed, bool w_transposed);
+// The products of the ring kernels (gemm_ring.hpp): forward (both operands normal; act 0 none, 1 ReLU, 2 GELU; y2: both
+// outputs) and gradient (w transposed, x too or not; post 1 ReLU, 2 GELU: times act'(aux)).  Contraction lengths of normal
+// operands are multiples of 64, Nout of 64.  t0 / t1 (both or neither): events for the kernel's own begin and end.
+hipError_t launch_ring_forward(int dtype, const RingArgs &a, int act, RingTile tile, const Tuning &tune, hipStream_t s, hipEvent_t t0 = nullptr,
+                               hipEvent_t t1 = nullptr);
+hipError_t launch_ring_gradient(int dtype, const RingArgs &a, bool x_transposed, int post, RingTile tile, const Tuning &tune, hipStream_t s);
 
 // One grouped fp32 product y[e][i][j] = sum_k X(i,k) W(j,k), operands and per-group extents as in TransposedGemm
 // (a normal w is [Nout][K]), with the epilogue of GroupedGemm: bias, act (0 none, 1 ReLU, 2 GELU), y2 = the product without

@@ -314,3 +314,45 @@ def test_expert_biases_in_every_tile(torch_cuda, tile, dtype, persist, monkeypat
         assert parity.normwise(to_host(layer.pre_save)[mask], pre[mask]) <= step
     finally:
         layer.close()
+
+
+# ---- ring kernels: every tile shape against the two-stage kernels, which add the same products in the same order.  Contractions of
+# three slabs, of an even and an odd number of them, and (weight gradients: a group's rows) of none, one, two and more with k-rows
+# that end inside a slab; buffers of skewed experts from empty to full, so rows end anywhere in a 128- or 256-row tile; columns that end inside
+# 128-, 192- and 256-wide tiles.
+RING_CASES = [
+    wl.small_config("ring_3_and_7_slabs", 2600, 192, 448, 3, 5, 300, "bf16", "gelu", skew=True, seed=371),
+    wl.small_config("ring_4_and_5_slabs_f16", 1700, 256, 320, 4, 6, 257, "f16", "relu", skew=True, seed=372),
+    wl.small_config("ring_15_slabs", 900, 960, 192, 2, 3, 170, "bf16", "relu", skew=True, seed=373, group_capacity=500),
+    wl.small_config("ring_70_experts", 2000, 192, 256, 10, 7, 64, "bf16", "gelu", skew=True, seed=374),
+]
+
+
+@pytest.mark.parametrize("cfg", RING_CASES, ids=lambda c: c.name)
+def test_ring_tiles_give_the_bits_of_the_two_stage_kernels(torch_cuda, cfg, monkeypatch):
+    from paper_2212_05191_amd.runner import GpuLayer
+    dy = wl.gen_output_grad(cfg)
+    want = None
+    for tile in range(5):   # 0: two-stage
+        monkeypatch.setenv("SMILE_FFN_TILE", str(tile))
+        monkeypatch.setenv("SMILE_TGEMM_TILE", str(tile))
+        layer = GpuLayer(cfg)
+        try:
+            layer.enable_saved_activations()
+            layer.forward()
+            layer.prepare_backward(dy)
+            layer.backward()
+            names = _launched(layer, layer.forward_fused)
+            assert sum("grouped_gemm_ring" in k for k in names) == (2 if tile else 0), names
+            kept = layer.buf.kept_count.cpu()
+            live = torch_cuda.arange(cfg.capacity)[None, :] < kept[:, None]
+            got = {k: getattr(layer.buf, k).cpu() for k in ("y",)} | {k: getattr(layer.bwd, k).cpu() for k in ("dx", "dw1", "dw2")}
+            got |= {"h": layer.h_save.cpu()[live], "pre": layer.pre_save.cpu()[live], "ye": layer.buf.ye.cpu()[live]}
+        finally:
+            layer.close()
+        if want is None:
+            want = got
+            if cfg.name != "ring_70_experts":
+                assert kept.min() < 64 and kept.max() == cfg.capacity
+        for k, v in got.items():
+            assert torch_cuda.equal(v, want[k]), f"tile {tile} {k}: {(v != want[k]).sum()} of {v.numel()} differ"
