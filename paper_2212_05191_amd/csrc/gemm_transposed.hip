@@ -430,7 +430,15 @@ hipError_t launch_grouped_gemm_t(int dtype, const TransposedGemm &g, hipStream_t
     RingArgs a{};
     a.x = g.x, a.w = g.w, a.y = g.y, a.aux = g.aux, a.rows_valid = g.rows_valid, a.k_valid = g.k_valid, a.N = g.N, a.Mrows = g.Mrows;
     a.Nout = g.Nout, a.K = g.K, a.ldx = g.ldx, a.ldw = g.ldw, a.sx = g.sx, a.sw = g.sw, a.sy = g.sy;
-    if (g.tune.tgemm_tile != 0 && g.Nout % 64 == 0 && ring_applies(a, g.Mrows, g.x_transposed, true)) {
+    // The two-stage kernel, whose plain grid needs no walk, keeps what is over before a ring pays: at most two tiles per CU with one or
+    // two slabs of rows to contract (weight gradients), or with rows for half a tile and less than eight slabs, and at most one tile per CU with
+    // four slabs (us per kernel: 111 experts x 4 rows, 128 x 384: dW 5.0, ring 6.0, dxe 6.2 and 6.5; 84 x 18, 64 x 192: dW 4.4 and 5.0;
+    // 43 x 10, 192 x 768: dpre 6.6 and 7.3; but 27 x 11, 128 x 512: dxe, eight slabs, 7.6 and 7.1; 7 x 600, 320 x 1280: dpre 16.3 and 12.1.
+    // Training step of 16 x 108 rows, 256 x 512: 73.8, all on the ring 75.1).
+    const long long tiles = (long long)g.N * ((g.Mrows + 127) / 128) * ((g.Nout + 127) / 128);
+    const bool small = g.x_transposed ? g.K <= 128 && tiles <= 2 * g.tune.cus
+                                      : (g.Mrows <= 64 && g.K < 512 && tiles <= 2 * g.tune.cus) || (g.K <= 256 && tiles <= g.tune.cus);
+    if ((g.tune.tgemm_tile > 0 || (g.tune.tgemm_tile < 0 && !small)) && g.Nout % 64 == 0 && ring_applies(a, g.Mrows, g.x_transposed, true)) {
         const int rows = g.tokens > 0 && g.rows_valid ? (g.tokens + g.N - 1) / g.N : g.Mrows;
         const RingTile tile = g.tune.tgemm_tile > 0 ? RingTile(g.tune.tgemm_tile - 1) : pick_ring_tile(g.tune, a, rows < g.Mrows ? rows : g.Mrows, true);
         return launch_ring_gradient(dtype, a, g.x_transposed, g.post, tile, g.tune, s);
