@@ -560,6 +560,9 @@ hipError_t launch_expert_ffn_down(const LayerDesc &d, const Workspace &ws, const
     const int32_t *y_rows = y_tokens ? ws.slot_token : nullptr;
     if (is_half(d.dtype)) {
         GemmArgs g{hidden, w2, b2, ye, kept_count, d.capacity, d.d_model, d.d_ff, 0, 0, 0, nullptr, y_rows, y_tokens, gate};
+        // From the last expert to the first: what the up-projection wrote last is still in the 256 MB memory-side cache (128 experts x 256
+        // rows, 768 x 3072, 188 MB of h: 447.0 -> 441.9 us a pass; behind the flat router 479.6 -> 474.9; others within 0.3 %)
+        g.backwards = true;
         g.tokens = d.T;
         return launch_half(d.dtype, g, N, 0, pick_tile(d.tune, g, N), d.tune, s);
     }
