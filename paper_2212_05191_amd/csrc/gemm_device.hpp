@@ -47,8 +47,9 @@ __device__ __forceinline__ float activate(float v)
         // degree 8 with P(0) = -1 gives the GELU within 4.4e-8 of its exact value before rounding (least maximum of the error in
         // the GELU itself, and of 4.4e-4 relative in the tail to x = 6.5).  Its leading coefficient is negative: beyond that Phi goes to 0.
         // Evaluated in fp32: largest error 2.6e-7, rms for v ~ N(0, 1) 3.6e-8, relative error down to v = -6.5 4.4e-4.  One
-        // transcendental and 10 VALU instructions; the rational erfc of Abramowitz & Stegun 7.1.26 took two and 13 and was
-        // off by 3.3e-7, 5.4e-8 and 4.9e-3.
+        // transcendental and 11 VALU instructions; the rational erfc of Abramowitz & Stegun 7.1.26 took two and 13 and was
+        // off by 3.3e-7, 5.4e-8 and 4.9e-3.  The factor in front of Phi is kept finite, so that a product that overflowed to
+        // infinity stays infinity (infinity * 0 would be NaN); NaN passes through P.
         const float av = fabsf(v);
         float p = fmaf(-5.313833071e-07f, av, 9.281394341e-06f);
         p = fmaf(p, av, -2.981505531e-05f);
@@ -58,7 +59,7 @@ __device__ __forceinline__ float activate(float v)
         p = fmaf(p, av, -4.590324461e-01f);
         p = fmaf(p, av, -1.151129365e+00f);
         p = fmaf(p, av, -1.0f);
-        return fmaf(-av, __builtin_amdgcn_exp2f(p), fmaxf(v, 0.f));
+        return fmaf(-fminf(av, 0x1p127f), __builtin_amdgcn_exp2f(p), fmaxf(v, 0.f));
     } else return v;
 }
 

@@ -356,3 +356,23 @@ def test_ring_tiles_give_the_bits_of_the_two_stage_kernels(torch_cuda, cfg, monk
                 assert kept.min() < 64 and kept.max() == cfg.capacity
         for k, v in got.items():
             assert torch_cuda.equal(v, want[k]), f"tile {tile} {k}: {(v != want[k]).sum()} of {v.numel()} differ"
+
+
+@pytest.mark.parametrize("tile", [0, 1])
+def test_gelu_of_an_overflowed_product_is_infinity(torch_cuda, tile, monkeypatch):
+    """2^100 * 2^100 has no value in 32 bits; the hidden activation is then infinity, and so is a sum of positive multiples of it."""
+    monkeypatch.setenv("SMILE_FFN_TILE", str(tile))
+    N, C, d, F = 2, 40, 192, 256
+    ctx = B.Ctx(B.make_desc(80, d, F, 1, N, C, "bf16", "gelu"))
+    try:
+        full = lambda *shape, value: torch_cuda.full(shape, value, dtype=torch_cuda.bfloat16, device="cuda:0")
+        xe, w1, w2 = full(N, C, d, value=2.0**100), full(N, F, d, value=2.0**100), full(N, d, F, value=0.5)
+        xe[1] = 2.0**-100   # a plain expert beside it: pre = d, ye = d * F / 2
+        kept = torch_cuda.full((N,), C, dtype=torch_cuda.int32, device="cuda:0")
+        ye = full(N, C, d, value=0.0)
+        B.smile_expert_ffn(ctx, xe, kept, w1, None, w2, None, ye)
+        torch_cuda.cuda.synchronize()
+        assert torch_cuda.isposinf(ye[0]).all()
+        assert (ye[1] == d * F / 2).all()
+    finally:
+        ctx.close()
