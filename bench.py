@@ -43,10 +43,10 @@ MEASURED_BF16_TFLOPS = 2485.0
 # scaled by what the same counter reads for a plain device copy of known size); the summary that backs each
 # figure is named beside it.  Workloads without a tracked summary report null.
 MEASURED_TRAFFIC = {
-    "cfg2": (137.32e6, "profiles/bench_cfg2_hbm_traffic_pmc.txt"),
-    "cfg3": (739.80e6, "profiles/bench_cfg3_hbm_traffic_pmc.txt"),
-    "cfg4": (840.30e6, "profiles/bench_cfg4_hbm_traffic_pmc.txt"),
-    "cfg5": (2266.25e6, "profiles/bench_cfg5_hbm_traffic_pmc.txt"),
+    "cfg2": (140.80e6, "profiles/bench_cfg2_hbm_traffic_pmc.txt"),
+    "cfg3": (893.55e6, "profiles/bench_cfg3_hbm_traffic_pmc.txt"),
+    "cfg4": (870.64e6, "profiles/bench_cfg4_hbm_traffic_pmc.txt"),
+    "cfg5": (2329.42e6, "profiles/bench_cfg5_hbm_traffic_pmc.txt"),
 }
 
 PRE_WARM_S = 0.25   # untimed ramp before the warm-up steps of every configuration
@@ -240,7 +240,7 @@ def bench_config(name, steps, warmup, hip, with_training, with_cpu, copy_calibra
         achieved_gbs = up_bytes / dom_s / 1e9
         t_mfma, t_hbm = up_flops / (PEAK_BF16_TFLOPS * 1e12), up_bytes / (PEAK_HBM_GBS * 1e9)
         traffic, traffic_src = MEASURED_TRAFFIC.get(cfg.name, (None, None))
-        common = {"kernel": "grouped_gemm_nt_kernel (expert FFN up-projection + activation)",
+        common = {"kernel": "grouped_gemm_ring_kernel (expert FFN up-projection + activation)",
                   "avg_launch_us": round(dom_ms * 1e3, 2), "alg_flops_per_launch": up_flops,
                   "alg_bytes_per_launch": up_bytes,
                   "lower_bound_us": {"mfma": round(t_mfma * 1e6, 2), "hbm": round(t_hbm * 1e6, 2)},

@@ -8,16 +8,18 @@
 // (8 consecutive k per lane), so tiles go global -> LDS -> registers as 16-byte pieces with no
 // transposition anywhere.
 //
-// 16-bit kernel (bf16 or fp16 storage; the hot kernel of the layer).  One workgroup computes a BM x BN tile
+// Large buffers of the 16-bit types run on the ring kernels (gemm_ring.hpp), which keep more loads in flight.  The two-stage
+// kernel below takes small buffers and narrow layers (64-row tiles, pick_tile) and what a ring does not take: contractions of fewer
+// than three slabs and operands whose offsets need more than 32 bits.
+//
+// Two-stage kernel (bf16 or fp16 storage).  One workgroup computes a BM x BN tile
 // of one expert with v_mfma_f32_32x32x16_bf16 / _f16 and fp32 accumulators.
 //   * K is cut into slabs of BK elements.  A slab travels global -> LDS directly
 //     (global_load_lds_dwordx4: no staging registers, no ds_write) into a ring of STAGES buffers
 //     with STAGES-1 slabs in flight.  Per slab: wait until this wave's part has landed (s_waitcnt
 //     vmcnt), one s_barrier (every wave's part landed, and every wave is done reading the buffer
 //     about to be refilled), issue the loads of the slab STAGES-1 ahead beside the MFMAs.  The wait for the next slab comes
-//     before the LAST k-step of a slab, so that no LDS read at a slab's start is waited for with the matrix cores idle
-//     (with the reads moved to the front of a k-step, whole forward pass, both sides in turn on one card, us: 16 experts x 512 rows,
-//     768 x 3072 125.1 -> 121.2, 128 experts 498.6 -> 487.1, 256 experts skewed 1006 -> 998).
+//     before the LAST k-step of a slab, so that no LDS read at a slab's start is waited for with the matrix cores idle.
 //   * A direct load writes 64 lanes x 16 bytes to consecutive LDS addresses, i.e. whole rows of a
 //     slab.  The bank swizzle is therefore applied on the global side: the lane that fills position
 //     p of a row fetches piece p ^ f(row), so piece c of a row sits at position c ^ f(row) and the
@@ -441,7 +443,8 @@ RingArgs ring_args(const GemmArgs &g, int N)
     return a;
 }
 
-// Tile choice; Tuning::ffn_tile (0..9 without 6) overrides it for tuning runs.  Large buffers take the ring kernels (pick_ring_tile).  Small buffers and narrow layers leave most of the chip
+// Tile choice; Tuning::ffn_tile (0..9 without 6) overrides it for tuning runs.  Large buffers take the ring kernels
+// (pick_ring_tile).  Small buffers and narrow layers leave most of the chip
 // without a 128-row tile (16 experts x 768 columns: 64 tiles of 192 columns on 256 CUs, each a serial chain of K / 64 slabs),
 // so they take 64-row tiles as long as those are few; the counts are those of 64 x 64 tiles over the whole buffers.  bf16, us:
 //   * up, one round of three workgroups per CU (<= 768): 64 x 64, three stages.  16 experts x 16 rows, 768 -> 3072: 22.3 -> 15.9;

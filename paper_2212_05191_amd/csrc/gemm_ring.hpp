@@ -459,7 +459,7 @@ __global__ __launch_bounds__(256, OCC) void grouped_gemm_ring_kernel(RingArgs a)
                             const int tok = *(const __attribute__((address_space(3))) int *)(meta + (row0 + lrow) * 4);
                             const float g = *(const __attribute__((address_space(3))) float *)(meta + BM * 4 + (row0 + lrow) * 4);
                             // No kernel of the pass reads y again, so its rows pass the L2 by and leave it to w2 and h (128
-                            // experts of 768 -> 3072, 8192 tokens: 437 -> 431 us a pass; 16 experts: 114.6 -> 113.8 us;
+                            // experts of 768 -> 3072, 32768 tokens: 437 -> 431 us a pass; 16 experts, 8192: 114.6 -> 113.8;
                             // the same at 64 experts of 1024 -> 4096, 429 us).
                             __builtin_nontemporal_store(scale_x8<E>(v, g), reinterpret_cast<u32x4 *>(static_cast<E *>(a.y_tok) + (size_t)tok * Nout + col));
                         }

@@ -9,6 +9,10 @@
 // without materialising any transposed copy.  y[e][i][j] = sum_k X(i,k) W(j,k) per group e, where a
 // normal operand is stored [i][k] (k contiguous) and a transposed one [k][i] (i contiguous).
 //
+// Most of these products run on the ring kernels (gemm_ring.hpp).  The two-stage kernel below takes small ones
+// (launch_grouped_gemm_t), normal operands of fewer than three slabs, outputs whose columns are no multiple of 64 and operands whose
+// offsets need more than 32 bits.
+//
 // Design (gfx950):
 //   * global -> LDS with the direct 16-byte loads of the forward kernel, STAGES-deep ring of K slabs
 //     (BK = 64).  A normal operand lands as [row][64 k] (8 pieces per row, XOR-swizzled); a transposed
