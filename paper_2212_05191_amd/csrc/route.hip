@@ -291,7 +291,9 @@ __global__ __launch_bounds__(NT, gate_waves_per_simd(NT, CT)) void gate_logits_r
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int b = blockIdx.x, t0 = b * RB, live = min(RB, a.T - t0);
 
-    for (int i = tid; i < kRankWaves * NC; i += NT) hist[i] = 0;
+    constexpr bool WIDE = GATE && CT == kWideTiles;
+    if (!WIDE)
+        for (int i = tid; i < kRankWaves * NC; i += NT) hist[i] = 0;
 
     // logit rows between memory and the tile: a power-of-two number of neighbouring threads per row (no divisions)
     auto copy_rows = [&](auto to_lds, float *at, const float *src, float *dst, int len) {
@@ -302,7 +304,19 @@ __global__ __launch_bounds__(NT, gate_waves_per_simd(NT, CT)) void gate_logits_r
                 else dst[(size_t)r * len + c] = at[r * stride + c];
             }
     };
-    if constexpr (GATE) {
+    if constexpr (WIDE) {
+        f32x4 logits[CT];
+        gate_wide<DT>(a.x, a.w_inter, a.w_intra, t0, a.T, a.d, n, m, reinterpret_cast<gate_piece *>(lds_f), logits);
+        __syncthreads();   // the stages lie where the tile and the counters come
+        for (int i = tid; i < kRankWaves * NC; i += NT) hist[i] = 0;
+        float *at = tile + (wave * 16 + (lane >> 4) * 4) * stride + (lane & 15);
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+            if (ct * 16 + (lane & 15) < cols)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) at[i * stride + ct * 16] = logits[ct][i];
+        __syncthreads();
+    } else if constexpr (GATE) {
         constexpr int RT = RB < 64 ? RB / 16 : 4;               // row tiles per unit of four waves: at most 64 tokens
         constexpr int kAhead = gate_chunks_in_flight(CT, RT, gate_waves_per_simd(NT, CT));
         const int unit = wave / kGateWaves, uw = wave % kGateWaves, r16 = lane & 15, kg = lane >> 4;
@@ -336,6 +350,8 @@ __global__ __launch_bounds__(NT, gate_waves_per_simd(NT, CT)) void gate_logits_r
                 __syncthreads();
             }
         }
+    }
+    if constexpr (GATE) {
         copy_rows(std::false_type{}, tile, nullptr, a.io.logits_inter + (size_t)t0 * n, n);
         copy_rows(std::false_type{}, tile + n, nullptr, a.io.logits_intra + (size_t)t0 * m, m);
     } else {
@@ -897,6 +913,12 @@ hipError_t launch_gate_ct(const RouteArgs &a, int blocks, size_t lds, hipStream_
     if (ct <= 2) return launch_block<NT, P, true, DT, 2>(a, blocks, lds, s);
     if constexpr (NT / P < 64)
         if (ct <= 3) return launch_block<NT, P, true, DT, 3>(a, blocks, lds, s);
+    // Blocks of 64 tokens and 49 to 144 columns of a 16-bit type (gate_wide), against the contraction split over the waves with five column tiles
+    // a pass (this kernel, us): 8300 x 768 with 49 / 80 / 129 columns 24.5 / 29.8 / 46.2 -> 17.6 / 20.7 / 23.3, 12288 x 1024 with 49 / 144
+    // 27.3 / 55.9 -> 19.8 / 30.9, 32768 x 768 with 65 / 129 37.0 / 60.2 -> 24.7 / 31.9, 65536 x 1024 with 129 121.5 -> 72.4.  A batch of one
+    // block keeps the split, which has more of its only block's loads in flight.
+    if constexpr (NT == 256 && NT / P == 64 && DT != SMILE_DTYPE_F32)
+        if (ct > 3 && ct <= kWideTiles && !a.one) return launch_block<NT, P, true, DT, kWideTiles>(a, blocks, std::max(lds, (size_t)kWideLds), s);
     return launch_block<NT, P, true, DT, 5>(a, blocks, lds, s);
 }
 

@@ -376,3 +376,36 @@ def test_gelu_of_an_overflowed_product_is_infinity(torch_cuda, tile, monkeypatch
         assert (ye[1] == d * F / 2).all()
     finally:
         ctx.close()
+
+
+# Wide routers whose logits the routing launch computes in one pass: 49 to 144 columns of a 16-bit type over blocks of 64 tokens, contractions of one chunk,
+# of odd counts and of more chunks than waves, a block that ends early; and 145 columns beside them.
+WIDE_GATE = [
+    wl.small_config("gate_49_columns", 8200, 64, 64, 17, 32, 17, "bf16", "relu", seed=381),
+    wl.small_config("gate_81_columns", 8200, 64, 64, 17, 64, 9, "bf16", "relu", seed=382),
+    wl.small_config("gate_96_columns_f16", 8230, 192, 64, 32, 64, 5, "f16", "relu", seed=383),
+    wl.small_config("gate_129_columns", 8193, 320, 64, 1, 128, 70, "bf16", "relu", seed=384),
+    wl.small_config("gate_144_columns", 8255, 448, 64, 16, 128, 6, "bf16", "relu", skew=True, seed=385, group_capacity=600),
+    wl.small_config("gate_145_columns", 8200, 128, 64, 1, 144, 60, "bf16", "relu", seed=386),
+]
+
+
+@pytest.mark.parametrize("cfg", WIDE_GATE, ids=lambda c: c.name)
+def test_wide_router_in_the_routing_launch(torch_cuda, cfg):
+    import numpy as np
+    from test_gpu_parity import _run
+    outs = {}
+    for how in ("steps", "fused"):
+        layer = _run(cfg, how)
+        try:
+            outs[how] = parity.fetch(layer)
+            if how == "fused":
+                assert not any("gate_logits_kernel" in k for k in _launched(layer, layer.forward_fused))
+            else:
+                parity.check_full(cfg, layer)
+        finally:
+            layer.close()
+    assert "logits_intra" in outs["steps"]
+    for k, v in outs["steps"].items():
+        if k not in ("xe", "ye"):
+            np.testing.assert_array_equal(outs["fused"][k], v, err_msg=k)
