@@ -416,7 +416,13 @@ hipError_t launch_typed(const TransposedGemm &g, hipStream_t s)
     TGemmArgs<E> a{static_cast<const E *>(g.x), static_cast<const E *>(g.w), static_cast<E *>(g.y),
                    static_cast<const E *>(g.aux), g.rows_valid, g.k_valid, g.Mrows, g.Nout, g.K, g.ldx, g.ldw,
                    g.sx, g.sw, g.sy, 0, 0, 0, g.N};
-    if (g.x_transposed) return launch_tile<E, 128, 128, 2, 2, true, true, 0>(a, g.N, g.tune, s);
+    if (g.x_transposed) {
+        // 192 columns a tile (whole rows of 384 bytes leave at once) where every CU still gets two and the columns pad by no more than a tenth
+        const long long tiles192 = (long long)g.N * ((g.Mrows + 127) / 128) * ((g.Nout + 191) / 192);
+        if (tiles192 >= 2 * g.tune.cus && (g.Nout + 191) / 192 * 192 * 10 <= (g.Nout + 127) / 128 * 128 * 11)
+            return launch_tile<E, 128, 192, 2, 2, true, true, 0>(a, g.N, g.tune, s);
+        return launch_tile<E, 128, 128, 2, 2, true, true, 0>(a, g.N, g.tune, s);
+    }
     if (g.post == 1) return launch_tile<E, 128, 128, 2, 2, false, true, 1>(a, g.N, g.tune, s);
     if (g.post == 2) return launch_tile<E, 128, 128, 2, 2, false, true, 2>(a, g.N, g.tune, s);
     return launch_tile<E, 128, 128, 2, 2, false, true, 0>(a, g.N, g.tune, s);
@@ -440,7 +446,10 @@ hipError_t launch_grouped_gemm_t(int dtype, const TransposedGemm &g, hipStream_t
     // 43 x 10, 192 x 768: dpre 6.6 and 7.3; but 27 x 11, 128 x 512: dxe, eight slabs, 7.6 and 7.1; 7 x 600, 320 x 1280: dpre 16.3 and 12.1.
     // Training step of 16 x 108 rows, 256 x 512: 73.8, all on the ring 75.1).
     const long long tiles = (long long)g.N * ((g.Mrows + 127) / 128) * ((g.Nout + 127) / 128);
-    const bool small = g.x_transposed ? g.K <= 128 && tiles <= 2 * g.tune.cus
+    // It also keeps all weight gradients of one slab (buffers of at most 64 rows): those are bound by their stores, which leave here in whole
+    // rows of a tile and there in runs of 64 and 128 bytes (128 experts x 2 rows, 1536 x 6144, dW2 and dW1: 473 and 468 us here, 5.1 TB/s, 566
+    // and 562 on the ring).
+    const bool small = g.x_transposed ? g.K <= BK || (g.K <= 128 && tiles <= 2 * g.tune.cus)
                                       : (g.Mrows <= 64 && g.K < 512 && tiles <= 2 * g.tune.cus) || (g.K <= 256 && tiles <= g.tune.cus);
     if ((g.tune.tgemm_tile > 0 || (g.tune.tgemm_tile < 0 && !small)) && g.Nout % 64 == 0 && ring_applies(a, g.Mrows, g.x_transposed, true)) {
         const int rows = g.tokens > 0 && g.rows_valid ? (g.tokens + g.N - 1) / g.N : g.Mrows;

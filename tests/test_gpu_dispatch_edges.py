@@ -409,3 +409,24 @@ def test_wide_router_in_the_routing_launch(torch_cuda, cfg):
     for k, v in outs["steps"].items():
         if k not in ("xe", "ye"):
             np.testing.assert_array_equal(outs["fused"][k], v, err_msg=k)
+
+
+def test_weight_gradients_of_one_slab(torch_cuda, monkeypatch):
+    """Buffers of at most 64 rows and two 192-column tiles per CU: the two-stage kernel, with the bits of the ring."""
+    from paper_2212_05191_amd.runner import GpuLayer
+    cfg = wl.small_config("one_slab_130_experts", 900, 256, 384, 13, 10, 9, "bf16", "relu", skew=True, seed=391)
+    dy, got = wl.gen_output_grad(cfg), {}
+    for tile in ("", "1"):
+        monkeypatch.setenv("SMILE_TGEMM_TILE", tile) if tile else monkeypatch.delenv("SMILE_TGEMM_TILE", raising=False)
+        layer = GpuLayer(cfg)
+        try:
+            layer.enable_saved_activations()
+            layer.forward()
+            layer.prepare_backward(dy)
+            layer.backward()
+            torch_cuda.cuda.synchronize()
+            got[tile] = [getattr(layer.bwd, k).cpu() for k in ("dw1", "dw2")]
+        finally:
+            layer.close()
+    assert all(torch_cuda.equal(a, b) for a, b in zip(got[""], got["1"]))
+    assert all(float(a.float().abs().sum()) > 0 for a in got[""])
