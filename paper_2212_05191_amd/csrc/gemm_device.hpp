@@ -3,6 +3,8 @@
 // the LDS bank swizzle.
 #pragma once
 
+#include <cfloat>
+
 #include "smile_internal.hpp"
 
 namespace smile {
@@ -49,7 +51,9 @@ __device__ __forceinline__ float activate(float v)
         // the tail keeps its relative accuracy as far as bf16 has values: 0.5 % at v = -6.5, 2 % at -10, 4 % at -13.  2^P(|v|) with one
         // polynomial P of degree 8 is one transcendental less (128 experts x 256 rows, 768 -> 3072: 492.7 -> 487.2 us a pass, the
         // base layer 122.6 -> 122.5), but is off by 10 % at -8 and by 90 % at -10.
-        // The factor in front is kept finite: a product that overflowed to infinity stays infinity (infinity * 0 would be NaN).
+        // A product that overflowed to infinity counts as the largest finite value, which rounds to infinity in 16 bits (infinity
+        // times the tail's 0 would be NaN).  Medians instead of fmaxf and fminf, which the compiler gives a second instruction each
+        // to quieten a signalling NaN: the clamp costs nothing over the plain form.
         const float av = fabsf(v);
         const float t = __builtin_amdgcn_rcpf(fmaf(0.3275911f * 0.70710678118654752f, av, 1.0f));
         float poly = fmaf(0.5f * 1.061405429f, t, 0.5f * -1.453152027f);
@@ -57,7 +61,7 @@ __device__ __forceinline__ float activate(float v)
         poly = fmaf(poly, t, 0.5f * -0.284496736f);
         poly = fmaf(poly, t, 0.5f * 0.254829592f);
         const float ex = __builtin_amdgcn_exp2f(v * v * (-0.5f * 1.4426950408889634f));
-        return fmaxf(v, 0.f) - fminf(av, 0x1p127f) * (poly * t * ex);
+        return __builtin_amdgcn_fmed3f(v, 0.f, FLT_MAX) - __builtin_amdgcn_fmed3f(av, 0.f, FLT_MAX) * (poly * t * ex);
     } else return v;
 }
 
