@@ -1,6 +1,9 @@
 // Forward expert GEMMs on the ring kernel (gemm_ring.hpp): both operands K-contiguous.
 #include "gemm_ring.hpp"
 
+#include <algorithm>
+#include <cmath>
+
 namespace smile {
 
 namespace {
@@ -39,37 +42,73 @@ bool ring_applies(const RingArgs &a, long long x_rows, bool x_transposed, bool w
     return (x_transposed || a.K >= 192) && x < limit && w < limit;
 }
 
-// Tile shapes, measured on the forward passes and training steps of the bf16 workloads (us per pass, the other GEMMs unchanged) and on
-// small training steps (us per kernel):
+// Tile shapes.  With tiles for many rounds of the chip, measured on the forward passes and training steps of the bf16 workloads (us per pass,
+// the other GEMMs unchanged):
 //   * short contractions (Nout >= K: up-projection, dpre) and the weight gradients: 128 x 192, two on a CU, so that one tile's epilogue
 //     overlaps the other's contraction (up, 64 experts 1024 -> 4096: 443; 128 x 256 alone on a CU 457, 256 x 192 506; dW of
 //     1600 x 6400: 1611 against 1666 and 1643).  Outputs that 192-wide tiles would pad by more than a quarter over 128-wide ones (up to
-//     128, 193 .. 256 columns, ...): 128 x 128.  So too where that leaves the chip few enough tiles: weight gradients with one per CU at
-//     most (7 experts x 600 rows, 320 x 1280: 10.6 against 12.3; 11 x 251, 576 x 1728, three per CU: 12.0 against 10.4), others
-//     with at most two, if 128 x 192 are at most one per CU and rows fill more than half of them (dpre of the two: 12.1 against 15.8, 14.4
-//     against 17.8; 8 x 36 rows, 1152 x 4608: 21.2 against 18.5).
-//   * long contractions, at most one 128 x 128 tile per CU: that (dxe of the three: 13.7 against 17.1 in 128 x 192, 17.2 against
-//     20.9, 34.8 against 39.5); at most one 128 x 192: that (down, 16 experts x 512 rows, 3072 -> 768: 101; 128 x 256 102, 256 x 192 113; dxe
-//     397, 128 x 128 409; down, 15 experts x 334 rows, 3840 -> 960: 125 against 134 and 134).
-//   * else, where 192-wide tiles pad by more than a tenth (1024 columns): 128 x 128 forward (64 experts x 256 rows, 4096 -> 1024: 437; 128 x 256
-//     443, 128 x 192 449), 128 x 256 for dxe, whose transposed operand makes narrow tiles dearer (256 skewed experts: 3514 against 3531).
+//     128, 193 .. 256 columns, ...): 128 x 128;
+//   * long contractions where 192-wide tiles pad by more than a tenth (1024 columns): 128 x 128 forward (64 experts x 256 rows,
+//     4096 -> 1024: 437; 128 x 256 443, 128 x 192 449), 128 x 256 for dxe, whose transposed operand makes narrow tiles dearer
+//     (256 skewed experts: 3514 against 3531), unless that pads by more than a fifth;
 //   * else 256 x 192 where buffers are expected to be full, so that one tile takes all rows of an expert and its weights cross L2 once
 //     (128 experts x 256 rows, 3072 -> 768: 441; 128 x 256 451, 128 x 192 455), and 128 x 256 where their fill varies and a second
 //     row tile would be nearly empty (16 experts x 512 rows in buffers of 1024, 6400 -> 1600: dxe 1486; 128 x 192 1507, 256 x 192 1511).
-// `rows`: tokens per group if they spread evenly; with room in the buffers half a tile more is counted.
+// With few rounds the last one decides: a shape is taken that needs less than eight ninths of the time of the one above by the estimate
+// rounds x time of a round.  The weights are the ratios of such times over 800 products of 4 to 256 experts, 8 to 2700 rows,
+// 128 x 512 to 1600 x 6400 (us per kernel): down, 16 experts x 144 rows, 6400 -> 1600: 224 tiles of 128 x 256 117, 288 of 128 x 192
+// 154; dxe, 64 x 240, 1280 -> 320: 384 of 128 x 128 25, 256 of 128 x 256, which pad by a third, 44; dpre, 16 x 128, 1024 -> 4096: one round of 512
+// tiles of 128 x 128 37, 352 of 128 x 192 46; up, 64 x 96, 256 -> 1024: 16.4 and 19.7.
+// `rows`: tokens per group if they spread evenly.
+namespace {
+
+struct RingShape {
+    int rows, cols, per_cu;   // tile, workgroups on a CU
+    double weight;            // time of a round
+};
+constexpr RingShape kShapes[kRingTiles] = {{128, 192, 2, 1.375}, {128, 256, 1, 1.0}, {256, 192, 1, 1.25}, {128, 128, 2, 1.0}};
+
+// Row tiles of a group that get `rows` tokens on the average of a random assignment: one, and one more for each boundary that a group's count,
+// spread by its square root, passes
+double expected_row_tiles(const RingArgs &a, int rows, int tile_rows)
+{
+    if (rows >= a.Mrows) return (a.Mrows + tile_rows - 1) / tile_rows;
+    const double spread = 2.0 * std::sqrt((double)rows);
+    const long long sure = std::max(0ll, (long long)std::floor((rows - spread) / tile_rows));   // boundaries that every group passes
+    double n = 1.0 + sure;
+    for (long long edge = (sure + 1) * tile_rows; edge < a.Mrows && edge < rows + spread; edge += tile_rows)
+        n += std::min(1.0, std::max(0.0, 0.5 + (rows - edge) / (2.0 * spread)));
+    return n;
+}
+
+double estimated_time(const Tuning &tune, const RingArgs &a, int rows, RingTile tile)
+{
+    const RingShape &s = kShapes[tile];
+    const double tiles = a.N * expected_row_tiles(a, rows, s.rows) * ((a.Nout + s.cols - 1) / s.cols);
+    const double rounds = tiles / ((double)tune.cus * s.per_cu);
+    // one workgroup of two on every CU: little more than half; beyond a few rounds workgroups are out of step and share the rest
+    if (s.per_cu == 2 && rounds <= 0.5) return s.weight * 0.55;
+    return s.weight * (rounds <= (s.per_cu == 2 ? 2.0 : 3.0) ? std::max(1.0, std::ceil(rounds - 0.03)) : rounds + 0.25);
+}
+
+}  // namespace
+
 RingTile pick_ring_tile(const Tuning &tune, const RingArgs &a, int rows, bool gradient)
 {
-    auto padded = [&](int width) { return (a.Nout + width - 1) / width * width; };
-    const double row_tiles = rows >= a.Mrows ? (a.Mrows + 127) / 128 : rows / 128.0 + 0.5;
-    const double tiles128 = a.N * row_tiles * (padded(128) / 128), tiles192 = a.N * row_tiles * (padded(192) / 192);
-    if (a.Nout >= a.K || a.k_valid) {
-        const bool few = a.k_valid ? tiles128 <= tune.cus : tiles192 <= tune.cus && tiles128 <= 2 * tune.cus && a.Mrows > 64;
-        return few || padded(192) * 4 > padded(128) * 5 ? kRing128x128x2 : kRing128x192x2;
+    auto padded = [&](int width) { return ((long long)a.Nout + width - 1) / width * width; };
+    const bool is_short = a.Nout >= a.K || a.k_valid;
+    RingTile best;
+    if (is_short) best = padded(192) * 4 > padded(128) * 5 ? kRing128x128x2 : kRing128x192x2;
+    else if (padded(192) * 10 > padded(128) * 11)
+        best = gradient && padded(256) * 10 <= padded(128) * 12 ? kRing128x256 : kRing128x128x2;
+    else best = rows >= a.Mrows && a.Mrows > 128 ? kRing256x192 : kRing128x256;
+    double time = estimated_time(tune, a, rows, best) / 1.125;
+    for (const RingTile t : {kRing128x128x2, kRing128x192x2, kRing128x256}) {
+        if (is_short && t == kRing128x256) continue;
+        const double other = estimated_time(tune, a, rows, t);
+        if (other < time) time = other, best = t;
     }
-    if (tiles128 <= tune.cus) return kRing128x128x2;
-    if (tiles192 <= tune.cus) return kRing128x192x2;
-    if (padded(192) * 10 > padded(128) * 11) return gradient ? kRing128x256 : kRing128x128x2;
-    return rows >= a.Mrows && a.Mrows > 128 ? kRing256x192 : kRing128x256;
+    return best;
 }
 
 hipError_t launch_ring_forward(int dtype, const RingArgs &a, int act, RingTile tile, const Tuning &tune, hipStream_t s, hipEvent_t t0,

@@ -1,0 +1,59 @@
+"""The choice of a ring tile for an expert GEMM (a host function of sizes alone), on both sides of its lines.  No kernel is launched here."""
+import ctypes as C
+
+import pytest
+
+from paper_2212_05191_amd import binding as B
+
+
+class _Tuning(C.Structure):
+    _fields_ = [(k, C.c_int) for k in ("ffn_tile", "tgemm_tile", "persist", "router_grad_mfma", "cus")]
+
+
+class _RingArgs(C.Structure):
+    _fields_ = [(k, C.c_void_p) for k in ("x", "w", "y", "y2", "aux", "bias", "rows_valid", "k_valid", "x_rows", "y_rows", "y_tok", "gate")] + \
+        [(k, C.c_int) for k in ("N", "Mrows", "Nout", "K", "ldx", "ldw")] + [(k, C.c_longlong) for k in ("sx", "sw", "sy")] + \
+        [("col_tiles", C.c_int), ("backwards", C.c_bool)]
+
+
+T128X192, T128X256, T256X192, T128X128 = range(4)
+
+# experts, expected rows, rows of a buffer, d_model, d_ff
+CASES = [
+    # many rounds: what the widths and the fill of the buffers ask for
+    ("down", 128, 256, 256, 768, 3072, T256X192),      # full buffers of two row tiles
+    ("down", 128, 200, 256, 768, 3072, T128X256),      # room in them
+    ("dxe", 128, 256, 256, 768, 3072, T256X192),
+    ("down", 64, 256, 320, 1024, 4096, T128X128),      # 192-wide tiles pad 1024 columns by an eighth
+    ("dxe", 200, 250, 256, 1024, 4096, T128X256),
+    ("up", 64, 256, 320, 1024, 4096, T128X192),
+    ("dpre", 16, 512, 1024, 1600, 6400, T128X192),
+    ("up", 300, 200, 200, 64, 256, T128X128),          # 384 columns of tiles for 256
+    ("dW", 64, 200, 256, 768, 3072, T128X192),
+    # few rounds: the last one decides
+    ("down", 16, 512, 512, 768, 3072, T128X192),       # one 128 x 192 tile per CU
+    ("dxe", 16, 512, 1024, 1600, 6400, T128X256),      # two rounds of 128 x 256, more than one of the others
+    ("down", 16, 144, 216, 1600, 6400, T128X256),      # nearly every expert has two row tiles: 224 of 256 columns, 288 of 192
+    ("dxe", 64, 240, 300, 320, 1280, T128X128),        # 384 of 128 columns in one round; 256 columns would pad 320 to 512
+    ("dxe", 64, 300, 600, 384, 1152, T128X192),        # three row tiles: 384 of 192 columns in one round, 576 of 128 in two
+    ("dpre", 16, 128, 128, 1024, 4096, T128X128),      # 512: one round of two on a CU
+    ("up", 64, 96, 120, 256, 1024, T128X128),
+    ("up", 70, 96, 120, 256, 1024, T128X192),          # 560: a second round
+    ("dW", 4, 128, 256, 256, 1024, T128X128),
+    # the smallest and the largest sizes that the estimate meets
+    ("down", 1, 1, 128, 192, 256, T128X128),
+    ("up", 4096, 1, 65, 64, 4096, T128X192),
+    ("up", 1, 2**31 - 1, 2**31 - 1, 64, 256, T128X128),
+    ("down", 1, 2**30, 2**31 - 1, 192, 2048, T128X192),
+]
+
+
+@pytest.mark.parametrize("product,N,rows,cap,d,F,want", CASES, ids=lambda v: str(v))
+def test_ring_tile(product, N, rows, cap, d, F, want):
+    pick = B.load()._ZN5smile14pick_ring_tileERKNS_6TuningERKNS_8RingArgsEib
+    pick.restype, pick.argtypes = C.c_int, [C.c_void_p, C.c_void_p, C.c_int, C.c_bool]
+    mrows, nout, k = {"up": (cap, F, d), "down": (cap, d, F), "dpre": (cap, F, d), "dxe": (cap, d, F), "dW": (d, F, cap)}[product]
+    a = _RingArgs(N=N, Mrows=mrows, Nout=nout, K=k, ldx=k, ldw=k, k_valid=8 if product == "dW" else None)
+    tune = _Tuning(-1, -1, -1, -1, 256)
+    got = pick(C.byref(tune), C.byref(a), min(rows, mrows) if product != "dW" else mrows, product in ("dpre", "dxe", "dW"))
+    assert got == want
