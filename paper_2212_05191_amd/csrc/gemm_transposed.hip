@@ -9,9 +9,8 @@
 // without materialising any transposed copy.  y[e][i][j] = sum_k X(i,k) W(j,k) per group e, where a
 // normal operand is stored [i][k] (k contiguous) and a transposed one [k][i] (i contiguous).
 //
-// Most of these products run on the ring kernels (gemm_ring.hpp).  The two-stage kernel below takes small ones
-// (launch_grouped_gemm_t), normal operands of fewer than three slabs, outputs whose columns are no multiple of 64 and operands whose
-// offsets need more than 32 bits.
+// Most of these products run on the ring kernels (gemm_ring.hpp).  The two-stage kernel below takes weight gradients of few rows and
+// other small products (launch_grouped_gemm_t), normal operands of fewer than three slabs and operands whose offsets need more than 32 bits.
 //
 // Design (gfx950):
 //   * global -> LDS with the direct 16-byte loads of the forward kernel, STAGES-deep ring of K slabs
@@ -32,6 +31,8 @@
 //     (no zero-padded copies, no work on empty buffer rows).
 //   * epilogue as in the forward kernel: fp32 -> bf16, staged through LDS, row-contiguous 16-byte
 //     stores; POST multiplies by act'(aux) there (the gradient at the pre-activation).
+#include <algorithm>
+#include <climits>
 #include <type_traits>
 
 #include "gemm_device.hpp"
@@ -410,17 +411,15 @@ hipError_t launch_tile(TGemmArgs<E> a, int N, const Tuning &tune, hipStream_t s)
     return hipGetLastError();
 }
 
+// wide: 192 columns a tile (weight gradients only)
 template <typename E>
-hipError_t launch_typed(const TransposedGemm &g, hipStream_t s)
+hipError_t launch_typed(const TransposedGemm &g, bool wide, hipStream_t s)
 {
     TGemmArgs<E> a{static_cast<const E *>(g.x), static_cast<const E *>(g.w), static_cast<E *>(g.y),
                    static_cast<const E *>(g.aux), g.rows_valid, g.k_valid, g.Mrows, g.Nout, g.K, g.ldx, g.ldw,
                    g.sx, g.sw, g.sy, 0, 0, 0, g.N};
     if (g.x_transposed) {
-        // 192 columns a tile (whole rows of 384 bytes leave at once) where every CU still gets two and the columns pad by no more than a tenth
-        const long long tiles192 = (long long)g.N * ((g.Mrows + 127) / 128) * ((g.Nout + 191) / 192);
-        if (tiles192 >= 2 * g.tune.cus && (g.Nout + 191) / 192 * 192 * 10 <= (g.Nout + 127) / 128 * 128 * 11)
-            return launch_tile<E, 128, 192, 2, 2, true, true, 0>(a, g.N, g.tune, s);
+        if (wide) return launch_tile<E, 128, 192, 2, 2, true, true, 0>(a, g.N, g.tune, s);
         return launch_tile<E, 128, 128, 2, 2, true, true, 0>(a, g.N, g.tune, s);
     }
     if (g.post == 1) return launch_tile<E, 128, 128, 2, 2, false, true, 1>(a, g.N, g.tune, s);
@@ -433,31 +432,34 @@ hipError_t launch_typed(const TransposedGemm &g, hipStream_t s)
 hipError_t launch_grouped_gemm_t(int dtype, const TransposedGemm &g, hipStream_t s)
 {
     if (!is_half(dtype)) return hipErrorInvalidValue;
-    if (g.K < 1 || g.Mrows < 1 || g.Nout % 8 || g.ldx % 8 || g.ldw % 8) return hipErrorInvalidValue;
+    if (g.K < 1 || g.Mrows < 1 || g.Nout % 64 || g.ldx % 8 || g.ldw % 8) return hipErrorInvalidValue;
     if (!g.x_transposed && g.K % BK) return hipErrorInvalidValue;   // a normal operand is read in whole 64-k slabs
     if (!g.w_transposed) return hipErrorInvalidValue;               // not needed by any caller
     if (g.x_transposed && (g.Mrows % 8 || g.post)) return hipErrorInvalidValue;
     RingArgs a{};
     a.x = g.x, a.w = g.w, a.y = g.y, a.aux = g.aux, a.rows_valid = g.rows_valid, a.k_valid = g.k_valid, a.N = g.N, a.Mrows = g.Mrows;
     a.Nout = g.Nout, a.K = g.K, a.ldx = g.ldx, a.ldw = g.ldw, a.sx = g.sx, a.sw = g.sw, a.sy = g.sy;
-    // The two-stage kernel, whose plain grid needs no walk, keeps what is over before a ring pays: at most two tiles per CU with one or
-    // two slabs of rows to contract (weight gradients), or with rows for half a tile and less than eight slabs, and at most one tile per CU with
-    // four slabs (us per kernel: 111 experts x 4 rows, 128 x 384: dW 5.0, ring 6.0, dxe 6.2 and 6.5; 84 x 18, 64 x 192: dW 4.4 and 5.0;
-    // 43 x 10, 192 x 768: dpre 6.6 and 7.3; but 27 x 11, 128 x 512: dxe, eight slabs, 7.6 and 7.1; 7 x 600, 320 x 1280: dpre 16.3 and 12.1.
-    // Training step of 16 x 108 rows, 256 x 512: 73.8, all on the ring 75.1).
+    const int expected = g.tokens > 0 ? (g.tokens + g.N - 1) / g.N : INT_MAX;   // rows per group if the tokens spread evenly
+    const RingTile tile = g.tune.tgemm_tile > 0 ? RingTile(g.tune.tgemm_tile - 1)
+                                                : pick_ring_tile(g.tune, a, std::min(g.rows_valid ? expected : INT_MAX, g.Mrows), true);
+    const bool wide = g.x_transposed && tile == kRing128x192x2;
+    // The two-stage kernel keeps what is over before a ring pays.
+    //   * Weight gradients of few rows, by the rows a group is expected to contract and not by its buffer: they are bound by their
+    //     stores, which leave here in whole rows of a tile and from the ring in runs of 64 and 128 bytes.  Up to 320 rows where the
+    //     tiles are 128 wide, 192 where they are 192 wide.  us, both kernels in the width they take, dW2: 96 experts x 80 rows in
+    //     buffers of 80, 1024 x 4096 283, ring 313; 64 x 96 in 144, 768 x 3072 114 and 133; 48 x 96 in 144, 1600 x 6400 340 and 381;
+    //     64 x 176, 768 x 3072 142 and 140; 64 x 208, 1024 x 4096 274 and 269; 64 x 300 309 and 294; 128 wide: 64 x 180,
+    //     256 x 1024 14.2 and 15.0; 21 x 240, 192 x 576 7.4 and 8.5; 64 x 800, 256 x 1024 47 and 46.
+    //   * Other products with rows for half a tile, less than eight slabs and at most two tiles per CU, or four slabs and at most one
+    //     tile per CU, where the plain grid needs no walk (us: 111 experts x 4 rows, 128 x 384: dxe 6.2, ring 6.5; 43 x 10, 192 x 768:
+    //     dpre 6.6 and 7.3; but 27 x 11, 128 x 512: dxe, eight slabs, 7.6 and 7.1; 7 x 600, 320 x 1280: dpre 16.3 and 12.1).
     const long long tiles = (long long)g.N * ((g.Mrows + 127) / 128) * ((g.Nout + 127) / 128);
-    // It also keeps all weight gradients of one slab (buffers of at most 64 rows): those are bound by their stores, which leave here in whole
-    // rows of a tile and there in runs of 64 and 128 bytes (128 experts x 2 rows, 1536 x 6144, dW2 and dW1: 473 and 468 us here, 5.1 TB/s, 566
-    // and 562 on the ring).
-    const bool small = g.x_transposed ? g.K <= BK || (g.K <= 128 && tiles <= 2 * g.tune.cus)
+    const bool small = g.x_transposed ? std::min(g.k_valid ? expected : INT_MAX, g.K) <= (wide ? 192 : 320)
                                       : (g.Mrows <= 64 && g.K < 512 && tiles <= 2 * g.tune.cus) || (g.K <= 256 && tiles <= g.tune.cus);
-    if ((g.tune.tgemm_tile > 0 || (g.tune.tgemm_tile < 0 && !small)) && g.Nout % 64 == 0 && ring_applies(a, g.Mrows, g.x_transposed, true)) {
-        const int rows = g.tokens > 0 && g.rows_valid ? (g.tokens + g.N - 1) / g.N : g.Mrows;
-        const RingTile tile = g.tune.tgemm_tile > 0 ? RingTile(g.tune.tgemm_tile - 1) : pick_ring_tile(g.tune, a, rows < g.Mrows ? rows : g.Mrows, true);
+    if ((g.tune.tgemm_tile > 0 || (g.tune.tgemm_tile < 0 && !small)) && ring_applies(a, g.Mrows, g.x_transposed, true))
         return launch_ring_gradient(dtype, a, g.x_transposed, g.post, tile, g.tune, s);
-    }
-    if (dtype == SMILE_DTYPE_BF16) return launch_typed<__bf16>(g, s);
-    return launch_typed<_Float16>(g, s);
+    if (dtype == SMILE_DTYPE_BF16) return launch_typed<__bf16>(g, wide, s);
+    return launch_typed<_Float16>(g, wide, s);
 }
 
 }  // namespace smile

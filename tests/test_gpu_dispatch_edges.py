@@ -436,22 +436,49 @@ def test_wide_router_in_the_routing_launch(torch_cuda, cfg):
             np.testing.assert_array_equal(outs["fused"][k], v, err_msg=k)
 
 
+def _weight_gradients(torch_cuda, cfg, tile, monkeypatch):
+    """dW1, dW2 and the names of the backward pass's expert GEMMs with SMILE_TGEMM_TILE = tile ("": the library's choice)"""
+    from paper_2212_05191_amd.runner import GpuLayer
+    monkeypatch.setenv("SMILE_TGEMM_TILE", tile) if tile else monkeypatch.delenv("SMILE_TGEMM_TILE", raising=False)
+    layer = GpuLayer(cfg)
+    try:
+        layer.enable_saved_activations()
+        layer.forward()
+        layer.prepare_backward(wl.gen_output_grad(cfg))
+        names = [k for k in _launched(layer, layer.backward) if "grouped_gemm" in k]
+        return [getattr(layer.bwd, k).cpu() for k in ("dw1", "dw2")], names
+    finally:
+        layer.close()
+
+
 def test_weight_gradients_of_one_slab(torch_cuda, monkeypatch):
     """Buffers of at most 64 rows and two 192-column tiles per CU: the two-stage kernel, with the bits of the ring."""
-    from paper_2212_05191_amd.runner import GpuLayer
     cfg = wl.small_config("one_slab_130_experts", 900, 256, 384, 13, 10, 9, "bf16", "relu", skew=True, seed=391)
-    dy, got = wl.gen_output_grad(cfg), {}
-    for tile in ("", "1"):
-        monkeypatch.setenv("SMILE_TGEMM_TILE", tile) if tile else monkeypatch.delenv("SMILE_TGEMM_TILE", raising=False)
-        layer = GpuLayer(cfg)
-        try:
-            layer.enable_saved_activations()
-            layer.forward()
-            layer.prepare_backward(dy)
-            layer.backward()
-            torch_cuda.cuda.synchronize()
-            got[tile] = [getattr(layer.bwd, k).cpu() for k in ("dw1", "dw2")]
-        finally:
-            layer.close()
-    assert all(torch_cuda.equal(a, b) for a, b in zip(got[""], got["1"]))
-    assert all(float(a.float().abs().sum()) > 0 for a in got[""])
+    got, names = _weight_gradients(torch_cuda, cfg, "", monkeypatch)
+    assert sum("grouped_gemm_t_kernel" in k for k in names) >= 2, names
+    ring, names = _weight_gradients(torch_cuda, cfg, "1", monkeypatch)
+    assert sum("grouped_gemm_ring" in k for k in names) == 4, names
+    assert all(torch_cuda.equal(a, b) for a, b in zip(got, ring))
+    assert all(float(a.float().abs().sum()) > 0 for a in got)
+
+
+# Weight gradients: the rows that a group is expected to contract decide, not its buffer.  192- and 128-wide tiles, both sides of their lines
+# and a quarter full buffers; kernels of the two-stage form among the four products (dpre of 256 -> 1024 is one, too).
+DW_ROUTES = [
+    (wl.small_config("dw_192_wide_192_rows", 9 * 192, 384, 1536, 3, 3, 260, "bf16", "relu", skew=True, seed=392), 2),
+    (wl.small_config("dw_192_wide_193_rows", 9 * 192 + 1, 384, 1536, 3, 3, 260, "bf16", "relu", skew=True, seed=393), 0),
+    (wl.small_config("dw_192_wide_70_of_270", 9 * 70, 384, 1536, 3, 3, 270, "f16", "relu", skew=True, seed=394), 2),
+    (wl.small_config("dw_128_wide_320_rows", 4 * 320, 256, 1024, 2, 2, 400, "bf16", "relu", skew=True, seed=395), 3),
+    (wl.small_config("dw_128_wide_321_rows", 4 * 320 + 1, 256, 1024, 2, 2, 400, "bf16", "relu", skew=True, seed=396), 1),
+]
+
+
+@pytest.mark.parametrize("cfg,two_stage", DW_ROUTES, ids=lambda c: getattr(c, "name", str(c)))
+def test_weight_gradients_by_expected_rows(torch_cuda, cfg, two_stage, monkeypatch):
+    got, names = _weight_gradients(torch_cuda, cfg, "", monkeypatch)
+    assert sum("grouped_gemm_t_kernel" in k for k in names) == two_stage and len(names) == 4, names
+    for tile, want in (("0", 0), ("1", 4), ("4", 4)):
+        other, names = _weight_gradients(torch_cuda, cfg, tile, monkeypatch)
+        assert sum("grouped_gemm_ring" in k for k in names) == want, names
+        assert all(torch_cuda.equal(a, b) for a, b in zip(got, other)), tile
+    assert all(float(a.float().abs().sum()) > 0 for a in got)
