@@ -54,11 +54,11 @@ bool ring_applies(const RingArgs &a, long long x_rows, bool x_transposed, bool w
 //   * else 256 x 192 where buffers are expected to be full, so that one tile takes all rows of an expert and its weights cross L2 once
 //     (128 experts x 256 rows, 3072 -> 768: 441; 128 x 256 451, 128 x 192 455), and 128 x 256 where their fill varies and a second
 //     row tile would be nearly empty (16 experts x 512 rows in buffers of 1024, 6400 -> 1600: dxe 1486; 128 x 192 1507, 256 x 192 1511).
-// With few rounds the last one decides: a shape is taken that needs less than eight ninths of the time of the one above by the estimate
-// rounds x time of a round.  The weights are the ratios of such times over 800 products of 4 to 256 experts, 8 to 2700 rows,
-// 128 x 512 to 1600 x 6400 (us per kernel): down, 16 experts x 144 rows, 6400 -> 1600: 224 tiles of 128 x 256 117, 288 of 128 x 192
-// 154; dxe, 64 x 240, 1280 -> 320: 384 of 128 x 128 25, 256 of 128 x 256, which pad by a third, 44; dpre, 16 x 128, 1024 -> 4096: one round of 512
-// tiles of 128 x 128 37, 352 of 128 x 192 46; up, 64 x 96, 256 -> 1024: 16.4 and 19.7.
+// Up to three rounds the last one decides: another shape is taken where this one needs 15 % longer by the estimate rounds x time of a
+// round, whose weights are what a CU multiplies in a round.  Measured on 800 products of 4 to 256 experts, 8 to 2700 rows, 128 x 512 to
+// 1600 x 6400 (us per kernel): down, 16 experts x 144 rows, 6400 -> 1600: 224 tiles of 128 x 256 117, 288 of 128 x 192 154; 21 x 144: 360
+// of 128 x 192 in one round 166, 281 of 128 x 256 in two 214; dxe, 64 x 240, 1280 -> 320: 384 of 128 x 128 25, 256 of 128 x 256, which pad by a
+// third, 44; dpre, 16 x 128, 1024 -> 4096: one round of 512 of 128 x 128 37, 352 of 128 x 192 46; up, 64 x 96, 256 -> 1024: 16.4 and 19.7.
 // `rows`: tokens per group if they spread evenly.
 namespace {
 
@@ -66,29 +66,40 @@ struct RingShape {
     int rows, cols, per_cu;   // tile, workgroups on a CU
     double weight;            // time of a round
 };
-constexpr RingShape kShapes[kRingTiles] = {{128, 192, 2, 1.375}, {128, 256, 1, 1.0}, {256, 192, 1, 1.25}, {128, 128, 2, 1.0}};
+constexpr RingShape kShapes[kRingTiles] = {{128, 192, 2, 1.5}, {128, 256, 1, 1.0}, {256, 192, 1, 1.25}, {128, 128, 2, 1.0}};
 
-// Row tiles of a group that get `rows` tokens on the average of a random assignment: one, and one more for each boundary that a group's count,
-// spread by its square root, passes
+// Row tiles of a group on the average of a random assignment of `rows` tokens to each: one, and one more for every boundary between tiles,
+// weighted with the chance (normal with the variance `rows`) that the group's count passes it
 double expected_row_tiles(const RingArgs &a, int rows, int tile_rows)
 {
-    if (rows >= a.Mrows) return (a.Mrows + tile_rows - 1) / tile_rows;
-    const double spread = 2.0 * std::sqrt((double)rows);
-    const long long sure = std::max(0ll, (long long)std::floor((rows - spread) / tile_rows));   // boundaries that every group passes
+    if (rows >= a.Mrows) return (double)(((long long)a.Mrows + tile_rows - 1) / tile_rows);
+    const double sd = std::sqrt((double)rows);
+    const long long sure = std::max(0ll, (long long)std::floor((rows - 4.0 * sd) / tile_rows));   // boundaries that every group passes
     double n = 1.0 + sure;
-    for (long long edge = (sure + 1) * tile_rows; edge < a.Mrows && edge < rows + spread; edge += tile_rows)
-        n += std::min(1.0, std::max(0.0, 0.5 + (rows - edge) / (2.0 * spread)));
+    for (long long edge = (sure + 1) * tile_rows; edge < a.Mrows && edge < rows + 4.0 * sd; edge += tile_rows)
+        n += 0.5 * std::erfc((edge - rows) / (sd * std::sqrt(2.0)));
     return n;
+}
+
+double rounds(const Tuning &tune, const RingArgs &a, int rows, RingTile tile)
+{
+    const RingShape &s = kShapes[tile];
+    return a.N * expected_row_tiles(a, rows, s.rows) * ((a.Nout + s.cols - 1) / s.cols) / ((double)tune.cus * s.per_cu);
 }
 
 double estimated_time(const Tuning &tune, const RingArgs &a, int rows, RingTile tile)
 {
-    const RingShape &s = kShapes[tile];
-    const double tiles = a.N * expected_row_tiles(a, rows, s.rows) * ((a.Nout + s.cols - 1) / s.cols);
-    const double rounds = tiles / ((double)tune.cus * s.per_cu);
-    // one workgroup of two on every CU: little more than half; beyond a few rounds workgroups are out of step and share the rest
-    if (s.per_cu == 2 && rounds <= 0.5) return s.weight * 0.55;
-    return s.weight * (rounds <= (s.per_cu == 2 ? 2.0 : 3.0) ? std::max(1.0, std::ceil(rounds - 0.03)) : rounds + 0.25);
+    const int per_cu = kShapes[tile].per_cu;
+    double n = rounds(tune, a, rows, tile);
+    if (n > (per_cu == 2 ? 2.0 : 3.0)) {
+        n += 0.25;   // by now workgroups are out of step and share the last round
+    } else if (per_cu == 2) {
+        const double tiles_of_cu = std::ceil(2.0 * n), pairs = std::floor(tiles_of_cu / 2.0);
+        n = tiles_of_cu > 2.0 * pairs ? pairs + 0.55 : pairs;   // a workgroup alone on its CU takes little more than half of two
+    } else {
+        n = std::ceil(n);
+    }
+    return kShapes[tile].weight * n;
 }
 
 }  // namespace
@@ -102,7 +113,8 @@ RingTile pick_ring_tile(const Tuning &tune, const RingArgs &a, int rows, bool gr
     else if (padded(192) * 10 > padded(128) * 11)
         best = gradient && padded(256) * 10 <= padded(128) * 12 ? kRing128x256 : kRing128x128x2;
     else best = rows >= a.Mrows && a.Mrows > 128 ? kRing256x192 : kRing128x256;
-    double time = estimated_time(tune, a, rows, best) / 1.125;
+    if (rounds(tune, a, rows, best) > 3.0) return best;
+    double time = estimated_time(tune, a, rows, best) / 1.15;
     for (const RingTile t : {kRing128x128x2, kRing128x192x2, kRing128x256}) {
         if (is_short && t == kRing128x256) continue;
         const double other = estimated_time(tune, a, rows, t);

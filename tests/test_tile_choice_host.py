@@ -38,13 +38,15 @@ CASES = [
     ("dxe", 64, 300, 600, 384, 1152, T128X192),        # three row tiles: 384 of 192 columns in one round, 576 of 128 in two
     ("dpre", 16, 128, 128, 1024, 4096, T128X128),      # 512: one round of two on a CU
     ("up", 64, 96, 120, 256, 1024, T128X128),
-    ("up", 70, 96, 120, 256, 1024, T128X192),          # 560: a second round
+    ("up", 70, 96, 120, 256, 1024, T128X192),          # 560: three tiles on some CUs; 420 of 192 columns in one round
+    ("down", 21, 144, 216, 1600, 6400, T128X192),      # one round against a second one of 128 x 256 for a tenth of the tiles
+    ("down", 64, 208, 416, 640, 1280, T128X128),
     ("dW", 4, 128, 256, 256, 1024, T128X128),
     # the smallest and the largest sizes that the estimate meets
     ("down", 1, 1, 128, 192, 256, T128X128),
     ("up", 4096, 1, 65, 64, 4096, T128X192),
     ("up", 1, 2**31 - 1, 2**31 - 1, 64, 256, T128X128),
-    ("down", 1, 2**30, 2**31 - 1, 192, 2048, T128X192),
+    ("down", 1, 2**30, 2**31 - 1, 192, 2048, T128X256),
 ]
 
 
