@@ -36,7 +36,7 @@
  *   - Floating-point inputs must be finite; NaN/Inf give unspecified results.
  *   - Tuning switches (never needed in normal use; tests and sweeps set them): smile_create and
  *     smile_create_with_workspace read the environment variables SMILE_FFN_TILE (0-9: tile shape of
- *     the forward expert GEMMs), SMILE_TGEMM_TILE (0-4: tile shape of the gradient GEMMs),
+ *     the forward expert GEMMs; 6 names none: the library's choice), SMILE_TGEMM_TILE (0-4: tile shape of the gradient GEMMs),
  *     SMILE_FFN_PERSIST (0/1: plain or persistent grid of the GEMM kernels that have both) and SMILE_ROUTER_GRAD_MFMA (0: vector-ALU
  *     router-gradient kernels) ONCE and keep the values in the ctx; no other call looks at the
  *     environment.  They change which kernel variant runs, never a result beyond rounding order.

@@ -258,7 +258,7 @@ def test_router_logits_of_very_long_rows(torch_cuda):
 
 
 # ---- expert biases.  Every 16-bit tile shape, plain and persistent, on columns that end inside a 128-, 192- and 256-wide tile (448, 320)
-# and rows that end inside a tile; fp32 too.
+# and rows that end inside a tile; fp32 too.  6 names no shape (the library's choice); the ring tiles, 1 to 4, have one grid for both values.
 def _layer_with_biases(cfg):
     import numpy as np
     from paper_2212_05191_amd.runner import GpuLayer, to_device
@@ -341,9 +341,9 @@ def test_ring_tiles_give_the_bits_of_the_two_stage_kernels(torch_cuda, cfg, monk
             layer.enable_saved_activations()
             layer.forward()
             layer.prepare_backward(dy)
-            layer.backward()
-            names = _launched(layer, layer.forward_fused)
-            assert sum("grouped_gemm_ring" in k for k in names) == (2 if tile else 0), names
+            for call, count in ((layer.backward, 4), (layer.forward_fused, 2)):
+                names = _launched(layer, call)
+                assert sum("grouped_gemm_ring" in k for k in names) == (count if tile else 0), names
             kept = layer.buf.kept_count.cpu()
             live = torch_cuda.arange(cfg.capacity)[None, :] < kept[:, None]
             got = {k: getattr(layer.buf, k).cpu() for k in ("y",)} | {k: getattr(layer.bwd, k).cpu() for k in ("dx", "dw1", "dw2")}
@@ -356,6 +356,57 @@ def test_ring_tiles_give_the_bits_of_the_two_stage_kernels(torch_cuda, cfg, monk
                 assert kept.min() < 64 and kept.max() == cfg.capacity
         for k, v in got.items():
             assert torch_cuda.equal(v, want[k]), f"tile {tile} {k}: {(v != want[k]).sum()} of {v.numel()} differ"
+
+
+# Several tiles per workgroup: what a ring kernel requests of the next tile before the epilogue of this one, and the tile that it then starts
+# on.  70 skewed experts (routing biases scaled so that some stay empty and most do not) give one or two row tiles and (weight gradients)
+# contractions of none to three slabs side by side; narrow one way, so that every product is wide in one of the two: up, dpre and dW2 or down,
+# dxe and dW1 have more tiles than the chip's 256 CUs hold workgroups.
+HAND_OVER = [
+    (wl.small_config("hand_over_192_to_2048", 9000, 192, 2048, 10, 7, 150, "bf16", "gelu", skew=True, seed=397), 0.45),
+    (wl.small_config("hand_over_2048_to_256_f16", 9000, 2048, 256, 10, 7, 150, "f16", "relu", skew=True, seed=398), 1.4),
+]
+
+
+@pytest.mark.parametrize("cfg,skew", HAND_OVER, ids=lambda c: getattr(c, "name", ""))
+def test_ring_tiles_one_after_the_other(torch_cuda, cfg, skew, monkeypatch):
+    import numpy as np
+    monkeypatch.setenv("SMILE_FFN_PERSIST", "0")   # two-stage kernels: one tile per workgroup
+    layer, _, _ = _layer_with_biases(cfg)
+    try:
+        layer.bias_inter.mul_(skew), layer.bias_intra.mul_(skew)
+        layer.enable_saved_activations()
+        layer.prepare_backward(wl.gen_output_grad(cfg))
+        want = None
+        for tile in range(5):   # 0: two-stage
+            monkeypatch.setenv("SMILE_FFN_TILE", str(tile))
+            monkeypatch.setenv("SMILE_TGEMM_TILE", str(tile))
+            layer.ctx.close()
+            layer.ctx = B.Ctx(layer.desc)
+            for t in (layer.buf.y, layer.buf.ye, layer.h_save, layer.pre_save, layer.bwd.dw1, layer.bwd.dw2, layer.bwd.dx):
+                t.fill_(-7)
+            got = {}
+            for call, count in ((layer.forward_fused, 2), (layer.forward, 2), (layer.backward, 4)):
+                names = _launched(layer, call)
+                assert sum("grouped_gemm_ring" in k for k in names) == (count if tile else 0), names
+                if call == layer.forward_fused:
+                    got |= {"y_fused": layer.buf.y.cpu()}
+                    layer.buf.y.fill_(-7)
+            kept = layer.buf.kept_count.cpu().numpy()
+            live = torch_cuda.arange(cfg.capacity)[None, :] < torch_cuda.from_numpy(kept)[:, None]
+            got |= {"y": layer.buf.y.cpu(), "ye": layer.buf.ye.cpu()[live], "h": layer.h_save.cpu()[live], "pre": layer.pre_save.cpu()[live]}
+            got |= {k: getattr(layer.bwd, k).cpu() for k in ("dx", "dw1", "dw2")}
+            if want is None:
+                want = got
+                slabs = np.unique((kept + 63) // 64)
+                assert set(slabs) == {0, 1, 2, 3}, slabs
+                # live tiles of the widest shape (128 x 256; one workgroup on a CU), which has the fewest beside its slots
+                assert (kept > 0).sum() * (max(cfg.d_model, cfg.d_ff) // 256) >= 512
+                assert all(bool((v != 0).any()) for v in got.values())
+            for k, v in got.items():
+                assert torch_cuda.equal(v, want[k]), f"tile {tile} {k}: {(v != want[k]).sum()} of {v.numel()} differ"
+    finally:
+        layer.close()
 
 
 @pytest.mark.parametrize("tile", [0, 1])
