@@ -14,7 +14,7 @@
 //
 // Two-stage kernel (bf16 or fp16 storage).  One workgroup computes a BM x BN tile
 // of one expert with v_mfma_f32_32x32x16_bf16 / _f16 and fp32 accumulators.
-//   * K is cut into slabs of BK elements.  A slab travels global -> LDS directly
+//   * K is cut into slabs of BK = 64 elements.  A slab travels global -> LDS directly
 //     (global_load_lds_dwordx4: no staging registers, no ds_write) into a ring of STAGES buffers
 //     with STAGES-1 slabs in flight.  Per slab: wait until this wave's part has landed (s_waitcnt
 //     vmcnt), one s_barrier (every wave's part landed, and every wave is done reading the buffer
@@ -58,8 +58,7 @@ namespace {
 // DUAL: the epilogue runs twice, storing act(product) to y and the bare product to y2 (the hidden
 // activation and its pre-activation from one GEMM, for the backward pass).
 // E: the 16-bit storage type (__bf16 or _Float16).
-template <typename E, int BM, int BN, int WGM, int WGN, int BK, int STAGES, int OCC, int SWZ, int ACT,
-          bool DUAL = false, bool PERSIST = false>
+template <typename E, int BM, int BN, int WGM, int WGN, int STAGES, int OCC, int ACT, bool DUAL = false, bool PERSIST = false>
 __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_nt_kernel(GemmArgs a)
 {
     typedef typename Half<E>::vec8 bf16x8;                                  // one MFMA operand: 8 elements
@@ -67,6 +66,7 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_nt_kernel(Gem
     constexpr int NW = WGM * WGN, NT = NW * 64;
     constexpr int WM = BM / WGM, WN = BN / WGN;   // wave tile
     constexpr int TM = WM / 32, TN = WN / 32;     // MFMA tiles per wave
+    constexpr int BK = 64;                        // slab depth
     constexpr int PPR = BK / 8;                   // 16-byte pieces per LDS row
     constexpr int RPI = 64 / PPR;                 // rows filled by one direct-load instruction
     constexpr int ROWS = BM + BN;                 // LDS rows per stage: token tile, then weight tile
@@ -74,7 +74,6 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_nt_kernel(Gem
     constexpr int STAGE = ROWS * PPR;             // 16-byte units per stage
     constexpr int OROWS = WGM * 32;               // output rows staged per epilogue pass
     constexpr int OSTRIDE = BN / 8 + 1;           // staged row length in 16-byte units (+1: bank spread)
-    static_assert(BK == 64 || BK == 32, "slab depth");
     static_assert(BM % (WGM * 32) == 0 && BN % (WGN * 32) == 0, "wave tile must be a multiple of 32");
     static_assert(ROWS % (RPI * NW) == 0 && BM % RPI == 0, "slab must divide into load instructions over the waves");
     static_assert(STAGES >= 2 && STAGES <= 4 && (STAGES - 2) * GPW < 64, "pipeline depth");
@@ -141,7 +140,7 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_nt_kernel(Gem
 #pragma unroll
         for (int i = 0; i < GPW; ++i) {
             const int row = (wave + i * NW) * RPI + lr;            // row of the stage
-            const int piece = lp ^ swz<BK, SWZ>(row);
+            const int piece = lp ^ swz(row);
             // rows past the end of the expert's tokens / of the weight matrix re-read the last valid one
             if (row < BM) {
                 const int xr = min(t.rt * BM + row, t.rows - 1);
@@ -164,7 +163,7 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_nt_kernel(Gem
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave % WGM, wn = wave / WGM;
     // LDS -> MFMA operands: lane reads row (lane & 31), pieces 2*kk + (lane >> 5)
-    const int frow = lane & 31, fhi = lane >> 5, fsw = swz<BK, SWZ>(lane);   // tile bases are multiples of 32
+    const int frow = lane & 31, fhi = lane >> 5, fsw = swz(lane);   // tile bases are multiples of 32
     const int xbase = (wm * WM + frow) * PPR, wbase = (BM + wn * WN + frow) * PPR;
 
     // The accumulators start at the bias: element v of a lane is column 8*(v/4) + 4*(lane/32) + v%4 of its 32x32 tile, four
@@ -365,26 +364,26 @@ void launch_timed(Kernel k, dim3 grid, dim3 block, hipStream_t s, hipEvent_t t0,
     else launch_kernel("grouped_gemm_nt_kernel", k, grid, block, 0, s, a);
 }
 
-template <typename E, int BM, int BN, int WGM, int WGN, int BK, int STAGES, int OCC = 1, int SWZ = 1>
+template <typename E, int BM, int BN, int WGM, int WGN, int STAGES, int OCC>
 hipError_t launch_half_tile(GemmArgs a, int N, int act, const Tuning &tune, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
 {
     a.row_tiles = (a.C + BM - 1) / BM;
     a.col_tiles = (a.Nout + BN - 1) / BN;
     a.tiles = N * a.row_tiles * a.col_tiles;
     a.N = N;
-    const int slots = workgroup_slots(tune, workgroups_per_cu(WGM * WGN, OCC, STAGES * (BM + BN) * BK * 2));
+    const int slots = workgroup_slots(tune, workgroups_per_cu(WGM * WGN, OCC, STAGES * (BM + BN) * 64 * 2));
     const dim3 block(WGM * WGN * 64);
     if (use_persistent_grid(tune, N, a.tiles, slots)) {
         const dim3 grid(slots);
-        if (act == 0) launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, BK, STAGES, OCC, SWZ, 0, false, true>, grid, block, s, t0, t1, a);
-        else if (act == 1) launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, BK, STAGES, OCC, SWZ, 1, false, true>, grid, block, s, t0, t1, a);
-        else launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, BK, STAGES, OCC, SWZ, 3, false, true>, grid, block, s, t0, t1, a);
+        if (act == 0) launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, STAGES, OCC, 0, false, true>, grid, block, s, t0, t1, a);
+        else if (act == 1) launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, STAGES, OCC, 1, false, true>, grid, block, s, t0, t1, a);
+        else launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, STAGES, OCC, 3, false, true>, grid, block, s, t0, t1, a);
         return hipGetLastError();
     }
     const dim3 grid((a.tiles + kXcds - 1) / kXcds * kXcds);
-    if (act == 0) launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, BK, STAGES, OCC, SWZ, 0>, grid, block, s, t0, t1, a);
-    else if (act == 1) launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, BK, STAGES, OCC, SWZ, 1>, grid, block, s, t0, t1, a);
-    else launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, BK, STAGES, OCC, SWZ, 3>, grid, block, s, t0, t1, a);
+    if (act == 0) launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, STAGES, OCC, 0>, grid, block, s, t0, t1, a);
+    else if (act == 1) launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, STAGES, OCC, 1>, grid, block, s, t0, t1, a);
+    else launch_timed(grouped_gemm_nt_kernel<E, BM, BN, WGM, WGN, STAGES, OCC, 3>, grid, block, s, t0, t1, a);
     return hipGetLastError();
 }
 
@@ -399,10 +398,10 @@ hipError_t launch_half_dual(GemmArgs a, int N, int act, const Tuning &tune, hipS
     const int slots = workgroup_slots(tune, workgroups_per_cu(4, OCC, STAGES * (BM + BN) * 64 * 2));
     const bool persist = use_persistent_grid(tune, N, a.tiles, slots);
     const dim3 grid(persist ? slots : (a.tiles + kXcds - 1) / kXcds * kXcds), block(256);
-    if (act == 1 && persist) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 1, true, true>), grid, block, 0, s, a);
-    else if (act == 1) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 1, true>), grid, block, 0, s, a);
-    else if (persist) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 3, true, true>), grid, block, 0, s, a);
-    else SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, 64, STAGES, OCC, 1, 3, true>), grid, block, 0, s, a);
+    if (act == 1 && persist) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, STAGES, OCC, 1, true, true>), grid, block, 0, s, a);
+    else if (act == 1) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, STAGES, OCC, 1, true>), grid, block, 0, s, a);
+    else if (persist) SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, STAGES, OCC, 3, true, true>), grid, block, 0, s, a);
+    else SMILE_LAUNCH((grouped_gemm_nt_kernel<E, BM, BN, 2, 2, STAGES, OCC, 3, true>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
@@ -415,7 +414,7 @@ hipError_t launch_half_dual_typed(const GemmArgs &a, int N, int act, int tile, c
     return launch_half_dual<E, 128, 192, 2, 2>(a, N, act, tune, s);
 }
 
-// Tile shapes of grouped_gemm_nt_kernel: id -> (BM, BN, waves along M, waves along N, BK, stages, waves/SIMD budget).  0 is the
+// Tile shapes of grouped_gemm_nt_kernel: id -> (BM, BN, waves along M, waves along N, stages, waves/SIMD budget).  0 is the
 // shape for contractions of one or two slabs, which the ring kernels do not take; the 64-row tiles are for few or small buffers: see
 // pick_tile.
 template <typename E>
@@ -423,11 +422,11 @@ hipError_t launch_half_typed(const GemmArgs &a, int N, int act, int tile, const 
                              hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr)
 {
     switch (tile) {
-    case 0: return launch_half_tile<E, 128, 192, 2, 2, 64, 2, 2>(a, N, act, tune, s, t0, t1);
-    case 5: return launch_half_tile<E, 64, 256, 1, 4, 64, 2, 2>(a, N, act, tune, s, t0, t1);
-    case 7: return launch_half_tile<E, 64, 64, 2, 2, 64, 4, 2>(a, N, act, tune, s, t0, t1);
-    case 8: return launch_half_tile<E, 64, 128, 2, 2, 64, 3, 2>(a, N, act, tune, s, t0, t1);
-    case 9: return launch_half_tile<E, 64, 64, 2, 2, 64, 3, 3>(a, N, act, tune, s, t0, t1);
+    case 0: return launch_half_tile<E, 128, 192, 2, 2, 2, 2>(a, N, act, tune, s, t0, t1);
+    case 5: return launch_half_tile<E, 64, 256, 1, 4, 2, 2>(a, N, act, tune, s, t0, t1);
+    case 7: return launch_half_tile<E, 64, 64, 2, 2, 4, 2>(a, N, act, tune, s, t0, t1);
+    case 8: return launch_half_tile<E, 64, 128, 2, 2, 3, 2>(a, N, act, tune, s, t0, t1);
+    case 9: return launch_half_tile<E, 64, 64, 2, 2, 3, 3>(a, N, act, tune, s, t0, t1);
     default: return hipErrorInvalidValue;
     }
 }

@@ -126,12 +126,10 @@ __device__ __forceinline__ void read_transposed(V &f, const lds_char *at)
 // source of k-rows beyond a ragged contraction length
 __device__ __attribute__((aligned(16))) const uint32_t kZeroPiece[4] = {0u, 0u, 0u, 0u};
 
-// Swizzle term of a row: rows are BK*2 bytes; consecutive rows must land on different banks.
-template <int BK, int SWZ>
+// Swizzle term of a row of 64 k (128 bytes): consecutive rows must land on different banks.
 __device__ __forceinline__ int swz(int row)
 {
-    if (BK == 64) return SWZ == 0 ? (row & 7) : ((row >> 1) & 7);
-    return SWZ == 0 ? ((row >> 1) & 3) : ((row >> 2) & 3);
+    return (row >> 1) & 7;
 }
 
 }  // namespace

@@ -13,7 +13,7 @@
 // other small products (launch_grouped_gemm_t), normal operands of fewer than three slabs and operands whose offsets need more than 32 bits.
 //
 // Design (gfx950):
-//   * global -> LDS with the direct 16-byte loads of the forward kernel, STAGES-deep ring of K slabs
+//   * global -> LDS with the direct 16-byte loads of the forward kernel, two stages of K slabs
 //     (BK = 64).  A normal operand lands as [row][64 k] (8 pieces per row, XOR-swizzled); a transposed
 //     one lands as it is in memory, [k][BM or BN columns] (16 or 32 pieces per row).
 //   * MFMA 32x32x16 bf16 wants, per lane, 8 consecutive k of one row/column.  From a normal tile that
@@ -41,7 +41,7 @@ namespace smile {
 
 namespace {
 
-constexpr int BK = 64;
+constexpr int BK = 64, STAGES = 2, kWorkgroupsPerCu = 2;   // one workgroup's loads and epilogue hide behind the other's MFMAs
 
 // E: the 16-bit storage type (__bf16 or _Float16)
 template <typename E>
@@ -83,12 +83,12 @@ struct OperandTile {
     }
 };
 
-template <typename E, int BM, int BN, int WGM, int WGN, int STAGES, int OCC, bool XT, bool WT, int POST, bool PERSIST = false>
-__global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGemmArgs<E> a)
+template <typename E, int BM, int BN, bool XT, bool WT, int POST, bool PERSIST = false>
+__global__ __launch_bounds__(256, kWorkgroupsPerCu) void grouped_gemm_t_kernel(TGemmArgs<E> a)
 {
     typedef typename Half<E>::vec8 bf16x8;                              // one MFMA operand: 8 elements
     typedef __attribute__((__vector_size__(4 * sizeof(E)))) E bf16x4;   // 4 rounded outputs
-    constexpr int NW = WGM * WGN, NT = NW * 64;
+    constexpr int WGM = 2, WGN = 2, NW = WGM * WGN, NT = NW * 64;   // waves along rows and columns
     constexpr int WM = BM / WGM, WN = BN / WGN;
     constexpr int TM = WM / 32, TN = WN / 32;
     using XTile = OperandTile<E, BM, XT>;
@@ -99,7 +99,6 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
     constexpr int OROWS = WGM * 32, OSTRIDE = BN / 8 + 1, OPR = BN / 8;
     static_assert((XI + WI) % NW == 0, "load instructions must divide over the waves");
     static_assert(BM % 32 == 0 && BN % 32 == 0 && BM >= 128 && BN >= 128, "rotation swizzle: rows of at least 16 pieces");
-    static_assert(STAGES >= 2 && STAGES <= 4 && (STAGES - 2) * GPW < 64, "pipeline depth");
     static_assert(OROWS * OSTRIDE <= STAGES * STAGE, "epilogue staging must fit in the pipeline buffers");
 
     __shared__ u32x4 lds[STAGES * STAGE];
@@ -245,14 +244,10 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
             else wf[KK & 1][I] = *(const __attribute__((address_space(3))) bf16x8 *)(from + woff[I] + (((2 * KK + fhi) ^ fsw) * 16));
         }
     };
-    // Waits for a slab (this wave's part landed, then everybody's); every wave is then also done reading the slab before it,
-    // whose buffer may be filled again.  `issued_after`: slabs requested after it by now.
-    auto enter_slab = [&](int issued_after, bool first) {
-        // a prefetched tile's first slabs were requested before the previous tile's stores: wait for all
-        if (PREFETCH && first) wait_vmcnt<0>();
-        else if (STAGES >= 4 && issued_after == 2) wait_vmcnt<2 * GPW>();
-        else if (STAGES >= 3 && issued_after == 1) wait_vmcnt<GPW>();
-        else wait_vmcnt<0>();
+    // Waits for the slab requested last (this wave's part landed, then everybody's); every wave is then also done reading the slab
+    // before it, whose buffer may be filled again.
+    auto enter_slab = [&]() {
+        wait_vmcnt<0>();
         __builtin_amdgcn_s_barrier();
     };
     // The MFMAs of k-step KK, and behind the first of them the reads of the k-step after it, so that the last ones cover
@@ -273,7 +268,7 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
         });
     };
     // All k-steps of a slab but the last, its first fragments already in registers, reading `from`.  MORE: with the load
-    // instructions of slab `slab`, into `fill`, which is another stage (STAGES >= 2).
+    // instructions of slab `slab`, into `fill`, the other stage.
     auto front_steps = [&](auto more_tag, int slab, const lds_char *__restrict from, lds_char *__restrict fill) {
         constexpr int G = decltype(more_tag)::value ? GPW : 0;
         for_constants<KS - 1>([&](auto kstep) {
@@ -290,7 +285,7 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
         const int fill = stage == 0 ? STAGES - 1 : stage - 1, next = stage + 1 == STAGES ? 0 : stage + 1;
         front_steps(more_tag, kt + STAGES - 1, (const lds_char *)(lds + stage * STAGE), (lds_char *)(lds + fill * STAGE));
         __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): the last k-step's fragments, this wave's last reads of the slab
-        if (MORE || kt + 1 < slabs) enter_slab(MORE ? STAGES - 2 : min(STAGES - 2, slabs - 2 - kt), false);
+        if (MORE || kt + 1 < slabs) enter_slab();
         // after the last slab: stale fragments, never multiplied
         multiply(std::integral_constant<int, KS - 1>{}, std::integral_constant<int, 0>{}, std::integral_constant<int, 0>{},
                  (const lds_char *)(lds + next * STAGE), 0, nullptr);
@@ -303,7 +298,7 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
         walk.advance();
         more = select(nxt_tile);
     }
-    if (slabs > 0) enter_slab(min(STAGES - 2, slabs - 1), true);
+    if (slabs > 0) enter_slab();
     int kt = 0, stage = 0;
     if (wave_live) {
         if (slabs > 0) for_constants<NF>([&](auto f) { fetch_one(f, std::integral_constant<int, 0>{}, (const lds_char *)lds); });
@@ -318,7 +313,7 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
     } else {
         // none of this wave's rows exists: it only helps loading
         for (; kt < slabs; ++kt) {
-            if (kt > 0) enter_slab(min(STAGES - 2, slabs - 1 - kt), false);
+            if (kt > 0) enter_slab();
             if (kt + STAGES - 1 < slabs) {
                 lds_char *fill = (lds_char *)(lds + (stage == 0 ? STAGES - 1 : stage - 1) * STAGE);
 #pragma unroll
@@ -392,20 +387,20 @@ __global__ __launch_bounds__(WGM *WGN * 64, OCC) void grouped_gemm_t_kernel(TGem
     }   // tile loop
 }
 
-template <typename E, int BM, int BN, int STAGES, int OCC, bool XT, bool WT, int POST>
+template <typename E, int BM, int BN, bool XT, bool WT, int POST>
 hipError_t launch_tile(TGemmArgs<E> a, int N, const Tuning &tune, hipStream_t s)
 {
     a.row_tiles = (a.Mrows + BM - 1) / BM;
     a.col_tiles = (a.Nout + BN - 1) / BN;
     a.tiles = N * a.row_tiles * a.col_tiles;
     a.N = N;
-    const int slots = workgroup_slots(tune, workgroups_per_cu(4, OCC, STAGES * (BM + BN) * BK * 2));
+    const int slots = workgroup_slots(tune, kWorkgroupsPerCu);
     if (use_persistent_grid(tune, N, a.tiles, slots)) {
-        SMILE_LAUNCH((grouped_gemm_t_kernel<E, BM, BN, 2, 2, STAGES, OCC, XT, WT, POST, true>), dim3(slots), dim3(256),
+        SMILE_LAUNCH((grouped_gemm_t_kernel<E, BM, BN, XT, WT, POST, true>), dim3(slots), dim3(256),
                            0, s, a);
     } else {
         const int per_xcd = (a.tiles + kXcds - 1) / kXcds;
-        SMILE_LAUNCH((grouped_gemm_t_kernel<E, BM, BN, 2, 2, STAGES, OCC, XT, WT, POST>), dim3(per_xcd * kXcds),
+        SMILE_LAUNCH((grouped_gemm_t_kernel<E, BM, BN, XT, WT, POST>), dim3(per_xcd * kXcds),
                            dim3(256), 0, s, a);
     }
     return hipGetLastError();
@@ -419,12 +414,12 @@ hipError_t launch_typed(const TransposedGemm &g, bool wide, hipStream_t s)
                    static_cast<const E *>(g.aux), g.rows_valid, g.k_valid, g.Mrows, g.Nout, g.K, g.ldx, g.ldw,
                    g.sx, g.sw, g.sy, 0, 0, 0, g.N};
     if (g.x_transposed) {
-        if (wide) return launch_tile<E, 128, 192, 2, 2, true, true, 0>(a, g.N, g.tune, s);
-        return launch_tile<E, 128, 128, 2, 2, true, true, 0>(a, g.N, g.tune, s);
+        if (wide) return launch_tile<E, 128, 192, true, true, 0>(a, g.N, g.tune, s);
+        return launch_tile<E, 128, 128, true, true, 0>(a, g.N, g.tune, s);
     }
-    if (g.post == 1) return launch_tile<E, 128, 128, 2, 2, false, true, 1>(a, g.N, g.tune, s);
-    if (g.post == 2) return launch_tile<E, 128, 128, 2, 2, false, true, 2>(a, g.N, g.tune, s);
-    return launch_tile<E, 128, 128, 2, 2, false, true, 0>(a, g.N, g.tune, s);
+    if (g.post == 1) return launch_tile<E, 128, 128, false, true, 1>(a, g.N, g.tune, s);
+    if (g.post == 2) return launch_tile<E, 128, 128, false, true, 2>(a, g.N, g.tune, s);
+    return launch_tile<E, 128, 128, false, true, 0>(a, g.N, g.tune, s);
 }
 
 }  // namespace
