@@ -43,10 +43,10 @@ MEASURED_BF16_TFLOPS = 2485.0
 # scaled by what the same counter reads for a plain device copy of known size); the summary that backs each
 # figure is named beside it.  Workloads without a tracked summary report null.
 MEASURED_TRAFFIC = {
-    "cfg2": (140.80e6, "profiles/bench_cfg2_hbm_traffic_pmc.txt"),
-    "cfg3": (893.55e6, "profiles/bench_cfg3_hbm_traffic_pmc.txt"),
-    "cfg4": (870.64e6, "profiles/bench_cfg4_hbm_traffic_pmc.txt"),
-    "cfg5": (2329.42e6, "profiles/bench_cfg5_hbm_traffic_pmc.txt"),
+    "cfg2": (142.74e6, "profiles/bench_cfg2_hbm_traffic_pmc.txt"),
+    "cfg3": (935.06e6, "profiles/bench_cfg3_hbm_traffic_pmc.txt"),
+    "cfg4": (890.37e6, "profiles/bench_cfg4_hbm_traffic_pmc.txt"),
+    "cfg5": (2349.40e6, "profiles/bench_cfg5_hbm_traffic_pmc.txt"),
 }
 
 PRE_WARM_S = 0.25   # untimed ramp before the warm-up steps of every configuration

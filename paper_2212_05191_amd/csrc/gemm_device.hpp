@@ -25,7 +25,7 @@ struct GemmArgs {
     const float *gate;      // [T]
     void *y2 = nullptr;     // [N][C][Nout]: the same product without the activation (DUAL kernels only)
     int N = 0;                   // experts (PERSIST kernels walk the live row tiles of all of them)
-    bool backwards = false;      // walk the tiles from the last expert to the first
+    bool backwards = false;      // ring kernels: walk the tiles from the last expert to the first
     int tokens = 0;              // T: rows of the gathered matrix, and what the experts' rows add up to at most (0: full buffers)
 };
 

@@ -25,10 +25,14 @@
 // gemm_transposed.hip); the pieces of k-row k are rotated so that four successive k-rows fall on distinct banks: by 4 * (k & 3) in rows
 // of 16 pieces (256 bytes), by 4 * ((k >> 1) & 1) in rows of 8.
 //
-// What the compiler's own waits would undo: it cannot count loads across the loop over slabs, so a value loaded before the loop and
-// used after it may cost a wait for all loads, i.e. the whole ring.  Row indices, tokens and gates are therefore loaded where the waits
-// in between already cover them (tokens at the start of a tile, gates in the phase D = -7), and contractions of one or two slabs, where they
-// would not, have code of their own.
+// What the compiler's own waits undo: it cannot count loads across the loop over slabs, so a value loaded before the loop and used after it
+// costs a wait for all loads, i.e. the whole ring.  Row indices, tokens and gates are requested early enough to have arrived (tokens and the
+// next tile's row indices at the start of a tile, gates in the phase D = -7), but the forward kernels, which may gather or scatter, do wait
+// for all that is in flight at D = -7, where the next tile's addresses are taken, and in front of the epilogue; the gradient kernels of
+// a normal x do not.  128 x 192 tiles fill the 256 registers of two workgroups on a CU and spill: forward 2 (6 with GELU), weight gradients 10 (in the
+// code for one and two slabs, too); what is reloaded at the start of a tile, of the walk, waits for its first units and the stores of the
+// tile before.  The other shapes spill no vector register.  Contractions of one or two slabs, whose waits would cover nothing, have code of
+// their own.
 #pragma once
 
 #include <type_traits>
@@ -460,7 +464,8 @@ __global__ __launch_bounds__(256, OCC) void grouped_gemm_ring_kernel(RingArgs a)
                             const float g = *(const __attribute__((address_space(3))) float *)(meta + BM * 4 + (row0 + lrow) * 4);
                             // No kernel of the pass reads y again, so its rows pass the L2 by and leave it to w2 and h (128
                             // experts of 768 -> 3072, 32768 tokens: 437 -> 431 us a pass; 16 experts, 8192: 114.6 -> 113.8;
-                            // the same at 64 experts of 1024 -> 4096, 429 us).
+                            // the same at 64 experts of 1024 -> 4096, 429 us).  With a reader right behind (y + x): 465.3 -> 460.8,
+                            // 117.1 -> 116.7, 459.2 -> 458.4; 2048 and 4096 tokens the same.
                             __builtin_nontemporal_store(scale_x8<E>(v, g), reinterpret_cast<u32x4 *>(static_cast<E *>(a.y_tok) + (size_t)tok * Nout + col));
                         }
                     }
