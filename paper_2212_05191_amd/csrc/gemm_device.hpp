@@ -3,8 +3,6 @@
 // the LDS bank swizzle.
 #pragma once
 
-#include <cfloat>
-
 #include "smile_internal.hpp"
 
 namespace smile {
@@ -61,7 +59,9 @@ __device__ __forceinline__ float activate(float v)
         poly = fmaf(poly, t, 0.5f * -0.284496736f);
         poly = fmaf(poly, t, 0.5f * 0.254829592f);
         const float ex = __builtin_amdgcn_exp2f(v * v * (-0.5f * 1.4426950408889634f));
-        return __builtin_amdgcn_fmed3f(v, 0.f, FLT_MAX) - __builtin_amdgcn_fmed3f(av, 0.f, FLT_MAX) * (poly * t * ex);
+        float most;   // in a scalar register: the compiler would keep it in a vector register, of which the ring kernels have none to spare
+        asm("s_mov_b32 %0, 0x7f7fffff" : "=s"(most));
+        return __builtin_amdgcn_fmed3f(v, 0.f, most) - __builtin_amdgcn_fmed3f(av, 0.f, most) * (poly * t * ex);
     } else return v;
 }
 

@@ -29,7 +29,7 @@
 // costs a wait for all loads, i.e. the whole ring.  Row indices, tokens and gates are requested early enough to have arrived (tokens and the
 // next tile's row indices at the start of a tile, gates in the phase D = -7), but the forward kernels, which may gather or scatter, do wait
 // for all that is in flight at D = -7, where the next tile's addresses are taken, and in front of the epilogue; the gradient kernels of
-// a normal x do not.  128 x 192 tiles fill the 256 registers of two workgroups on a CU and spill: forward 2 (6 with GELU), weight gradients 10 (in the
+// a normal x do not.  128 x 192 tiles fill the 256 registers of two workgroups on a CU and spill: forward 2 (4 with GELU), weight gradients 10 (in the
 // code for one and two slabs, too); what is reloaded at the start of a tile, of the walk, waits for its first units and the stores of the
 // tile before.  The other shapes spill no vector register.  Contractions of one or two slabs, whose waits would cover nothing, have code of
 // their own.
