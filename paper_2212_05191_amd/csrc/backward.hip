@@ -3,7 +3,8 @@
 // the forward steps:
 //
 //   combine_backward       dye[row(t)] = gate_t * dy[t],  dgate[t] = <dy[t], ye[row(t)]>     (HBM streaming)
-//   route_backward         softmax Jacobians of the two routers: dgate and the Eq. 4 terms -> dlogits
+//   route_backward         softmax Jacobians of the two routers: dgate and the Eq. 4 terms -> dlogits (in the chained pass in
+//                          the same launch as combine_backward)
 //   expert_ffn_backward    (pre, h) = xe . W1^T   unless saved by the forward pass (one launch of the forward kernel)
 //                          dpre = (dye . W2) * act'(pre),  dxe = dpre . W1,
 //                          dW2 = dye^T . h,  dW1 = dpre^T . xe   (contraction over the expert's rows)
@@ -54,144 +55,136 @@ struct Piece {
     }
 };
 
-// ------------------------------------------------------------------------------------ combine backward
+// ------------------------------------------------------------------------------------ combine and route backward
 
-// LPR consecutive lanes own one token row (as in the forward dispatch / combine kernels).
-template <int DT, int LPR>
+__device__ __forceinline__ float exp_neg(float v) { return __builtin_amdgcn_exp2f(v * 1.4426950408889634f); }
+
+// Sum over the LPR lanes of a token, in a fixed order; every lane gets it.
+template <int LPR>
+__device__ __forceinline__ float token_sum(float v)
+{
+#pragma unroll
+    for (int off = LPR / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    return v;
+}
+
+struct RouteBackwardArgs {
+    const float *logits_inter, *logits_intra, *bias_inter, *bias_intra;
+    const int32_t *group_idx, *local_idx, *group_count, *local_count;
+    int T, n, m;
+    float coef_inter, coef_intra;
+    float *dlp, *dlq;
+};
+
+// One softmax row backwards by the LPR lanes of a token, columns sub, sub + LPR, ...: with z = sum exp(a - a_top) (so the top
+// probability is 1 / z) and u_k = coef * count_k + [k == top] * extra,  dl_k = p_k * (u_k - sum_i u_i p_i).
+// Rows of up to 2 LPR columns stay in registers; wider ones are read again by each of the three passes.
+template <int LPR>
+struct SoftmaxRow {
+    const float *row, *bias;
+    int len, top, sub;
+    float held[2], mx, inv_z;
+    __device__ __forceinline__ float at(int i) const { return bias ? __fadd_rn(row[i], bias[i]) : row[i]; }
+    template <typename F>
+    __device__ __forceinline__ void each(F f) const
+    {
+        if (len <= 2 * LPR) {
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+                if (sub + k * LPR < len) f(sub + k * LPR, held[k]);
+        } else {
+            for (int i = sub; i < len; i += LPR) f(i, at(i));
+        }
+    }
+    // reads the row; 1 / z is the top probability
+    __device__ __forceinline__ SoftmaxRow(const float *row_, const float *bias_, int len_, int top_, int sub_)
+        : row(row_), bias(bias_), len(len_), top(top_), sub(sub_)
+    {
+#pragma unroll
+        for (int k = 0; k < 2; ++k) held[k] = sub + k * LPR < len ? at(sub + k * LPR) : 0.f;
+        mx = at(top);
+    }
+    __device__ __forceinline__ void normalise()
+    {
+        float z = 0.f;
+        each([&](int, float a) { z += exp_neg(a - mx); });
+        inv_z = 1.0f / token_sum<LPR>(z);
+    }
+    __device__ __forceinline__ void backward(float coef, const int32_t *__restrict__ count, float extra, float *__restrict__ out) const
+    {
+        auto u = [&](int i) { return coef * (float)count[i] + (i == top ? extra : 0.f); };
+        float dot = 0.f;
+        each([&](int i, float a) { dot = fmaf(u(i), exp_neg(a - mx) * inv_z, dot); });
+        dot = token_sum<LPR>(dot);
+        each([&](int i, float a) { out[i] = exp_neg(a - mx) * inv_z * (u(i) - dot); });
+    }
+};
+
+template <int LPR>
+__device__ __forceinline__ void route_backward_token(SoftmaxRow<LPR> &p, SoftmaxRow<LPR> &q, const RouteBackwardArgs &a, int t, float dg)
+{
+    p.normalise();
+    q.normalise();
+    p.backward(a.coef_inter, a.group_count, dg * q.inv_z, a.dlp + (size_t)t * a.n);
+    q.backward(a.coef_intra, a.local_count, dg * p.inv_z, a.dlq + (size_t)t * a.m);
+}
+
+// LPR consecutive lanes own one token row (as in the forward dispatch / combine kernels).  ROUTE: they go on with the token's two softmax
+// rows, whose logits were requested in front of the rows of dy and ye.  Bound: the rows (3 K d elements); the softmax part on its own is a
+// launch of small loads.  Against two launches, the second with a thread for each token (us): 8192 x 768 with 2 + 8 columns 9.1 + 7.4 -> 10.9,
+// 32768 x 768 with 1 + 128 28.1 + 39.4 -> 42.2, 65536 x 1024 with 32 + 8 24.0 + 31.4 -> 42.7, fp32 2048 x 256 with 2 + 4 4.3 + 5.6 -> 5.3.
+template <int DT, int LPR, bool ROUTE>
 __global__ __launch_bounds__(kThreads) void combine_backward_kernel(
-    const u32x4 *__restrict__ dy, const u32x4 *__restrict__ ye, const int32_t *__restrict__ group_idx,
-    const int32_t *__restrict__ local_idx, const int32_t *__restrict__ slot, const float *__restrict__ gate,
-    u32x4 *__restrict__ dye, float *__restrict__ dgate, int T, int ppr, int m, int C)
+    const u32x4 *__restrict__ dy, const u32x4 *__restrict__ ye, const int32_t *__restrict__ slot, const float *__restrict__ gate,
+    u32x4 *__restrict__ dye, float *__restrict__ dgate, int ppr, int C, RouteBackwardArgs a)
 {
     constexpr int E = Piece<DT>::kElems;
     const int t = blockIdx.x * (kThreads / LPR) + threadIdx.x / LPR, sub = threadIdx.x % LPR;
     // every lane of a row group takes the same branch, and a group never straddles a wave
-    if (t >= T) return;
-    const int sl = slot[t];
-    if (sl < 0) {
-        if (sub == 0) dgate[t] = 0.f;
-        return;
-    }
-    const float gt = gate[t];
-    const size_t row = (size_t)(group_idx[t] * m + local_idx[t]) * C + sl;
-    const u32x4 *src = dy + (size_t)t * ppr, *act = ye + row * ppr;
-    u32x4 *dst = dye + row * ppr;
-    float dot = 0.f;
-    for (int c = sub; c < ppr; c += LPR) {
-        float a[E], b[E], o[E];
-        Piece<DT>::unpack(src[c], a);
-        Piece<DT>::unpack(act[c], b);
+    if (t >= a.T) return;
+    const int sl = slot[t], g = a.group_idx[t], l = a.local_idx[t];
+    auto rows = [&]() {
+        if (sl < 0) return 0.f;
+        const float gt = gate[t];
+        const size_t row = (size_t)(g * a.m + l) * C + sl;
+        const u32x4 *src = dy + (size_t)t * ppr, *act = ye + row * ppr;
+        u32x4 *dst = dye + row * ppr;
+        float dot = 0.f;
+        for (int c = sub; c < ppr; c += LPR) {
+            float x[E], y[E], o[E];
+            Piece<DT>::unpack(src[c], x);
+            Piece<DT>::unpack(act[c], y);
 #pragma unroll
-        for (int k = 0; k < E; ++k) {
-            dot = fmaf(a[k], b[k], dot);
-            o[k] = a[k] * gt;
+            for (int k = 0; k < E; ++k) {
+                dot = fmaf(x[k], y[k], dot);
+                o[k] = x[k] * gt;
+            }
+            dst[c] = Piece<DT>::pack(o);
         }
-        dst[c] = Piece<DT>::pack(o);
-    }
-#pragma unroll
-    for (int off = LPR / 2; off > 0; off >>= 1) dot += __shfl_xor(dot, off, 64);
-    if (sub == 0) dgate[t] = dot;
-}
-
-// ------------------------------------------------------------------------------------ route backward
-
-__device__ __forceinline__ float exp_neg(float v) { return __builtin_amdgcn_exp2f(v * 1.4426950408889634f); }
-
-// One thread per token.  For each router: z = sum exp(a - a_top) (so the top probability is 1/z), then
-//   u_k = coef * count_k + [k == top] * extra,   dl_k = p_k * (u_k - sum_i u_i p_i).
-__device__ __forceinline__ float softmax_z(const float *__restrict__ row, const float *__restrict__ bias, int len,
-                                           int top, float &mx)
-{
-    mx = bias ? __fadd_rn(row[top], bias[top]) : row[top];
-    float z = 0.f;
-    for (int i = 0; i < len; ++i) z += exp_neg((bias ? __fadd_rn(row[i], bias[i]) : row[i]) - mx);
-    return z;
-}
-
-// (row and out may be the same array: element i of out is written after the last read of element i of row)
-__device__ __forceinline__ void softmax_backward_row(const float *row, const float *__restrict__ bias,
-                                                     int len, int top, float mx, float inv_z, float coef,
-                                                     const int32_t *__restrict__ count, float extra, float *out)
-{
-    float dot = 0.f;
-    for (int i = 0; i < len; ++i) {
-        const float p = exp_neg((bias ? __fadd_rn(row[i], bias[i]) : row[i]) - mx) * inv_z;
-        const float u = coef * (float)count[i] + (i == top ? extra : 0.f);
-        dot = fmaf(u, p, dot);
-    }
-    for (int i = 0; i < len; ++i) {
-        const float p = exp_neg((bias ? __fadd_rn(row[i], bias[i]) : row[i]) - mx) * inv_z;
-        const float u = coef * (float)count[i] + (i == top ? extra : 0.f);
-        out[i] = p * (u - dot);
-    }
-}
-
-__global__ __launch_bounds__(kThreads) void route_backward_kernel(
-    const float *__restrict__ logits_inter, const float *__restrict__ logits_intra,
-    const float *__restrict__ bias_inter, const float *__restrict__ bias_intra,
-    const int32_t *__restrict__ group_idx, const int32_t *__restrict__ local_idx, const float *__restrict__ dgate,
-    const int32_t *__restrict__ group_count, const int32_t *__restrict__ local_count,
-    int T, int n, int m, float coef_inter, float coef_intra, float *__restrict__ dlp, float *__restrict__ dlq)
-{
-    const int t = blockIdx.x * kThreads + threadIdx.x;
-    if (t >= T) return;
-    const int g = group_idx[t], l = local_idx[t];
-    const float *rp = logits_inter + (size_t)t * n, *rq = logits_intra + (size_t)t * m;
-    const float *bq = bias_intra ? bias_intra + (size_t)g * m : nullptr;
-    float mx_p, mx_q;
-    const float iz_p = 1.0f / softmax_z(rp, bias_inter, n, g, mx_p);   // = p[g]
-    const float iz_q = 1.0f / softmax_z(rq, bq, m, l, mx_q);           // = q[l]
-    const float dg = dgate[t];
-    softmax_backward_row(rp, bias_inter, n, g, mx_p, iz_p, coef_inter, group_count, dg * iz_q, dlp + (size_t)t * n);
-    softmax_backward_row(rq, bq, m, l, mx_q, iz_q, coef_intra, local_count, dg * iz_p, dlq + (size_t)t * m);
-}
-
-// The same arithmetic with coalesced memory traffic: a workgroup's logit rows are contiguous in memory, so they are
-// copied to LDS with consecutive lanes on consecutive addresses (a thread reading its own row straight from memory
-// touches one cache line per lane and instruction), the gradients replace them in place, and the tile is copied
-// back the same way.  Row strides in LDS are odd, so the per-token threads fall on distinct banks.
-__global__ __launch_bounds__(kThreads) void route_backward_tiled_kernel(
-    const float *__restrict__ logits_inter, const float *__restrict__ logits_intra,
-    const float *__restrict__ bias_inter, const float *__restrict__ bias_intra,
-    const int32_t *__restrict__ group_idx, const int32_t *__restrict__ local_idx, const float *__restrict__ dgate,
-    const int32_t *__restrict__ group_count, const int32_t *__restrict__ local_count,
-    int T, int n, int m, float coef_inter, float coef_intra, float *__restrict__ dlp, float *__restrict__ dlq,
-    int tokens_per_block)
-{
-    extern __shared__ float route_bwd_lds[];
-    const int sp = n | 1, sq = m | 1;
-    float *tp = route_bwd_lds, *tq = route_bwd_lds + (size_t)tokens_per_block * sp;
-    const int t0 = blockIdx.x * tokens_per_block, cnt = min(tokens_per_block, T - t0);
-    const float *gp = logits_inter + (size_t)t0 * n, *gq = logits_intra + (size_t)t0 * m;
-    // element i of the contiguous tile <-> (row i / len, column i % len), advanced without divisions
-    auto copy_tile = [&](auto to_lds, float *tile, int stride, const float *src, float *dst, int len) {
-        const int dr = kThreads / len, dc = kThreads % len;
-        int r = threadIdx.x / len, c = threadIdx.x % len;
-        for (int i = threadIdx.x; i < cnt * len; i += kThreads) {
-            if constexpr (decltype(to_lds)::value) tile[r * stride + c] = src[i];
-            else dst[i] = tile[r * stride + c];
-            r += dr, c += dc;
-            if (c >= len) c -= len, ++r;
-        }
+        return token_sum<LPR>(dot);
     };
-    copy_tile(std::true_type{}, tp, sp, gp, nullptr, n);
-    copy_tile(std::true_type{}, tq, sq, gq, nullptr, m);
-    __syncthreads();
-    if ((int)threadIdx.x < cnt) {
-        const int t = t0 + threadIdx.x;
-        const int g = group_idx[t], l = local_idx[t];
-        float *rp = tp + threadIdx.x * sp, *rq = tq + threadIdx.x * sq;
-        const float *bq = bias_intra ? bias_intra + (size_t)g * m : nullptr;
-        float mx_p, mx_q;
-        const float iz_p = 1.0f / softmax_z(rp, bias_inter, n, g, mx_p);   // = p[g]
-        const float iz_q = 1.0f / softmax_z(rq, bq, m, l, mx_q);           // = q[l]
-        const float dg = dgate[t];
-        softmax_backward_row(rp, bias_inter, n, g, mx_p, iz_p, coef_inter, group_count, dg * iz_q, rp);
-        softmax_backward_row(rq, bq, m, l, mx_q, iz_q, coef_intra, local_count, dg * iz_p, rq);
+    if constexpr (ROUTE) {
+        SoftmaxRow<LPR> p(a.logits_inter + (size_t)t * a.n, a.bias_inter, a.n, g, sub);
+        SoftmaxRow<LPR> q(a.logits_intra + (size_t)t * a.m, a.bias_intra ? a.bias_intra + (size_t)g * a.m : nullptr, a.m, l, sub);
+        const float dg = rows();
+        if (sub == 0) dgate[t] = dg;
+        route_backward_token(p, q, a, t, dg);
+    } else {
+        const float dg = rows();
+        if (sub == 0) dgate[t] = dg;
     }
-    __syncthreads();
-    copy_tile(std::false_type{}, tp, sp, nullptr, dlp + (size_t)t0 * n, n);
-    copy_tile(std::false_type{}, tq, sq, nullptr, dlq + (size_t)t0 * m, m);
+}
+
+// The softmax part on its own, by as many lanes a token as the kernel above gives it, so that both add in the same order.
+template <int LPR>
+__global__ __launch_bounds__(kThreads) void route_backward_kernel(const float *__restrict__ dgate, RouteBackwardArgs a)
+{
+    const int t = blockIdx.x * (kThreads / LPR) + threadIdx.x / LPR, sub = threadIdx.x % LPR;
+    if (t >= a.T) return;
+    const int g = a.group_idx[t], l = a.local_idx[t];
+    SoftmaxRow<LPR> p(a.logits_inter + (size_t)t * a.n, a.bias_inter, a.n, g, sub);
+    SoftmaxRow<LPR> q(a.logits_intra + (size_t)t * a.m, a.bias_intra ? a.bias_intra + (size_t)g * a.m : nullptr, a.m, l, sub);
+    route_backward_token(p, q, a, t, dgate[t]);
 }
 
 // ------------------------------------------------------------------------------------ dispatch backward
@@ -376,42 +369,38 @@ BackwardLayout backward_workspace_layout(const smile_layer_desc &d)
     return L;
 }
 
-hipError_t launch_combine_backward(const smile_layer_desc &d, const void *dy, const void *ye, const int32_t *group_idx,
-                                   const int32_t *local_idx, const int32_t *slot, const float *gate, void *dye,
-                                   float *dgate, hipStream_t s)
-{
-    const int ppr = d.d_model * elem_size(d.dtype) / 16;
-    const int lpr = lanes_per_row(ppr);
-    const dim3 grid((d.T + kThreads / lpr - 1) / (kThreads / lpr)), block(kThreads);
-    SMILE_DTYPE_SWITCH(d.dtype, SMILE_BWD_LPR_SWITCH(
-        lpr, SMILE_LAUNCH((combine_backward_kernel<DT, L>), grid, block, 0, s, static_cast<const u32x4 *>(dy),
-                                static_cast<const u32x4 *>(ye), group_idx, local_idx, slot, gate,
-                                static_cast<u32x4 *>(dye), dgate, d.T, ppr, d.m_local, d.capacity)));
-    return hipGetLastError();
-}
-
-hipError_t launch_route_backward(const smile_layer_desc &d, const float *logits_inter, const float *logits_intra,
-                                 const float *bias_inter, const float *bias_intra, const int32_t *group_idx,
-                                 const int32_t *local_idx, const float *dgate, const int32_t *group_count,
-                                 const int32_t *local_count, float dloss, float *dlp, float *dlq, hipStream_t s)
+static RouteBackwardArgs route_backward_args(const smile_layer_desc &d, const RouteBackwardIo &io, float dloss)
 {
     // d(alpha * n * sum_i f_i P_i) / dp[t,i] = alpha * n * (count_i / T) / T
     const float inv_t2 = 1.0f / ((float)d.T * (float)d.T);
-    const float ci = dloss * d.alpha * (float)d.n_groups * inv_t2, cq = dloss * d.beta * (float)d.m_local * inv_t2;
-    // tokens per workgroup of the tiled kernel: as many as keep its LDS tile within 64 KB; routers too wide even for
-    // 64 tokens take the kernel that reads its rows from memory
-    const size_t row_bytes = (size_t)((d.n_groups | 1) + (d.m_local | 1)) * sizeof(float);
-    int tokens = kThreads;
-    while (tokens >= 64 && tokens * row_bytes > 64 * 1024) tokens /= 2;
-    if (tokens >= 64 && d.n_groups + d.m_local >= 32) {   // narrower routers: measured faster from memory
-        SMILE_LAUNCH(route_backward_tiled_kernel, dim3((d.T + tokens - 1) / tokens), dim3(kThreads),
-                           tokens * row_bytes, s, logits_inter, logits_intra, bias_inter, bias_intra, group_idx, local_idx,
-                           dgate, group_count, local_count, d.T, d.n_groups, d.m_local, ci, cq, dlp, dlq, tokens);
-        return hipGetLastError();
-    }
-    SMILE_LAUNCH(route_backward_kernel, dim3((d.T + kThreads - 1) / kThreads), dim3(kThreads), 0, s, logits_inter,
-                       logits_intra, bias_inter, bias_intra, group_idx, local_idx, dgate, group_count, local_count, d.T,
-                       d.n_groups, d.m_local, ci, cq, dlp, dlq);
+    return {io.logits_inter, io.logits_intra, io.bias_inter, io.bias_intra, io.group_idx, io.local_idx, io.group_count, io.local_count,
+            d.T, d.n_groups, d.m_local, dloss * d.alpha * (float)d.n_groups * inv_t2, dloss * d.beta * (float)d.m_local * inv_t2, io.dlp, io.dlq};
+}
+
+hipError_t launch_combine_backward(const smile_layer_desc &d, const void *dy, const void *ye, const int32_t *slot, const float *gate, void *dye,
+                                   float *dgate, const RouteBackwardIo &io, bool route, float dloss, hipStream_t s)
+{
+    const int ppr = d.d_model * elem_size(d.dtype) / 16;
+    const int lpr = lanes_per_row(ppr);
+    const RouteBackwardArgs a = route_backward_args(d, io, dloss);
+    const dim3 grid((d.T + kThreads / lpr - 1) / (kThreads / lpr)), block(kThreads);
+    auto launch = [&](auto with) {
+        constexpr bool ROUTE = decltype(with)::value;
+        SMILE_DTYPE_SWITCH(d.dtype, SMILE_BWD_LPR_SWITCH(
+            lpr, SMILE_LAUNCH((combine_backward_kernel<DT, L, ROUTE>), grid, block, 0, s, static_cast<const u32x4 *>(dy),
+                              static_cast<const u32x4 *>(ye), slot, gate, static_cast<u32x4 *>(dye), dgate, ppr, d.capacity, a)));
+    };
+    if (route) launch(std::true_type{});
+    else launch(std::false_type{});
+    return hipGetLastError();
+}
+
+hipError_t launch_route_backward(const smile_layer_desc &d, const float *dgate, const RouteBackwardIo &io, float dloss, hipStream_t s)
+{
+    const int lpr = lanes_per_row(d.d_model * elem_size(d.dtype) / 16);
+    const RouteBackwardArgs a = route_backward_args(d, io, dloss);
+    const dim3 grid((d.T + kThreads / lpr - 1) / (kThreads / lpr));
+    SMILE_BWD_LPR_SWITCH(lpr, SMILE_LAUNCH(route_backward_kernel<L>, grid, dim3(kThreads), 0, s, dgate, a));
     return hipGetLastError();
 }
 

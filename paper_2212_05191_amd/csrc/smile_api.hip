@@ -421,8 +421,9 @@ smile_status smile_combine_backward(smile_ctx *ctx, const void *dy, const void *
     if (!ctx || bad(dy) || bad(ye) || bad(group_idx) || bad(local_idx) || bad(slot) || bad(gate) || bad(dye) ||
         bad(dgate))
         return SMILE_INVALID_ARG;
-    return from_hip(launch_combine_backward(ctx->desc, dy, ye, group_idx, local_idx, slot, gate, dye, dgate,
-                                            static_cast<hipStream_t>(stream)));
+    RouteBackwardIo io{};
+    io.group_idx = group_idx, io.local_idx = local_idx;
+    return from_hip(launch_combine_backward(ctx->desc, dy, ye, slot, gate, dye, dgate, io, false, 0.f, static_cast<hipStream_t>(stream)));
 }
 
 smile_status smile_route_backward(smile_ctx *ctx, const float *logits_inter, const float *logits_intra,
@@ -436,9 +437,8 @@ smile_status smile_route_backward(smile_ctx *ctx, const float *logits_inter, con
         bad(group_idx) || bad(local_idx) || bad(dgate) || bad(group_count) || bad(local_count) || bad(dlp) || bad(dlq))
         return SMILE_INVALID_ARG;
     if (!std::isfinite(dloss)) return SMILE_BAD_SHAPE;
-    return from_hip(launch_route_backward(ctx->desc, logits_inter, logits_intra, bias_inter, bias_intra, group_idx,
-                                          local_idx, dgate, group_count, local_count, dloss, dlp, dlq,
-                                          static_cast<hipStream_t>(stream)));
+    const RouteBackwardIo io{logits_inter, logits_intra, bias_inter, bias_intra, group_idx, local_idx, group_count, local_count, dlp, dlq};
+    return from_hip(launch_route_backward(ctx->desc, dgate, io, dloss, static_cast<hipStream_t>(stream)));
 }
 
 smile_status smile_expert_ffn_backward(smile_ctx *ctx, const void *xe, const int32_t *kept_count,
@@ -499,12 +499,9 @@ smile_status smile_layer_backward(smile_ctx *ctx, const smile_backward_io *io, f
     if (st != SMILE_OK) return st;
     const LayerDesc &d = ctx->desc;
     hipStream_t s = static_cast<hipStream_t>(stream);
-    hipError_t err = launch_combine_backward(d, io->dy, io->ye, io->group_idx, io->local_idx, io->slot, io->gate,
-                                             io->dye, io->dgate, s);
-    if (err == hipSuccess)
-        err = launch_route_backward(d, io->logits_inter, io->logits_intra, io->bias_inter, io->bias_intra,
-                                    io->group_idx, io->local_idx, io->dgate, io->group_count, io->local_count, dloss,
-                                    io->dlp, io->dlq, s);
+    const RouteBackwardIo route{io->logits_inter, io->logits_intra, io->bias_inter, io->bias_intra, io->group_idx, io->local_idx,
+                                io->group_count, io->local_count, io->dlp, io->dlq};
+    hipError_t err = launch_combine_backward(d, io->dy, io->ye, io->slot, io->gate, io->dye, io->dgate, route, true, dloss, s);
     if (err == hipSuccess)
         err = launch_expert_ffn_backward(d, workspace, io->xe, io->kept_count, io->w1, io->w2, io->dye, io->h, io->pre,
                                          io->dxe, io->dw1, io->dw2, s);

@@ -490,13 +490,16 @@ struct BackwardLayout {
 };
 BackwardLayout backward_workspace_layout(const smile_layer_desc &d);
 
-hipError_t launch_combine_backward(const smile_layer_desc &d, const void *dy, const void *ye, const int32_t *group_idx,
-                                   const int32_t *local_idx, const int32_t *slot, const float *gate, void *dye,
-                                   float *dgate, hipStream_t s);
-hipError_t launch_route_backward(const smile_layer_desc &d, const float *logits_inter, const float *logits_intra,
-                                 const float *bias_inter, const float *bias_intra, const int32_t *group_idx,
-                                 const int32_t *local_idx, const float *dgate, const int32_t *group_count,
-                                 const int32_t *local_count, float dloss, float *dlp, float *dlq, hipStream_t s);
+// What the routers' backward step reads and writes (smile_route_backward), but dgate
+struct RouteBackwardIo {
+    const float *logits_inter, *logits_intra, *bias_inter, *bias_intra;
+    const int32_t *group_idx, *local_idx, *group_count, *local_count;
+    float *dlp, *dlq;
+};
+// route: the routers' backward step in the same launch (else only group_idx and local_idx of `io` are used)
+hipError_t launch_combine_backward(const smile_layer_desc &d, const void *dy, const void *ye, const int32_t *slot, const float *gate, void *dye,
+                                   float *dgate, const RouteBackwardIo &io, bool route, float dloss, hipStream_t s);
+hipError_t launch_route_backward(const smile_layer_desc &d, const float *dgate, const RouteBackwardIo &io, float dloss, hipStream_t s);
 // h / pre (both or neither): the hidden activation and pre-activation saved by the forward pass; null: recomputed
 hipError_t launch_expert_ffn_backward(const LayerDesc &d, void *workspace, const void *xe,
                                       const int32_t *kept_count, const void *w1, const void *w2, const void *dye,

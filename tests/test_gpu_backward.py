@@ -396,3 +396,32 @@ def test_saved_activations_equal_recomputation(torch_cuda, cfg):
     finally:
         a.close()
         b.close()
+
+
+# Router widths around the columns that a token's lanes hold in registers (two each: 8, 16 or 32 lanes by the bytes of a row of x), with
+# routing biases and dropped tokens
+ROUTE_BACKWARD_EDGES = [
+    wl.small_config("route_bwd_8_lanes", 333, 64, 64, 16, 17, 2, "bf16", "gelu", skew=True, seed=71),
+    wl.small_config("route_bwd_16_lanes", 333, 64, 64, 33, 32, 2, "f32", "relu", skew=True, seed=72),
+    wl.small_config("route_bwd_32_lanes", 333, 256, 64, 64, 1, 5, "f16", "gelu", skew=True, seed=73),
+    wl.small_config("route_bwd_32_lanes_wide", 333, 320, 64, 1, 65, 5, "bf16", "gelu", skew=True, seed=74),
+    wl.small_config("route_bwd_one_column", 70, 64, 64, 1, 1, 40, "bf16", "gelu", seed=75),
+]
+
+
+@pytest.mark.parametrize("cfg", ROUTE_BACKWARD_EDGES, ids=lambda c: c.name)
+def test_router_logit_gradients_at_the_register_edges(torch_cuda, cfg):
+    """The routers' backward step in the launch of the combine step (chained) and on its own: the same bits, and the oracle's
+    gradients (fp32 sums of at most 65 terms and exponentials of relative error 1e-6: 1e-5 norm-wise)."""
+    a, b = _forward_backward(cfg), _forward_backward(cfg, chained=True)
+    try:
+        fwd, oa, ob = parity.fetch(b), _fetch_backward(a), _fetch_backward(b)
+        for k in ("dgate", "dlp", "dlq"):
+            np.testing.assert_array_equal(oa[k], ob[k], err_msg=k)
+        _, _, _, bi, bq = parity.host_inputs(cfg)
+        dlp, dlq = oracle.route_backward(fwd["logits_inter"], fwd["logits_intra"], fwd["group_idx"], fwd["local_idx"],
+                                         ob["dgate"].astype(np.float64), fwd["group_count"], fwd["local_count"], ALPHA, BETA, 1.0, bi, bq)
+        assert normwise(ob["dlp"], dlp) <= TOL_F32_SUM and normwise(ob["dlq"], dlq) <= TOL_F32_SUM
+    finally:
+        a.close()
+        b.close()
