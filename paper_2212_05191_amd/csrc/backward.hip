@@ -12,7 +12,8 @@
 //                          the slow one, nothing transposed in memory
 //   dispatch_backward      dx[t] = dxe[row(t)] + dlp[t,:] . W_p + dlq[t,:] . W_q
 //   gate_weights_backward  dW_p = dlp^T . x, dW_q = dlq^T . x: per-block partial sums, then a fixed-order
-//                          reduction over the blocks (bit-reproducible, no atomics)
+//                          reduction over the blocks (bit-reproducible, no atomics); the partial sums in the same launch as
+//                          dispatch_backward where both are small
 #include <type_traits>
 
 
@@ -190,15 +191,24 @@ __global__ __launch_bounds__(kThreads) void route_backward_kernel(const float *_
 // ------------------------------------------------------------------------------------ dispatch backward
 
 // dx[t] = dxe[row(t)] (kept tokens) + sum_i dlp[t,i] W_p[i] + sum_j dlq[t,j] W_q[j], one rounding.
+struct DispatchBackwardArgs {
+    const u32x4 *dxe;
+    const int32_t *group_idx, *local_idx, *slot;
+    const float *dlp, *dlq;
+    const u32x4 *w_inter, *w_intra;
+    u32x4 *dx;
+    int T, ppr, n, m, C;
+};
 template <int DT, int LPR>
-__global__ __launch_bounds__(kThreads) void dispatch_backward_kernel(
-    const u32x4 *__restrict__ dxe, const int32_t *__restrict__ group_idx, const int32_t *__restrict__ local_idx,
-    const int32_t *__restrict__ slot, const float *__restrict__ dlp, const float *__restrict__ dlq,
-    const u32x4 *__restrict__ w_inter, const u32x4 *__restrict__ w_intra, u32x4 *__restrict__ dx,
-    int T, int ppr, int n, int m, int C)
+__device__ __forceinline__ void dispatch_backward_block(const DispatchBackwardArgs &a, int block)
 {
     constexpr int E = Piece<DT>::kElems;
-    const int t = blockIdx.x * (kThreads / LPR) + threadIdx.x / LPR, sub = threadIdx.x % LPR;
+    const u32x4 *__restrict__ dxe = a.dxe, *__restrict__ w_inter = a.w_inter, *__restrict__ w_intra = a.w_intra;
+    const int32_t *__restrict__ group_idx = a.group_idx, *__restrict__ local_idx = a.local_idx, *__restrict__ slot = a.slot;
+    const float *__restrict__ dlp = a.dlp, *__restrict__ dlq = a.dlq;
+    u32x4 *__restrict__ dx = a.dx;
+    const int T = a.T, ppr = a.ppr, n = a.n, m = a.m, C = a.C;
+    const int t = block * (kThreads / LPR) + threadIdx.x / LPR, sub = threadIdx.x % LPR;
     if (t >= T) return;
     const int sl = slot[t];
     const u32x4 *src = sl >= 0 ? dxe + ((size_t)(group_idx[t] * m + local_idx[t]) * C + sl) * ppr : nullptr;
@@ -247,14 +257,21 @@ constexpr int kGwChunk = 16;     // logit columns per pass over the token tile
 // (dlp first, then dlq).  The x tile (fp32) and a chunk of 16 logit-gradient columns sit in LDS; lane =
 // column of x, wave w owns logit columns 4w .. 4w+3 of the chunk, so its four dl values of a token come
 // from one broadcast LDS read.  Tokens are summed serially: a fixed order.
+struct GateWeightsArgs {
+    const void *x;
+    const float *dlp, *dlq;
+    float *partial;
+    int T, d, n, m;
+};
 template <int DT>
-__global__ __launch_bounds__(kThreads) void gate_weights_partial_kernel(
-    const void *__restrict__ x, const float *__restrict__ dlp, const float *__restrict__ dlq,
-    float *__restrict__ partial, int T, int d, int n, int m)
+__device__ __forceinline__ void gate_weights_block(const GateWeightsArgs &a, int b, int col_block)
 {
     __shared__ float xs[kGwTokens][kGwCols + 1];
     __shared__ __attribute__((aligned(16))) float dls[kGwTokens][kGwChunk];
-    const int b = blockIdx.x, k0 = blockIdx.y * kGwCols;
+    const void *__restrict__ x = a.x;
+    const float *__restrict__ dlp = a.dlp, *__restrict__ dlq = a.dlq;
+    float *__restrict__ partial = a.partial;
+    const int T = a.T, d = a.d, n = a.n, m = a.m, k0 = col_block * kGwCols;
     const int t0 = b * kGwTokens;
     const int cnt = min(kGwTokens, T - t0);
     {
@@ -309,6 +326,17 @@ __global__ __launch_bounds__(kThreads) void gate_weights_partial_kernel(
             }
         }
     }
+}
+
+// dx by the first dx_blocks workgroups, the partial sums of the router weights by the others (DX, GW: with that part)
+template <int DT, int LPR, bool DX, bool GW>
+__global__ __launch_bounds__(kThreads) void router_grad_kernel(DispatchBackwardArgs dx, GateWeightsArgs gw, int dx_blocks, int gw_col_blocks)
+{
+    const int b = blockIdx.x;
+    if constexpr (DX) {
+        if (!GW || b < dx_blocks) return dispatch_backward_block<DT, LPR>(dx, b);
+    }
+    if constexpr (GW) gate_weights_block<DT>(gw, (b - dx_blocks) / gw_col_blocks, (b - dx_blocks) % gw_col_blocks);
 }
 
 // dw[i][k] = sum_b partial[b][i][k], blocks in index order.
@@ -450,45 +478,58 @@ hipError_t launch_expert_ffn_backward(const LayerDesc &d, void *workspace, const
     return hipSuccess;
 }
 
-hipError_t launch_dispatch_backward(const LayerDesc &d, const void *dxe, const int32_t *group_idx,
-                                    const int32_t *local_idx, const int32_t *slot, const float *dlp, const float *dlq,
-                                    const void *w_inter, const void *w_intra, void *dx, hipStream_t s)
+// The vector-ALU kernels (fp32, fp16, wide routers)
+static hipError_t launch_router_grad_valu(const LayerDesc &d, const RouterGradIo &io, bool with_dx, bool with_gw, float *partial, int blocks, hipStream_t s)
 {
-    // Tuning::router_grad_mfma = 0 keeps the vector-ALU kernels (tuning / comparison runs)
-    if (dispatch_backward_mfma_applies(d) && d.tune.router_grad_mfma != 0)
-        return launch_dispatch_backward_mfma(d, dxe, group_idx, local_idx, slot, dlp, dlq, w_inter, w_intra, dx, s);
-    const int ppr = d.d_model * elem_size(d.dtype) / 16;
-    const int lpr = lanes_per_row(ppr);
-    const dim3 grid((d.T + kThreads / lpr - 1) / (kThreads / lpr)), block(kThreads);
-    SMILE_DTYPE_SWITCH(d.dtype, SMILE_BWD_LPR_SWITCH(
-        lpr, SMILE_LAUNCH((dispatch_backward_kernel<DT, L>), grid, block, 0, s, static_cast<const u32x4 *>(dxe),
-                                group_idx, local_idx, slot, dlp, dlq, static_cast<const u32x4 *>(w_inter),
-                                static_cast<const u32x4 *>(w_intra), static_cast<u32x4 *>(dx), d.T, ppr, d.n_groups,
-                                d.m_local, d.capacity)));
+    const int ppr = d.d_model * elem_size(d.dtype) / 16, lpr = lanes_per_row(ppr), per_block = kThreads / lpr;
+    const int dx_blocks = with_dx ? (d.T + per_block - 1) / per_block : 0, col_blocks = (d.d_model + kGwCols - 1) / kGwCols;
+    // In one launch while a CU has at most two workgroups of dx (us: fp32 2048 x 256, 256 of them, 4.7 + 9.6 -> 7.5): beyond, the registers and
+    // the LDS of the other part keep theirs from sharing a CU (fp16 8192 x 768, 1024 of them, 13.3 + 12.1 -> 28.3).
+    if (with_dx && with_gw && dx_blocks > 2 * (d.tune.cus > 0 ? d.tune.cus : 256)) {
+        const hipError_t err = launch_router_grad_valu(d, io, true, false, nullptr, 0, s);
+        return err == hipSuccess ? launch_router_grad_valu(d, io, false, true, partial, blocks, s) : err;
+    }
+    const DispatchBackwardArgs dx{static_cast<const u32x4 *>(io.dxe), io.group_idx, io.local_idx, io.slot, io.dlp, io.dlq,
+                                  static_cast<const u32x4 *>(io.w_inter), static_cast<const u32x4 *>(io.w_intra), static_cast<u32x4 *>(io.dx),
+                                  d.T, ppr, d.n_groups, d.m_local, d.capacity};
+    const GateWeightsArgs gw{io.x, io.dlp, io.dlq, partial, d.T, d.d_model, d.n_groups, d.m_local};
+    const dim3 grid(dx_blocks + (with_gw ? blocks * col_blocks : 0)), block(kThreads);
+    auto launch = [&](auto dx_tag, auto gw_tag) {
+        constexpr bool DX = decltype(dx_tag)::value, GW = decltype(gw_tag)::value;
+        SMILE_DTYPE_SWITCH(d.dtype, SMILE_BWD_LPR_SWITCH(
+            DX ? lpr : 8, SMILE_LAUNCH((router_grad_kernel<DT, (DX ? L : 8), DX, GW>), grid, block, 0, s, dx, gw, dx_blocks, col_blocks)));
+    };
+    if (with_dx && with_gw) launch(std::true_type{}, std::true_type{});
+    else if (with_dx) launch(std::true_type{}, std::false_type{});
+    else launch(std::false_type{}, std::true_type{});
     return hipGetLastError();
 }
 
-hipError_t launch_gate_weights_backward(const LayerDesc &d, void *workspace, const void *x, const float *dlp,
-                                        const float *dlq, float *dw_inter, float *dw_intra, hipStream_t s)
+hipError_t launch_router_gradients(const LayerDesc &d, void *workspace, const RouterGradIo &io, bool with_dx, bool with_gw, hipStream_t s)
 {
+    // Tuning::router_grad_mfma = 0 keeps the vector-ALU kernels (tuning / comparison runs)
+    const bool mfma = d.tune.router_grad_mfma != 0, dx_mfma = mfma && dispatch_backward_mfma_applies(d), gw_mfma = mfma && gate_weights_mfma_applies(d);
     const BackwardLayout L = backward_workspace_layout(d);
-    float *partial = reinterpret_cast<float *>(static_cast<char *>(workspace) + L.off_gw_partial);
-    int blocks = L.gw_blocks;
-    hipError_t err;
-    if (gate_weights_mfma_applies(d) && d.tune.router_grad_mfma != 0) {
-        const int tokens = gate_weights_mfma_block_tokens(d, kGwTokens);
+    float *partial = with_gw ? reinterpret_cast<float *>(static_cast<char *>(workspace) + L.off_gw_partial) : nullptr;
+    int blocks = L.gw_blocks, tokens = kGwTokens;
+    if (gw_mfma) {
+        tokens = gate_weights_mfma_block_tokens(d, kGwTokens);
         blocks = (d.T + tokens - 1) / tokens;   // <= L.gw_blocks: the partial sums fit the same scratch area
-        err = launch_gate_weights_mfma(d, x, dlp, dlq, partial, blocks, tokens, s);
-    } else {
-        const dim3 grid(L.gw_blocks, (d.d_model + kGwCols - 1) / kGwCols), block(kThreads);
-        SMILE_DTYPE_SWITCH(d.dtype, SMILE_LAUNCH(gate_weights_partial_kernel<DT>, grid, block, 0, s, x, dlp, dlq,
-                                                       partial, d.T, d.d_model, d.n_groups, d.m_local));
-        err = hipGetLastError();
     }
-    if (err != hipSuccess) return err;
+    hipError_t err = hipSuccess;
+    if (with_dx && with_gw && dx_mfma == gw_mfma) {
+        err = dx_mfma ? launch_router_grad_mfma(d, io, true, true, partial, blocks, tokens, s)
+                      : launch_router_grad_valu(d, io, true, true, partial, blocks, s);
+    } else {
+        if (with_dx) err = dx_mfma ? launch_router_grad_mfma(d, io, true, false, nullptr, 0, 0, s) : launch_router_grad_valu(d, io, true, false, nullptr, 0, s);
+        if (with_gw && err == hipSuccess)
+            err = gw_mfma ? launch_router_grad_mfma(d, io, false, true, partial, blocks, tokens, s)
+                          : launch_router_grad_valu(d, io, false, true, partial, blocks, s);
+    }
+    if (!with_gw || err != hipSuccess) return err;
     const long long total = (long long)(d.n_groups + d.m_local) * d.d_model;
     SMILE_LAUNCH(gate_weights_reduce_kernel, dim3((unsigned)((total + kThreads - 1) / kThreads)), dim3(kThreads), 0, s,
-                       partial, dw_inter, dw_intra, blocks, d.d_model, d.n_groups, d.m_local);
+                       partial, io.dw_inter, io.dw_intra, blocks, d.d_model, d.n_groups, d.m_local);
     return hipGetLastError();
 }
 

@@ -49,19 +49,32 @@ __device__ __forceinline__ int perm_col(int i) { return 16 * ((i >> 2) & 1) + 4 
 // (wt[column][logit column], bf16); each wave splits the logit gradients of its 32 tokens into bf16 planes once
 // (registers) and then walks the column range 64 columns at a time: 2*KC*3 MFMAs, add the expert-buffer row, round,
 // store; rows are read and written whole (128 bytes of a row per 8 lanes), through a per-wave LDS tile.
+struct DxArgs {
+    const __bf16 *dxe;
+    const int32_t *group_idx, *local_idx, *slot;
+    const float *dlp, *dlq;
+    const __bf16 *w_inter, *w_intra;
+    __bf16 *dx;
+    int T, d, n, m, C, kp;   // kp: 16-wide chunks of inter columns
+};
 template <int KC>
-__global__ __launch_bounds__(kThreads) void dispatch_backward_mfma_kernel(
-    const __bf16 *__restrict__ dxe, const int32_t *__restrict__ group_idx, const int32_t *__restrict__ local_idx,
-    const int32_t *__restrict__ slot, const float *__restrict__ dlp, const float *__restrict__ dlq,
-    const __bf16 *__restrict__ w_inter, const __bf16 *__restrict__ w_intra, __bf16 *__restrict__ dx, int T, int d,
-    int n, int m, int C, int kp)
+struct DxLds {
+    static constexpr int kCols = dx_cols(KC), kStride = KC * 16 + 8;   // row stride of wt in elements (+8: bank spread, keeps 16-byte alignment)
+    __attribute__((aligned(16))) __bf16 wt[kCols * kStride];
+    u32x4 io[kThreads / 64][32 * 9];   // per wave: 32 rows x 8 pieces (+1: bank spread)
+};
+
+template <int KC>
+__device__ __forceinline__ void dispatch_backward_block(const DxArgs &args, DxLds<KC> &lds, int token_block, int col_block)
 {
-    constexpr int kDxCols = dx_cols(KC);
-    constexpr int RS = KC * 16 + 8;   // row stride of wt in elements (+8: bank spread, keeps 16-byte alignment)
-    __shared__ __attribute__((aligned(16))) __bf16 wt[kDxCols * RS];
-    __shared__ u32x4 io[kThreads / 64][32 * 9];   // per wave: 32 rows x 8 pieces (+1: bank spread)
+    constexpr int kDxCols = DxLds<KC>::kCols, RS = DxLds<KC>::kStride;
+    const __bf16 *__restrict__ dxe = args.dxe, *__restrict__ w_inter = args.w_inter, *__restrict__ w_intra = args.w_intra;
+    const int32_t *__restrict__ group_idx = args.group_idx, *__restrict__ local_idx = args.local_idx, *__restrict__ slot = args.slot;
+    const float *__restrict__ dlp = args.dlp, *__restrict__ dlq = args.dlq;
+    __bf16 *__restrict__ dx = args.dx, *const wt = lds.wt;
+    const int T = args.T, d = args.d, n = args.n, m = args.m, C = args.C, kp = args.kp;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c_base = blockIdx.y * kDxCols;
+    const int c_base = col_block * kDxCols;
 
     // ---- weights of this column range, transposed: piece = 8 columns of one weight row
     for (int p = tid; p < KC * 16 * (kDxCols / 8); p += kThreads) {
@@ -77,7 +90,7 @@ __global__ __launch_bounds__(kThreads) void dispatch_backward_mfma_kernel(
     }
 
     // ---- logit gradients of this wave's tokens as bf16 planes: lane = (token lane & 31, k-group lane >> 5)
-    const int t = blockIdx.x * kDxTokens + wave * 32 + (lane & 31), g = lane >> 5;
+    const int t = token_block * kDxTokens + wave * 32 + (lane & 31), g = lane >> 5;
     const bool t_ok = t < T;
     bf16x8 plane[KC][3];
 #pragma unroll
@@ -108,8 +121,8 @@ __global__ __launch_bounds__(kThreads) void dispatch_backward_mfma_kernel(
         const unsigned lo = __shfl((unsigned)p, mrow + 8 * it, 64), hi = __shfl((unsigned)(p >> 32), mrow + 8 * it, 64);
         msrc[it] = reinterpret_cast<const __bf16 *>(((unsigned long long)hi << 32) | lo);
     }
-    const int t_wave = blockIdx.x * kDxTokens + wave * 32;   // first token of the wave
-    u32x4 *tile = io[wave];
+    const int t_wave = token_block * kDxTokens + wave * 32;   // first token of the wave
+    u32x4 *tile = lds.io[wave];
     __syncthreads();
 
     const int arow = perm_col(lane & 31);
@@ -164,20 +177,6 @@ __global__ __launch_bounds__(kThreads) void dispatch_backward_mfma_kernel(
     }
 }
 
-template <int KC>
-hipError_t launch_dx(const smile_layer_desc &d, const void *dxe, const int32_t *group_idx, const int32_t *local_idx,
-                     const int32_t *slot, const float *dlp, const float *dlq, const void *w_inter, const void *w_intra,
-                     void *dx, int kp, hipStream_t s)
-{
-    const dim3 grid((d.T + kDxTokens - 1) / kDxTokens, (d.d_model + dx_cols(KC) - 1) / dx_cols(KC)), block(kThreads);
-    SMILE_LAUNCH(dispatch_backward_mfma_kernel<KC>, grid, block, 0, s, static_cast<const __bf16 *>(dxe), group_idx,
-                       local_idx, slot, dlp, dlq, static_cast<const __bf16 *>(w_inter),
-                       static_cast<const __bf16 *>(w_intra), static_cast<__bf16 *>(dx), d.T, d.d_model, d.n_groups,
-                       d.m_local, d.capacity, kp);
-    return hipGetLastError();
-}
-
-
 // ------------------------------------------------------------------------------------ dW_p, dW_q
 
 constexpr int kGwCb = 256;         // columns of x per workgroup
@@ -195,20 +194,34 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 //   * the planes are written transposed, pl[plane][r][token], by the threads that split the values.
 // The next tile's global loads are in flight while the current one is multiplied.  Tokens are summed in a fixed
 // order and the blocks are added by the reduce kernel in index order: deterministic.
+struct GwArgs {
+    const __bf16 *x;
+    const float *dlp, *dlq;
+    float *partial;
+    int T, d, n, m, tokens_per_block;
+};
 template <int RT>
-__global__ __launch_bounds__(kThreads) void gate_weights_mfma_kernel(
-    const __bf16 *__restrict__ x, const float *__restrict__ dlp, const float *__restrict__ dlq,
-    float *__restrict__ partial, int T, int d, int n, int m, int tokens_per_block)
+struct GwLds {
+    static constexpr int kStride = 64 + 8;   // row stride of a plane in elements (+8: bank spread, keeps 16-byte alignment)
+    u32x4 xs[64 * kGwCb / 8];
+    __attribute__((aligned(16))) __bf16 pl[3][RT * 32][kStride];
+};
+
+template <int RT>
+__device__ __forceinline__ void gate_weights_block(const GwArgs &args, GwLds<RT> &lds, int token_block, int col_block)
 {
     constexpr int PPK = kGwCb / 8;   // 16-byte pieces per token row of the tile
-    constexpr int PS = 64 + 8;       // row stride of a plane in elements (+8: bank spread, keeps 16-byte alignment)
+    constexpr int PS = GwLds<RT>::kStride;
     constexpr int XP = 64 * PPK / kThreads;   // x pieces per thread
     constexpr int DLV = (64 * RT * 32 + kThreads - 1) / kThreads;   // dl values per thread (upper bound)
-    __shared__ u32x4 xs[64 * PPK];
-    __shared__ __attribute__((aligned(16))) __bf16 pl[3][RT * 32][PS];
+    const __bf16 *__restrict__ x = args.x;
+    const float *__restrict__ dlp = args.dlp, *__restrict__ dlq = args.dlq;
+    u32x4 (&xs)[64 * PPK] = lds.xs;
+    __bf16 (&pl)[3][RT * 32][PS] = lds.pl;
+    const int T = args.T, d = args.d, n = args.n, m = args.m;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int c_base = blockIdx.y * kGwCb, R = n + m;
-    const int t_begin = blockIdx.x * tokens_per_block, t_end = min(T, t_begin + tokens_per_block);
+    const int c_base = col_block * kGwCb, R = n + m;
+    const int t_begin = token_block * args.tokens_per_block, t_end = min(T, t_begin + args.tokens_per_block);
 
     // rows of the planes beyond the n + m logit columns stay zero
     for (int i = tid; i < 3 * RT * 32 * PS / 8; i += kThreads) reinterpret_cast<u32x4 *>(&pl[0][0][0])[i] = u32x4{0u, 0u, 0u, 0u};
@@ -301,7 +314,7 @@ __global__ __launch_bounds__(kThreads) void gate_weights_mfma_kernel(
     }
 
     // accumulator element v of a lane: logit column rt*32 + (lane & 31), x column 8*(v/4) + 4*(lane>>5) + v%4
-    float *out = partial + (size_t)blockIdx.x * R * d;
+    float *out = args.partial + (size_t)token_block * R * d;
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         const int r = rt * 32 + (lane & 31);
@@ -318,38 +331,37 @@ __global__ __launch_bounds__(kThreads) void gate_weights_mfma_kernel(
     }
 }
 
-template <int RT>
-hipError_t launch_gw(const smile_layer_desc &d, const void *x, const float *dlp, const float *dlq, float *partial,
-                     int blocks, int tokens_per_block, hipStream_t s)
-{
-    const dim3 grid(blocks, (d.d_model + kGwCb - 1) / kGwCb), block(kThreads);
-    SMILE_LAUNCH(gate_weights_mfma_kernel<RT>, grid, block, 0, s, static_cast<const __bf16 *>(x), dlp, dlq, partial,
-                       d.T, d.d_model, d.n_groups, d.m_local, tokens_per_block);
-    return hipGetLastError();
-}
+// Both products of a backward pass in one launch: they do not depend on each other, and neither fills the chip with latency to spare (few
+// workgroups, or rows that wait for memory).  The first dx.blocks workgroups take dx, the others the router weights.
+struct RouterGradArgs {
+    DxArgs dx;
+    GwArgs gw;
+    int dx_blocks, dx_col_blocks, gw_col_blocks;   // workgroups of the dx part, column blocks of the two parts
+};
 
+// KC, RT 0: without that part
+template <int KC, int RT>
+__global__ __launch_bounds__(kThreads) void router_grad_mfma_kernel(RouterGradArgs a)
+{
+    union Lds {
+        __device__ Lds() {}
+        DxLds<KC ? KC : 2> dx;
+        GwLds<RT ? RT : 1> gw;
+    };
+    __shared__ Lds lds;
+    const int b = blockIdx.x;
+    if (KC && (!RT || b < a.dx_blocks)) {
+        if constexpr (KC) dispatch_backward_block<KC>(a.dx, lds.dx, b / a.dx_col_blocks, b % a.dx_col_blocks);
+    } else {
+        if constexpr (RT) gate_weights_block<RT>(a.gw, lds.gw, (b - a.dx_blocks) / a.gw_col_blocks, (b - a.dx_blocks) % a.gw_col_blocks);
+    }
+}
 }  // namespace
 
 bool dispatch_backward_mfma_applies(const smile_layer_desc &d)
 {
     const int kc = (d.n_groups + 15) / 16 + (d.m_local + 15) / 16;
     return d.dtype == SMILE_DTYPE_BF16 && kc <= kDxMaxChunks && d.d_model % 8 == 0;
-}
-
-hipError_t launch_dispatch_backward_mfma(const smile_layer_desc &d, const void *dxe, const int32_t *group_idx,
-                                         const int32_t *local_idx, const int32_t *slot, const float *dlp,
-                                         const float *dlq, const void *w_inter, const void *w_intra, void *dx,
-                                         hipStream_t s)
-{
-    const int kp = (d.n_groups + 15) / 16, kc = kp + (d.m_local + 15) / 16;
-#define SMILE_DX_CASE(K) \
-    case K: return launch_dx<K>(d, dxe, group_idx, local_idx, slot, dlp, dlq, w_inter, w_intra, dx, kp, s);
-    switch (kc) {
-        SMILE_DX_CASE(2) SMILE_DX_CASE(3) SMILE_DX_CASE(4) SMILE_DX_CASE(5) SMILE_DX_CASE(6) SMILE_DX_CASE(7)
-        SMILE_DX_CASE(8) SMILE_DX_CASE(9) SMILE_DX_CASE(10)
-    default: return hipErrorInvalidValue;
-    }
-#undef SMILE_DX_CASE
 }
 
 bool gate_weights_mfma_applies(const smile_layer_desc &d)
@@ -367,17 +379,58 @@ int gate_weights_mfma_block_tokens(const smile_layer_desc &d, int granule)
     return granule * k;
 }
 
-hipError_t launch_gate_weights_mfma(const smile_layer_desc &d, const void *x, const float *dlp, const float *dlq,
-                                    float *partial, int blocks, int tokens_per_block, hipStream_t s)
+hipError_t launch_router_grad_mfma(const LayerDesc &d, const RouterGradIo &io, bool with_dx, bool with_gw, float *partial, int blocks,
+                                   int tokens_per_block, hipStream_t s)
 {
-    switch ((d.n_groups + d.m_local + 31) / 32) {
-    case 1: return launch_gw<1>(d, x, dlp, dlq, partial, blocks, tokens_per_block, s);
-    case 2: return launch_gw<2>(d, x, dlp, dlq, partial, blocks, tokens_per_block, s);
-    case 3: return launch_gw<3>(d, x, dlp, dlq, partial, blocks, tokens_per_block, s);
-    case 4: return launch_gw<4>(d, x, dlp, dlq, partial, blocks, tokens_per_block, s);
-    case 5: return launch_gw<5>(d, x, dlp, dlq, partial, blocks, tokens_per_block, s);
-    default: return hipErrorInvalidValue;
+    const int kp = (d.n_groups + 15) / 16, kc = kp + (d.m_local + 15) / 16, rt = (d.n_groups + d.m_local + 31) / 32;
+    // One launch for both where the two parts need about the same LDS (39 and 46 KB with two chunks of logit columns), or where there are
+    // few workgroups of dx.  us, dx and router weights apart -> in one launch: 8192 x 768, 2 + 8 columns 12.1 + 9.0 -> 13.9; 8192 x 1600
+    // 19.2 + 11.6 -> 24.3; 32768 x 768, 16 + 8 28.8 + 20.3 -> 44.3; but 65536 x 1024, 32 + 8 (47 and 60 KB, 2048 workgroups) 77.3 + 61.4 -> 146.3.
+    const long long dx_groups = (long long)((d.T + kDxTokens - 1) / kDxTokens) * ((d.d_model + dx_cols(kc) - 1) / dx_cols(kc));
+    if (with_dx && with_gw && (kc > 3 || (kc == 3 && dx_groups > 2 * (d.tune.cus > 0 ? d.tune.cus : 256)))) {
+        const hipError_t err = launch_router_grad_mfma(d, io, true, false, nullptr, 0, 0, s);
+        return err == hipSuccess ? launch_router_grad_mfma(d, io, false, true, partial, blocks, tokens_per_block, s) : err;
     }
+    RouterGradArgs a{};
+    a.dx = {static_cast<const __bf16 *>(io.dxe), io.group_idx, io.local_idx, io.slot, io.dlp, io.dlq, static_cast<const __bf16 *>(io.w_inter),
+            static_cast<const __bf16 *>(io.w_intra), static_cast<__bf16 *>(io.dx), d.T, d.d_model, d.n_groups, d.m_local, d.capacity, kp};
+    a.gw = {static_cast<const __bf16 *>(io.x), io.dlp, io.dlq, partial, d.T, d.d_model, d.n_groups, d.m_local, tokens_per_block};
+    a.dx_col_blocks = (d.d_model + dx_cols(kc) - 1) / dx_cols(kc), a.gw_col_blocks = (d.d_model + kGwCb - 1) / kGwCb;
+    a.dx_blocks = with_dx ? (d.T + kDxTokens - 1) / kDxTokens * a.dx_col_blocks : 0;
+    const dim3 grid(a.dx_blocks + (with_gw ? blocks * a.gw_col_blocks : 0)), block(kThreads);
+#define SMILE_CASE(K, R) SMILE_LAUNCH((router_grad_mfma_kernel<K, R>), grid, block, 0, s, a); break;
+    if (with_dx && with_gw) {
+        switch (kc * 4 + rt) {
+        case 2 * 4 + 1: SMILE_CASE(2, 1)
+        case 3 * 4 + 1: SMILE_CASE(3, 1)
+        case 3 * 4 + 2: SMILE_CASE(3, 2)
+        default: return hipErrorInvalidValue;
+        }
+    } else if (with_dx) {
+        switch (kc) {
+        case 2: SMILE_CASE(2, 0)
+        case 3: SMILE_CASE(3, 0)
+        case 4: SMILE_CASE(4, 0)
+        case 5: SMILE_CASE(5, 0)
+        case 6: SMILE_CASE(6, 0)
+        case 7: SMILE_CASE(7, 0)
+        case 8: SMILE_CASE(8, 0)
+        case 9: SMILE_CASE(9, 0)
+        case 10: SMILE_CASE(10, 0)
+        default: return hipErrorInvalidValue;
+        }
+    } else {
+        switch (rt) {
+        case 1: SMILE_CASE(0, 1)
+        case 2: SMILE_CASE(0, 2)
+        case 3: SMILE_CASE(0, 3)
+        case 4: SMILE_CASE(0, 4)
+        case 5: SMILE_CASE(0, 5)
+        default: return hipErrorInvalidValue;
+        }
+    }
+#undef SMILE_CASE
+    return hipGetLastError();
 }
 
 }  // namespace smile

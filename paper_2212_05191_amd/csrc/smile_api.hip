@@ -466,8 +466,8 @@ smile_status smile_dispatch_backward(smile_ctx *ctx, const void *dxe, const int3
     if (!ctx || bad(dxe) || bad(group_idx) || bad(local_idx) || bad(slot) || bad(dlp) || bad(dlq) || bad(w_inter) ||
         bad(w_intra) || bad(dx))
         return SMILE_INVALID_ARG;
-    return from_hip(launch_dispatch_backward(ctx->desc, dxe, group_idx, local_idx, slot, dlp, dlq, w_inter, w_intra,
-                                             dx, static_cast<hipStream_t>(stream)));
+    const RouterGradIo io{dxe, group_idx, local_idx, slot, dlp, dlq, w_inter, w_intra, dx, nullptr, nullptr, nullptr};
+    return from_hip(launch_router_gradients(ctx->desc, nullptr, io, true, false, static_cast<hipStream_t>(stream)));
 }
 
 smile_status smile_gate_weights_backward(smile_ctx *ctx, const void *x, const float *dlp, const float *dlq,
@@ -478,8 +478,8 @@ smile_status smile_gate_weights_backward(smile_ctx *ctx, const void *x, const fl
     if (!ctx || bad(x) || bad(dlp) || bad(dlq) || bad(dw_inter) || bad(dw_intra)) return SMILE_INVALID_ARG;
     const smile_status st = check_backward_workspace(ctx, workspace, workspace_bytes);
     if (st != SMILE_OK) return st;
-    return from_hip(launch_gate_weights_backward(ctx->desc, workspace, x, dlp, dlq, dw_inter, dw_intra,
-                                                 static_cast<hipStream_t>(stream)));
+    const RouterGradIo io{nullptr, nullptr, nullptr, nullptr, dlp, dlq, nullptr, nullptr, nullptr, x, dw_inter, dw_intra};
+    return from_hip(launch_router_gradients(ctx->desc, workspace, io, false, true, static_cast<hipStream_t>(stream)));
 }
 
 smile_status smile_layer_backward(smile_ctx *ctx, const smile_backward_io *io, float dloss,
@@ -505,11 +505,9 @@ smile_status smile_layer_backward(smile_ctx *ctx, const smile_backward_io *io, f
     if (err == hipSuccess)
         err = launch_expert_ffn_backward(d, workspace, io->xe, io->kept_count, io->w1, io->w2, io->dye, io->h, io->pre,
                                          io->dxe, io->dw1, io->dw2, s);
-    if (err == hipSuccess)
-        err = launch_dispatch_backward(d, io->dxe, io->group_idx, io->local_idx, io->slot, io->dlp, io->dlq,
-                                       io->w_inter, io->w_intra, io->dx, s);
-    if (err == hipSuccess)
-        err = launch_gate_weights_backward(d, workspace, io->x, io->dlp, io->dlq, io->dw_inter, io->dw_intra, s);
+    const RouterGradIo routers{io->dxe, io->group_idx, io->local_idx, io->slot, io->dlp, io->dlq, io->w_inter, io->w_intra, io->dx,
+                               io->x, io->dw_inter, io->dw_intra};
+    if (err == hipSuccess) err = launch_router_gradients(d, workspace, routers, true, true, s);
     return from_hip(err);
 }
 

@@ -504,22 +504,26 @@ hipError_t launch_route_backward(const smile_layer_desc &d, const float *dgate, 
 hipError_t launch_expert_ffn_backward(const LayerDesc &d, void *workspace, const void *xe,
                                       const int32_t *kept_count, const void *w1, const void *w2, const void *dye,
                                       const void *h, const void *pre, void *dxe, void *dw1, void *dw2, hipStream_t s);
-hipError_t launch_dispatch_backward(const LayerDesc &d, const void *dxe, const int32_t *group_idx,
-                                    const int32_t *local_idx, const int32_t *slot, const float *dlp, const float *dlq,
-                                    const void *w_inter, const void *w_intra, void *dx, hipStream_t s);
-// bf16 storage and at most 10 chunks of 16 logit columns: the same product on the matrix cores
+// What the last two steps of the backward pass read and write: the token gradient (smile_dispatch_backward) and the router weights
+// (smile_gate_weights_backward)
+struct RouterGradIo {
+    const void *dxe;
+    const int32_t *group_idx, *local_idx, *slot;
+    const float *dlp, *dlq;
+    const void *w_inter, *w_intra;
+    void *dx;
+    const void *x;
+    float *dw_inter, *dw_intra;
+};
+// with_dx / with_gw: which of the two; both share a launch where that is faster
+hipError_t launch_router_gradients(const LayerDesc &d, void *workspace, const RouterGradIo &io, bool with_dx, bool with_gw, hipStream_t s);
+// bf16 storage and routers of a limited width (at most 10 chunks of 16 logit columns / 160 columns): the products on the matrix cores,
+// the router weights as partial sums of `blocks` token blocks
 bool dispatch_backward_mfma_applies(const smile_layer_desc &d);
-hipError_t launch_dispatch_backward_mfma(const smile_layer_desc &d, const void *dxe, const int32_t *group_idx,
-                                         const int32_t *local_idx, const int32_t *slot, const float *dlp,
-                                         const float *dlq, const void *w_inter, const void *w_intra, void *dx,
-                                         hipStream_t s);
-// bf16 storage and at most 160 logit columns: the per-block partial sums on the matrix cores
 bool gate_weights_mfma_applies(const smile_layer_desc &d);
 int gate_weights_mfma_block_tokens(const smile_layer_desc &d, int granule);
-hipError_t launch_gate_weights_mfma(const smile_layer_desc &d, const void *x, const float *dlp, const float *dlq,
-                                    float *partial, int blocks, int tokens_per_block, hipStream_t s);
-hipError_t launch_gate_weights_backward(const LayerDesc &d, void *workspace, const void *x, const float *dlp,
-                                        const float *dlq, float *dw_inter, float *dw_intra, hipStream_t s);
+hipError_t launch_router_grad_mfma(const LayerDesc &d, const RouterGradIo &io, bool with_dx, bool with_gw, float *partial, int blocks,
+                                   int tokens_per_block, hipStream_t s);
 
 hipError_t launch_aux_loss(const smile_layer_desc &d, const int32_t *group_count, const int32_t *local_count,
                            const float *p_sum, const float *q_sum, float *out3, hipStream_t s);

@@ -425,3 +425,28 @@ def test_router_logit_gradients_at_the_register_edges(torch_cuda, cfg):
     finally:
         a.close()
         b.close()
+
+
+# dx and the partial sums of the router weights in one launch: every pair of matrix-core variants that shares one, and the vector-ALU
+# kernels; token counts and widths that end inside a block of either part
+SHARED_LAUNCH_CASES = [
+    wl.small_config("router_grads_2_1", 645, 320, 64, 16, 16, 5, "bf16", "gelu", seed=81),
+    wl.small_config("router_grads_3_1", 129, 576, 64, 17, 8, 3, "bf16", "gelu", seed=82),
+    wl.small_config("router_grads_3_2", 1025, 192, 64, 32, 16, 4, "bf16", "gelu", seed=83),
+    wl.small_config("router_grads_f16", 259, 320, 64, 5, 12, 6, "f16", "gelu", seed=84),
+    wl.small_config("router_grads_f32", 1, 72, 64, 3, 2, 1, "f32", "gelu", seed=85),
+]
+
+
+@pytest.mark.parametrize("cfg", SHARED_LAUNCH_CASES, ids=lambda c: c.name)
+def test_router_gradients_in_one_launch(torch_cuda, cfg):
+    """The chained pass, whose dx and router-weight products share a launch, has the bits of the separate calls, which match the oracle."""
+    a, b = _forward_backward(cfg), _forward_backward(cfg, chained=True)
+    try:
+        _check_steps(cfg, a)
+        oa, ob = _fetch_backward(a), _fetch_backward(b)
+        for k in ("dx", "dw_inter", "dw_intra"):
+            np.testing.assert_array_equal(oa[k], ob[k], err_msg=k)
+    finally:
+        a.close()
+        b.close()
