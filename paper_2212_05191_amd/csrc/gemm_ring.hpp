@@ -401,6 +401,21 @@ __global__ __launch_bounds__(256, OCC) void grouped_gemm_ring_kernel(RingArgs a)
         constexpr int j = decltype(jj)::value;
         const int row0 = (j < QA0 ? j * 64 : kExt[A0] + (j - QA0) * 64) + wm * 32;   // inside the tile
         if (cur.rt * BM + row0 >= rows) return;
+        // The second factor of the row block is requested before anything of it is staged: one wait in place of two (dpre, us: 128 experts 768 x 3072
+        // 266 -> 260, 1600 x 6400 224 -> 220, 16 experts 768 x 3072 63.3 -> 61.9; for the whole tile at once it spills).  Pieces of part 0, then of 1.
+        u32x4 aux[POST != 0 ? 2 * TN : 1];
+        if constexpr (POST != 0) {
+            for_constants<2>([&](auto part) {
+                constexpr int H = decltype(part)::value, P = (H == 0 ? QB0 : QB1) * 4;
+                const int col0 = cur.ct * BN + (H == 0 ? wn * QB0 * 32 : kExt[B0] + wn * QB1 * 32);
+#pragma unroll
+                for (int it = 0; it < P / 2; ++it) {
+                    const int id = it * 64 + olane, lrow = id / P, row = cur.rt * BM + row0 + lrow, col = col0 + (id - lrow * P) * 8;
+                    aux[(H == 0 ? 0 : 2 * QB0) + it] = *reinterpret_cast<const u32x4 *>(
+                        static_cast<const E *>(a.aux) + (size_t)e * a.sy + (size_t)min(row, rows - 1) * Nout + min(col, Nout - 8));
+                }
+            });
+        }
         for_constants<2>([&](auto part) {
             constexpr int H = decltype(part)::value, QB = H == 0 ? QB0 : QB1, P = QB * 4, NIT = 32 * P / 64;
             const int col0 = cur.ct * BN + (H == 0 ? wn * QB0 * 32 : kExt[B0] + wn * QB1 * 32);
@@ -410,16 +425,6 @@ __global__ __launch_bounds__(256, OCC) void grouped_gemm_ring_kernel(RingArgs a)
                 lrow = id / P;
                 row = cur.rt * BM + row0 + lrow, col = col0 + (id - lrow * P) * 8;
             };
-            u32x4 aux[NIT];
-            if constexpr (POST != 0) {
-#pragma unroll
-                for (int it = 0; it < NIT; ++it) {
-                    int row, col, lrow;
-                    at(it, row, col, lrow);
-                    aux[it] = *reinterpret_cast<const u32x4 *>(static_cast<const E *>(a.aux) + (size_t)e * a.sy +
-                                                               (size_t)min(row, rows - 1) * Nout + min(col, Nout - 8));
-                }
-            }
 #pragma unroll
             for (int pass = 0; pass < (DUAL ? 2 : 1); ++pass) {
 #pragma unroll
@@ -450,8 +455,8 @@ __global__ __launch_bounds__(256, OCC) void grouped_gemm_ring_kernel(RingArgs a)
                         if constexpr (POST != 0) {
 #pragma unroll
                             for (int k = 0; k < 4; ++k)
-                                v[k] = Half<E>::pack(Half<E>::lo(v[k]) * activate_grad<POST>(Half<E>::lo(aux[it][k])),
-                                                     Half<E>::hi(v[k]) * activate_grad<POST>(Half<E>::hi(aux[it][k])));
+                                v[k] = Half<E>::pack(Half<E>::lo(v[k]) * activate_grad<POST>(Half<E>::lo(aux[(H == 0 ? 0 : 2 * QB0) + it][k])),
+                                                     Half<E>::hi(v[k]) * activate_grad<POST>(Half<E>::hi(aux[(H == 0 ? 0 : 2 * QB0) + it][k])));
                         }
                         if (dst) {
                             u32x4 *to = reinterpret_cast<u32x4 *>(dst + (size_t)row * Nout + col);
