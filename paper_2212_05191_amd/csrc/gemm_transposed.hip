@@ -387,6 +387,120 @@ __global__ __launch_bounds__(256, kWorkgroupsPerCu) void grouped_gemm_t_kernel(T
     }   // tile loop
 }
 
+// Weight gradients whose contraction is short: y[e][i][j] = sum over the group's rows of X(i,k) W(j,k), both operands transposed, 128 x 128
+// outputs for a workgroup of four waves.  A tile is a slab or a few of them and then its stores, a serial chain (load, wait, multiply, stage,
+// store) whose latencies no prefetch inside one workgroup covers, so here many workgroups share a CU instead of pipelining one: a
+// single slab buffer (32 KB, which the epilogue stages in) and 128 registers leave room for four, on a plain grid that the hardware
+// deals out.  256 skewed experts (55 rows on average) of 1024 x 4096, 2.15 GB of gradients, us: ring 650, two-stage 649, here 571; with nothing to
+// contract, stores alone, 364 (5.9 TB/s); without the stores 281: a quarter of the time is neither, mostly loads that wait behind stores.
+// Three or five workgroups on a CU instead of four: 571, 585; cached stores 606 and the next kernel 11 % slower.
+// Stores are whole lines (rows of 64 columns, 128 bytes): tiles written in runs of 64 bytes reach 3.9 TB/s, of 128 bytes 5.9.
+// The XCDs take chunks of tiles in turn, as the weight gradients of the ring kernels do (LiveTileWalk).
+template <typename E>
+__global__ __launch_bounds__(256, 4) void weight_gradient_kernel(TGemmArgs<E> a)
+{
+    typedef typename Half<E>::vec8 vec8;
+    typedef __attribute__((__vector_size__(4 * sizeof(E)))) E vec4;
+    constexpr int BM = 128, BN = 128, NW = 4, OPERAND = BK * 256;   // bytes of an operand's slab: [64 k][16 pieces], rotated by 4 * (k & 3)
+    __shared__ __attribute__((aligned(16))) char slab_lds[2 * OPERAND];
+    lds_char *const lds = (lds_char *)slab_lds;
+
+    const int chunks = max(1, (a.tiles + 1023) / 1024), chunk = (a.tiles + 8 * chunks - 1) / (8 * chunks);
+    const int local = blockIdx.x / kXcds, ticket = ((local / chunk) * kXcds + blockIdx.x % kXcds) * chunk + local % chunk;
+    if (ticket >= a.tiles) return;
+    const int per_group = a.row_tiles * a.col_tiles;
+    // neighbours go along the longer side, so that they share the operand tile of the shorter one
+    const int e = ticket / per_group, rem = ticket - e * per_group, fast = a.row_tiles > a.col_tiles ? a.row_tiles : a.col_tiles;
+    const int slow_tile = rem / fast, fast_tile = rem - slow_tile * fast;
+    const int rt = a.row_tiles > a.col_tiles ? fast_tile : slow_tile, ct = a.row_tiles > a.col_tiles ? slow_tile : fast_tile;
+    const int kv = a.k_valid ? min(a.k_valid[e], a.K) : a.K, slabs = (kv + BK - 1) / BK;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), wm = wave & 1, wn = wave >> 1;
+    // loads: instruction wave + 4 i of an operand is its k-rows 4 (wave + 4 i) .. + 3
+    const int krow = lane >> 4, piece = ((lane & 15) - 4 * (krow & 3)) & 15;
+    const E *const x = a.x + (size_t)e * a.sx + min(rt * BM + piece * 8, a.Mrows - 8);
+    const E *const w = a.w + (size_t)e * a.sw + min(ct * BN + piece * 8, a.Nout - 8);
+    const E *const zero = reinterpret_cast<const E *>(kZeroPiece);
+
+    f32x16 acc[2][2];   // [columns][rows] of the wave's 64 x 64
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+
+    // fragments: lane = 16 g + 4 j + b addresses k-row 8 (g / 2) + j and the 4 columns 16 (g % 2) + 4 b of its 32 (see the header)
+    const int tj = (lane >> 2) & 3, tk0 = 8 * (lane >> 5) + tj, tcol = 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+    int xoff[2], woff[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const int xc = wm * 64 + b * 32 + tcol, wc = wn * 64 + b * 32 + tcol;
+        xoff[b] = tk0 * 256 + (((xc >> 3) + 4 * tj) & 15) * 16 + (xc & 4) * 2;
+        woff[b] = OPERAND + tk0 * 256 + (((wc >> 3) + 4 * tj) & 15) * 16 + (wc & 4) * 2;
+    }
+    for (int s = 0; s < slabs; ++s) {
+        if (s > 0) __syncthreads();   // every wave is done with the slab before
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int inst = wave + i * NW, k = s * BK + inst * 4 + krow;
+            __builtin_amdgcn_global_load_lds(SMILE_GPTR(k < kv ? x + (size_t)k * a.ldx : zero), SMILE_LPTR(lds + inst * 1024), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds(SMILE_GPTR(k < kv ? w + (size_t)k * a.ldw : zero), SMILE_LPTR(lds + OPERAND + inst * 1024), 16, 0, 0);
+        }
+        wait_vmcnt<0>();
+        __syncthreads();
+        for_constants<BK / 16>([&](auto kk) {
+            constexpr int AT = decltype(kk)::value * 16 * 256;
+            vec8 xf[2], wf[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                read_transposed<4 * 256>(xf[b], lds + xoff[b] + AT);
+                read_transposed<4 * 256>(wf[b], lds + woff[b] + AT);
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = Half<E>::mfma_32x32x16(wf[i], xf[j], acc[i][j]);
+        });
+    }
+
+    // ---- epilogue: a block of 32 rows x 64 columns of each wave at a time through the wave's own 4 KB (piece c of a row at c ^ ((row >> 1) & 7))
+    if (slabs > 0) __syncthreads();
+    E *const y = a.y + (size_t)e * a.sy;
+    lds_char *const stg = lds + wave * 4096;
+    const int col = ct * BN + wn * 64 + (lane & 7) * 8;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        const int row0 = rt * BM + wm * 64 + j * 32;
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                vec4 out;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) out[v] = (E)acc[i][j][4 * q + v];
+                const int r = lane & 31;
+                *(__attribute__((address_space(3))) vec4 *)(stg + r * 128 + (((i * 4 + q) ^ ((r >> 1) & 7)) * 16) + (lane >> 5) * 8) = out;
+            }
+#pragma unroll
+        for (int it = 0; it < 4; ++it) {
+            const int r = it * 8 + (lane >> 3);
+            const u32x4 v = *(const __attribute__((address_space(3))) u32x4 *)(stg + r * 128 + (((lane & 7) ^ ((r >> 1) & 7)) * 16));
+            // weight gradients are not read again soon: keep them out of the way of the operands in L2
+            if (row0 + r < a.Mrows && col < a.Nout) __builtin_nontemporal_store(v, reinterpret_cast<u32x4 *>(y + (size_t)(row0 + r) * a.Nout + col));
+        }
+    }
+}
+
+template <typename E>
+hipError_t launch_weight_gradient(TGemmArgs<E> a, int N, hipStream_t s)
+{
+    a.row_tiles = (a.Mrows + 127) / 128, a.col_tiles = (a.Nout + 127) / 128, a.tiles = N * a.row_tiles * a.col_tiles, a.N = N;
+    const int chunks = std::max(1, (a.tiles + 1023) / 1024), chunk = (a.tiles + 8 * chunks - 1) / (8 * chunks);
+    SMILE_LAUNCH(weight_gradient_kernel<E>, dim3(8 * chunks * chunk), dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+
 template <typename E, int BM, int BN, bool XT, bool WT, int POST>
 hipError_t launch_tile(TGemmArgs<E> a, int N, const Tuning &tune, hipStream_t s)
 {
@@ -406,14 +520,15 @@ hipError_t launch_tile(TGemmArgs<E> a, int N, const Tuning &tune, hipStream_t s)
     return hipGetLastError();
 }
 
-// wide: 192 columns a tile (weight gradients only)
+// wide: 192 columns a tile; short_sums: weight_gradient_kernel (weight gradients only)
 template <typename E>
-hipError_t launch_typed(const TransposedGemm &g, bool wide, hipStream_t s)
+hipError_t launch_typed(const TransposedGemm &g, bool wide, bool short_sums, hipStream_t s)
 {
     TGemmArgs<E> a{static_cast<const E *>(g.x), static_cast<const E *>(g.w), static_cast<E *>(g.y),
                    static_cast<const E *>(g.aux), g.rows_valid, g.k_valid, g.Mrows, g.Nout, g.K, g.ldx, g.ldw,
                    g.sx, g.sw, g.sy, 0, 0, 0, g.N};
     if (g.x_transposed) {
+        if (short_sums) return launch_weight_gradient<E>(a, g.N, s);
         if (wide) return launch_tile<E, 128, 192, true, true, 0>(a, g.N, g.tune, s);
         return launch_tile<E, 128, 128, true, true, 0>(a, g.N, g.tune, s);
     }
@@ -439,7 +554,7 @@ hipError_t launch_grouped_gemm_t(int dtype, const TransposedGemm &g, hipStream_t
                                                 : pick_ring_tile(g.tune, a, std::min(g.rows_valid ? expected : INT_MAX, g.Mrows), true);
     const bool wide = g.x_transposed && tile == kRing128x192x2;
     // The two-stage kernel keeps what is over before a ring pays.
-    //   * Weight gradients of few rows, by the rows a group is expected to contract and not by its buffer: they are bound by their
+    //   * Weight gradients of few rows and few tiles, by the rows a group is expected to contract and not by its buffer: they are bound by their
     //     stores, which leave here in whole rows of a tile and from the ring in runs of 64 and 128 bytes.  Up to 320 rows where the
     //     tiles are 128 wide, 192 where they are 192 wide.  us, both kernels in the width they take, dW2: 96 experts x 80 rows in
     //     buffers of 80, 1024 x 4096 283, ring 313; 64 x 96 in 144, 768 x 3072 114 and 133; 48 x 96 in 144, 1600 x 6400 340 and 381;
@@ -448,13 +563,21 @@ hipError_t launch_grouped_gemm_t(int dtype, const TransposedGemm &g, hipStream_t
     //   * Other products with rows for half a tile, less than eight slabs and at most two tiles per CU, or four slabs and at most one
     //     tile per CU, where the plain grid needs no walk (us: 111 experts x 4 rows, 128 x 384: dxe 6.2, ring 6.5; 43 x 10, 192 x 768:
     //     dpre 6.6 and 7.3; but 27 x 11, 128 x 512: dxe, eight slabs, 7.6 and 7.1; 7 x 600, 320 x 1280: dpre 16.3 and 12.1).
-    const long long tiles = (long long)g.N * ((g.Mrows + 127) / 128) * ((g.Nout + 127) / 128);
-    const bool small = g.x_transposed ? std::min(g.k_valid ? expected : INT_MAX, g.K) <= (wide ? 192 : 320)
+    const long long tiles = (long long)g.N * ((g.Mrows + 127) / 128) * ((g.Nout + 127) / 128);   // of 128 x 128
+    // With more than four tiles per CU, weight gradients of at most 256 expected rows take weight_gradient_kernel, which hides a tile's chain behind the
+    // other workgroups of its CU.  us, dW2 / dW1, the better one of the ring and the two-stage kernel first: 16 experts x 125 rows, 768 x 3072
+    // 22.4 / 22.4 -> 20.7 / 21.3; x 188 26.5 / 26.6 -> 25.4 / 25.4; x 256 32.7 / 34.1 -> 32.8 / 31.1; x 288 (not taken) 36.0 / 33.9 -> 34.9 / 35.7; x 375 (not
+    // taken) 43.4 / 42.4 -> 45.3 / 47.4; 64 experts x 140 rows 117 / 116 -> 108 / 108; x 256, 1024 x 4096 264 / 274 -> 252 / 246; 48 x 188, 1600 x 6400
+    // 383 / 383 -> 362 / 368; 256 skewed experts, 1024 x 4096 650 / 662 -> 571 / 570; 128 x 234, 256 x 768 26.4 / 26.4 -> 27.8 / 24.9.  With fewer tiles nothing
+    // hides the chain: 32 x 200, 256 x 1024 (512 tiles) 8.0 / 7.9 -> 8.7 / 8.5; 21 x 238, 192 x 576 6.0 / 6.1 -> 6.5 / 6.5.
+    const bool short_sums = g.x_transposed && g.tune.tgemm_tile < 0 && tiles > 4LL * (g.tune.cus > 0 ? g.tune.cus : 256) &&
+                            std::min(g.k_valid ? expected : INT_MAX, g.K) <= 256;
+    const bool small = g.x_transposed ? short_sums || std::min(g.k_valid ? expected : INT_MAX, g.K) <= (wide ? 192 : 320)
                                       : (g.Mrows <= 64 && g.K < 512 && tiles <= 2 * g.tune.cus) || (g.K <= 256 && tiles <= g.tune.cus);
     if ((g.tune.tgemm_tile > 0 || (g.tune.tgemm_tile < 0 && !small)) && ring_applies(a, g.Mrows, g.x_transposed, true))
         return launch_ring_gradient(dtype, a, g.x_transposed, g.post, tile, g.tune, s);
-    if (dtype == SMILE_DTYPE_BF16) return launch_typed<__bf16>(g, wide, s);
-    return launch_typed<_Float16>(g, wide, s);
+    if (dtype == SMILE_DTYPE_BF16) return launch_typed<__bf16>(g, wide, short_sums, s);
+    return launch_typed<_Float16>(g, wide, short_sums, s);
 }
 
 }  // namespace smile

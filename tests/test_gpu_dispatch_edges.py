@@ -533,3 +533,35 @@ def test_weight_gradients_by_expected_rows(torch_cuda, cfg, two_stage, monkeypat
         assert sum("grouped_gemm_ring" in k for k in names) == want, names
         assert all(torch_cuda.equal(a, b) for a, b in zip(got, other)), tile
     assert all(float(a.float().abs().sum()) > 0 for a in got)
+
+
+# Weight gradients of short sums and many tiles (weight_gradient_kernel): experts of no row, of one slab, of several and a ragged one, tiles that end
+# inside, and both sides of the lines (256 expected rows; more than four 128 x 128 tiles per CU)
+SHORT_SUMS = [
+    (wl.small_config("dw_short_one_slab", 900, 320, 320, 13, 10, 9, "bf16", "relu", skew=True, seed=401), 2),
+    (wl.small_config("dw_short_f16_ragged", 4000, 576, 704, 8, 5, 200, "f16", "relu", skew=True, seed=402), 2),
+    (wl.small_config("dw_short_256_rows", 30 * 256, 768, 704, 6, 5, 300, "bf16", "relu", skew=True, seed=403), 2),
+    (wl.small_config("dw_short_257_rows", 30 * 256 + 1, 768, 704, 6, 5, 300, "bf16", "relu", skew=True, seed=404), 0),
+    (wl.small_config("dw_short_four_tiles_per_cu", 2000, 256, 1024, 8, 8, 40, "bf16", "relu", skew=True, seed=405), 0),
+]
+
+
+@pytest.mark.parametrize("cfg,short", SHORT_SUMS, ids=lambda c: getattr(c, "name", str(c)))
+def test_weight_gradients_of_short_sums(torch_cuda, cfg, short, monkeypatch):
+    """The bits of the ring and of the two-stage kernel (a row's products are added in the order of k by all three)."""
+    from paper_2212_05191_amd.runner import GpuLayer
+    monkeypatch.delenv("SMILE_TGEMM_TILE", raising=False)
+    layer = GpuLayer(cfg)
+    try:
+        layer.forward()
+        layer.prepare_backward(wl.gen_output_grad(cfg))
+        layer.bwd.dw1.fill_(-77)
+        layer.bwd.dw2.fill_(-77)
+        names = _launched(layer, layer.backward)
+        assert sum("weight_gradient_kernel" in k for k in names) == short, names
+        got = [layer.bwd.dw1.cpu(), layer.bwd.dw2.cpu()]
+    finally:
+        layer.close()
+    for tile in ("0", "1"):
+        other, _ = _weight_gradients(torch_cuda, cfg, tile, monkeypatch)
+        assert all(torch_cuda.equal(a, b) for a, b in zip(got, other)), tile
