@@ -43,6 +43,7 @@
 // LDS) before it can exit, in turn with the live ones.
 //
 // fp32 storage: gemm_f32.hip.
+#include <algorithm>
 #include <type_traits>
 
 #include <hip/hip_ext.h>
@@ -445,15 +446,22 @@ RingArgs ring_args(const GemmArgs &g, int N)
 // Tile choice; Tuning::ffn_tile (0..9 without 6) overrides it for tuning runs.  Large buffers take the ring kernels
 // (pick_ring_tile).  Small buffers and narrow layers leave most of the chip
 // without a 128-row tile (16 experts x 768 columns: 64 tiles of 192 columns on 256 CUs, each a serial chain of K / 64 slabs),
-// so they take 64-row tiles as long as those are few; the counts are those of 64 x 64 tiles over the whole buffers.  bf16, us:
+// so they take 64-row tiles as long as those are few; the counts are those of 64 x 64 tiles over the whole buffers, or, where an expert
+// expects more than one row tile, over the rows it expects (tiles of empty rows exit at once).  bf16, us:
 //   * up, one round of three workgroups per CU (<= 768): 64 x 64, three stages.  16 experts x 16 rows, 768 -> 3072: 22.3 -> 15.9;
-//     32 x 188 rows, 256 -> 512: 10.8 -> 6.6; 4 x 100 rows, 960 -> 3840: 19.9 -> 9.1.  Beyond the line, 16 x 80 rows (1536 tiles): 24.4 -> 28.2.
+//     32 x 188 rows, 256 -> 512: 10.8 -> 6.6; 4 x 100 rows, 960 -> 3840: 19.9 -> 9.1.  Beyond the line, 16 x 80 rows (1536 tiles): 24.4 -> 28.2.  Up to
+//     320, about one a CU, with a fourth stage: 5 x 28 rows, 704 -> 2816 (220) 6.9 -> 5.9, 4 x 35, 960 -> 2880 (180) 7.9 -> 6.9, 32 x 15, 192 -> 576
+//     (288) 4.8 -> 4.4; 21 x 58, 320 -> 640 (420) 5.4 -> 5.6.
 //   * up, buffers of at most 64 rows: 64 x 128 up to 8192 (64 x 6 rows, 1024 -> 4096: 107.6 -> 93.1; 128 x 16, 768 -> 3072: 123.8 -> 114.8),
 //     beyond that the chip is full anyway and 64 x 256 reads the token rows least often (256 x 63 rows, 1024 -> 4096: 444.6 -> 404.4; 64 x 128: 415.1).
-//   * down, two rounds of two per CU (<= 1024): 64 x 64 with four stages, K is long.  16 x 16 rows, 3072 -> 768: 31.0 -> 17.2;
-//     8 x 469 rows, 1024 -> 256: 17.2 -> 7.2; 64 x 6, 4096 -> 1024: 123.1 -> 97.0; at 768 of 256 rows 44.8 -> 42.7-44.1, at 1536 of 512 rows 46.9 -> 75.2.
-//   * down, buffers of at most 64 rows: 64 x 128 up to 2048 (128 x 16 rows, 3072 -> 768: 117.0 -> 104.9), then 64 x 256
-//     (256 x 63 rows, 4096 -> 1024: 374.9 -> 369.2; 64 x 128: 379.8).
+//   * down, one round of two per CU (<= 512): 64 x 64 with four stages, K is long.  16 x 16 rows, 3072 -> 768: 31.0 -> 17.2;
+//     8 x 469 rows, 1024 -> 256: 17.2 -> 7.2; 64 x 6, 4096 -> 1024: 123.1 -> 97.0; 5 x 488 rows, 3072 -> 768 (480 of 600 expected) 22.1, ring 26.8.
+//   * down, a second round of those (to 1024) is where the ring's 128-row tiles are faster: 16 x 209 rows, 3840 -> 960 (960) 64.4 -> 39.2; 32 x 79,
+//     3584 -> 896 (896) 62.8 -> 50.5; 5 x 395, 2816 -> 1408 (770) 35.1 -> 26.4; 16 x 256, 3072 -> 768 (768) 35.4 -> 31.0.  What narrow layers have to
+//     768 fits one round of three per CU with three stages: 21 x 644, 576 -> 192 (693) 11.4 -> 8.8, ring 9.4; 32 x 244, 1024 -> 256 (512)
+//     14.7 -> 11.8, ring 12.4; so do buffers of at most 64 rows, which would leave half of a 128-row tile empty: 128 x 26, 1536 -> 384 34.8 -> 31.0.
+//   * down, buffers of at most 64 rows: 64 x 128 up to 2048 (128 x 16 rows, 3072 -> 768: 117.0 -> 104.9; 64 x 41, 2880 -> 960 (960): 64 x 64 76.5, 72.3),
+//     then 64 x 256 (256 x 63 rows, 4096 -> 1024: 374.9 -> 369.2; 64 x 128: 379.8).
 // Every tile adds a row's products in the same order: the results are the same bits.
 int pick_tile(const Tuning &tune, const GemmArgs &g, int N)
 {
@@ -461,17 +469,22 @@ int pick_tile(const Tuning &tune, const GemmArgs &g, int N)
     const RingArgs ring = ring_args(g, N);
     const bool ring_ok = ring_applies(ring, g.x_rows ? g.tokens : C, false, false);
     if (tune.ffn_tile >= 0 && tune.ffn_tile != 6) return is_ring_tile(tune.ffn_tile) && !ring_ok ? 0 : tune.ffn_tile;
-    const long long small = (long long)N * ((C + 63) / 64) * ((Nout + 63) / 64);   // 64 x 64 tiles
+    const long long cols = (Nout + 63) / 64, small = N * ((C + 63ll) / 64) * cols;   // 64 x 64 tiles
+    const int rows = g.tokens > 0 ? std::min(C, (g.tokens - 1) / N + 1) : C;          // that an expert expects
     if (Nout >= K) {
+        if (small <= 320) return 7;
         if (small <= 768) return 9;
         if (C <= 64) return small <= 8192 ? 8 : 5;
-    } else {
-        if (small <= 1024) return 7;
-        if (C <= 64) return small <= 2048 ? 8 : 5;
+    } else if (small <= 1024) {
+        const long long live = rows > 64 ? N * ((rows + 63ll) / 64) * cols : small;
+        if (live <= 512 || !ring_ok) return 7;
+        if (C <= 64) return small <= 768 ? 9 : 8;
+        if (live <= 768 && Nout <= 320) return 9;
+    } else if (C <= 64) {
+        return small <= 2048 ? 8 : 5;
     }
     if (!ring_ok) return 0;
-    const int rows = g.tokens > 0 ? (g.tokens + N - 1) / N : C;
-    return kRingTile0 + pick_ring_tile(tune, ring, rows < C ? rows : C, false);
+    return kRingTile0 + pick_ring_tile(tune, ring, rows, false);
 }
 
 // dtype dispatch of the two MFMA launchers
