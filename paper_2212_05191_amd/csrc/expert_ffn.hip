@@ -452,6 +452,10 @@ RingArgs ring_args(const GemmArgs &g, int N)
 //     32 x 188 rows, 256 -> 512: 10.8 -> 6.6; 4 x 100 rows, 960 -> 3840: 19.9 -> 9.1.  Beyond the line, 16 x 80 rows (1536 tiles): 24.4 -> 28.2.  Up to
 //     320, about one a CU, with a fourth stage: 5 x 28 rows, 704 -> 2816 (220) 6.9 -> 5.9, 4 x 35, 960 -> 2880 (180) 7.9 -> 6.9, 32 x 15, 192 -> 576
 //     (288) 4.8 -> 4.4; 21 x 58, 320 -> 640 (420) 5.4 -> 5.6.
+//   * up, one round of two per CU of 64 x 128 (<= 512 of them): 16 experts x 203 rows, 256 -> 1024: 9.5 -> 8.1; 21 x 173, 320 -> 960 11.8 -> 9.0; 4 x
+//     107, 1152 -> 3456 15.4 -> 13.8; at 528 16 x 185, 448 -> 1344 13.0 -> 14.0.  Contractions of one slab, and of two up to 4096 tiles, which
+//     have nothing to pipeline: 64 x 551, 128 -> 256 21.1 -> 14.9, 128 x 591, 64 -> 256 29.2 -> 22.8, 16 x 4063, 64 -> 256 22.4 -> 18.6; two slabs, 16 x 4063,
+//     128 -> 512 (8192) 33.6 -> 37.2.
 //   * up, buffers of at most 64 rows: 64 x 128 up to 8192 (64 x 6 rows, 1024 -> 4096: 107.6 -> 93.1; 128 x 16, 768 -> 3072: 123.8 -> 114.8),
 //     beyond that the chip is full anyway and 64 x 256 reads the token rows least often (256 x 63 rows, 1024 -> 4096: 444.6 -> 404.4; 64 x 128: 415.1).
 //   * down, one round of two per CU (<= 512): 64 x 64 with four stages, K is long.  16 x 16 rows, 3072 -> 768: 31.0 -> 17.2;
@@ -475,6 +479,7 @@ int pick_tile(const Tuning &tune, const GemmArgs &g, int N)
         if (small <= 320) return 7;
         if (small <= 768) return 9;
         if (C <= 64) return small <= 8192 ? 8 : 5;
+        if (K <= 64 || (K < 192 && small <= 4096) || N * ((C + 63ll) / 64) * ((Nout + 127) / 128) <= 512) return 8;
     } else if (small <= 1024) {
         const long long live = rows > 64 ? N * ((rows + 63ll) / 64) * cols : small;
         if (live <= 512 || !ring_ok) return 7;

@@ -565,3 +565,43 @@ def test_weight_gradients_of_short_sums(torch_cuda, cfg, short, monkeypatch):
     for tile in ("0", "1"):
         other, _ = _weight_gradients(torch_cuda, cfg, tile, monkeypatch)
         assert all(torch_cuda.equal(a, b) for a, b in zip(got, other)), tile
+
+
+# Both sides of the lines between the 64-row tiles and the others in pick_tile: what takes another tile than before, against 128 x 192 tiles
+PICK_TILE_EDGES = [
+    wl.small_config("up_320_small_tiles", 700, 192, 640, 8, 4, 40, "bf16", "gelu", skew=True, seed=411),
+    wl.small_config("up_330_small_tiles_f16", 700, 192, 704, 10, 3, 40, "f16", "relu", skew=True, seed=412),
+    wl.small_config("up_one_round_of_64x128", 3000, 192, 1024, 4, 4, 256, "bf16", "gelu", skew=True, seed=413),
+    wl.small_config("up_beyond_one_round_of_64x128", 3000, 192, 1024, 4, 4, 257, "bf16", "relu", skew=True, seed=414),
+    wl.small_config("up_one_slab_ragged", 5000, 64, 320, 8, 5, 150, "bf16", "gelu", skew=True, seed=415),
+    wl.small_config("up_two_slabs_f16", 5000, 128, 320, 8, 5, 150, "f16", "gelu", skew=True, seed=416),
+    wl.small_config("down_512_of_600_live", 16 * 250, 512, 1024, 4, 4, 300, "bf16", "relu", skew=True, seed=417),
+    wl.small_config("down_narrow_768", 32 * 250, 192, 768, 8, 4, 300, "bf16", "relu", skew=True, seed=418),
+    wl.small_config("down_second_round", 16 * 210, 960, 1920, 4, 4, 210, "bf16", "relu", skew=True, seed=419),
+    wl.small_config("down_64_rows_768", 600, 384, 768, 16, 8, 64, "bf16", "relu", skew=True, seed=420),
+    wl.small_config("down_64_rows_896", 600, 448, 896, 16, 8, 64, "f16", "relu", skew=True, seed=421),
+]
+
+
+@pytest.mark.parametrize("cfg", PICK_TILE_EDGES, ids=lambda c: c.name)
+def test_tiles_of_medium_products(torch_cuda, cfg, monkeypatch):
+    """The library's tiles give the bits of 128 x 192 tiles in every form of the forward pass (every tile adds in the order of k)."""
+    from paper_2212_05191_amd.runner import GpuLayer
+    got = {}
+    for tile in ("0", ""):
+        monkeypatch.setenv("SMILE_FFN_TILE", tile) if tile else monkeypatch.delenv("SMILE_FFN_TILE", raising=False)
+        layer, _, _ = _layer_with_biases(cfg)
+        try:
+            layer.forward_fused()
+            got[tile, "y"] = layer.buf.y.cpu()
+            layer.enable_saved_activations()
+            layer.h_save.zero_(), layer.pre_save.zero_()
+            layer.buf.y.fill_(-7)
+            layer.forward()
+            torch_cuda.cuda.synchronize()
+            got[tile, "y_saving"], got[tile, "h"], got[tile, "pre"] = layer.buf.y.cpu(), layer.h_save.cpu(), layer.pre_save.cpu()
+        finally:
+            layer.close()
+    assert torch_cuda.equal(got["", "y"], got["", "y_saving"]) and float(got["", "y"].float().abs().sum()) > 0
+    for k in ("y", "y_saving", "h", "pre"):
+        assert torch_cuda.equal(got["0", k], got["", k]), k
