@@ -450,3 +450,26 @@ def test_router_gradients_in_one_launch(torch_cuda, cfg):
     finally:
         a.close()
         b.close()
+
+
+# Partial sums of the router weights over more blocks than the runs that add them side by side (of 8: some empty, a ragged last one), and
+# with one thread an element
+REDUCE_CASES = [
+    wl.small_config("reduce_1_block", 100, 64, 64, 2, 3, 40, "bf16", "relu", seed=91),
+    wl.small_config("reduce_9_blocks", 1100, 72, 64, 2, 3, 300, "f32", "relu", seed=92),
+    wl.small_config("reduce_79_blocks", 10000, 64, 64, 2, 3, 2000, "bf16", "relu", seed=93),
+    wl.small_config("reduce_wide_10_blocks", 1200, 576, 64, 1, 129, 20, "bf16", "relu", seed=94),
+]
+
+
+@pytest.mark.parametrize("cfg", REDUCE_CASES, ids=lambda c: c.name)
+def test_router_weight_sums_over_blocks(torch_cuda, cfg):
+    """fp32 sums of at most 10000 products of values near 1: 1e-5 of the largest, as for the other fp32 sums."""
+    layer = _forward_backward(cfg, chained=True)
+    try:
+        out = _fetch_backward(layer)
+        x = parity.host_inputs(cfg)[0]
+        dwi, dwq = oracle.gate_weights_backward(x, out["dlp"].astype(np.float64), out["dlq"].astype(np.float64))
+        assert normwise(out["dw_inter"], dwi) <= TOL_F32_SUM and normwise(out["dw_intra"], dwq) <= TOL_F32_SUM
+    finally:
+        layer.close()
