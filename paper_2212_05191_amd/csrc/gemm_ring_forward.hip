@@ -113,7 +113,13 @@ RingTile pick_ring_tile(const Tuning &tune, const RingArgs &a, int rows, bool gr
     else if (padded(192) * 10 > padded(128) * 11)
         best = gradient && padded(256) * 10 <= padded(128) * 12 ? kRing128x256 : kRing128x128x2;
     else best = rows >= a.Mrows && a.Mrows > 128 ? kRing256x192 : kRing128x256;
-    if (rounds(tune, a, rows, best) > 3.0) return best;
+    if (rounds(tune, a, rows, best) > 3.0) {
+        // Where a second 256-row tile is filled to a half at most, three of 128 rows pad less (us: down, 128 experts x 320 rows, 3072 -> 768, 291 ->
+        // 263; 64 x 320, 5120 -> 1280, 436 -> 341, x 288 417 -> 364; dxe, 128 x 320, 283 -> 244; skewed counts 143 -> 134, 222 -> 214).  One of
+        // fewer than 32 rows costs little: 64 x 272, 5120 -> 1280, 321 and 370.
+        if (best == kRing256x192 && a.Mrows >= 288 && estimated_time(tune, a, rows, kRing128x256) < 0.9 * estimated_time(tune, a, rows, best)) return kRing128x256;
+        return best;
+    }
     double time = estimated_time(tune, a, rows, best) / 1.15;
     for (const RingTile t : {kRing128x128x2, kRing128x192x2, kRing128x256}) {
         if (is_short && t == kRing128x256) continue;

@@ -580,6 +580,7 @@ PICK_TILE_EDGES = [
     wl.small_config("down_second_round", 16 * 210, 960, 1920, 4, 4, 210, "bf16", "relu", skew=True, seed=419),
     wl.small_config("down_64_rows_768", 600, 384, 768, 16, 8, 64, "bf16", "relu", skew=True, seed=420),
     wl.small_config("down_64_rows_896", 600, 448, 896, 16, 8, 64, "f16", "relu", skew=True, seed=421),
+    wl.small_config("down_290_rows_of_many_experts", 104 * 290, 768, 832, 13, 8, 290, "bf16", "relu", skew=True, seed=422),
 ]
 
 
