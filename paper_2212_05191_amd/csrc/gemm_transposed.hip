@@ -11,6 +11,7 @@
 //
 // Most of these products run on the ring kernels (gemm_ring.hpp).  The two-stage kernel below takes weight gradients of few rows and
 // other small products (launch_grouped_gemm_t), normal operands of fewer than three slabs and operands whose offsets need more than 32 bits.
+// weight_gradient_kernel takes the weight gradients of short sums where there are many tiles.
 //
 // Design (gfx950):
 //   * global -> LDS with the direct 16-byte loads of the forward kernel, two stages of K slabs
