@@ -59,19 +59,20 @@ struct DxArgs {
 };
 template <int KC>
 struct DxLds {
-    static constexpr int kCols = dx_cols(KC), kStride = KC * 16 + 8;   // row stride of wt in elements (+8: bank spread, keeps 16-byte alignment)
-    __attribute__((aligned(16))) __bf16 wt[kCols * kStride];
-    u32x4 io[kThreads / 64][32 * 9];   // per wave: 32 rows x 8 pieces (+1: bank spread)
+    static constexpr int kStride = KC * 16 + 8;   // row stride of the weights in elements (+8: bank spread, keeps 16-byte alignment)
+    typedef __bf16 Weights[dx_cols(KC) * kStride] __attribute__((aligned(16)));
+    typedef u32x4 Rows[kThreads / 64][32 * 9];     // per wave: 32 rows x 8 pieces (+1: bank spread)
 };
 
 template <int KC>
-__device__ __forceinline__ void dispatch_backward_block(const DxArgs &args, DxLds<KC> &lds, int token_block, int col_block)
+__device__ __forceinline__ void dispatch_backward_block(const DxArgs &args, typename DxLds<KC>::Weights &wt, typename DxLds<KC>::Rows &io, int token_block,
+                                                        int col_block)
 {
-    constexpr int kDxCols = DxLds<KC>::kCols, RS = DxLds<KC>::kStride;
+    constexpr int kDxCols = dx_cols(KC), RS = DxLds<KC>::kStride;
     const __bf16 *__restrict__ dxe = args.dxe, *__restrict__ w_inter = args.w_inter, *__restrict__ w_intra = args.w_intra;
     const int32_t *__restrict__ group_idx = args.group_idx, *__restrict__ local_idx = args.local_idx, *__restrict__ slot = args.slot;
     const float *__restrict__ dlp = args.dlp, *__restrict__ dlq = args.dlq;
-    __bf16 *__restrict__ dx = args.dx, *const wt = lds.wt;
+    __bf16 *__restrict__ dx = args.dx;
     const int T = args.T, d = args.d, n = args.n, m = args.m, C = args.C, kp = args.kp;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c_base = col_block * kDxCols;
@@ -122,7 +123,7 @@ __device__ __forceinline__ void dispatch_backward_block(const DxArgs &args, DxLd
         msrc[it] = reinterpret_cast<const __bf16 *>(((unsigned long long)hi << 32) | lo);
     }
     const int t_wave = token_block * kDxTokens + wave * 32;   // first token of the wave
-    u32x4 *tile = lds.io[wave];
+    u32x4 *tile = io[wave];
     __syncthreads();
 
     const int arow = perm_col(lane & 31);
@@ -203,12 +204,13 @@ struct GwArgs {
 template <int RT>
 struct GwLds {
     static constexpr int kStride = 64 + 8;   // row stride of a plane in elements (+8: bank spread, keeps 16-byte alignment)
-    u32x4 xs[64 * kGwCb / 8];
-    __attribute__((aligned(16))) __bf16 pl[3][RT * 32][kStride];
+    typedef u32x4 Tokens[64 * kGwCb / 8];
+    typedef __bf16 Planes[3][RT * 32][kStride] __attribute__((aligned(16)));
 };
 
 template <int RT>
-__device__ __forceinline__ void gate_weights_block(const GwArgs &args, GwLds<RT> &lds, int token_block, int col_block)
+__device__ __forceinline__ void gate_weights_block(const GwArgs &args, typename GwLds<RT>::Tokens &xs, typename GwLds<RT>::Planes &pl, int token_block,
+                                                   int col_block)
 {
     constexpr int PPK = kGwCb / 8;   // 16-byte pieces per token row of the tile
     constexpr int PS = GwLds<RT>::kStride;
@@ -216,8 +218,6 @@ __device__ __forceinline__ void gate_weights_block(const GwArgs &args, GwLds<RT>
     constexpr int DLV = (64 * RT * 32 + kThreads - 1) / kThreads;   // dl values per thread (upper bound)
     const __bf16 *__restrict__ x = args.x;
     const float *__restrict__ dlp = args.dlp, *__restrict__ dlq = args.dlq;
-    u32x4 (&xs)[64 * PPK] = lds.xs;
-    __bf16 (&pl)[3][RT * 32][PS] = lds.pl;
     const int T = args.T, d = args.d, n = args.n, m = args.m;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c_base = col_block * kGwCb, R = n + m;
@@ -339,21 +339,35 @@ struct RouterGradArgs {
     int dx_blocks, dx_col_blocks, gw_col_blocks;   // workgroups of the dx part, column blocks of the two parts
 };
 
-// KC, RT 0: without that part
+// KC, RT 0: without that part, its LDS and its registers.  What one part alone needs are arrays of their own, which the compiler can tell
+// apart; the parts that share a launch share their LDS.
 template <int KC, int RT>
 __global__ __launch_bounds__(kThreads) void router_grad_mfma_kernel(RouterGradArgs a)
 {
-    union Lds {
-        __device__ Lds() {}
-        DxLds<KC ? KC : 2> dx;
-        GwLds<RT ? RT : 1> gw;
-    };
-    __shared__ Lds lds;
     const int b = blockIdx.x;
-    if (KC && (!RT || b < a.dx_blocks)) {
-        if constexpr (KC) dispatch_backward_block<KC>(a.dx, lds.dx, b / a.dx_col_blocks, b % a.dx_col_blocks);
+    if constexpr (RT == 0) {
+        __shared__ typename DxLds<KC>::Weights wt;
+        __shared__ typename DxLds<KC>::Rows io;
+        dispatch_backward_block<KC>(a.dx, wt, io, b / a.dx_col_blocks, b % a.dx_col_blocks);
+    } else if constexpr (KC == 0) {
+        __shared__ typename GwLds<RT>::Tokens xs;
+        __shared__ typename GwLds<RT>::Planes pl;
+        gate_weights_block<RT>(a.gw, xs, pl, b / a.gw_col_blocks, b % a.gw_col_blocks);
     } else {
-        if constexpr (RT) gate_weights_block<RT>(a.gw, lds.gw, (b - a.dx_blocks) / a.gw_col_blocks, (b - a.dx_blocks) % a.gw_col_blocks);
+        union Lds {
+            __device__ Lds() {}
+            struct {
+                typename DxLds<KC>::Weights wt;
+                typename DxLds<KC>::Rows io;
+            } dx;
+            struct {
+                typename GwLds<RT>::Tokens xs;
+                typename GwLds<RT>::Planes pl;
+            } gw;
+        };
+        __shared__ Lds lds;
+        if (b < a.dx_blocks) dispatch_backward_block<KC>(a.dx, lds.dx.wt, lds.dx.io, b / a.dx_col_blocks, b % a.dx_col_blocks);
+        else gate_weights_block<RT>(a.gw, lds.gw.xs, lds.gw.pl, (b - a.dx_blocks) / a.gw_col_blocks, (b - a.dx_blocks) % a.gw_col_blocks);
     }
 }
 }  // namespace

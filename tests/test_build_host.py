@@ -1,5 +1,11 @@
-"""Host-side checks of the build script's incremental rule (no compiler is run)."""
+"""Host-side checks of the build script's incremental rule and of what the built kernels hold (no compiler is run)."""
 import os
+import re
+import shutil
+import struct
+import subprocess
+
+import pytest
 
 from paper_2212_05191_amd import build as B
 
@@ -42,3 +48,33 @@ def test_every_source_of_the_library_exists_and_every_hip_file_is_built():
     on_disk = {f for f in os.listdir(B.CSRC) if f.endswith(".hip")}
     assert set(B.SOURCES) | {"peaks_probe.hip"} == on_disk
     assert "-packed-fp32-ops" in B.FLAGS and "--offload-arch=gfx950" in B.FLAGS
+
+
+def _kernel_resources(tmp_path):
+    """Kernel symbol -> (LDS bytes, vector registers), from the metadata notes of the device code in the built library."""
+    readelf = shutil.which("llvm-readelf") or "/opt/rocm/llvm/bin/llvm-readelf"
+    if not (os.path.exists(B.LIB) and os.path.exists(readelf)):
+        pytest.skip("needs the built library and llvm-readelf")
+    blob, magic, found, at = open(B.LIB, "rb").read(), b"__CLANG_OFFLOAD_BUNDLE__", {}, 0
+    while (at := blob.find(magic, at)) >= 0:     # magic, entries, then of each: offset, size, length of the target's name, name
+        pos = at + len(magic) + 8
+        for _ in range(struct.unpack_from("<Q", blob, pos - 8)[0]):
+            offset, size, length = struct.unpack_from("<3Q", blob, pos)
+            target, pos = blob[pos + 24:pos + 24 + length], pos + 24 + length
+            if b"gfx950" in target:
+                (tmp_path / "code").write_bytes(blob[at + offset:at + offset + size])
+                notes = subprocess.run([readelf, "--notes", str(tmp_path / "code")], stdout=subprocess.PIPE, text=True, check=True).stdout
+                for k in notes.split(".agpr_count:")[1:]:
+                    field = {f: re.search(rf"\.{f}:\s+(\S+)", k)[1] for f in ("name", "group_segment_fixed_size", "vgpr_count")}
+                    found[field["name"]] = int(field["group_segment_fixed_size"]), int(field["vgpr_count"])
+        at += len(magic)
+    return found
+
+
+def test_a_router_gradient_kernel_of_one_part_holds_that_part_only(tmp_path):
+    """The kernel of the token gradient for two chunks of logit columns leaves room for four workgroups of four waves on a CU (160 KB of LDS, 512
+    registers a SIMD lane); with the LDS of the router weights it had 46 KB and 136 registers, three."""
+    res = _kernel_resources(tmp_path)
+    (lds, regs), = [v for k, v in res.items() if "router_grad_mfma_kernelILi2ELi0E" in k]
+    assert lds == 256 * (2 * 16 + 8) * 2 + 4 * 32 * 9 * 16 and 4 * lds <= 160 * 1024    # transposed weights, rows of x
+    assert regs <= 512 // 4
