@@ -336,7 +336,8 @@ __global__ __launch_bounds__(kThreads) void router_grad_kernel(DispatchBackwardA
     if constexpr (DX) {
         if (!GW || b < dx_blocks) return dispatch_backward_block<DT, LPR>(dx, b);
     }
-    if constexpr (GW) gate_weights_block<DT>(gw, (b - dx_blocks) / gw_col_blocks, (b - dx_blocks) % gw_col_blocks);
+    if constexpr (!DX) gate_weights_block<DT>(gw, b, blockIdx.y);
+    else if constexpr (GW) gate_weights_block<DT>(gw, (b - dx_blocks) / gw_col_blocks, (b - dx_blocks) % gw_col_blocks);
 }
 
 // dw[i][k] = sum_b partial[b][i][k]: PARTS runs of the blocks side by side, each in index order, then the runs in order.  A thread that adds all
@@ -510,7 +511,7 @@ static hipError_t launch_router_grad_valu(const LayerDesc &d, const RouterGradIo
                                   static_cast<const u32x4 *>(io.w_inter), static_cast<const u32x4 *>(io.w_intra), static_cast<u32x4 *>(io.dx),
                                   d.T, ppr, d.n_groups, d.m_local, d.capacity};
     const GateWeightsArgs gw{io.x, io.dlp, io.dlq, partial, d.T, d.d_model, d.n_groups, d.m_local};
-    const dim3 grid(dx_blocks + (with_gw ? blocks * col_blocks : 0)), block(kThreads);
+    const dim3 block(kThreads), grid = with_dx ? dim3(dx_blocks + (with_gw ? blocks * col_blocks : 0)) : dim3(blocks, col_blocks);
     auto launch = [&](auto dx_tag, auto gw_tag) {
         constexpr bool DX = decltype(dx_tag)::value, GW = decltype(gw_tag)::value;
         SMILE_DTYPE_SWITCH(d.dtype, SMILE_BWD_LPR_SWITCH(

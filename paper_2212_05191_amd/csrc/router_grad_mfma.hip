@@ -340,7 +340,7 @@ struct RouterGradArgs {
 };
 
 // KC, RT 0: without that part, its LDS and its registers.  What one part alone needs are arrays of their own, which the compiler can tell
-// apart; the parts that share a launch share their LDS.
+// apart; the parts that share a launch share their LDS.  dx on its own has its column blocks in blockIdx.y.
 template <int KC, int RT>
 __global__ __launch_bounds__(kThreads) void router_grad_mfma_kernel(RouterGradArgs a)
 {
@@ -348,7 +348,7 @@ __global__ __launch_bounds__(kThreads) void router_grad_mfma_kernel(RouterGradAr
     if constexpr (RT == 0) {
         __shared__ typename DxLds<KC>::Weights wt;
         __shared__ typename DxLds<KC>::Rows io;
-        dispatch_backward_block<KC>(a.dx, wt, io, b / a.dx_col_blocks, b % a.dx_col_blocks);
+        dispatch_backward_block<KC>(a.dx, wt, io, b, blockIdx.y);
     } else if constexpr (KC == 0) {
         __shared__ typename GwLds<RT>::Tokens xs;
         __shared__ typename GwLds<RT>::Planes pl;
@@ -410,8 +410,9 @@ hipError_t launch_router_grad_mfma(const LayerDesc &d, const RouterGradIo &io, b
             static_cast<const __bf16 *>(io.w_intra), static_cast<__bf16 *>(io.dx), d.T, d.d_model, d.n_groups, d.m_local, d.capacity, kp};
     a.gw = {static_cast<const __bf16 *>(io.x), io.dlp, io.dlq, partial, d.T, d.d_model, d.n_groups, d.m_local, tokens_per_block};
     a.dx_col_blocks = (d.d_model + dx_cols(kc) - 1) / dx_cols(kc), a.gw_col_blocks = (d.d_model + kGwCb - 1) / kGwCb;
-    a.dx_blocks = with_dx ? (d.T + kDxTokens - 1) / kDxTokens * a.dx_col_blocks : 0;
-    const dim3 grid(a.dx_blocks + (with_gw ? blocks * a.gw_col_blocks : 0)), block(kThreads);
+    const int dx_token_blocks = (d.T + kDxTokens - 1) / kDxTokens;
+    a.dx_blocks = with_dx ? dx_token_blocks * a.dx_col_blocks : 0;
+    const dim3 block(kThreads), grid = with_gw ? dim3(a.dx_blocks + blocks * a.gw_col_blocks) : dim3(dx_token_blocks, a.dx_col_blocks);
 #define SMILE_CASE(K, R) SMILE_LAUNCH((router_grad_mfma_kernel<K, R>), grid, block, 0, s, a); break;
     if (with_dx && with_gw) {
         switch (kc * 4 + rt) {
