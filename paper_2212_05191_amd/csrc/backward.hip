@@ -342,25 +342,25 @@ __global__ __launch_bounds__(kThreads) void router_grad_kernel(DispatchBackwardA
 
 // dw[i][k] = sum_b partial[b][i][k]: PARTS runs of the blocks side by side, each in index order, then the runs in order.  A thread that adds all
 // blocks itself waits for memory once per eight of them; with less than a workgroup per CU nothing hides that, so eight threads share an
-// element there (us: 512 blocks of 16 x 64 22.7 -> 5.3, 256 of 24 x 768 12.5 -> 4.5, 128 of 40 x 1024 12.0 -> 7.8; 256 of 129 x 768,
-// 387 workgroups, 15.3 against 16.6).
+// element there, from 48 blocks on (us: 512 blocks of 16 x 64 22.7 -> 5.3, 256 of 24 x 768 12.5 -> 4.8, 128 of 40 x 1024 6.9 -> 4.9, 64 of 10 x 64 and of
+// 10 x 768 3.8 -> 2.4 and 3.9; but 32 of them 2.5 and 3.0, 8 of 10 x 64 1.5 and 2.3; 256 of 129 x 768, 387 workgroups, 15.3 and 16.6).
 template <int PARTS>
 __global__ __launch_bounds__(kThreads) void gate_weights_reduce_kernel(
     const float *__restrict__ partial, float *__restrict__ dw_inter, float *__restrict__ dw_intra, int B, int d, int n,
     int m)
 {
     constexpr int ELEMS = kThreads / PARTS;
-    __shared__ float sums[PARTS][ELEMS];
-    const int part = threadIdx.x / ELEMS, elem = threadIdx.x % ELEMS;
+    const int part = PARTS > 1 ? threadIdx.x / ELEMS : 0, elem = threadIdx.x % ELEMS;
     const long long id = (long long)blockIdx.x * ELEMS + elem;
     const long long total = (long long)(n + m) * d;
-    const int per = (B + PARTS - 1) / PARTS, b1 = min(B, (part + 1) * per);
+    const int per = (B + PARTS - 1) / PARTS, b1 = PARTS > 1 ? min(B, (part + 1) * per) : B;
     float s = 0.f;
     if (id < total) {
 #pragma unroll 8
         for (int b = part * per; b < b1; ++b) s += partial[(size_t)b * total + id];
     }
     if constexpr (PARTS > 1) {
+        __shared__ float sums[PARTS][ELEMS];
         sums[part][elem] = s;
         __syncthreads();
         if (part != 0) return;
@@ -547,7 +547,7 @@ hipError_t launch_router_gradients(const LayerDesc &d, void *workspace, const Ro
     if (!with_gw || err != hipSuccess) return err;
     const long long total = (long long)(d.n_groups + d.m_local) * d.d_model;
     const long long groups = (total + kThreads - 1) / kThreads;   // workgroups of a thread an element
-    if (groups < (d.tune.cus > 0 ? d.tune.cus : 256))
+    if (blocks >= 48 && groups < (d.tune.cus > 0 ? d.tune.cus : 256))
         SMILE_LAUNCH(gate_weights_reduce_kernel<8>, dim3((unsigned)((total + kThreads / 8 - 1) / (kThreads / 8))), dim3(kThreads), 0, s, partial,
                      io.dw_inter, io.dw_intra, blocks, d.d_model, d.n_groups, d.m_local);
     else

@@ -452,21 +452,27 @@ def test_router_gradients_in_one_launch(torch_cuda, cfg):
         b.close()
 
 
-# Partial sums of the router weights over more blocks than the runs that add them side by side (of 8: some empty, a ragged last one), and
-# with one thread an element
+# Partial sums of the router weights by one thread an element and, from 48 blocks on and with less than a workgroup per CU, by runs of the
+# blocks side by side (of 8: the last one empty, or shorter)
 REDUCE_CASES = [
-    wl.small_config("reduce_1_block", 100, 64, 64, 2, 3, 40, "bf16", "relu", seed=91),
-    wl.small_config("reduce_9_blocks", 1100, 72, 64, 2, 3, 300, "f32", "relu", seed=92),
-    wl.small_config("reduce_79_blocks", 10000, 64, 64, 2, 3, 2000, "bf16", "relu", seed=93),
-    wl.small_config("reduce_wide_10_blocks", 1200, 576, 64, 1, 129, 20, "bf16", "relu", seed=94),
+    (wl.small_config("reduce_1_block", 100, 64, 64, 2, 3, 40, "bf16", "relu", seed=91), 1),
+    (wl.small_config("reduce_9_blocks", 1100, 72, 64, 2, 3, 300, "f32", "relu", seed=92), 1),
+    (wl.small_config("reduce_47_blocks", 47 * 128, 64, 64, 2, 3, 1200, "f16", "relu", seed=95), 1),
+    (wl.small_config("reduce_49_blocks", 48 * 128 + 1, 72, 64, 2, 3, 1200, "f32", "relu", seed=96), 8),
+    (wl.small_config("reduce_79_blocks", 10000, 64, 64, 2, 3, 2000, "bf16", "relu", seed=93), 8),
+    (wl.small_config("reduce_wide_10_blocks", 1200, 576, 64, 1, 129, 20, "bf16", "relu", seed=94), 1),
+    (wl.small_config("reduce_wide_49_blocks", 48 * 128 + 1, 576, 64, 1, 129, 60, "bf16", "relu", seed=97), 1),
 ]
 
 
-@pytest.mark.parametrize("cfg", REDUCE_CASES, ids=lambda c: c.name)
-def test_router_weight_sums_over_blocks(torch_cuda, cfg):
+@pytest.mark.parametrize("cfg,runs", REDUCE_CASES, ids=lambda c: getattr(c, "name", str(c)))
+def test_router_weight_sums_over_blocks(torch_cuda, cfg, runs):
     """fp32 sums of at most 10000 products of values near 1: 1e-5 of the largest, as for the other fp32 sums."""
+    from test_gpu_dispatch_edges import _launched
     layer = _forward_backward(cfg, chained=True)
     try:
+        names = _launched(layer, layer.backward)
+        assert [k for k in names if "gate_weights_reduce" in k] == [f"gate_weights_reduce_kernel<{runs}>"], names
         out = _fetch_backward(layer)
         x = parity.host_inputs(cfg)[0]
         dwi, dwq = oracle.gate_weights_backward(x, out["dlp"].astype(np.float64), out["dlq"].astype(np.float64))
