@@ -24,6 +24,7 @@ namespace smile {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kMaxGridX = 1 << 20;   // workgroups in x where a grid is dealt out over x and y
 
 typedef __attribute__((__vector_size__(4 * sizeof(uint32_t)))) uint32_t u32x4;
 
@@ -79,50 +80,60 @@ struct RouteBackwardArgs {
 
 // One softmax row backwards by the LPR lanes of a token, columns sub, sub + LPR, ...: with z = sum exp(a - a_top) (so the top
 // probability is 1 / z) and u_k = coef * count_k + [k == top] * extra,  dl_k = p_k * (u_k - sum_i u_i p_i).
-// Rows of up to 2 LPR columns stay in registers; wider ones are read again by each of the three passes.
-template <int LPR>
+// Rows of up to HELD * LPR columns stay in registers; wider ones are read again by each of the three passes.
+// VIRTUAL: the bits of VIRTUAL * LPR lanes, or of any more that have no columns (their zeros change nothing), for rows of at most HELD * LPR columns:
+// column k of a lane's own belongs to virtual lane k % VIRTUAL, whose terms are added in a chain, and the virtual lanes are added in the order
+// of token_sum.
+template <int LPR, int HELD = 2, int VIRTUAL = 1>
 struct SoftmaxRow {
+    static_assert(VIRTUAL == 1 || VIRTUAL == 2 || VIRTUAL == 4, "see sum()");
     const float *row, *bias;
     int len, top, sub;
-    float held[2], mx, inv_z;
+    float held[HELD], mx, inv_z;
     __device__ __forceinline__ float at(int i) const { return bias ? __fadd_rn(row[i], bias[i]) : row[i]; }
     template <typename F>
     __device__ __forceinline__ void each(F f) const
     {
-        if (len <= 2 * LPR) {
+        if (VIRTUAL > 1 || len <= HELD * LPR) {
 #pragma unroll
-            for (int k = 0; k < 2; ++k)
-                if (sub + k * LPR < len) f(sub + k * LPR, held[k]);
+            for (int k = 0; k < HELD; ++k)
+                if (sub + k * LPR < len) f(sub + k * LPR, held[k], k);
         } else {
-            for (int i = sub; i < len; i += LPR) f(i, at(i));
+            for (int i = sub; i < len; i += LPR) f(i, at(i), 0);
         }
+    }
+    // add(i, a, s) = s and column i's term
+    template <typename F>
+    __device__ __forceinline__ float sum(F add) const
+    {
+        float s[VIRTUAL] = {};
+        each([&](int i, float a, int k) { s[k % VIRTUAL] = add(i, a, s[k % VIRTUAL]); });
+        if constexpr (VIRTUAL == 4) s[0] += s[2], s[1] += s[3];
+        if constexpr (VIRTUAL >= 2) s[0] += s[1];
+        return token_sum<LPR>(s[0]);
     }
     // reads the row; 1 / z is the top probability
     __device__ __forceinline__ SoftmaxRow(const float *row_, const float *bias_, int len_, int top_, int sub_)
         : row(row_), bias(bias_), len(len_), top(top_), sub(sub_)
     {
 #pragma unroll
-        for (int k = 0; k < 2; ++k) held[k] = sub + k * LPR < len ? at(sub + k * LPR) : 0.f;
+        for (int k = 0; k < HELD; ++k) held[k] = sub + k * LPR < len ? at(sub + k * LPR) : 0.f;
         mx = at(top);
     }
     __device__ __forceinline__ void normalise()
     {
-        float z = 0.f;
-        each([&](int, float a) { z += exp_neg(a - mx); });
-        inv_z = 1.0f / token_sum<LPR>(z);
+        inv_z = 1.0f / sum([&](int, float a, float s) { return s + exp_neg(a - mx); });
     }
     __device__ __forceinline__ void backward(float coef, const int32_t *__restrict__ count, float extra, float *__restrict__ out) const
     {
         auto u = [&](int i) { return coef * (float)count[i] + (i == top ? extra : 0.f); };
-        float dot = 0.f;
-        each([&](int i, float a) { dot = fmaf(u(i), exp_neg(a - mx) * inv_z, dot); });
-        dot = token_sum<LPR>(dot);
-        each([&](int i, float a) { out[i] = exp_neg(a - mx) * inv_z * (u(i) - dot); });
+        const float dot = sum([&](int i, float a, float s) { return fmaf(u(i), exp_neg(a - mx) * inv_z, s); });
+        each([&](int i, float a, int) { out[i] = exp_neg(a - mx) * inv_z * (u(i) - dot); });
     }
 };
 
-template <int LPR>
-__device__ __forceinline__ void route_backward_token(SoftmaxRow<LPR> &p, SoftmaxRow<LPR> &q, const RouteBackwardArgs &a, int t, float dg)
+template <typename Row>
+__device__ __forceinline__ void route_backward_token(Row &p, Row &q, const RouteBackwardArgs &a, int t, float dg)
 {
     p.normalise();
     q.normalise();
@@ -176,15 +187,18 @@ __global__ __launch_bounds__(kThreads) void combine_backward_kernel(
     }
 }
 
-// The softmax part on its own, by as many lanes a token as the kernel above gives it, so that both add in the same order.
-template <int LPR>
+// The softmax part on its own, with the bits of the kernel above (launch_route_backward: by how many lanes).  The token blocks are dealt out over
+// blockIdx.x and y: a launch has fewer than 2^32 threads in x.
+template <int LPR, int VIRTUAL>
 __global__ __launch_bounds__(kThreads) void route_backward_kernel(const float *__restrict__ dgate, RouteBackwardArgs a)
 {
-    const int t = blockIdx.x * (kThreads / LPR) + threadIdx.x / LPR, sub = threadIdx.x % LPR;
-    if (t >= a.T) return;
+    const long long token = ((long long)blockIdx.y * gridDim.x + blockIdx.x) * (kThreads / LPR) + threadIdx.x / LPR;
+    if (token >= a.T) return;
+    const int t = (int)token, sub = threadIdx.x % LPR;
     const int g = a.group_idx[t], l = a.local_idx[t];
-    SoftmaxRow<LPR> p(a.logits_inter + (size_t)t * a.n, a.bias_inter, a.n, g, sub);
-    SoftmaxRow<LPR> q(a.logits_intra + (size_t)t * a.m, a.bias_intra ? a.bias_intra + (size_t)g * a.m : nullptr, a.m, l, sub);
+    typedef SoftmaxRow<LPR, 4, VIRTUAL> Row;
+    Row p(a.logits_inter + (size_t)t * a.n, a.bias_inter, a.n, g, sub);
+    Row q(a.logits_intra + (size_t)t * a.m, a.bias_intra ? a.bias_intra + (size_t)g * a.m : nullptr, a.m, l, sub);
     route_backward_token(p, q, a, t, dgate[t]);
 }
 
@@ -443,10 +457,25 @@ hipError_t launch_combine_backward(const smile_layer_desc &d, const void *dy, co
 
 hipError_t launch_route_backward(const smile_layer_desc &d, const float *dgate, const RouteBackwardIo &io, float dloss, hipStream_t s)
 {
-    const int lpr = lanes_per_row(d.d_model * elem_size(d.dtype) / 16);
+    // As few lanes a token as hold the wider row, two columns each up to 16 and four beyond, up to those that the chained pass gives it: that pass
+    // has them for the rows of dy, here the ones without a column would be most of the launch.  us, 524288 tokens, rows of 1536 bytes, 32 lanes -> here (a
+    // kernel of one thread a token, or through LDS from 32 columns on): 1 + 1 columns 92 -> 4.4 (4.3), 2 + 8 93 -> 16.5 (33), 16 + 16 96 -> 35 (44),
+    // 32 + 8 95 -> 40 (69); 65536 tokens: 2 + 8 11.4 -> 4.2 (6.7), 1 + 64 15.3 -> 11.1 (21.9).  Two columns and four: 8 + 8 19.7 and 23.8, 16 + 16 35.0 and 35.4 (at
+    // 8192 tokens 3.6 and 4.4), 24 + 8 57.3 and 34.7, 32 + 32 82 and 69.
+    const int most = lanes_per_row(d.d_model * elem_size(d.dtype) / 16), width = d.n_groups > d.m_local ? d.n_groups : d.m_local;
+    const int columns = width <= 16 ? 2 : 4;
+    int lanes = 1;
+    while (lanes < most && columns * lanes < width) lanes *= 2;
     const RouteBackwardArgs a = route_backward_args(d, io, dloss);
-    const dim3 grid((d.T + kThreads / lpr - 1) / (kThreads / lpr));
-    SMILE_BWD_LPR_SWITCH(lpr, SMILE_LAUNCH(route_backward_kernel<L>, grid, dim3(kThreads), 0, s, dgate, a));
+    const long long blocks = ((long long)d.T * lanes + kThreads - 1) / kThreads;
+    const dim3 grid((unsigned)(blocks < kMaxGridX ? blocks : kMaxGridX), (unsigned)((blocks + kMaxGridX - 1) / kMaxGridX));
+#define SMILE_CASE(L, V) case L * 8 + V: SMILE_LAUNCH((route_backward_kernel<L, V>), grid, dim3(kThreads), 0, s, dgate, a); break;
+    switch (lanes * 8 + (most / lanes < 4 ? most / lanes : 4)) {
+        SMILE_CASE(1, 4) SMILE_CASE(2, 4) SMILE_CASE(4, 4) SMILE_CASE(8, 4)
+        SMILE_CASE(4, 2) SMILE_CASE(8, 2) SMILE_CASE(16, 2)
+        SMILE_CASE(8, 1) SMILE_CASE(16, 1) SMILE_CASE(32, 1)
+    }
+#undef SMILE_CASE
     return hipGetLastError();
 }
 

@@ -398,23 +398,37 @@ def test_saved_activations_equal_recomputation(torch_cuda, cfg):
         b.close()
 
 
-# Router widths around the columns that a token's lanes hold in registers (two each: 8, 16 or 32 lanes by the bytes of a row of x), with
-# routing biases and dropped tokens
+# Router widths around the columns that a token's lanes hold in registers (chained: two each, of 8, 16 or 32 lanes by the bytes of a row of
+# x; on its own: as many lanes as the columns ask for, two or four each, for the sums of two or four lanes of the chained pass), with routing biases
+# and dropped tokens
 ROUTE_BACKWARD_EDGES = [
-    wl.small_config("route_bwd_8_lanes", 333, 64, 64, 16, 17, 2, "bf16", "gelu", skew=True, seed=71),
-    wl.small_config("route_bwd_16_lanes", 333, 64, 64, 33, 32, 2, "f32", "relu", skew=True, seed=72),
-    wl.small_config("route_bwd_32_lanes", 333, 256, 64, 64, 1, 5, "f16", "gelu", skew=True, seed=73),
-    wl.small_config("route_bwd_32_lanes_wide", 333, 320, 64, 1, 65, 5, "bf16", "gelu", skew=True, seed=74),
-    wl.small_config("route_bwd_one_column", 70, 64, 64, 1, 1, 40, "bf16", "gelu", seed=75),
+    (wl.small_config("route_bwd_8_lanes", 333, 64, 64, 16, 17, 2, "bf16", "gelu", skew=True, seed=71), (8, 1)),
+    (wl.small_config("route_bwd_16_lanes", 333, 64, 64, 33, 32, 2, "f32", "relu", skew=True, seed=72), (16, 1)),
+    (wl.small_config("route_bwd_32_lanes", 333, 256, 64, 64, 1, 5, "f16", "gelu", skew=True, seed=73), (16, 2)),
+    (wl.small_config("route_bwd_32_lanes_wide", 333, 320, 64, 1, 65, 5, "bf16", "gelu", skew=True, seed=74), (32, 1)),
+    (wl.small_config("route_bwd_one_column", 70, 64, 64, 1, 1, 40, "bf16", "gelu", seed=75), (1, 4)),
+    (wl.small_config("route_bwd_2_of_32_columns", 333, 256, 64, 2, 1, 100, "bf16", "gelu", skew=True, seed=76), (1, 4)),
+    (wl.small_config("route_bwd_4_of_8_lanes", 333, 64, 64, 3, 4, 15, "f16", "gelu", skew=True, seed=77), (2, 4)),
+    (wl.small_config("route_bwd_8_columns", 333, 64, 64, 8, 7, 4, "bf16", "gelu", skew=True, seed=78), (4, 2)),
+    (wl.small_config("route_bwd_8_of_32_columns", 333, 64, 64, 5, 8, 4, "f32", "relu", skew=True, seed=79), (4, 4)),
+    (wl.small_config("route_bwd_16_of_32_columns", 333, 256, 64, 16, 9, 2, "bf16", "gelu", skew=True, seed=86), (8, 4)),
+    (wl.small_config("route_bwd_31_of_32_columns", 333, 576, 64, 31, 5, 2, "bf16", "gelu", skew=True, seed=87), (8, 4)),
+    (wl.small_config("route_bwd_32_of_16_lanes", 333, 128, 64, 17, 32, 2, "f16", "gelu", skew=True, seed=88), (8, 2)),
+    (wl.small_config("route_bwd_9_of_8_lanes", 333, 64, 64, 9, 9, 4, "bf16", "gelu", skew=True, seed=89), (8, 1)),
 ]
 
 
-@pytest.mark.parametrize("cfg", ROUTE_BACKWARD_EDGES, ids=lambda c: c.name)
-def test_router_logit_gradients_at_the_register_edges(torch_cuda, cfg):
+@pytest.mark.parametrize("cfg,lanes", ROUTE_BACKWARD_EDGES, ids=lambda c: getattr(c, "name", str(c)))
+def test_router_logit_gradients_at_the_register_edges(torch_cuda, cfg, lanes):
     """The routers' backward step in the launch of the combine step (chained) and on its own: the same bits, and the oracle's
     gradients (fp32 sums of at most 65 terms and exponentials of relative error 1e-6: 1e-5 norm-wise)."""
+    from test_gpu_dispatch_edges import _launched
     a, b = _forward_backward(cfg), _forward_backward(cfg, chained=True)
     try:
+        f, w = a.buf, a.bwd
+        names = _launched(a, lambda: B.smile_route_backward(a.ctx, f.logits_inter, f.logits_intra, a.bias_inter, a.bias_intra, f.group_idx,
+                                                            f.local_idx, w.dgate, f.group_count, f.local_count, 1.0, w.dlp, w.dlq))
+        assert names == ["(route_backward_kernel<%d, %d>)" % lanes], names
         fwd, oa, ob = parity.fetch(b), _fetch_backward(a), _fetch_backward(b)
         for k in ("dgate", "dlp", "dlq"):
             np.testing.assert_array_equal(oa[k], ob[k], err_msg=k)
@@ -425,6 +439,37 @@ def test_router_logit_gradients_at_the_register_edges(torch_cuda, cfg):
     finally:
         a.close()
         b.close()
+
+
+# 2^27 tokens by the 32 lanes of the chained pass would be more threads than a launch has; 2^23 tokens of a row of 65 columns are more workgroups than
+# the launch has in x, the rest of them ragged
+@pytest.mark.parametrize("T,n,m", [(1 << 27, 2, 1), ((1 << 23) + 5, 1, 65)])
+def test_router_logit_gradients_of_very_many_tokens(torch_cuda, T, n, m):
+    """The first, last and middle tokens against fp64 (sums of at most 65 terms and exponentials of relative error 1e-6: 1e-5 norm-wise), and every
+    token written."""
+    torch = torch_cuda
+    _say(f"[case] route backward of {T} tokens, {n} + {m} columns")
+    ctx = B.Ctx(B.make_desc(T, 256, 64, n, m, 1, "bf16", "relu", ALPHA, BETA))
+    gen = torch.Generator(device="cuda").manual_seed(98)
+    li, lq = torch.randn((T, n), generator=gen, device="cuda"), torch.randn((T, m), generator=gen, device="cuda")
+    gi, qi = (torch.argmax(v, 1).to(torch.int32) for v in (li, lq))
+    dgate = torch.randn(T, generator=gen, device="cuda")
+    counts = [torch.bincount(i, minlength=k).to(torch.int32) for i, k in ((gi, n), (qi, m))]
+    counts = [torch.cat([c, c.new_zeros(4)])[:c.numel()] for c in counts]     # 16-byte aligned whatever the length
+    dlp, dlq = torch.full_like(li, float("nan")), torch.full_like(lq, float("nan"))
+    B.smile_route_backward(ctx, li, lq, None, None, gi, qi, dgate, counts[0], counts[1], 1.0, dlp, dlq)
+    torch.cuda.synchronize()
+    assert not bool(torch.isnan(dlp).any()) and not bool(torch.isnan(dlq).any())
+    for t in (0, T // 2 - 300, T - 601):
+        s = slice(t, t + 601)
+        p, q = torch.softmax(li[s].double(), 1), torch.softmax(lq[s].double(), 1)
+        pg, ql = p.gather(1, gi[s, None].long()), q.gather(1, qi[s, None].long())
+        for probs, top, idx, other, coef, count, got in ((p, pg, gi, ql, ALPHA * n, counts[0], dlp), (q, ql, qi, pg, BETA * m, counts[1], dlq)):
+            u = coef * count.double()[None, :] / T / T + torch.zeros_like(probs).scatter(1, idx[s, None].long(), dgate[s, None].double() * other)
+            want = probs * (u - (u * probs).sum(1, keepdim=True))
+            # a router of one column has no gradient: what is left is rounding of u
+            assert float((got[s] - want).abs().max()) <= 1e-5 * max(float(want.abs().max()), float(u.abs().max()))
+    ctx.close()
 
 
 # dx and the partial sums of the router weights in one launch: every pair of matrix-core variants that shares one, and the vector-ALU
