@@ -443,15 +443,18 @@ RingArgs ring_args(const GemmArgs &g, int N)
     return a;
 }
 
+}  // namespace
+
 // Tile choice; Tuning::ffn_tile (0..9 without 6) overrides it for tuning runs.  Large buffers take the ring kernels
 // (pick_ring_tile).  Small buffers and narrow layers leave most of the chip
 // without a 128-row tile (16 experts x 768 columns: 64 tiles of 192 columns on 256 CUs, each a serial chain of K / 64 slabs),
 // so they take 64-row tiles as long as those are few; the counts are those of 64 x 64 tiles over the whole buffers, or, where an expert
 // expects more than one row tile, over the rows it expects (tiles of empty rows exit at once).  bf16, us:
 //   * up, one round of three workgroups per CU (<= 768): 64 x 64, three stages.  16 experts x 16 rows, 768 -> 3072: 22.3 -> 15.9;
-//     32 x 188 rows, 256 -> 512: 10.8 -> 6.6; 4 x 100 rows, 960 -> 3840: 19.9 -> 9.1.  Beyond the line, 16 x 80 rows (1536 tiles): 24.4 -> 28.2.  Up to
-//     320, about one a CU, with a fourth stage: 5 x 28 rows, 704 -> 2816 (220) 6.9 -> 5.9, 4 x 35, 960 -> 2880 (180) 7.9 -> 6.9, 32 x 15, 192 -> 576
-//     (288) 4.8 -> 4.4; 21 x 58, 320 -> 640 (420) 5.4 -> 5.6.
+//     32 x 188 rows, 256 -> 512: 10.8 -> 6.6; 4 x 100 rows, 960 -> 3840: 19.9 -> 9.1.  Beyond the line, 16 x 80 rows (1536 tiles): 24.4 -> 28.2.  At
+//     most one a CU and from eleven slabs on, a fourth stage: 5 x 28 rows, 704 -> 2816 (220) 6.9 -> 5.9, 4 x 35, 960 -> 2880 (180) 7.9 -> 6.9; of shorter
+//     ones the fill is longer than the sum (16 x 15, 256 -> 1024 4.3 -> 5.0, 6 x 248, 128 -> 384 4.5 -> 5.2), and where a CU has two they share it (4 x
+//     13, 1472 -> 4416 (276) 11.6 -> 12.7).
 //   * up, one round of two per CU of 64 x 128 (<= 512 of them): 16 experts x 203 rows, 256 -> 1024: 9.5 -> 8.1; 21 x 173, 320 -> 960 11.8 -> 9.0; 4 x
 //     107, 1152 -> 3456 15.4 -> 13.8; at 528 16 x 185, 448 -> 1344 13.0 -> 14.0.  Contractions of one slab, and of two up to 4096 tiles, which
 //     have nothing to pipeline: 64 x 551, 128 -> 256 21.1 -> 14.9, 128 x 591, 64 -> 256 29.2 -> 22.8, 16 x 4063, 64 -> 256 22.4 -> 18.6; two slabs, 16 x 4063,
@@ -467,16 +470,16 @@ RingArgs ring_args(const GemmArgs &g, int N)
 //   * down, buffers of at most 64 rows: 64 x 128 up to 2048 (128 x 16 rows, 3072 -> 768: 117.0 -> 104.9; 64 x 41, 2880 -> 960 (960): 64 x 64 76.5, 72.3),
 //     then 64 x 256 (256 x 63 rows, 4096 -> 1024: 374.9 -> 369.2; 64 x 128: 379.8).
 // Every tile adds a row's products in the same order: the results are the same bits.
-int pick_tile(const Tuning &tune, const GemmArgs &g, int N)
+int pick_forward_tile(const Tuning &tune, int N, int C, int Nout, int K, int tokens, bool gathered)
 {
-    const int C = g.C, Nout = g.Nout, K = g.K;
-    const RingArgs ring = ring_args(g, N);
-    const bool ring_ok = ring_applies(ring, g.x_rows ? g.tokens : C, false, false);
+    RingArgs ring{};
+    ring.N = N, ring.Mrows = C, ring.Nout = Nout, ring.K = ring.ldx = ring.ldw = K;
+    const bool ring_ok = ring_applies(ring, gathered ? tokens : C, false, false);
     if (tune.ffn_tile >= 0 && tune.ffn_tile != 6) return is_ring_tile(tune.ffn_tile) && !ring_ok ? 0 : tune.ffn_tile;
     const long long cols = (Nout + 63) / 64, small = N * ((C + 63ll) / 64) * cols;   // 64 x 64 tiles
-    const int rows = g.tokens > 0 ? std::min(C, (g.tokens - 1) / N + 1) : C;          // that an expert expects
+    const int rows = tokens > 0 ? std::min(C, (tokens - 1) / N + 1) : C;              // that an expert expects
     if (Nout >= K) {
-        if (small <= 320) return 7;
+        if (small <= 256 && K >= 704) return 7;
         if (small <= 768) return 9;
         if (C <= 64) return small <= 8192 ? 8 : 5;
         if (K <= 64 || (K < 192 && small <= 4096) || N * ((C + 63ll) / 64) * ((Nout + 127) / 128) <= 512) return 8;
@@ -490,6 +493,13 @@ int pick_tile(const Tuning &tune, const GemmArgs &g, int N)
     }
     if (!ring_ok) return 0;
     return kRingTile0 + pick_ring_tile(tune, ring, rows, false);
+}
+
+namespace {
+
+int pick_tile(const Tuning &tune, const GemmArgs &g, int N)
+{
+    return pick_forward_tile(tune, N, g.C, g.Nout, g.K, g.tokens, g.x_rows != nullptr);
 }
 
 // dtype dispatch of the two MFMA launchers

@@ -452,6 +452,9 @@ struct RingArgs {
 enum RingTile { kRing128x192x2, kRing128x256, kRing256x192, kRing128x128x2, kRingTiles };
 // The shape for one product (gemm_ring_forward.hip); `rows`: expected rows per group
 RingTile pick_ring_tile(const Tuning &tune, const RingArgs &a, int rows, bool gradient);
+// The tile of a 16-bit forward product (expert_ffn.hip): N experts, buffers of C rows, Nout columns, contraction K, `tokens` spread over the experts
+// (0: not known), `gathered`: rows read from the token matrix
+int pick_forward_tile(const Tuning &tune, int N, int C, int Nout, int K, int tokens, bool gathered);
 // Whether the ring kernels take a product: three slabs or more where an operand is read in whole slabs, and byte offsets that fit
 // the 32 bits a lane keeps (x_rows: rows of the gathered matrix, or of a group's operand)
 bool ring_applies(const RingArgs &a, long long x_rows, bool x_transposed, bool w_transposed);

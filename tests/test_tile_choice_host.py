@@ -1,4 +1,4 @@
-"""The choice of a ring tile for an expert GEMM (a host function of sizes alone), on both sides of its lines.  No kernel is launched here."""
+"""The choice of a tile for an expert GEMM (host functions of sizes alone), on both sides of its lines.  No kernel is launched here."""
 import ctypes as C
 
 import pytest
@@ -59,3 +59,31 @@ def test_ring_tile(product, N, rows, cap, d, F, want):
     tune = _Tuning(-1, -1, -1, -1, 256)
     got = pick(C.byref(tune), C.byref(a), min(rows, mrows) if product != "dW" else mrows, product in ("dpre", "dxe", "dW"))
     assert got == want
+
+
+# tiles of pick_forward_tile; the ring shapes are those above, one up
+T64X256, T64X64_4, T64X128, T64X64 = 5, 7, 8, 9
+
+# direction, experts, tokens, rows of a buffer, d_model, d_ff
+FORWARD_CASES = [
+    # up: 64 x 64 tiles, at most one on a CU and eleven slabs or more: four stages
+    ("up", 4, 96, 24, 960, 4096, T64X64_4),
+    ("up", 4, 96, 24, 704, 4096, T64X64_4),
+    ("up", 4, 96, 24, 640, 4096, T64X64),
+    ("up", 4, 96, 24, 960, 4160, T64X64),
+    ("up", 16, 240, 15, 256, 1024, T64X64),
+    ("up", 12, 96, 8, 1024, 4096, T64X64),              # 768
+    ("up", 13, 96, 8, 1024, 4096, T64X128),
+]
+
+
+def forward_tile(way, N, T, cap, d, F):
+    pick = B.load()._ZN5smile17pick_forward_tileERKNS_6TuningEiiiiib
+    pick.restype, pick.argtypes = C.c_int, [C.c_void_p] + [C.c_int] * 5 + [C.c_bool]
+    tune = _Tuning(-1, -1, -1, -1, 256)
+    return pick(C.byref(tune), N, cap, *((F, d) if way == "up" else (d, F)), T, way == "up")
+
+
+@pytest.mark.parametrize("way,N,T,cap,d,F,want", FORWARD_CASES, ids=lambda v: str(v))
+def test_forward_tile(way, N, T, cap, d, F, want):
+    assert forward_tile(way, N, T, cap, d, F) == want
