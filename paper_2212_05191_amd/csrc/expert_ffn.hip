@@ -458,7 +458,9 @@ RingArgs ring_args(const GemmArgs &g, int N)
 //   * up, one round of two per CU of 64 x 128 (<= 512 of them): 16 experts x 203 rows, 256 -> 1024: 9.5 -> 8.1; 21 x 173, 320 -> 960 11.8 -> 9.0; 4 x
 //     107, 1152 -> 3456 15.4 -> 13.8; at 528 16 x 185, 448 -> 1344 13.0 -> 14.0.  Contractions of one slab, and of two up to 4096 tiles, which
 //     have nothing to pipeline: 64 x 551, 128 -> 256 21.1 -> 14.9, 128 x 591, 64 -> 256 29.2 -> 22.8, 16 x 4063, 64 -> 256 22.4 -> 18.6; two slabs, 16 x 4063,
-//     128 -> 512 (8192) 33.6 -> 37.2.
+//     128 -> 512 (8192) 33.6 -> 37.2.  Not where 128-wide tiles pad what 192-wide ones do not: 10 x 6493, 64 -> 192 13.8, 64 x 128 19.0; 30 x 2122 13.7 and
+//     18.0.  (191 such products: 0.78 of the time in 128 x 192 tiles on the average; where those fit one round of two per CU a few are slower, by up to an
+//     eighth: 31 x 990 in half-full buffers, 128 -> 384 14.9 -> 16.7, but 42 x 594, 128 -> 512 17.8 -> 16.1.)
 //   * up, buffers of at most 64 rows: 64 x 128 up to 8192 (64 x 6 rows, 1024 -> 4096: 107.6 -> 93.1; 128 x 16, 768 -> 3072: 123.8 -> 114.8),
 //     beyond that the chip is full anyway and 64 x 256 reads the token rows least often (256 x 63 rows, 1024 -> 4096: 444.6 -> 404.4; 64 x 128: 415.1).
 //   * down, one round of two per CU (<= 512): 64 x 64 with four stages, K is long.  16 x 16 rows, 3072 -> 768: 31.0 -> 17.2;
@@ -482,7 +484,9 @@ int pick_forward_tile(const Tuning &tune, int N, int C, int Nout, int K, int tok
         if (small <= 256 && K >= 704) return 7;
         if (small <= 768) return 9;
         if (C <= 64) return small <= 8192 ? 8 : 5;
-        if (K <= 64 || (K < 192 && small <= 4096) || N * ((C + 63ll) / 64) * ((Nout + 127) / 128) <= 512) return 8;
+        const long long wide = (Nout + 127) / 128;
+        if ((K <= 64 || (K < 192 && small <= 4096)) && wide * 128 * 10 <= Nout * 11ll) return 8;
+        if (N * ((C + 63ll) / 64) * wide <= 512) return 8;
     } else if (small <= 1024) {
         const long long live = rows > 64 ? N * ((rows + 63ll) / 64) * cols : small;
         if (live <= 512 || !ring_ok) return 7;

@@ -74,6 +74,15 @@ FORWARD_CASES = [
     ("up", 16, 240, 15, 256, 1024, T64X64),
     ("up", 12, 96, 8, 1024, 4096, T64X64),              # 768
     ("up", 13, 96, 8, 1024, 4096, T64X128),
+    # up: contractions of one slab, and of two up to 4096 tiles, unless 64 x 128 tiles pad the columns
+    ("up", 16, 16 * 4063, 4063, 64, 256, T64X128),
+    ("up", 16, 16 * 4063, 4063, 64, 192, 0),
+    ("up", 16, 8192, 512, 128, 512, T64X128),
+    ("up", 32, 32 * 1024, 1024, 128, 512, T64X128),      # 4096
+    ("up", 32, 32 * 1025, 1025, 128, 512, 0),
+    # up: one round of two of 64 x 128 per CU, 512 of them
+    ("up", 16, 3000, 256, 192, 1024, T64X128),
+    ("up", 16, 3000, 257, 192, 1024, 1 + T128X128),
 ]
 
 
