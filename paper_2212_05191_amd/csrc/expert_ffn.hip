@@ -448,8 +448,8 @@ RingArgs ring_args(const GemmArgs &g, int N)
 // Tile choice; Tuning::ffn_tile (0..9 without 6) overrides it for tuning runs.  Large buffers take the ring kernels
 // (pick_ring_tile).  Small buffers and narrow layers leave most of the chip
 // without a 128-row tile (16 experts x 768 columns: 64 tiles of 192 columns on 256 CUs, each a serial chain of K / 64 slabs),
-// so they take 64-row tiles as long as those are few; the counts are those of 64 x 64 tiles over the whole buffers, or, where an expert
-// expects more than one row tile, over the rows it expects (tiles of empty rows exit at once).  bf16, us:
+// so they take 64-row tiles as long as those are few; the counts are those of 64 x 64 tiles over the whole buffers, and in one rule of the
+// down-projection (`live`) over the rows that an expert expects (tiles of empty rows exit at once).  bf16, us:
 //   * up, one round of three workgroups per CU (<= 768): 64 x 64, three stages.  16 experts x 16 rows, 768 -> 3072: 22.3 -> 15.9;
 //     32 x 188 rows, 256 -> 512: 10.8 -> 6.6; 4 x 100 rows, 960 -> 3840: 19.9 -> 9.1.  Beyond the line, 16 x 80 rows (1536 tiles): 24.4 -> 28.2.  At
 //     most one a CU and from eleven slabs on, a fourth stage: 5 x 28 rows, 704 -> 2816 (220) 6.9 -> 5.9, 4 x 35, 960 -> 2880 (180) 7.9 -> 6.9; of shorter
@@ -466,11 +466,17 @@ RingArgs ring_args(const GemmArgs &g, int N)
 //   * down, one round of two per CU (<= 512): 64 x 64 with four stages, K is long.  16 x 16 rows, 3072 -> 768: 31.0 -> 17.2;
 //     8 x 469 rows, 1024 -> 256: 17.2 -> 7.2; 64 x 6, 4096 -> 1024: 123.1 -> 97.0; 5 x 488 rows, 3072 -> 768 (480 of 600 expected) 22.1, ring 26.8.
 //   * down, a second round of those (to 1024) is where the ring's 128-row tiles are faster: 16 x 209 rows, 3840 -> 960 (960) 64.4 -> 39.2; 32 x 79,
-//     3584 -> 896 (896) 62.8 -> 50.5; 5 x 395, 2816 -> 1408 (770) 35.1 -> 26.4; 16 x 256, 3072 -> 768 (768) 35.4 -> 31.0.  What narrow layers have to
-//     768 fits one round of three per CU with three stages: 21 x 644, 576 -> 192 (693) 11.4 -> 8.8, ring 9.4; 32 x 244, 1024 -> 256 (512)
-//     14.7 -> 11.8, ring 12.4; so do buffers of at most 64 rows, which would leave half of a 128-row tile empty: 128 x 26, 1536 -> 384 34.8 -> 31.0.
-//   * down, buffers of at most 64 rows: 64 x 128 up to 2048 (128 x 16 rows, 3072 -> 768: 117.0 -> 104.9; 64 x 41, 2880 -> 960 (960): 64 x 64 76.5, 72.3),
-//     then 64 x 256 (256 x 63 rows, 4096 -> 1024: 374.9 -> 369.2; 64 x 128: 379.8).
+//     3584 -> 896 (896) 62.8 -> 50.5; 5 x 395, 2816 -> 1408 (770) 35.1 -> 26.4; 16 x 256, 3072 -> 768 (768) 35.4 -> 31.0.  Of more than 64 experts a skewed
+//     router leaves most without a row, and the few live tiles of 128 rows leave CUs idle: 90 x 82, 1280 -> 320, 21 experts live, 9.2, ring 16.8; 144 x 143, 256 ->
+//     128, 9 live, 4.8 and 7.0 (evenly spread, N > 64: 0.85 to 0.93).  What narrow layers have to 768 fits one round of three per CU with three stages:
+//     21 x 644, 576 -> 192 (693) 11.4 -> 8.8, ring 9.4; 88 x 107, 1024 -> 256 (704) 0.90 of four stages; beyond, half-empty buffers of many experts
+//     still do by the rows expected: 160 x 177, 512 -> 128 (960, 640 live) 0.83.
+//   * down, buffers of at most 64 rows, which would leave half of a 128-row tile empty: three stages and three per CU to 768 where the sum is short and
+//     experts expect three rows or more, so that nearly all are live: 128 x 26, 1536 -> 384 34.8 -> 31.0; 189 x 6, 768 -> 256 0.92; but 112 x 2, 1280 -> 320 11.2 and
+//     13.2, 32 x 57, 5120 -> 1280 91.0 and 93.4, 80 x 24, 1792 -> 448 skewed 12.0 and 13.8.  From there to 1024 64 x 128 where it pads nothing and as many as 64 experts
+//     are live: 54 x 56, 4096 -> 1024 0.92, 50 x 8, 2304 -> 1152 0.90; but 74 x 1, 2816 -> 704 22.0 and 31.6, 60 x 4, 4096 -> 1024 1.06, 200 x 49, 1280 -> 320 39.2 and 48.2, 140
+//     x 32, 1152 -> 384 skewed 9.2 and 11.2.  Then 64 x 128 up to 2048 (128 x 16 rows, 3072 -> 768: 117.0 -> 104.9), then 64 x 256 (256 x 63 rows, 4096 -> 1024:
+//     374.9 -> 369.2; 64 x 128: 379.8).
 // Every tile adds a row's products in the same order: the results are the same bits.
 int pick_forward_tile(const Tuning &tune, int N, int C, int Nout, int K, int tokens, bool gathered)
 {
@@ -490,8 +496,10 @@ int pick_forward_tile(const Tuning &tune, int N, int C, int Nout, int K, int tok
     } else if (small <= 1024) {
         const long long live = rows > 64 ? N * ((rows + 63ll) / 64) * cols : small;
         if (live <= 512 || !ring_ok) return 7;
-        if (C <= 64) return small <= 768 ? 9 : 8;
-        if (live <= 768 && Nout <= 320) return 9;
+        if (C <= 64 && small <= 768) return rows >= 3 && K <= 1536 ? 9 : 7;
+        if (C <= 64) return rows >= 5 && N <= 64 && Nout % 128 == 0 ? 8 : 7;
+        if (Nout <= 320 && (small <= 768 || (N > 64 && live <= 768))) return 9;
+        if (N > 64) return 7;
     } else if (C <= 64) {
         return small <= 2048 ? 8 : 5;
     }

@@ -83,6 +83,30 @@ FORWARD_CASES = [
     # up: one round of two of 64 x 128 per CU, 512 of them
     ("up", 16, 3000, 256, 192, 1024, T64X128),
     ("up", 16, 3000, 257, 192, 1024, 1 + T128X128),
+    # down: 512 live 64 x 64 tiles, four stages
+    ("down", 16, 4000, 300, 512, 1024, T64X64_4),           # 640 in the buffers, 512 live
+    ("down", 16, 4800, 300, 512, 1024, 1 + T128X128),       # 640 live
+    # down: to 1024 over the buffers, the ring, of up to 64 experts
+    ("down", 16, 16 * 209, 209, 960, 3840, 1 + T128X128),
+    ("down", 64, 64 * 100, 100, 512, 1024, 1 + T128X128),
+    ("down", 65, 65 * 90, 90, 448, 1024, T64X64_4),
+    # down: narrow layers, three stages: 768 over the buffers, and of more experts 768 live
+    ("down", 21, 21 * 644, 644, 192, 576, T64X64),
+    ("down", 24, 24 * 644, 644, 192, 576, 1 + T128X192),
+    ("down", 72, 72 * 120, 192, 256, 1024, T64X64),        # 864, 576 live
+    ("down", 160, 160 * 88, 177, 128, 512, T64X64),        # 960, 640 live
+    ("down", 84, 84 * 150, 190, 256, 1024, T64X64_4),      # 1008, 1008 live
+    # down: buffers of at most 64 rows
+    ("down", 128, 128 * 20, 26, 384, 1536, T64X64),
+    ("down", 128, 256, 2, 384, 1536, T64X64_4),
+    ("down", 40, 40 * 20, 26, 960, 3840, T64X64_4),
+    ("down", 54, 54 * 50, 56, 1024, 4096, T64X128),
+    ("down", 60, 60 * 4, 4, 1024, 4096, T64X64_4),
+    ("down", 72, 72 * 20, 26, 768, 3072, T64X64_4),
+    ("down", 60, 60 * 22, 22, 1088, 3264, T64X64_4),
+    ("down", 65, 65 * 20, 26, 1024, 4096, T64X128),        # 1040
+    ("down", 128, 128 * 20, 26, 1024, 4096, T64X128),      # 2048
+    ("down", 129, 129 * 20, 26, 1024, 4096, T64X256),
 ]
 
 
