@@ -114,11 +114,13 @@ RingTile pick_ring_tile(const Tuning &tune, const RingArgs &a, int rows, bool gr
         best = gradient && padded(256) * 10 <= padded(128) * 12 ? kRing128x256 : kRing128x128x2;
     else best = rows >= a.Mrows && a.Mrows > 128 ? kRing256x192 : kRing128x256;
     if (rounds(tune, a, rows, best) > 3.0) {
-        // Where a second 256-row tile is filled to a half at most, three of 128 rows pad less (us: down, 128 experts x 320 rows, 3072 -> 768, 291 ->
-        // 263; 64 x 320, 5120 -> 1280, 436 -> 341, x 288 417 -> 364; dxe, 128 x 320, 283 -> 244; skewed counts 143 -> 134, 222 -> 214).  One of
-        // fewer than 32 rows costs little: 64 x 272, 5120 -> 1280, 321 and 370.
-        if (best == kRing256x192 && a.Mrows >= 288 && estimated_time(tune, a, rows, kRing128x256) < 0.9 * estimated_time(tune, a, rows, best)) return kRing128x256;
-        return best;
+        // Where a second 256-row tile is filled to a third at most, three row tiles of 128 x 256 pad less, if three of them side by side cover the
+        // columns of four of 256 x 192 (us: down, 128 experts x 300 rows, 3072 -> 768 271 -> 264, x 320 291 -> 263; 1536 columns: 128 x 300 572 -> 460, 80 x
+        // 288 660 -> 573; dxe, 128 x 320, 768 columns 283 -> 244; skewed counts: 128 x 288, 768 columns 190 -> 178, 192 x 320 207 -> 220).  Fewer than 32
+        // rows more than a tile cost little, and from 350 on three tiles cost what two do: 128 x 384, 768 columns, 264 and 281, skewed 128 x 368 156 and 171.
+        // Other widths gain or lose by how their tiles fall: 960 columns 0.79 to 1.03, 576 1.08 to 1.22.
+        const bool third = best == kRing256x192 && a.Mrows >= 288 && a.Mrows <= 336 && (a.Nout + 255) / 256 * 4 <= (a.Nout + 191) / 192 * 3;
+        return third ? kRing128x256 : best;
     }
     double time = estimated_time(tune, a, rows, best) / 1.15;
     for (const RingTile t : {kRing128x128x2, kRing128x192x2, kRing128x256}) {

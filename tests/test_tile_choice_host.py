@@ -23,6 +23,15 @@ CASES = [
     # many rounds: what the widths and the fill of the buffers ask for
     ("down", 128, 256, 256, 768, 3072, T256X192),      # full buffers of two row tiles
     ("down", 128, 200, 256, 768, 3072, T128X256),      # room in them
+    ("down", 128, 287, 287, 768, 3072, T256X192),      # a second row tile of 31 rows, of 32 and of 80
+    ("down", 128, 288, 288, 768, 3072, T128X256),
+    ("down", 128, 336, 336, 768, 3072, T128X256),
+    ("down", 128, 337, 337, 768, 3072, T256X192),
+    ("down", 128, 384, 384, 768, 3072, T256X192),
+    ("dxe", 128, 320, 320, 768, 3072, T128X256),
+    ("down", 64, 300, 300, 1536, 6144, T128X256),
+    ("down", 128, 320, 320, 960, 3840, T256X192),      # four tiles of 256 columns against five of 192
+    ("down", 128, 320, 320, 576, 2304, T256X192),
     ("dxe", 128, 256, 256, 768, 3072, T256X192),
     ("down", 64, 256, 320, 1024, 4096, T128X128),      # 192-wide tiles pad 1024 columns by an eighth
     ("dxe", 200, 250, 256, 1024, 4096, T128X256),
