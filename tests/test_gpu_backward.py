@@ -472,22 +472,31 @@ def test_router_logit_gradients_of_very_many_tokens(torch_cuda, T, n, m):
     ctx.close()
 
 
-# dx and the partial sums of the router weights in one launch: every pair of matrix-core variants that shares one, and the vector-ALU
-# kernels; token counts and widths that end inside a block of either part
+# dx and the partial sums of the router weights: every pair of matrix-core variants that shares a launch, and the vector-ALU kernels; token
+# counts and widths that end inside a block of either part.  Then what does not share one: four chunks of logit columns, three and more than
+# two workgroups of dx per CU, the same of the vector-ALU kernels, and routers whose dx has too many chunks for the matrix cores but whose weights do
+# not have too many columns.
 SHARED_LAUNCH_CASES = [
-    wl.small_config("router_grads_2_1", 645, 320, 64, 16, 16, 5, "bf16", "gelu", seed=81),
-    wl.small_config("router_grads_3_1", 129, 576, 64, 17, 8, 3, "bf16", "gelu", seed=82),
-    wl.small_config("router_grads_3_2", 1025, 192, 64, 32, 16, 4, "bf16", "gelu", seed=83),
-    wl.small_config("router_grads_f16", 259, 320, 64, 5, 12, 6, "f16", "gelu", seed=84),
-    wl.small_config("router_grads_f32", 1, 72, 64, 3, 2, 1, "f32", "gelu", seed=85),
+    (wl.small_config("router_grads_2_1", 645, 320, 64, 16, 16, 5, "bf16", "gelu", seed=81), ["mfma_kernel<2, 1>"]),
+    (wl.small_config("router_grads_3_1", 129, 576, 64, 17, 8, 3, "bf16", "gelu", seed=82), ["mfma_kernel<3, 1>"]),
+    (wl.small_config("router_grads_3_2", 1025, 192, 64, 32, 16, 4, "bf16", "gelu", seed=83), ["mfma_kernel<3, 2>"]),
+    (wl.small_config("router_grads_f16", 259, 320, 64, 5, 12, 6, "f16", "gelu", seed=84), ["kernel<DT"]),
+    (wl.small_config("router_grads_f32", 1, 72, 64, 3, 2, 1, "f32", "gelu", seed=85), ["kernel<DT"]),
+    (wl.small_config("router_grads_4_2_apart", 300, 192, 64, 33, 16, 2, "bf16", "gelu", seed=101), ["mfma_kernel<4, 0>", "mfma_kernel<0, 2>"]),
+    (wl.small_config("router_grads_3_1_apart", 512 * 128 + 1, 64, 64, 17, 8, 500, "bf16", "relu", seed=102), ["mfma_kernel<3, 0>", "mfma_kernel<0, 1>"]),
+    (wl.small_config("router_grads_f16_apart", 512 * 8 + 1, 256, 64, 3, 4, 400, "f16", "gelu", seed=103), ["kernel<DT", "kernel<DT"]),
+    (wl.small_config("router_grads_mixed", 400, 320, 64, 1, 150, 4, "bf16", "gelu", seed=104), ["kernel<DT", "mfma_kernel<0, 5>"]),
 ]
 
 
-@pytest.mark.parametrize("cfg", SHARED_LAUNCH_CASES, ids=lambda c: c.name)
-def test_router_gradients_in_one_launch(torch_cuda, cfg):
-    """The chained pass, whose dx and router-weight products share a launch, has the bits of the separate calls, which match the oracle."""
+@pytest.mark.parametrize("cfg,kernels", SHARED_LAUNCH_CASES, ids=lambda c: getattr(c, "name", ""))
+def test_router_gradients_in_one_launch(torch_cuda, cfg, kernels):
+    """The chained pass, whose dx and router-weight products share a launch or do not, has the bits of the separate calls, which match the oracle."""
+    from test_gpu_dispatch_edges import _launched
     a, b = _forward_backward(cfg), _forward_backward(cfg, chained=True)
     try:
+        names = [k for k in _launched(b, b.backward) if "router_grad_" in k]
+        assert len(names) == len(kernels) and all("router_grad_" + k in name for k, name in zip(kernels, names)), names
         _check_steps(cfg, a)
         oa, ob = _fetch_backward(a), _fetch_backward(b)
         for k in ("dx", "dw_inter", "dw_intra"):

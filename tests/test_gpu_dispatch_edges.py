@@ -567,7 +567,7 @@ def test_weight_gradients_of_short_sums(torch_cuda, cfg, short, monkeypatch):
         assert all(torch_cuda.equal(a, b) for a, b in zip(got, other)), tile
 
 
-# Both sides of the lines between the 64-row tiles and the others in pick_tile: what takes another tile than before, against 128 x 192 tiles
+# Both sides of the lines between the 64-row tiles and the others in pick_forward_tile (which tile: test_tile_choice_host.py)
 PICK_TILE_EDGES = [
     wl.small_config("up_320_small_tiles", 700, 192, 640, 8, 4, 40, "bf16", "gelu", skew=True, seed=411),
     wl.small_config("up_330_small_tiles_f16", 700, 192, 704, 10, 3, 40, "f16", "relu", skew=True, seed=412),
@@ -580,20 +580,29 @@ PICK_TILE_EDGES = [
     wl.small_config("down_second_round", 16 * 210, 960, 1920, 4, 4, 210, "bf16", "relu", skew=True, seed=419),
     wl.small_config("down_64_rows_768", 600, 384, 768, 16, 8, 64, "bf16", "relu", skew=True, seed=420),
     wl.small_config("down_64_rows_896", 600, 448, 896, 16, 8, 64, "f16", "relu", skew=True, seed=421),
+    wl.small_config("down_64_rows_64x128", 500, 1024, 1088, 8, 7, 60, "bf16", "relu", skew=True, seed=423),
+    wl.small_config("down_narrow_many_experts", 72 * 120, 256, 320, 9, 8, 192, "bf16", "relu", skew=True, seed=424),
+    wl.small_config("down_65_experts", 65 * 90, 448, 512, 13, 5, 90, "f16", "relu", skew=True, seed=425),
+    wl.small_config("up_one_slab_192_columns", 5000, 64, 192, 8, 5, 150, "bf16", "gelu", skew=True, seed=426),
     wl.small_config("down_290_rows_of_many_experts", 104 * 290, 768, 832, 13, 8, 290, "bf16", "relu", skew=True, seed=422),
 ]
 
 
 @pytest.mark.parametrize("cfg", PICK_TILE_EDGES, ids=lambda c: c.name)
 def test_tiles_of_medium_products(torch_cuda, cfg, monkeypatch):
-    """The library's tiles give the bits of 128 x 192 tiles in every form of the forward pass (every tile adds in the order of k)."""
+    """The library's tiles give the bits of 128 x 192 tiles in every form of the forward pass (every tile adds in the order of k), and are those that
+    the choice by sizes names: a ring kernel or a two-stage one for each of the two products."""
     from paper_2212_05191_amd.runner import GpuLayer
+    from test_tile_choice_host import forward_tile
+    tiles = [forward_tile(way, cfg.N, cfg.T, cfg.capacity, cfg.d_model, cfg.d_ff) for way in ("up", "down")]
+    want = ["grouped_gemm_" + ("ring" if 1 <= t <= 4 else "nt") + "_kernel" for t in tiles]
     got = {}
     for tile in ("0", ""):
         monkeypatch.setenv("SMILE_FFN_TILE", tile) if tile else monkeypatch.delenv("SMILE_FFN_TILE", raising=False)
         layer, _, _ = _layer_with_biases(cfg)
         try:
-            layer.forward_fused()
+            names = [k for k in _launched(layer, layer.forward_fused) if "gemm" in k]
+            assert tile or names == want, (tiles, names)
             got[tile, "y"] = layer.buf.y.cpu()
             layer.enable_saved_activations()
             layer.h_save.zero_(), layer.pre_save.zero_()
