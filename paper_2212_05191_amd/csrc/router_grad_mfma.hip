@@ -400,6 +400,8 @@ hipError_t launch_router_grad_mfma(const LayerDesc &d, const RouterGradIo &io, b
     // One launch for both where the two parts need about the same LDS (39 and 46 KB with two chunks of logit columns), or where there are
     // few workgroups of dx.  us, dx and router weights apart -> in one launch: 8192 x 768, 2 + 8 columns 12.1 + 9.0 -> 13.9; 8192 x 1600
     // 19.2 + 11.6 -> 24.3; 32768 x 768, 16 + 8 28.8 + 20.3 -> 44.3; but 65536 x 1024, 32 + 8 (47 and 60 KB, 2048 workgroups) 77.3 + 61.4 -> 146.3.
+    // Two chunks gain at every size, less as both parts fill the chip (a whole backward pass of narrow experts, apart -> in one launch: 8192 x 768 73.0 ->
+    // 65.8; 65536 x 1024, 16 + 16, 2048 workgroups of dx 393.6 -> 391.0; 65536 x 1600, 16 + 16, 3584 592.1 -> 585.4; 131072 x 1024, 2 + 8, 4096 714.9 -> 711.7).
     const long long dx_groups = (long long)((d.T + kDxTokens - 1) / kDxTokens) * ((d.d_model + dx_cols(kc) - 1) / dx_cols(kc));
     if (with_dx && with_gw && (kc > 3 || (kc == 3 && dx_groups > 2 * (d.tune.cus > 0 ? d.tune.cus : 256)))) {
         const hipError_t err = launch_router_grad_mfma(d, io, true, false, nullptr, 0, 0, s);
